@@ -83,7 +83,7 @@ hipError_t fill_f32(hipStream_t s, float* dst, float v, size_t n) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ embedding, gather
+// ------------------------------------------------------------------ embedding
 __global__ void embed_kernel(float* X, const bf16* emb, const int* tokens, int h) {
   const int row = blockIdx.x;
   const bf16* e = emb + (size_t)tokens[row] * h;
@@ -97,15 +97,6 @@ __global__ void embed_kernel(float* X, const bf16* emb, const int* tokens, int h
 hipError_t embed_rows(hipStream_t s, float* X, const bf16* emb, const int* tokens, int n, int h) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(embed_kernel, dim3(n), dim3(256), 0, s, X, emb, tokens, h);
-  return hipGetLastError();
-}
-__global__ void gather_rows_kernel(float* dst, const float* src, const int* rows, int h) {
-  const float* a = src + (size_t)rows[blockIdx.x] * h;
-  for (int c = threadIdx.x; c < h; c += blockDim.x) dst[(size_t)blockIdx.x * h + c] = a[c];
-}
-hipError_t gather_rows_f32(hipStream_t s, float* dst, const float* src, const int* rows, int n, int h) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(n), dim3(256), 0, s, dst, src, rows, h);
   return hipGetLastError();
 }
 
@@ -125,16 +116,17 @@ __device__ __forceinline__ float block_sum(float v, float* red) {   // red: one 
 // elements stay in registers between the sum of squares and the scaling (PER 16-byte loads per
 // thread and row); longer rows are read a second time.
 template <int R, int PER>
-__global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X, const float* gain, float eps, int h, int n) {
+__global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X, const float* gain, float eps, int h, int n, const int* idx) {
   __shared__ float red[R][16];
   const int row0 = blockIdx.x * R;
+  auto src_row = [&](int r) { const int q = min(r, n - 1); return idx ? idx[q] : q; };
   const bool in_regs = h <= 1024 * PER;
   f32x4 v[R][PER];
   float ss[R];
 #pragma unroll
   for (int r = 0; r < R; r++) {
     ss[r] = 0.f;
-    const float* x = X + (size_t)min(row0 + r, n - 1) * h;
+    const float* x = X + (size_t)src_row(row0 + r) * h;
     if (in_regs) {
 #pragma unroll
       for (int i = 0; i < PER; i++) {
@@ -149,7 +141,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X,
 #pragma unroll
       for (int i = 0; i < PER; i++) ss[r] += v[r][i][0] * v[r][i][0] + v[r][i][1] * v[r][i][1] + v[r][i][2] * v[r][i][2] + v[r][i][3] * v[r][i][3];
     } else {
-      const float* x = X + (size_t)min(row0 + r, n - 1) * h;
+      const float* x = X + (size_t)src_row(row0 + r) * h;
       for (int c = threadIdx.x * 4; c < h; c += 1024) {
         const f32x4 t = *reinterpret_cast<const f32x4*>(x + c);
         ss[r] += t[0] * t[0] + t[1] * t[1] + t[2] * t[2] + t[3] * t[3];
@@ -169,7 +161,7 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X,
     if (row0 + r >= n) break;
     const float tot = red[r][0] + red[r][1] + red[r][2] + red[r][3];
     const float inv = rsqrtf(tot / (float)h + eps);
-    const float* x = X + (size_t)(row0 + r) * h;
+    const float* x = X + (size_t)src_row(row0 + r) * h;
     bf16* o_row = out + (size_t)(row0 + r) * h;
     if (in_regs) {
 #pragma unroll
@@ -198,7 +190,25 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X,
 // Embedding rows and the first layer's RMSNorm in one pass: the row is in registers anyway, so the residual stream
 // (fp32) and its normalised bf16 copy are written together and the stream is not read back. One workgroup per row,
 // 8 elements per thread and 2048-column slab, rows of up to 8192 elements.
-__global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int h) {
+// A decode step also has its rotation angles written here, once for all layers: cosines and sines of row's position in rot.
+__device__ __forceinline__ void write_rotation(float* rot, int row, int pos, const double* inv_freq, int half) {
+  for (int i = threadIdx.x; i < half; i += blockDim.x) {
+    double sv, cv;
+    sincos((double)pos * inv_freq[i], &sv, &cv);
+    rot[(size_t)row * 2 * half + i] = (float)cv;
+    rot[(size_t)row * 2 * half + half + i] = (float)sv;
+  }
+}
+__global__ void rotation_kernel(float* rot, const DecodeSeq* seqs, const double* inv_freq, int half) {
+  write_rotation(rot, blockIdx.x, seqs[blockIdx.x].cl, inv_freq, half);
+}
+hipError_t decode_rotation(hipStream_t s, float* rot, const DecodeSeq* seqs, const double* inv_freq, int n, int d) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(rotation_kernel, dim3(n), dim3(64), 0, s, rot, seqs, inv_freq, d >> 1);
+  return hipGetLastError();
+}
+__global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int h,
+                                                         float* rot, const DecodeSeq* seqs, const double* inv_freq, int half) {
   constexpr int PER = 4;
   __shared__ float red[4];
   const int row = blockIdx.x;
@@ -214,6 +224,7 @@ __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, co
       for (int j = 0; j < 8; j++) { const float f = bf2f(v[i][j]); ss += f * f; }
     }
   }
+  if (rot) write_rotation(rot, row, seqs[row].cl, inv_freq, half);      // while the row is on its way
   const float w = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
   __syncthreads();
@@ -237,17 +248,18 @@ __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, co
     }
   }
 }
-hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h) {
+hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h,
+                           float* rot, const DecodeSeq* seqs, const double* inv_freq, int d) {
   if (n == 0) return hipSuccess;
   if (h > 8192 || h % 8 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_norm_kernel, dim3(n), dim3(256), 0, s, X, out, emb, tokens, gain, eps, h);
+  hipLaunchKernelGGL(embed_norm_kernel, dim3(n), dim3(256), 0, s, X, out, emb, tokens, gain, eps, h, rot, seqs, inv_freq, d >> 1);
   return hipGetLastError();
 }
 
-hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* gain, float eps, int n, int h) {
+hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* gain, float eps, int n, int h, const int* idx) {
   if (n == 0) return hipSuccess;
-  if (n >= 1024) hipLaunchKernelGGL((rmsnorm_kernel<2, 4>), dim3((n + 1) / 2), dim3(256), 0, s, out, X, gain, eps, h, n);
-  else hipLaunchKernelGGL((rmsnorm_kernel<1, 8>), dim3(n), dim3(256), 0, s, out, X, gain, eps, h, n);
+  if (n >= 1024) hipLaunchKernelGGL((rmsnorm_kernel<2, 4>), dim3((n + 1) / 2), dim3(256), 0, s, out, X, gain, eps, h, n, idx);
+  else hipLaunchKernelGGL((rmsnorm_kernel<1, 8>), dim3(n), dim3(256), 0, s, out, X, gain, eps, h, n, idx);
   return hipGetLastError();
 }
 
@@ -324,26 +336,17 @@ hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const Prefill
 }
 
 // ------------------------------------------------------------------ decode: QKV finish
-// Sums the split-K partials of the QKV projection, rotates q and k for position cl, stores q
+// Sums the split-K partials of the QKV projection, rotates q and k (rot: the step's angles), stores q
 // (bf16) for the attention kernel and appends k and v to the request's last page.
 __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* partials, int splits, long long split_stride, int ld,
                                                                 const DecodeSeq* seqs, const int* block_tables,
-                                                                const double* inv_freq, bf16* q_out, bf16* pool,
+                                                                const float* rot, bf16* q_out, bf16* pool,
                                                                 KvGeom geo, int n_q) {
   // blockIdx.x = request, blockIdx.y = group of 8 head slots out of n_q (Q) + n_kv (K) + n_kv (V)
-  __shared__ float cs[128], sn[128];
   const int row = blockIdx.x, d = geo.d, half = d >> 1;
   const int slot0 = blockIdx.y * 8, n_slots = n_q + 2 * geo.n_kv, slot1 = min(n_slots, slot0 + 8);
   const DecodeSeq sq = seqs[row];
   const int pos = sq.cl;
-  if (slot0 < n_q + geo.n_kv) {               // this group holds rotated heads
-    for (int i = threadIdx.x; i < half; i += blockDim.x) {
-      double sv, cv;
-      sincos((double)pos * inv_freq[i], &sv, &cv);
-      cs[i] = (float)cv; sn[i] = (float)sv;
-    }
-  }
-  __syncthreads();
   const int page = block_tables[sq.bt_off + pos / geo.page_tokens], slot = pos % geo.page_tokens;
   const float* pr = partials + (size_t)row * ld;
   // a work item is four consecutive rotation pairs of a Q or K head, or four consecutive elements of a V head
@@ -358,13 +361,14 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
         a += *reinterpret_cast<const f32x4*>(pr + z * split_stride + hd * d + i0);
         b += *reinterpret_cast<const f32x4*>(pr + z * split_stride + hd * d + i0 + half);
       }
+      const f32x4 cs = *reinterpret_cast<const f32x4*>(rot + (size_t)row * d + i0), sn = *reinterpret_cast<const f32x4*>(rot + (size_t)row * d + half + i0);
       bf16x4 ya, yb;
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         // the projection's result is rounded to bf16 before the rotation, as in the prefill path
         const float fa = bf2f(f2bf(a[e])), fb = bf2f(f2bf(b[e]));
-        ya[e] = f2bf(fa * cs[i0 + e] - fb * sn[i0 + e]);
-        yb[e] = f2bf(fa * sn[i0 + e] + fb * cs[i0 + e]);
+        ya[e] = f2bf(fa * cs[e] - fb * sn[e]);
+        yb[e] = f2bf(fa * sn[e] + fb * cs[e]);
       }
       bf16* dst = hd < n_q ? q_out + (size_t)row * n_q * d + hd * d
                            : pool + ((size_t)page * geo.n_kv + (hd - n_q)) * geo.head_elems() + (size_t)slot * d;
@@ -383,11 +387,11 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
   }
 }
 hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, long long split_stride, int ld,
-                             const DecodeSeq* seqs, const int* block_tables, const double* inv_freq,
+                             const DecodeSeq* seqs, const int* block_tables, const float* rot,
                              bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(decode_qkv_finish_kernel, dim3(n, (n_q + 2 * geo.n_kv + 7) / 8), dim3(256), 0, s, partials, splits, split_stride, ld, seqs,
-                     block_tables, inv_freq, q_out, pool, geo, n_q);
+                     block_tables, rot, q_out, pool, geo, n_q);
   return hipGetLastError();
 }
 

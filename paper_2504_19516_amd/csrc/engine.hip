@@ -61,9 +61,10 @@ struct Phase {
   bool ran = false;
   // device workspace
   float* X = nullptr; bf16* Xn = nullptr; bf16* QKV = nullptr; bf16* A = nullptr; bf16* H = nullptr;
-  float* part = nullptr; float* attn_ws = nullptr; bf16* Q = nullptr;
+  float* part = nullptr; size_t part_floats = 0; float* attn_ws = nullptr; bf16* Q = nullptr;
+  float* rot = nullptr; float* ssq = nullptr;                 // decode: rotation angles of the step, shares of the rows' sums of squares
   float* tail_ws = nullptr; size_t tail_ws_bytes = 0;         // prefill GEMM tail pieces
-  float* Xlast = nullptr; bf16* Xlast_n = nullptr; float* logits = nullptr; int* next = nullptr;
+  bf16* Xlast_n = nullptr; float* logits = nullptr; int* next = nullptr;
   // Per-call metadata (sequence records, block tables, work items, token ids) is packed into one
   // pinned block and reaches the device in a single copy; the pointers below are views into the
   // two blocks, laid out afresh by every launch.
@@ -373,6 +374,41 @@ double plan_decode_gemm(const StreamRates& r, int m, int n, int k, int cus, bool
   return best_t;
 }
 
+// Estimated seconds of a GEMM that finishes its own output (gemm_kslice.hip): the weights at the rate of a read-only
+// stream, or what its workgroups make the busiest CU pull -- the weights of their 16 or 32 columns and, for each of them, the
+// activations of the whole K, whose 16-byte pieces cost about twice their bytes. Measured against it: 28672 x 4096 at 1 / 16 rows
+// 37 / 41 us on 256 CUs (38 / 38 estimated), 46 / 62 on 128 (42 / 65), 153 / 220 on 32 (140 / 260).
+double kslice_time(const sts_ctx* ctx, int epi, int m, int n, int k, int cus) {
+  const int c = std::max(cus, 8), cols = kslice_cols(epi, n, c), wgs = n / cols;
+  const double per_cu = wgs <= c ? 1.0 : (double)wgs / c;
+  return std::max(2.0 * n * k / (0.95 * ctx->stream_bw_gpu), per_cu * 2.0 * k * (cols + 2 * m) / (0.93 * ctx->stream_bw_cu)) + 2.5e-6;
+}
+constexpr double SMALL_KERNEL_S = 4.5e-6;     // one of the kernels that add up partial sums (4.6 to 5.4 us at 1 to 64 rows)
+
+// The GEMMs of one decode layer. kslice: all four finish their own output and no reduce kernel runs; taken when the sum of the
+// estimates, with the reduce kernels of the split form, is the smaller one. Otherwise tile and split of each, with SwiGLU in the
+// gate/up GEMM unless cutting K is estimated faster. Both measured on 256 CUs, 8B shape: 1 row 73 us of GEMMs against 82 + 20 of
+// reduce kernels; at 32 rows 112 us against 86 + 20, so the form ends at 16 rows (one row block of the matrix cores).
+struct DecodeGemm { int cfg = 0, splits = 1; };
+struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu, down; };
+DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
+  const sts_model_desc& d = ctx->d;
+  DecodePlan p;
+  DecodeGemm fused;
+  double t = pick_decode_gemm(ctx, n, ctx->qkvn, d.hidden, cus, true, true, &p.qkv.cfg, &p.qkv.splits);
+  t += pick_decode_gemm(ctx, n, d.hidden, ctx->qd, cus, true, true, &p.o.cfg, &p.o.splits);
+  t += pick_decode_gemm(ctx, n, d.hidden, d.mlp, cus, true, true, &p.down.cfg, &p.down.splits);
+  const double t_split = pick_decode_gemm(ctx, n, 2 * d.mlp, d.hidden, cus, true, true, &p.gu.cfg, &p.gu.splits) + 4e-6;
+  const double t_fused = pick_decode_gemm(ctx, n, 2 * d.mlp, d.hidden, cus, false, false, &fused.cfg, &fused.splits);
+  const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
+  if (can_fuse && (t_fused <= t_split || p.gu.splits == 1)) { p.gu_fused = true; p.gu = fused; }
+  t += (p.gu_fused ? t_fused : t_split) + 3 * SMALL_KERNEL_S;
+  if (n <= KSLICE_MAX_ROWS)
+    p.kslice = kslice_time(ctx, KS_QKV, n, ctx->qkvn, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, ctx->qd, cus) +
+               kslice_time(ctx, KS_SWIGLU, n, 2 * d.mlp, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, d.mlp, cus) < t;
+  return p;
+}
+
 int64_t now_ns();
 
 // Wait for a stream with a short busy poll before blocking: a layer slice or a decode step lasts
@@ -413,6 +449,34 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
 }
 
 bf16* layer_pool(sts_ctx* c, int l) { return c->pool + (size_t)l * c->pool_layer_elems; }
+
+// Final norm and LM head of n rows into ph.logits. x: the residual stream, whose rows (rows idx[i] if idx is given) are normalised
+// into xn; null if xn holds them normalised already. With scale.ssq xn holds the rows scaled by the final gains, and a head that
+// applies the row factor itself needs no norm. The head runs unsplit, or with K cut over workgroups and a kernel that adds up the partial sums (a small vocabulary has too few tiles:
+// 1024 x 4096 took 33 us unsplit against 7 + 4), or as a GEMM that cuts K inside its workgroups.
+int run_head(sts_ctx* c, Phase& ph, const float* x, const int* idx, bf16* xn, RowScale scale, int n, float* scratch, size_t scratch_floats, bool nt) {
+  const int v = c->d.vocab, h = c->d.hidden;
+  int cfg, one, split_cfg, splits;
+  const double t_one = pick_decode_gemm(c, n, v, h, ph.cus, false, false, &cfg, &one);
+  const double t_split = pick_decode_gemm(c, n, v, h, ph.cus, true, true, &split_cfg, &splits) + SMALL_KERNEL_S;
+  const double t_norm = scale.ssq ? SMALL_KERNEL_S : 0.0;
+  const bool split = splits > 1 && t_split < t_one && (size_t)splits * n * v <= scratch_floats;
+  const bool kslice = n <= KSLICE_MAX_ROWS && kslice_time(c, KS_F32, n, v, h, ph.cus) < (split ? t_split : t_one) + t_norm;
+  if (x && !(kslice && scale.ssq)) {
+    KL(ph, STS_K_NORM, rmsnorm_rows(ph.stream, xn, x, c->gf, c->d.rms_eps, n, h, idx));
+    scale = RowScale{nullptr, 0, 0.f};
+  }
+  if (kslice) {
+    KL(ph, STS_K_HEAD, kslice_f32(ph.stream, KsliceIn{xn, h, scale, c->lm, n, v, h}, ph.cus, ph.logits, v));
+  } else if (split) {
+    const int ksteps = h / 64, per = (ksteps + splits - 1) / splits, used = (ksteps + per - 1) / per;   // slices the launch makes
+    KL(ph, STS_K_HEAD, gemm_bf16(ph.stream, split_cfg, EPI_F32, xn, h, c->lm, h, scratch, v, n, v, h, splits, (long long)n * v, nullptr, true, nt));
+    KL(ph, STS_K_REDUCE, reduce_f32(ph.stream, ph.logits, scratch, used, (long long)n * v, (size_t)n * v));
+  } else {
+    KL(ph, STS_K_HEAD, gemm_bf16(ph.stream, cfg, EPI_F32, xn, h, c->lm, h, ph.logits, v, n, v, h, 1, 0, nullptr, true, nt));
+  }
+  return STS_OK;
+}
 
 // ------------------------------------------------------------------------------------ prefill
 // Checks of a prefill slice that touch no state: arguments, the order of layer slices, and the
@@ -531,11 +595,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     KL(ph, STS_K_DOWN, prefill_gemm(c, ph, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp));
   }
   if (le == d.n_layers && want_logits) {
-    KL(ph, STS_K_HEAD, gather_rows_f32(st, ph.Xlast, ph.X, ph.d_rows, n_seqs, h));
-    KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xlast_n, ph.Xlast, c->gf, d.rms_eps, n_seqs, h));
-    int head_cfg, head_splits;
-    pick_decode_gemm(c, n_seqs, d.vocab, h, ph.cus, false, false, &head_cfg, &head_splits);
-    KL(ph, STS_K_HEAD, gemm_bf16(st, head_cfg, EPI_F32, ph.Xlast_n, h, c->lm, h, ph.logits, d.vocab, n_seqs, d.vocab, h, 1, 0));
+    STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false));
     HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, (size_t)n_seqs * d.vocab * sizeof(float), hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
@@ -660,54 +720,55 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   HIPCK(hipMemcpyAsync(ph.d_meta, ph.h_meta, ph.meta_used, hipMemcpyHostToDevice, st));
   const int h = d.hidden;
   if (h <= 8192) {
-    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h));
+    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h, ph.rot, ph.d_dseq, c->inv_freq, d.head_dim));
   } else {
     KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, n, h));
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, c->layers[0].g1, d.rms_eps, n, h));
+    KL(ph, STS_K_ROPE, decode_rotation(st, ph.rot, ph.d_dseq, c->inv_freq, n, d.head_dim));
   }
   // On a large partition the decode streams (K and V, the weights of the skinny tiles) are fetched with the non-temporal
   // hint: measured on a 6-layer model, the layer-step is 6 % shorter on 256 CUs (attention 72 -> 63 us), 3 % on 128,
   // and no different on 32, where the same hint cost a prefill slice running beside it 0.5 %.
   const bool nt_attn = ph.cus >= 128, nt_w = nt_attn;
-  auto skinny = [&](int kind, const bf16* A, int lda, const bf16* W, int N, int K, int* splits_out, long long* stride_out) -> int {
-    const long long stride = (long long)n * N;
-    *stride_out = stride;
-    int cfg, splits;
-    pick_decode_gemm(c, n, N, K, ph.cus, true, true, &cfg, &splits);
-    *splits_out = splits;
-    KL(ph, kind, gemm_bf16(st, cfg, EPI_F32, A, lda, W, K, ph.part, N, n, N, K, splits, stride, nullptr, true, nt_w));
+  const DecodePlan plan = decode_layer_plan(c, n, ph.cus);
+  auto partials = [&](int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) -> int {
+    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt_w));
     return STS_OK;
   };
+  // kslice layers: the residual GEMMs leave Xn scaled by the next gains and the rows' sums of squares in ssq
+  const RowScale by_rms{ph.ssq, h / kslice_cols(KS_RESID, h, ph.cus), d.rms_eps};
+  RowScale xn_scale{nullptr, 0, 0.f};
   for (int l = 0; l < d.n_layers; l++) {
     const LayerW& w = c->layers[l];
-    int sp; long long ss;
-    STSCK(skinny(STS_K_QKV, ph.Xn, h, w.wqkv, c->qkvn, h, &sp, &ss));
-    KL(ph, STS_K_ROPE, decode_qkv_finish(st, ph.part, sp, ss, c->qkvn, ph.d_dseq, ph.d_bt, c->inv_freq, ph.Q, layer_pool(c, l), c->geo, n, d.n_q_heads));
-    KL(ph, STS_K_ATTN, attn_decode(st, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, nt_attn));
-    STSCK(skinny(STS_K_O, ph.A, c->qd, w.wo, h, c->qd, &sp, &ss));
-    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, sp, ss, ph.Xn, w.g2, d.rms_eps, n, h));
-    {
-      // gate/up: SwiGLU is the GEMM's epilogue unless cutting K, with its partial sums and the kernel that reduces them
-      // (taken as 4 us of launch and start-up), is estimated faster
-      int gu_cfg, gu_splits, fu_cfg, fu_splits;
-      const double t_split = pick_decode_gemm(c, n, 2 * d.mlp, h, ph.cus, true, true, &gu_cfg, &gu_splits) + 4e-6;
-      const double t_fused = pick_decode_gemm(c, n, 2 * d.mlp, h, ph.cus, false, false, &fu_cfg, &fu_splits);
-      const bool can_fuse = fu_cfg == GEMM_64x128 || (fu_cfg >= GEMM_64x256S && fu_cfg <= GEMM_64x512S);
-      if (can_fuse && (t_fused <= t_split || gu_splits == 1)) {
-        KL(ph, STS_K_GATEUP, gemm_bf16(st, fu_cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt_w));
-      } else {
-        STSCK(skinny(STS_K_GATEUP, ph.Xn, h, w.wgu, 2 * d.mlp, h, &sp, &ss));
-        KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, sp, ss, n, d.mlp));
-      }
-    }
-    STSCK(skinny(STS_K_DOWN, ph.H, d.mlp, w.wd, h, d.mlp, &sp, &ss));
     const float* next_gain = (l + 1 < d.n_layers) ? c->layers[l + 1].g1 : c->gf;
-    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, sp, ss, ph.Xn, next_gain, d.rms_eps, n, h));
+    if (plan.kslice) {
+      KL(ph, STS_K_QKV, kslice_qkv(st, KsliceIn{ph.Xn, h, xn_scale, w.wqkv, n, c->qkvn, h}, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, d.n_q_heads));
+    } else {
+      STSCK(partials(STS_K_QKV, plan.qkv, ph.Xn, w.wqkv, c->qkvn, h));
+      KL(ph, STS_K_ROPE, decode_qkv_finish(st, ph.part, plan.qkv.splits, (long long)n * c->qkvn, c->qkvn, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, n, d.n_q_heads));
+    }
+    KL(ph, STS_K_ATTN, attn_decode(st, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, nt_attn));
+    if (plan.kslice) {
+      KL(ph, STS_K_O, kslice_resid(st, KsliceIn{ph.A, c->qd, RowScale{nullptr, 0, 0.f}, w.wo, n, h, c->qd}, ph.cus, ph.X, w.g2, ph.Xn, ph.ssq));
+      KL(ph, STS_K_GATEUP, kslice_swiglu(st, KsliceIn{ph.Xn, h, by_rms, w.wgu, n, 2 * d.mlp, h}, ph.H));
+      KL(ph, STS_K_DOWN, kslice_resid(st, KsliceIn{ph.H, d.mlp, RowScale{nullptr, 0, 0.f}, w.wd, n, h, d.mlp}, ph.cus, ph.X, next_gain, ph.Xn, ph.ssq));
+      xn_scale = by_rms;
+      continue;
+    }
+    STSCK(partials(STS_K_O, plan.o, ph.A, w.wo, h, c->qd));
+    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.o.splits, (long long)n * h, ph.Xn, w.g2, d.rms_eps, n, h));
+    if (plan.gu_fused) {
+      KL(ph, STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt_w));
+    } else {
+      STSCK(partials(STS_K_GATEUP, plan.gu, ph.Xn, w.wgu, 2 * d.mlp, h));
+      KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));
+    }
+    STSCK(partials(STS_K_DOWN, plan.down, ph.H, w.wd, h, d.mlp));
+    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.down.splits, (long long)n * h, ph.Xn, next_gain, d.rms_eps, n, h));
   }
   if (want_logits || want_next) {
-    int head_cfg, head_splits;
-    pick_decode_gemm(c, n, d.vocab, h, ph.cus, false, false, &head_cfg, &head_splits);
-    KL(ph, STS_K_HEAD, gemm_bf16(st, head_cfg, EPI_F32, ph.Xn, h, c->lm, h, ph.logits, d.vocab, n, d.vocab, h, 1, 0, nullptr, true, nt_w));
+    // (the last reduce kernel of the split form has written Xn normalised)
+    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt_w));
     if (want_next) {
       KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.next, ph.logits, n, d.vocab));
       HIPCK(hipMemcpyAsync(ph.h_next, ph.next, n * sizeof(int), hipMemcpyDeviceToHost, st));
@@ -745,7 +806,6 @@ int alloc_phase(sts_ctx* c, int side) {
   STSCK(dev_alloc(c, &ph.Xn, rows * d.hidden));
   STSCK(dev_alloc(c, &ph.A, rows * c->qd));
   STSCK(dev_alloc(c, &ph.H, rows * d.mlp));
-  STSCK(dev_alloc(c, &ph.Xlast, nseq * d.hidden));
   STSCK(dev_alloc(c, &ph.Xlast_n, nseq * d.hidden));
   STSCK(dev_alloc(c, &ph.logits, nseq * d.vocab));
   STSCK(dev_alloc(c, &ph.next, nseq));
@@ -768,7 +828,10 @@ int alloc_phase(sts_ctx* c, int side) {
   } else {
     const size_t widest = std::max<size_t>(std::max(c->qkvn, 2 * d.mlp), d.hidden);
     const size_t max_chunks = decode_max_chunks((int)mp);
-    STSCK(dev_alloc(c, &ph.part, 8 * rows * widest));
+    ph.part_floats = 8 * rows * widest;
+    STSCK(dev_alloc(c, &ph.part, ph.part_floats));
+    STSCK(dev_alloc(c, &ph.rot, rows * d.head_dim));
+    STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
     STSCK(dev_alloc(c, &ph.Q, rows * c->qd));
     STSCK(dev_alloc(c, &ph.attn_ws, attn_decode_ws_floats((int)rows, d.n_q_heads, d.head_dim, (int)max_chunks)));
   }

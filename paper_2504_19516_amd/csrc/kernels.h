@@ -76,14 +76,17 @@ hipError_t export_weight(hipStream_t s, float* dst, const bf16* src, int ld, int
 hipError_t fill_f32(hipStream_t s, float* dst, float v, size_t n);
 hipError_t embed_rows(hipStream_t s, float* X, const bf16* emb, const int* tokens, int n, int h);
 // embedding rows into the fp32 residual stream X and, in the same pass, their RMSNorm into out (bf16); h <= 8192
-hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h);
-hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* gain, float eps, int n, int h);
-hipError_t gather_rows_f32(hipStream_t s, float* dst, const float* src, const int* rows, int n, int h);
+// (a decode step passes rot too: the rotation angles of its requests' positions, [n][d / 2 cosines | d / 2 sines])
+hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h,
+                           float* rot = nullptr, const DecodeSeq* seqs = nullptr, const double* inv_freq = nullptr, int d = 0);
+hipError_t decode_rotation(hipStream_t s, float* rot, const DecodeSeq* seqs, const double* inv_freq, int n, int d);
+// rows idx[i] of X if idx is given
+hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* gain, float eps, int n, int h, const int* idx = nullptr);
 hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const PrefillSeq* seqs, int n_seqs,
                                  const int* block_tables, const double* inv_freq, bf16* pool, KvGeom geo,
                                  int n_rows, int n_q);
 hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, long long split_stride, int ld,
-                             const DecodeSeq* seqs, const int* block_tables, const double* inv_freq,
+                             const DecodeSeq* seqs, const int* block_tables, const float* rot,
                              bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q);
 hipError_t reduce_resid_norm(hipStream_t s, float* X, const float* partials, int splits, long long split_stride,
                              bf16* out_norm, const float* gain, float eps, int n, int h);
@@ -110,5 +113,19 @@ hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq*
                        const int* block_tables, const bf16* pool, KvGeom geo, int n, int n_q, int chunk_pages, int max_chunks, float* ws,
                        bool stream_nt = false);
 int attn_decode_max_chunk_tokens();
+
+// ---- decode GEMMs that finish their own output (gemm_kslice.hip) ----------------------------
+enum KsliceEpilogue { KS_F32 = 0, KS_RESID = 1, KS_SWIGLU = 2, KS_QKV = 3 };
+constexpr int KSLICE_MAX_ROWS = 16;
+// Row factor of a GEMM's activations: 1 / sqrt(sum of `parts` shares of the row's sum of squares / K + eps); none if ssq is null.
+struct RowScale { const float* ssq; int parts; float eps; };
+// A [M, lda] row-major, W [N, K] in the packed layout.
+struct KsliceIn { const bf16* A; int lda; RowScale scale; const bf16* W; int M, N, K; };
+int kslice_cols(int epi, int n, int cus);
+hipError_t kslice_f32(hipStream_t s, const KsliceIn& in, int cus, float* C, int ldc);
+hipError_t kslice_resid(hipStream_t s, const KsliceIn& in, int cus, float* X, const float* gain, bf16* Xg, float* ssq_out);
+hipError_t kslice_swiglu(hipStream_t s, const KsliceIn& in, bf16* H);
+hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const DecodeSeq* seqs, const int* block_tables, const float* rot, bf16* q_out, bf16* pool,
+                      KvGeom geo, int n_q);
 
 }  // namespace sts

@@ -649,3 +649,52 @@ def test_profiler_builds_a_profile_the_estimator_loads(sts):
     dpred = prof.query(desc, dict(decode_ctx=[pr.eng.seq_length(s) for s in seqs], decode_cus=256, prefill_cus=0))[1]
     assert 0.6 < dpred / dns < 1.6
     pr.close()
+
+
+@pytest.fixture(scope="module")
+def ragged_case(sts):
+    """One layer whose extents end inside the tiles of the decode GEMMs: hidden 1152 (18 K tiles of 64), MLP 3648 (57), groups of
+    four 128-wide heads, vocabulary 640; 17 requests of 3 to 40 cached tokens and their logits from the oracle."""
+    desc = synth.ModelDesc(2, 1152, 8, 2, 128, 3648, 640, 16, 1.0e4, 1.0e-5, "bf16")
+    w = synth.make_weights(desc, 77)
+    ctx = [synth.tokens(500 + i, int(c), desc.vocab) for i, c in enumerate(synth.uniform_lengths(41, 17, 3, 40))]
+    tok = synth.tokens(42, 17, desc.vocab)
+    orc = T.Oracle(desc, w, 64)
+    page = 0
+    for i, t in enumerate(ctx):
+        k = (len(t) + 16) // 16
+        orc.kv.add_sequence(i, list(range(page, page + k)))
+        page += k
+        orc.prefill_append(i, t)
+    ref = orc.decode_step(list(range(17)), tok)
+    eng = new_engine(sts, desc, weight_seed=77, max_decode_batch=32)
+    eng.load_all(w)
+    yield eng, ctx, tok, ref
+    eng.close()
+
+
+@pytest.mark.parametrize("cus", [256, 32])
+@pytest.mark.parametrize("n", [1, 15, 16, 17])
+def test_decode_gemms_that_finish_their_output(ragged_case, n, cus):
+    """Up to 16 requests the decode GEMMs cut K over the waves of a workgroup and apply residual, SwiGLU and rotary embedding
+    themselves (no RoPE and no reduce kernel runs); 17 take the split form. 256 CUs: 16-column workgroups, 32: 32-column ones.
+    Logits against the oracle, the appended K and V against a prefill of the same tokens."""
+    eng, ctx, tok, ref = ragged_case
+    eng.set_partition(256, 256)
+    seqs = gpu_contexts(eng, ctx[:n])
+    eng.set_partition(256, cus)
+    eng.kernel_timing(True)
+    eng.kernel_times(1, reset=True)
+    got, nxt = eng.decode_step(seqs, tok[:n])
+    kinds = eng.kernel_times(1, reset=True)
+    eng.kernel_timing(False)
+    assert ("rope" in kinds) == (n > 16) and ("qkv" in kinds)
+    assert rel(got, ref[:n]) <= TOL
+    assert all(nxt[i] == int(np.argmax(got[i])) for i in range(n))
+    # the K and V rows this step appended in layer 0 are those a prefill of the same tokens writes (bf16 of one projection each:
+    # two roundings apart at most, 2^-7 of the largest value)
+    again = gpu_contexts(eng, [np.concatenate([ctx[n - 1], tok[n - 1:n]])])
+    pos = len(ctx[n - 1])
+    for a, b in zip(eng.kv_read(0, seqs[n - 1], pos, 1), eng.kv_read(0, again[0], pos, 1)):
+        assert rel(a, b) <= 2.0 ** -7
+    free_all(eng, seqs + again)
