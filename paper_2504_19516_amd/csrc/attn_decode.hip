@@ -268,27 +268,57 @@ __global__ void __launch_bounds__(256, 2) attn_decode_mfma_kernel(const bf16* __
 }
 
 // Merge the chunks of one (request, query head): out = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m).
+// Bound by memory latency, not by its few hundred KB: a workgroup's chunks are dealt to groups of D / 2 lanes (4 or 8 of them,
+// two elements a lane), each keeps four chunks' loads in flight and rescales as its maximum grows, and the groups meet in LDS.
+// One thread per element walking its chunks took 6.4 us for one request of 9 chunks and 12.1 for 24 requests of 64 heads (now 4.3
+// and 5.0, which is what a kernel of a few memory round trips takes here).
 template <int D>
-__global__ void attn_decode_merge_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeSeq* __restrict__ seqs,
+__global__ void __launch_bounds__(256) attn_decode_merge_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeSeq* __restrict__ seqs,
                                          const int* __restrict__ multi, int n_q, int n_kv, int G, int chunk_pages, int max_chunks) {
-  const int head = blockIdx.x, req = multi[blockIdx.y], dd = threadIdx.x;
+  constexpr int LPC = D / 2, GROUPS = 256 / LPC, DEPTH = 4;
+  __shared__ float sm[GROUPS], sl[GROUPS], so[GROUPS][D];
+  const int head = blockIdx.x, req = multi[blockIdx.y], grp = threadIdx.x / LPC, dd = threadIdx.x % LPC * 2;
   const int kvh = head / G, g = head % G;
   const int n_pages = (seqs[req].cl + 1 + 15) >> 4;
   const int chunks = (n_pages + chunk_pages - 1) / chunk_pages;
   if (chunks == 1) return;                         // (not listed by the caller: the attention kernel stored this request's output itself)
   const float* base = ws + (((size_t)req * n_kv + kvh) * max_chunks) * G * (D + 2) + g * (D + 2);
   const size_t cstride = (size_t)G * (D + 2);
-  float m = -INFINITY;
-  for (int c = 0; c < chunks; c++) m = fmaxf(m, base[c * cstride + D]);
-  float l = 0.f, o = 0.f;
-  for (int c = 0; c < chunks; c++) {
-    const float w = __builtin_amdgcn_exp2f(base[c * cstride + D] - m);
-    l += base[c * cstride + D + 1] * w;
-    o += base[c * cstride + dd] * w;
+  float m = -INFINITY, l = 0.f;
+  f32x2 o = {0.f, 0.f};
+  for (int c0 = grp; c0 < chunks; c0 += GROUPS * DEPTH) {
+    f32x2 ml[DEPTH], v[DEPTH];
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) {              // past the last chunk: that chunk again, with no weight
+      const float* p = base + min(c0 + u * GROUPS, chunks - 1) * cstride;
+      ml[u] = *reinterpret_cast<const f32x2*>(p + D);
+      v[u] = *reinterpret_cast<const f32x2*>(p + dd);
+    }
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) mx = fmaxf(mx, ml[u][0]);
+    const float corr = __builtin_amdgcn_exp2f(m - mx);       // 0 the first time; a chunk's maximum is finite
+    m = mx; l *= corr; o[0] *= corr; o[1] *= corr;
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) {
+      const float w = c0 + u * GROUPS < chunks ? __builtin_amdgcn_exp2f(ml[u][0] - mx) : 0.f;
+      l += ml[u][1] * w; o[0] += v[u][0] * w; o[1] += v[u][1] * w;
+    }
   }
-  out[((size_t)req * n_q + head) * D + dd] = f2bf(o / l);
+  if (threadIdx.x % LPC == 0) { sm[grp] = m; sl[grp] = l; }
+  so[grp][dd] = o[0]; so[grp][dd + 1] = o[1];
+  __syncthreads();
+  if (threadIdx.x >= D) return;
+  float mx = sm[0], lt = 0.f, ot = 0.f;
+#pragma unroll
+  for (int i = 1; i < GROUPS; i++) mx = fmaxf(mx, sm[i]);
+#pragma unroll
+  for (int i = 0; i < GROUPS; i++) {
+    const float w = __builtin_amdgcn_exp2f(sm[i] - mx);      // 0 for a group without a chunk
+    lt += sl[i] * w; ot += so[i][threadIdx.x] * w;
+  }
+  out[((size_t)req * n_q + head) * D + threadIdx.x] = f2bf(ot / lt);
 }
-
 
 size_t attn_decode_ws_floats(int n, int n_q, int d, int chunks) { return (size_t)n * n_q * chunks * (d + 2); }
 
@@ -311,7 +341,7 @@ static void launch_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeS
   if (stream_nt) launch_decode_kernel<D, G, true>(s, q, out, seqs, items, n_items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
   else launch_decode_kernel<D, G, false>(s, q, out, seqs, items, n_items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
   if (n_multi > 0)
-    hipLaunchKernelGGL(attn_decode_merge_kernel<D>, dim3(n_q, n_multi), dim3(D), 0, s, out, ws, seqs, multi, n_q, geo.n_kv, G, chunk_pages, max_chunks);
+    hipLaunchKernelGGL(attn_decode_merge_kernel<D>, dim3(n_q, n_multi), dim3(256), 0, s, out, ws, seqs, multi, n_q, geo.n_kv, G, chunk_pages, max_chunks);
 }
 
 // q, out: [n, n_q * d] bf16 (q already rotated). A context is cut into chunks of `chunk_pages`

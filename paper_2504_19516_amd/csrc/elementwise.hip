@@ -1,6 +1,8 @@
 // Memory-bound kernels between the contractions: weight generation, embedding, RMSNorm,
 // rotary embedding + KV page writes, split-K reductions fused with residual/norm/SwiGLU,
 // greedy argmax, and the copy kernel used as the bandwidth probe.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace sts {
@@ -335,10 +337,40 @@ hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const Prefill
   return hipGetLastError();
 }
 
+// Partial sums z = 0 .. S - 1 of four consecutive elements, added in that order onto v. S is a template argument of the
+// kernels below: with the count known all the loads are under way before the first is used, and these kernels are bound by the
+// latency of that chain (a loop over a runtime count waits for each load in turn).
+template <int S>
+__device__ __forceinline__ f32x4 add_partials(f32x4 v, const float* p, long long split_stride) {
+  f32x4 q[S];
+#pragma unroll
+  for (int z = 0; z < S; z++) q[z] = *reinterpret_cast<const f32x4*>(p + z * split_stride);
+#pragma unroll
+  for (int z = 0; z < S; z++) v += q[z];
+  return v;
+}
+// Launches with the split count (1 .. 8) as a compile-time constant S.
+template <typename F>
+hipError_t by_splits(int splits, F&& launch) {
+  switch (splits) {
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 5: launch(std::integral_constant<int, 5>{}); break;
+    case 6: launch(std::integral_constant<int, 6>{}); break;
+    case 7: launch(std::integral_constant<int, 7>{}); break;
+    case 8: launch(std::integral_constant<int, 8>{}); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ decode: QKV finish
 // Sums the split-K partials of the QKV projection, rotates q and k (rot: the step's angles), stores q
 // (bf16) for the attention kernel and appends k and v to the request's last page.
-__global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* partials, int splits, long long split_stride, int ld,
+template <int S>
+__global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* partials, long long split_stride, int ld,
                                                                 const DecodeSeq* seqs, const int* block_tables,
                                                                 const float* rot, bf16* q_out, bf16* pool,
                                                                 KvGeom geo, int n_q) {
@@ -356,11 +388,8 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
   for (int t = threadIdx.x; t < n_items; t += blockDim.x) {
     if (t < n_rot_slots * per_rot) {
       const int hd = slot0 + t / per_rot, i0 = (t % per_rot) * 4;
-      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
-      for (int z = 0; z < splits; z++) {
-        a += *reinterpret_cast<const f32x4*>(pr + z * split_stride + hd * d + i0);
-        b += *reinterpret_cast<const f32x4*>(pr + z * split_stride + hd * d + i0 + half);
-      }
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      const f32x4 a = add_partials<S>(zero, pr + hd * d + i0, split_stride), b = add_partials<S>(zero, pr + hd * d + i0 + half, split_stride);
       const f32x4 cs = *reinterpret_cast<const f32x4*>(rot + (size_t)row * d + i0), sn = *reinterpret_cast<const f32x4*>(rot + (size_t)row * d + half + i0);
       bf16x4 ya, yb;
 #pragma unroll
@@ -378,8 +407,7 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
       const int tv = t - n_rot_slots * per_rot;
       const int hd = slot0 + n_rot_slots + tv / per_v, dd0 = (tv % per_v) * 4;
       const int vh = hd - n_q - geo.n_kv;
-      f32x4 a = {0.f, 0.f, 0.f, 0.f};
-      for (int z = 0; z < splits; z++) a += *reinterpret_cast<const f32x4*>(pr + z * split_stride + hd * d + dd0);
+      const f32x4 a = add_partials<S>(f32x4{0.f, 0.f, 0.f, 0.f}, pr + hd * d + dd0, split_stride);
       bf16* v = pool + ((size_t)page * geo.n_kv + vh) * geo.head_elems() + (size_t)geo.page_tokens * d;
 #pragma unroll
       for (int e = 0; e < 4; e++) v[(size_t)(dd0 + e) * geo.page_tokens + slot] = f2bf(a[e]);
@@ -390,14 +418,16 @@ hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, l
                              const DecodeSeq* seqs, const int* block_tables, const float* rot,
                              bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(decode_qkv_finish_kernel, dim3(n, (n_q + 2 * geo.n_kv + 7) / 8), dim3(256), 0, s, partials, splits, split_stride, ld, seqs,
-                     block_tables, rot, q_out, pool, geo, n_q);
-  return hipGetLastError();
+  return by_splits(splits, [&](auto S) {
+    hipLaunchKernelGGL((decode_qkv_finish_kernel<decltype(S)::value>), dim3(n, (n_q + 2 * geo.n_kv + 7) / 8), dim3(256), 0, s, partials, split_stride, ld, seqs,
+                       block_tables, rot, q_out, pool, geo, n_q);
+  });
 }
 
 // ------------------------------------------------------------------ split-K reductions
 // X[row] += sum of partials; optionally out = rmsnorm(X[row]) * gain (bf16).
-__global__ void __launch_bounds__(1024) reduce_resid_norm_kernel(float* X, const float* partials, int splits, long long split_stride,
+template <int S>
+__global__ void __launch_bounds__(1024) reduce_resid_norm_kernel(float* X, const float* partials, long long split_stride,
                                                                  bf16* out, const float* gain, float eps, int h) {
   __shared__ float red[16];
   float* x = X + (size_t)blockIdx.x * h;
@@ -405,11 +435,7 @@ __global__ void __launch_bounds__(1024) reduce_resid_norm_kernel(float* X, const
   const int step = blockDim.x * 4;
   float ss = 0.f;
   for (int c = threadIdx.x * 4; c < h; c += step) {
-    f32x4 v = *reinterpret_cast<const f32x4*>(x + c);
-    for (int z = 0; z < splits; z++) {
-      f32x4 q = *reinterpret_cast<const f32x4*>(p + z * split_stride + c);
-      v += q;
-    }
+    const f32x4 v = add_partials<S>(*reinterpret_cast<const f32x4*>(x + c), p + c, split_stride);
     *reinterpret_cast<f32x4*>(x + c) = v;
     ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
   }
@@ -428,21 +454,20 @@ hipError_t reduce_resid_norm(hipStream_t s, float* X, const float* partials, int
                              bf16* out_norm, const float* gain, float eps, int n, int h) {
   if (n == 0) return hipSuccess;
   const int threads = h >= 4096 ? 1024 : (h >= 2048 ? 512 : 256);      // one float4 per thread where the row allows
-  hipLaunchKernelGGL(reduce_resid_norm_kernel, dim3(n), dim3(threads), 0, s, X, partials, splits, split_stride, out_norm, gain, eps, h);
-  return hipGetLastError();
+  return by_splits(splits, [&](auto S) {
+    hipLaunchKernelGGL((reduce_resid_norm_kernel<decltype(S)::value>), dim3(n), dim3(threads), 0, s, X, partials, split_stride, out_norm, gain, eps, h);
+  });
 }
 
 // H[row][j] = silu(sum gate_j) * sum up_j; gate/up columns are interleaved in blocks of 32.
-__global__ void __launch_bounds__(256) reduce_swiglu_kernel(bf16* H, const float* partials, int splits, long long split_stride, int mlp) {
+template <int S>
+__global__ void __launch_bounds__(256) reduce_swiglu_kernel(bf16* H, const float* partials, long long split_stride, int mlp) {
   const int row = blockIdx.y;
   const int j = (blockIdx.x * blockDim.x + threadIdx.x) * 4;         // four consecutive outputs, inside one block of 32
   if (j >= mlp) return;
   const float* p = partials + (size_t)row * 2 * mlp + (j >> 5) * 64 + (j & 31);
-  f32x4 g = {0.f, 0.f, 0.f, 0.f}, u = {0.f, 0.f, 0.f, 0.f};
-  for (int z = 0; z < splits; z++) {
-    g += *reinterpret_cast<const f32x4*>(p + z * split_stride);
-    u += *reinterpret_cast<const f32x4*>(p + z * split_stride + 32);
-  }
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  const f32x4 g = add_partials<S>(zero, p, split_stride), u = add_partials<S>(zero, p + 32, split_stride);
   bf16x4 o;
 #pragma unroll
   for (int e = 0; e < 4; e++) o[e] = f2bf(g[e] / (1.f + __expf(-g[e])) * u[e]);
@@ -451,8 +476,9 @@ __global__ void __launch_bounds__(256) reduce_swiglu_kernel(bf16* H, const float
 hipError_t reduce_swiglu(hipStream_t s, bf16* H, const float* partials, int splits, long long split_stride, int n, int mlp) {
   if (n == 0) return hipSuccess;
   if (mlp % 32 != 0 || split_stride % 4 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(reduce_swiglu_kernel, dim3((mlp / 4 + 255) / 256, n), dim3(256), 0, s, H, partials, splits, split_stride, mlp);
-  return hipGetLastError();
+  return by_splits(splits, [&](auto S) {
+    hipLaunchKernelGGL((reduce_swiglu_kernel<decltype(S)::value>), dim3((mlp / 4 + 255) / 256, n), dim3(256), 0, s, H, partials, split_stride, mlp);
+  });
 }
 
 __global__ void reduce_f32_kernel(float* out, const float* partials, int splits, long long split_stride, size_t n) {

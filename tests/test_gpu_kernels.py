@@ -186,6 +186,22 @@ def test_prefill_attention(sts, t, prior, nq, nkv, d):
     assert np.array_equal(got, got2)
 
 
+@pytest.mark.parametrize("nq,nkv,d,ctx", [(8, 1, 128, [700, 257, 256, 17]), (8, 2, 128, [63, 65]), (4, 4, 64, [530, 513, 511, 33])])
+def test_decode_attention_merges_many_chunks(sts, nq, nkv, d, ctx):
+    """One page a chunk: 2 to 44 chunks a context, below, at and above what the merge kernel keeps in flight (16 or 32)."""
+    q = synth.normal_bf16(65, (len(ctx), nq, d))
+    k = synth.normal_bf16(66, (sum(ctx), nkv, d))
+    v = synth.normal_bf16(67, (sum(ctx), nkv, d))
+    got = sts.op_attn_decode(q, k, v, ctx, 1)
+    off = 0
+    for r, c in enumerate(ctx):
+        kk, vv = k[off:off + c].astype(np.float64), v[off:off + c].astype(np.float64)
+        for h in range(nq):
+            ref = T.attend_one(q[r, h].astype(np.float64), kk[:, h // (nq // nkv)], vv[:, h // (nq // nkv)])
+            assert rel(got[r, h], ref) <= BF16_TOL, (r, h)
+        off += c
+
+
 @pytest.mark.parametrize("nq,nkv,d,ctx,chunks", [(4, 4, 64, [32, 256, 1, 17, 100], 32), (4, 4, 64, [250, 33], 4),
                                                  (32, 8, 128, [1000, 40, 513, 16], 8), (8, 1, 128, [700], 5),
                                                  (32, 8, 128, [2048, 100], 16), (4, 4, 64, [129, 3], 1),
