@@ -216,10 +216,10 @@ int sts_probe_read(sts_ctx* ctx, int32_t side, int32_t cus, size_t bytes, int32_
  * Returns device ns for `iters` launches. The offline profiler (Section 3.2.4) times the tile shapes with it. */
 int sts_probe_gemm(sts_ctx* ctx, int32_t cus, int32_t tile_cfg, int32_t product, int32_t m, int32_t n, int32_t iters, int64_t* ns_out);
 /* What the engine's choice of GEMM tile and of the cut of a partly filled last wave (Section 2.2.1) assumes about
- * the part: GFLOP/s per busy CU of the 128x128 tiles (two workgroups per CU), of the 256x256 tiles (one) and of the
- * 128x256 tiles (planned one per CU, for the projections with a residual epilogue; their start-up and epilogue are
- * not hidden behind a second workgroup, so a tile costs gemm_fixed_128x256 ns plus its flops at the rate), and MB/s
- * per CU for partial tiles written and read back. The offline profiler measures them and stores them in the
+ * the part: GFLOP/s per busy CU of the 128x128 tiles (two workgroups per CU) and of the 256x256 tiles (one; the times of
+ * shorter 256-column tiles are taken relative to it), and MB/s per CU for partial tiles written and read back.
+ * gemm_rate_128x256 and gemm_fixed_128x256 (a tile of 128 x 256 measured apart) are kept for profiles that hold them; the
+ * choice of tiles does not read them. The offline profiler measures them and stores them in the
  * profile (sts_profile_tile_model reads them back); until set, figures measured on the 8B shape apply. Takes
  * effect for the next launch; STS_ESTATE while a launch is outstanding. */
 int sts_set_tile_model(sts_ctx* ctx, int64_t gemm_rate_128, int64_t gemm_rate_256, int64_t gemm_rate_128x256, int64_t gemm_fixed_128x256,
@@ -244,7 +244,8 @@ int64_t sts_weight_packed_index(int32_t row, int32_t col, int32_t ld);
  * workgroups at once -- the tiles of the last, partly filled wave (Section 2.2.1) are cut along
  * K into pieces that fill the wave, and a second kernel sums the pieces. 0 = whole tiles only. */
 enum { STS_GEMM_128x128 = 0 /* 4 waves, two workgroups per CU */, STS_GEMM_64x256 /* 8 waves */, STS_GEMM_64x128 /* 4 waves, two per CU */,
-       STS_GEMM_256x256 /* 8 waves */, STS_GEMM_128x256 /* 4 waves, planned one per CU; no SwiGLU epilogue */,
+       STS_GEMM_256x256 /* 8 waves; the last row tile is cut to its rows in blocks of 32 */,
+       STS_GEMM_128x256 /* the same with at most 128 rows a tile; no SwiGLU epilogue */,
        /* decode batches: 64-row tiles of 4 to 8 waves, 64 columns per wave, the weights of the library's packed
           layout streamed straight into registers (no row-major form: sts_op_gemm_noalloc rejects them; whole tiles
           only: tail_slots is ignored) */

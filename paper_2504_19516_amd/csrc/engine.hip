@@ -244,45 +244,48 @@ int pick_cfg(int m, int n, int k, int cus) {
 // estimated time, which is where wave quantisation (paper Section 2.2.1) enters -- complete
 // waves of workgroups at the tile's busy-CU rate, then the last wave, whole or cut along K.
 // Rates are measured busy-CU throughputs in TFLOP/s per CU: 128x128 tiles run two workgroups
-// per CU, 256x256 (8 waves) one.
-int pick_prefill_cfg(const sts_ctx* ctx, int epi, int m, int n, int k, int cus, size_t tail_ws_bytes) {
-  if (m <= 64) return GEMM_64x128;
-  struct Cand { int cfg; double rate; };
-  const Cand cands[3] = {{GEMM_128x128, ctx->rate_128}, {GEMM_256x256, ctx->rate_256}, {GEMM_128x256, ctx->rate_128x256}};
-  int best = GEMM_128x128; double best_cost = 1e300;
-  for (const Cand& c : cands) {
-    // 128x256: planned one tile per CU although two fit, so the pieces of a cut last wave run in the second slot beside
-    // the whole tiles; the shape of the O and down projections (a little more than one such tile per CU), instantiated
-    // for their residual epilogue
-    if (c.cfg == GEMM_128x256 && epi != EPI_RESID_F32) continue;
-    const int tm = gemm_tile_m(c.cfg), tn = gemm_tile_n(c.cfg), per_cu = gemm_wgs_per_cu(c.cfg);
-    if (n % tn != 0) continue;
-    const int tiles = ((m + tm - 1) / tm) * (n / tn);
-    const int slots = per_cu * std::max(cus, 8);
+// per CU, the 256-column tiles (8 waves) one. The latter come in heights of 32 to 256 rows: the rows
+// are dealt to any number of row tiles, so that they fill whole waves of workgroups.
+struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; };
+// Time of a 256-column tile of 32 (h + 1) rows against one of 256. Measured on 256 CUs at K = 4096 and 14336, weights from HBM and
+// from the memory-side cache; the mean (a short tile still streams its 256 columns of weights): 0.50 / 0.41 / 0.28 at 32 rows,
+// 0.68 / 0.56 / 0.53 at 128, 0.81 / 0.76 / 0.76 at 192.
+constexpr double TILE_HEIGHT_COST[8] = {0.40, 0.43, 0.52, 0.59, 0.70, 0.78, 0.91, 1.0};
+PrefillGemm pick_prefill_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, size_t tail_ws_bytes) {
+  PrefillGemm best;
+  if (m <= 64) return best;
+  double best_cost = 1e300;
+  const int c = std::max(cus, 8), blocks = (m + 31) / 32;
+  // in units of the candidate's tile time: complete waves, then the last wave -- whole, or in rounds of 1/f with a start-up
+  // charge per round, plus the partial tiles written and read back (4 bytes out, 4 in per element and piece, at the
+  // measured per-CU rate)
+  auto consider = [&](int cfg, int row_tiles, int tiles, int slots, int tile_elems, double tile_s) {
     int n_full, f;
-    gemm_tail_plan(tiles, k / 64, slots, (long long)(tail_ws_bytes / ((size_t)tm * tn * sizeof(float))), &n_full, &f);
-    // in units of this configuration's tile time: complete waves, then the last wave -- whole, or
-    // in rounds of 1/f with a start-up charge per round, plus the partial tiles written and read
-    // back (4 bytes out, 4 in per element and piece, at the measured per-CU rate)
-    // one 128x256 tile per CU: start-up and epilogue are exposed, a measured fixed time on top of the flops
-    const double tile_s = 2.0 * tm * tn * k / (c.rate * 1e12 / per_cu) + (c.cfg == GEMM_128x256 ? ctx->fixed_128x256 : 0.0);
+    gemm_tail_plan(tiles, k / 64, slots, (long long)(tail_ws_bytes / (tile_elems * sizeof(float))), &n_full, &f);
     double t;
     if (f > 1) {
       const int rest = tiles - n_full, rounds = (rest * f + slots - 1) / slots;
-      t = (n_full / slots + rounds * (1.0 / f + 0.03)) * tile_s + (double)rest * f * tm * tn * 8.0 / (std::max(cus, 8) * ctx->partial_bw) + 6e-6;
+      t = (n_full / slots + rounds * (1.0 / f + 0.03)) * tile_s + (double)rest * f * tile_elems * 8.0 / (c * ctx->partial_bw) + 6e-6;
     } else {
       t = (double)((tiles + slots - 1) / slots) * tile_s;
     }
-    const double cost = t;
-    if (cost < best_cost) { best_cost = cost; best = c.cfg; }
+    if (t < best_cost) { best_cost = t; best = PrefillGemm{cfg, row_tiles}; }
+  };
+  consider(GEMM_128x128, 0, ((m + 127) / 128) * (n / 128), 2 * c, 128 * 128, 2.0 * 128 * 128 * k / (ctx->rate_128 * 1e12 / 2));
+  if (n % 256 == 0) {
+    const double tall_s = 2.0 * 256 * 256 * k / (ctx->rate_256 * 1e12);
+    const int least = (blocks + 7) / 8;
+    for (int t = least; t <= std::min(blocks, 2 * least + 2); t++) {       // beyond that a tile is mostly its weights
+      const int h = (blocks + t - 1) / t;
+      consider(GEMM_256x256, t, t * (n / 256), c, h * 32 * 256, TILE_HEIGHT_COST[h - 1] * tall_s);
+    }
   }
   return best;
 }
-// A prefill GEMM on the phase's partition: tile choice, and the last wave of tiles cut along K.
-hipError_t prefill_gemm(const sts_ctx* ctx, Phase& ph, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k) {
-  int cfg = pick_prefill_cfg(ctx, epi, m, n, k, ph.cus, ph.tail_ws_bytes);
-  const GemmTail tail{gemm_wgs_per_cu(cfg) * ph.cus, ph.tail_ws, ph.tail_ws_bytes};
-  return gemm_bf16(ph.stream, cfg, epi, A, lda, W, ldw, C, ldc, m, n, k, 1, 0, &tail);
+// A prefill GEMM on the phase's partition, the last wave of tiles cut along K.
+hipError_t prefill_gemm(const Phase& ph, const PrefillGemm& gm, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k) {
+  const GemmTail tail{gemm_wgs_per_cu(gm.cfg) * ph.cus, ph.tail_ws, ph.tail_ws_bytes};
+  return gemm_bf16(ph.stream, gm.cfg, epi, A, lda, W, ldw, C, ldc, m, n, k, 1, 0, &tail, true, false, gm.row_tiles);
 }
 int plan_splits(double rate_256, double partial_bw, int cfg, int m, int n, int k, int cus);
 int pick_splits(const sts_ctx* ctx, int cfg, int m, int n, int k, int cus) { return plan_splits(ctx->rate_256, ctx->partial_bw, cfg, m, n, k, cus); }
@@ -583,16 +586,18 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
   if (fused_embed) KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h));
   else if (lb == 0) KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, rows, h));
+  auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
+  const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
   for (int l = lb; l < le; l++) {
     const LayerW& w = c->layers[l];
     if (!(fused_embed && l == 0)) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
-    KL(ph, STS_K_QKV, prefill_gemm(c, ph, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
+    KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
     KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, c->inv_freq, layer_pool(c, l), c->geo, rows, d.n_q_heads));
     KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads));
-    KL(ph, STS_K_O, prefill_gemm(c, ph, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd));
+    KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd));
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
-    KL(ph, STS_K_GATEUP, prefill_gemm(c, ph, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
-    KL(ph, STS_K_DOWN, prefill_gemm(c, ph, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp));
+    KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
+    KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp));
   }
   if (le == d.n_layers && want_logits) {
     STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false));

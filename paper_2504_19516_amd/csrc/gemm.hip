@@ -4,17 +4,18 @@
 // holds 8 consecutive k of one A row (or one W row). A workgroup owns a BM x BN tile and each of
 // its waves accumulates a (BM/WGM) x (BN/WGN) sub-tile in 32x32 MFMA blocks.
 //
-// Three main loops. gemm_dl_kernel: K tiles of 64 of both operands go global -> LDS directly (no
+// Main loops. gemm_rows_kernel: the prefill tiles of 256 columns and any multiple of 32 rows up to 256 (8 waves); only
+// the activation tile goes through LDS, the W operands go from the packed weight layout straight into registers.
+// gemm_dl_kernel: K tiles of 64 of both operands go global -> LDS directly (no
 // staging registers, no LDS store instructions): activations into 128-byte rows whose 16-byte chunks
 // are XOR-swizzled so that the 16-byte operand reads are bank-conflict free, packed weights as the
 // operand-order blocks they are in memory; two or three LDS stages;
 // operand reads of the next 16-wide step are slotted between the MFMAs of the current one. It runs
 // the 128x128 tiles with 4 waves (two workgroups per CU) for prefill, the 64x128 (4 waves, two per
 // CU) and 64x256 (8 waves) tiles with split-K for decode batches, and row-major W of callers that
-// bring their own weights. gemm_wreg_kernel: the 256x256 (8 waves) and 128x256 (4 waves) prefill tiles;
-// only the activation tile goes through LDS, the W operands go from the packed weight layout straight
-// into registers. gemm_skinny_kernel: the same for decode batches of up to 64 rows -- tiles of 256 to 512
-// columns, the W operands three K tiles deep in registers.
+// bring their own weights (256-column tiles of those: gemm_rowmajor256_kernel).
+// gemm_skinny_kernel: decode batches of up to 64 rows -- tiles of 256 to 512 columns, the W operands three K tiles deep in
+// registers.
 // Epilogues: bf16 store, fp32 store (split-K partial sums), fp32 residual add, SwiGLU on interleaved
 // gate/up rows.
 //
@@ -25,8 +26,10 @@
 //
 // Lane layout of the 32x32 accumulator block (register r of lane l):
 //   row = 8*(r/4) + 4*(l/32) + r%4,  col = l%32.
+// gemm_rows_kernel uses the 16x16 block with W as the first operand: register r of lane l is column 4*(l/16) + r, row l%16.
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "kernels.h"
 
@@ -51,7 +54,10 @@ struct GemmArgs {
   // so that wave takes 1/tail_f of a tile time; pieces leave fp32 partial tiles in tail_ws and a
   // second small kernel adds them up in a fixed order and applies the epilogue.
   int n_full, full_per_xcd, tail_f, n_pieces, piece_per_xcd;
+  int piece_stride;           // floats between consecutive partial tiles
   float* tail_ws;
+  int row_blocks;             // gemm_rows_kernel: 32-row blocks of M, dealt evenly to tiles_m row tiles, or (tile_blocks > 0)
+  int tile_blocks;            // tile_blocks to each and the rest to the last
 };
 
 // tile index -> tile coordinates: tiles are walked in groups of group_m tile rows so that
@@ -305,27 +311,9 @@ __global__ void __launch_bounds__(WGM* WGN * 64) gemm_dl_kernel(GemmArgs g) {
   store_tile<BM, BN, WGM, WGN, EPI>(g, acc, m0, n0, piece, wm, wn, l32, lh);
 }
 
-// ---- main loop of the 256-column prefill tiles: W operands straight from global memory -----------
-// (WGM = 2: 256 x 256, eight waves; WGM = 1: 128 x 256, four waves with the same 128 x 64 wave tiles, where no W
-// block is shared by two waves and the activation stages are 16 KB)
-// With both operands staged through LDS the 256 x 256 tile moves 256 KB through LDS per 64-wide K tile
-// (64 KB written by the tile loads, 192 KB read as operands by the 8 waves), which at 128 bytes per cycle
-// is as long as the tile's matrix-core work: the loop ran at the LDS's pace, not the MFMAs'. Here only the
-// activation tile goes through LDS (three stages of 32 KB, loaded as above). Each wave reads its W
-// operands -- 64 columns, so two 32-row blocks of the packed layout -- directly into registers, one
-// 16-byte load per lane and 16-wide step from 1 KiB of consecutive memory. One register set serves: the
-// operands of step kk of the next K tile are requested right after step kk of this one has used them, a
-// whole iteration before they are needed. The two waves of a 256 x 256 tile that share a column block load
-// it twice; those bytes come from L2.
-//
-// A wave's vector-memory operations complete in order, and in iteration t it queues: the A loads of tile
-// t + 2 (4), then after each step kk the two W loads of (tile t + 1, step kk). When step kk of tile t waits
-// for its operands, the operations queued after them are the W loads of the later steps of tile t, the A
-// loads of tile t + 2 and the W loads of the earlier steps of tile t + 1: 10 in the steady state, fewer in
-// the last two iterations. The A tile of iteration t + 1 was queued before the operands step 2 waits for,
-// so it has landed when the wave reaches the barrier. The W loads are written in assembly, so the compiler
-// does not know when their registers are valid; the wait names them as in/out operands, which keeps every
-// use behind it.
+// ---- W operands straight from global memory into registers ------------------------------------------
+// The loads are written in assembly, so the compiler does not know when their registers are valid; the wait names them as
+// in/out operands, which keeps every use behind it.
 template <bool NT = false>
 __device__ __forceinline__ void load_w16(bf16x8& dst, const unsigned char* base, unsigned lane_off, int step) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -353,182 +341,6 @@ __device__ __forceinline__ void wait_vmem_for(bf16x8& a, bf16x8& b) {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N) : "memory");
 #endif
-}
-
-template <int EPI, int WGM>
-__global__ void __launch_bounds__(WGM * 256, 2) gemm_wreg_kernel(GemmArgs g) {
-  constexpr int BM = WGM * 128, BN = 256, WGN = 4, BK = 64, NT = WGM * 256, NS = 3;
-  constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
-  constexpr int ROWB = BK * 2, A_CH = BM * 8 / NT, STAGE = BM * ROWB;
-  static_assert(TN == 2 && A_CH == 4, "the waits below count 4 A loads per tile and 2 W loads per step");
-  extern __shared__ __align__(16) unsigned char smem[];
-  unsigned char* arena = smem + GEMM_DL_LDS_BASE;
-
-  int v, kbeg, kend, piece;
-  if (!block_work<BK>(g, &v, &kbeg, &kend, &piece)) return;
-  int tm, tn;
-  tile_coords(g, v, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, lh = lane >> 5;
-  const int swave = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = swave / WGN, wn = swave % WGN;
-
-  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.A + (size_t)m0 * g.lda);
-  unsigned a_off[A_CH];
-#pragma unroll
-  for (int j = 0; j < A_CH; j++) {
-    const int q = j * NT + tid, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
-    a_off[j] = (unsigned)(min(m0 + row, g.M - 1) - m0) * (unsigned)g.lda * 2u + ch * 16;
-  }
-  auto issue_a = [&](int stage, int k) {
-    unsigned char* sa = arena + stage * STAGE + swave * 1024;
-    const unsigned char* ak = a_base + (size_t)k * 2;
-#pragma unroll
-    for (int j = 0; j < A_CH; j++) lds_dma16(ak, a_off[j], sa + j * NT * 16);
-  };
-  // this wave's two 32-row blocks of W: 4 KiB per K tile each, the blocks of one row K / 64 * 4 KiB apart
-  const size_t wrow = (size_t)(g.K >> 6) * 4096;
-  const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.W) + (size_t)((n0 >> 5) + wn * TN) * wrow;
-  const unsigned w_lane = (unsigned)lane * 16u;
-  bf16x8 w[TN][4];
-#pragma unroll
-  for (int j = 0; j < TN; j++)
-#pragma unroll
-    for (int kk = 0; kk < 4; kk++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) w[j][kk][e] = 0;
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; i++)
-#pragma unroll
-    for (int j = 0; j < TN; j++)
-#pragma unroll
-      for (int r = 0; r < 16; r++) acc[i][j][r] = 0.f;
-
-  int koff[4];
-#pragma unroll
-  for (int kk = 0; kk < 4; kk++) koff[kk] = ((kk * 2 + lh) ^ ((l32 >> 1) & 7)) * 16;
-  const int a_row = (wm * WTM + l32) * ROWB;
-
-  const int nk = (kend - kbeg) / BK;
-  // Every iteration queues the same operations, also the last ones, whose loads have no tile left to fetch and
-  // re-read the last K tile into a stage (or registers) nobody uses any more: the waits then count alike throughout.
-  auto tile_k = [&](int t) { return kbeg + min(t, nk - 1) * BK; };
-  // prologue: A(0), A(1), then W(0) step by step; A(0) has landed once at most A(1) and W(0) are outstanding
-  issue_a(0, tile_k(0));
-  issue_a(1, tile_k(1));
-  {
-    const unsigned char* wk = w_base + (size_t)(tile_k(0) >> 6) * 4096;
-#pragma unroll
-    for (int kk = 0; kk < 4; kk++)
-#pragma unroll
-      for (int j = 0; j < TN; j++) load_w16(w[j][kk], wk + j * wrow, w_lane, kk);
-  }
-  wait_vmem<A_CH + 4 * TN>();
-  __syncthreads();
-  bf16x8 af[2][TM];
-#pragma unroll
-  for (int i = 0; i < TM; i++) af[0][i] = *reinterpret_cast<const bf16x8*>(arena + a_row + i * 32 * ROWB + koff[0]);
-
-  int cur = 0;
-  for (int t = 0; t < nk; t++) {
-    const int nxt = cur + 1 == NS ? 0 : cur + 1;
-    const int nx2 = nxt + 1 == NS ? 0 : nxt + 1;
-    const unsigned char* Ac = arena + cur * STAGE + a_row;
-    const unsigned char* An = arena + nxt * STAGE + a_row;
-    const unsigned char* wk = w_base + (size_t)(tile_k(t + 1) >> 6) * 4096;       // W of tile t + 1
-    __builtin_amdgcn_sched_barrier(0);
-    // tile t + 2 goes into the stage that tile t - 1 left at the last barrier
-    issue_a(nx2, tile_k(t + 2));
-    auto step = [&](auto kk_c) {
-      constexpr int kk = decltype(kk_c)::value;
-      __builtin_amdgcn_sched_barrier(0);
-      // queued after these operands: the W loads of the later steps of this tile (6 - 2 kk), the A loads of tile
-      // t + 2 (4), the W loads of the earlier steps of the next tile (2 kk)
-      wait_vmem_for<2 * TN + A_CH + 2>(w[0][kk], w[1][kk]);
-      if constexpr (kk == 3) {
-        // every wave's A loads of tile t + 1 landed before its step-2 operands did: publish the tile, retire this one
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TM; i++) af[0][i] = *reinterpret_cast<const bf16x8*>(An + i * 32 * ROWB + koff[0]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < TM; i++) af[(kk + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(Ac + i * 32 * ROWB + koff[kk + 1]);
-      }
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], w[j][kk], acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int x = 0; x < TM; x++) {
-        __builtin_amdgcn_sched_group_barrier(0x008, TN, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < TN; j++) load_w16(w[j][kk], wk + j * wrow, w_lane, kk);
-    };
-    step(std::integral_constant<int, 0>{});
-    step(std::integral_constant<int, 1>{});
-    step(std::integral_constant<int, 2>{});
-    step(std::integral_constant<int, 3>{});
-    cur = nxt;
-  }
-  // the surplus loads of the last iterations must not land in registers the epilogue reuses
-  wait_vmem_for<0>(w[0][0], w[1][0]);
-  wait_vmem_for<0>(w[0][1], w[1][1]);
-  wait_vmem_for<0>(w[0][2], w[1][2]);
-  wait_vmem_for<0>(w[0][3], w[1][3]);
-  if constexpr ((EPI == EPI_BF16 || EPI == EPI_SWIGLU_BF16) && WGM == 2) {
-    // bf16 outputs leave through LDS: a lane holds one column of its accumulator blocks, so stored directly a wave
-    // instruction writes 64-byte pieces of rows; staged as a [rows][columns] image in the (now free) A stages, every
-    // lane stores 16 bytes and a row of the tile goes out as whole 128-byte lines.
-    if (piece < 0) {
-      constexpr bool SW = EPI == EPI_SWIGLU_BF16;
-      constexpr int OC = SW ? BN / 2 : BN;                    // output columns of the tile
-      constexpr int PR = 64 * 1024 / (OC * 2);                // rows per pass: 64 KB of LDS
-      constexpr int PASSES = BM / PR;                         // SwiGLU: all 256 rows at once; bf16 store: the two wave rows in turn
-      static_assert(PR % WTM == 0 && 3 * STAGE >= 64 * 1024, "a pass holds whole wave rows and fits the A stages");
-      bf16* img = reinterpret_cast<bf16*>(arena);
-      bf16* outp = reinterpret_cast<bf16*>(g.C);
-      const int oc0 = SW ? (n0 >> 1) : n0;
-#pragma unroll
-      for (int pass = 0; pass < PASSES; pass++) {
-        __syncthreads();                                      // the stage reads of the main loop (or the last pass's copy) are done
-        if (wm * WTM / PR == pass) {
-          const int rb = wm * WTM % PR + 4 * lh;
-#pragma unroll
-          for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-              bf16* dst = img + (size_t)(rb + i * 32 + 8 * (r >> 2) + (r & 3)) * OC;
-              if constexpr (SW) {
-                const float gate = acc[i][0][r], up = acc[i][1][r];
-                dst[wn * (WTN / 2) + l32] = f2bf(gate / (1.f + __expf(-gate)) * up);
-              } else {
-#pragma unroll
-                for (int j = 0; j < TN; j++) dst[wn * WTN + j * 32 + l32] = f2bf(acc[i][j][r]);
-              }
-            }
-        }
-        __syncthreads();
-        constexpr int CPRW = OC / 8;                          // 16-byte chunks per row
-#pragma unroll
-        for (int c = 0; c < PR * CPRW / NT; c++) {
-          const int q = c * NT + tid, row = q / CPRW, cc = q % CPRW;
-          const int grow = m0 + pass * PR + row;
-          if (grow < g.M)
-            *reinterpret_cast<u32x4*>(outp + (size_t)grow * g.ldc + oc0 + cc * 8) = *reinterpret_cast<const u32x4*>(img + (size_t)row * OC + cc * 8);
-        }
-      }
-      return;
-    }
-  }
-  store_tile<BM, BN, WGM, WGN, EPI>(g, acc, m0, n0, piece, wm, wn, l32, lh);
 }
 
 // ---- decode batches (up to 64 rows per tile): weights streamed through registers, several K tiles deep ----
@@ -689,6 +501,35 @@ __global__ void __launch_bounds__(512, 2) gemm_skinny_kernel(GemmArgs g) {
   store_tile<BM, 256, 1, 4, EPI>(g, acc, m0, n0, piece, 0, wn, l32, lh);
 }
 
+// Four consecutive columns c .. c + 3 of a tail tile's row: its pieces (stride floats apart, p in the first) added in piece order,
+// then the epilogue. n0: the tile's first column.
+template <int EPI>
+__device__ __forceinline__ void store_fixed_up(const GemmArgs& g, const float* p, int stride, int row, int n0, int c) {
+  f32x4 sum = *reinterpret_cast<const f32x4*>(p), up = {0.f, 0.f, 0.f, 0.f};
+  if (EPI == EPI_SWIGLU_BF16) up = *reinterpret_cast<const f32x4*>(p + 32);
+  for (int z = 1; z < g.tail_f; z++) {
+    sum += *reinterpret_cast<const f32x4*>(p + (size_t)z * stride);
+    if (EPI == EPI_SWIGLU_BF16) up += *reinterpret_cast<const f32x4*>(p + (size_t)z * stride + 32);
+  }
+  const int col = n0 + c;
+  if constexpr (EPI == EPI_SWIGLU_BF16) {
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; i++) o[i] = f2bf(sum[i] / (1.f + __expf(-sum[i])) * up[i]);
+    const int ocol = ((n0 + (c & ~63)) >> 1) + (c & 31);
+    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + ocol) = o;
+  } else if constexpr (EPI == EPI_BF16) {
+    bf16x4 o;
+#pragma unroll
+    for (int i = 0; i < 4; i++) o[i] = f2bf(sum[i]);
+    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + col) = o;
+  } else {
+    f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col);
+    if constexpr (EPI == EPI_RESID_F32) *dst += sum;
+    else *dst = sum;
+  }
+}
+
 // Adds the tail pieces of each split tile in piece order and applies the epilogue. One thread per
 // four consecutive columns.
 template <int BM, int BN, int EPI>
@@ -701,30 +542,373 @@ __global__ void __launch_bounds__(256) gemm_tail_fixup(GemmArgs g) {
   const int row = tm * BM + r;
   if (row >= g.M) return;
   if (EPI == EPI_SWIGLU_BF16 && ((c >> 5) & 1)) return;      // "up" columns are consumed by their gate thread
-  const float* p = g.tail_ws + (size_t)t * g.tail_f * (BM * BN) + (size_t)r * BN + c;
-  f32x4 sum = *reinterpret_cast<const f32x4*>(p), up = {0.f, 0.f, 0.f, 0.f};
-  if (EPI == EPI_SWIGLU_BF16) up = *reinterpret_cast<const f32x4*>(p + 32);
-  for (int z = 1; z < g.tail_f; z++) {
-    sum += *reinterpret_cast<const f32x4*>(p + (size_t)z * (BM * BN));
-    if (EPI == EPI_SWIGLU_BF16) up += *reinterpret_cast<const f32x4*>(p + (size_t)z * (BM * BN) + 32);
+  store_fixed_up<EPI>(g, g.tail_ws + (size_t)t * g.tail_f * (BM * BN) + (size_t)r * BN + c, BM * BN, row, tn * BN, c);
+}
+
+// The operand of a 16 x 16 x 32 step: 32-wide step 0 or 1 of a packed block.
+__device__ __forceinline__ void load_w16x16(bf16x8& dst, const unsigned char* base, unsigned lane_off, int step) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (step == 0) asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(dst) : "v"(lane_off), "s"(base) : "memory");
+  else asm volatile("global_load_dwordx4 %0, %1, %2 offset:2048" : "=v"(dst) : "v"(lane_off), "s"(base) : "memory");
+#endif
+}
+
+// ---- the 256-column prefill tiles of eight waves: row tiles of any multiple of 32 rows up to 256 -------------------
+// A launch's rows are cut into `tiles_m` row tiles of nearly equal height in blocks of 32 (row_range), and a workgroup runs
+// the loop compiled for its height: nothing is computed for padding beyond the last block, and the number of row tiles is
+// free to make whole waves of workgroups (Section 2.2.1): 2048 x 4096 outputs on 224 CUs are 14 x 16 tiles of at most 160 rows,
+// one per CU, where 256-row tiles leave 96 CUs idle or cut along K. T = 301 rows run as two tiles of 160.
+//
+// Eight waves, each all rows x 32 columns in 16 x 16 matrix-core blocks. Only the activation tile goes through LDS (SETS + 1
+// stages, read by every wave); a wave reads its own columns' W operands from the packed layout straight into registers, SETS K tiles
+// ahead. What this split is after is bytes: with all CUs busy the L2s give a CU about 57 GB/s, and two rows of four waves,
+// which load every W block twice (96 KB per 64-wide K tile of 256 x 256, against 64 here), ran at exactly that rate --
+// 28672 x 4096, two row tiles, weights from HBM: 82 / 89 / 93 / 110 us at heights 32 / 128 / 160 / 256, now 54 / 73 / 83 / 109; 14 row
+// tiles of 128 x 4096 x 14336 236 -> 186. The price is LDS traffic (288 KB per K tile instead of 160), which the LDS still delivers
+// in the tile's matrix-core time. Four K tiles ahead pay on short tiles (54 us against 62 with two), two on tall ones.
+//
+// Bound by power on a full GPU: the 32 x 32 x 16 instruction kept the matrix cores busier (77 % of the cycles against 65 %) but
+// at 1.47 GHz, where 16 x 16 x 32, which moves half the accumulator registers per product, holds 1.90 GHz (8192 x 28672 x 4096 on
+// 256 CUs: 1434 -> 1392 us). The W block is the first operand, so a lane holds four consecutive output columns: fp32 results
+// leave in 16-byte pieces.
+//
+// Order of a wave's vector-memory operations (they complete in order): iteration t queues the ACH A loads of tile t + SETS, then after
+// step s the TN W loads of (tile t + SETS, step s); the prologue queues the first SETS tiles in the same order. When step s
+// of tile t waits for its operands, WAIT = TN + ACH + (SETS - 1)(ACH + 2 TN) operations were queued after them, in every iteration: the
+// last ones re-read the last K tile into stages and registers nobody uses. At the barrier of iteration t the A loads of tile
+// t + 1 must have landed: WAIT - ACH operations are younger. Tile t + SETS goes into the stage that tile t - 1 left at the
+// last barrier (SETS + 1 stages). Waves without a full share of the A tile's 1 KiB pieces queue loads of its first bytes into
+// a spare KiB, so that all count alike.
+constexpr int ROWS_LDS = 136 * 1024;              // A stages of a gemm_rows_kernel workgroup (or its output image)
+__device__ __forceinline__ void row_range(const GemmArgs& g, int tm, int* row0, int* blocks) {
+  const int b0 = g.tile_blocks ? tm * g.tile_blocks : (int)((long long)tm * g.row_blocks / g.tiles_m);
+  const int b1 = g.tile_blocks ? min(b0 + g.tile_blocks, g.row_blocks) : (int)((long long)(tm + 1) * g.row_blocks / g.tiles_m);
+  *row0 = b0 * 32; *blocks = b1 - b0;
+}
+
+template <typename F, int... P>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, P...>) { (f(std::integral_constant<int, P>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+template <int EPI, int TM>
+__device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char* arena, int m0, int n0, int kbeg, int kend, int piece) {
+  constexpr int BM = 32 * TM, BN = 256, BK = 64, NT = 512, TN = 2, RB = 2 * TM;
+  constexpr int SETS = TM > 4 ? 2 : 4, NS = SETS + 1;
+  constexpr int ROWB = BK * 2, STAGE = BM * ROWB, PIECES = STAGE / 1024, ACH = (PIECES + 7) / 8;
+  constexpr int WAIT = TN + ACH + (SETS - 1) * (ACH + 2 * TN);
+  static_assert(NS * STAGE <= ROWS_LDS && WAIT < 64, "the stages fit the launch's LDS, the waits vmcnt");
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int swave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.A + (size_t)m0 * g.lda);
+  unsigned a_off[ACH];
+#pragma unroll
+  for (int j = 0; j < ACH; j++) {
+    const int q = (j * 8 + swave) * 64 + lane, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
+    a_off[j] = j * 8 + swave < PIECES ? (unsigned)(min(m0 + row, g.M - 1) - m0) * (unsigned)g.lda * 2u + ch * 16 : 0u;
   }
-  const int col = tn * BN + c;
-  if constexpr (EPI == EPI_SWIGLU_BF16) {
-    bf16x4 o;
+  auto issue_a = [&](int stage, int k) {
+    const unsigned char* ak = a_base + (size_t)k * 2;
 #pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = f2bf(sum[i] / (1.f + __expf(-sum[i])) * up[i]);
-    const int ocol = ((tn * BN + (c & ~63)) >> 1) + (c & 31);
-    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + ocol) = o;
-  } else if constexpr (EPI == EPI_BF16) {
-    bf16x4 o;
+    for (int j = 0; j < ACH; j++)
+      lds_dma16(ak, a_off[j], j * 8 + swave < PIECES ? arena + stage * STAGE + (j * 8 + swave) * 1024 : arena + ROWS_LDS);
+  };
+  // A wave's 32 columns are one half (16 columns) of each of two neighbouring 32-column blocks -- a gate block and its up
+  // block in the SwiGLU form. Operand of block j, step s: 256 bytes out of each quarter of a 2 KiB half of the block's 4 KiB.
+  const size_t wrow = (size_t)(g.K >> 6) * 4096;
+  const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.W) + (size_t)((n0 >> 5) + (swave & ~1)) * wrow;
+  const unsigned w_lane = (unsigned)((lq >> 1) * 1024 + (lq & 1) * 512 + l16 * 16 + (swave & 1) * 256);
+  bf16x8 w[SETS][2][TN];
 #pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = f2bf(sum[i]);
-    *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + col) = o;
+  for (int z = 0; z < SETS; z++)
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int e = 0; e < 8; e++) w[z][s][j][e] = 0;
+  auto load_w = [&](int z, int s, const unsigned char* wk) {
+#pragma unroll
+    for (int j = 0; j < TN; j++) load_w16x16(w[z][s][j], wk + j * wrow, w_lane, s);
+  };
+
+  f32x4 acc[RB][TN];
+#pragma unroll
+  for (int i = 0; i < RB; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int koff[2];
+#pragma unroll
+  for (int s = 0; s < 2; s++) koff[s] = ((s * 4 + lq) ^ ((l16 >> 1) & 7)) * 16;
+  const int a_row = l16 * ROWB;
+
+  const int nk = (kend - kbeg) / BK;
+  auto tile_k = [&](int t) { return kbeg + min(t, nk - 1) * BK; };
+#pragma unroll
+  for (int z = 0; z < SETS; z++) {
+    issue_a(z, tile_k(z));
+    const unsigned char* wk = w_base + (size_t)(tile_k(z) >> 6) * 4096;
+    load_w(z, 0, wk);
+    load_w(z, 1, wk);
+  }
+  wait_vmem<WAIT - ACH + TN>();                              // A(0) has landed
+  __syncthreads();
+  // A step's RB row blocks are taken in groups of up to four: a group's operands are read while the group before it is
+  // multiplied.
+  constexpr int G = (RB + 3) / 4, GROUPS = 2 * G;
+  bf16x8 af[2][4];
+#pragma unroll
+  for (int i = 0; i < (RB < 4 ? RB : 4); i++) af[0][i] = *reinterpret_cast<const bf16x8*>(arena + a_row + i * 16 * ROWB + koff[0]);
+
+  int cur = 0;
+  auto tile = [&](int t, auto z_c) {
+    constexpr int z = decltype(z_c)::value;                  // register set of tile t: t % SETS
+    const bool live = t < nk;                                // the surplus tiles of the last round only keep the queue's shape
+    const int nxt = cur + 1 == NS ? 0 : cur + 1;
+    const unsigned char* Ac = arena + cur * STAGE + a_row;
+    const unsigned char* An = arena + nxt * STAGE + a_row;
+    const int ka = tile_k(t + SETS);
+    const unsigned char* wk = w_base + (size_t)(ka >> 6) * 4096;
+    __builtin_amdgcn_sched_barrier(0);
+    issue_a(cur == 0 ? NS - 1 : cur - 1, ka);
+    static_for<GROUPS>([&](auto p_c) {
+      constexpr int p = decltype(p_c)::value, s = p / G, h = p % G, cnt = RB - h * 4 < 4 ? RB - h * 4 : 4;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (h == 0) {
+        wait_vmem_for<WAIT>(w[z][s][0], w[z][s][1]);
+      }
+      constexpr int pn = p + 1 == GROUPS ? 0 : p + 1, sn = pn / G, hn = pn % G, cntn = RB - hn * 4 < 4 ? RB - hn * 4 : 4;
+      if constexpr (pn == 0) {
+        wait_vmem<WAIT - ACH>();                             // publish tile t + 1, retire this one
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const unsigned char* src = pn == 0 ? An : Ac;
+#pragma unroll
+      for (int i = 0; i < cntn; i++) af[(p + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(src + (hn * 4 + i) * 16 * ROWB + koff[sn]);
+      if (live) {
+#pragma unroll
+        for (int i = 0; i < cnt; i++)
+#pragma unroll
+          for (int j = 0; j < TN; j++)
+            acc[h * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[z][s][j], af[p & 1][i], acc[h * 4 + i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (h == G - 1) load_w(z, s, wk);
+    });
+    cur = nxt;
+  };
+  for (int t = 0; t < nk; t += SETS) static_for<SETS>([&](auto z_c) { tile(t + decltype(z_c)::value, z_c); });
+  // the surplus loads of the last iterations must not land in registers the epilogue reuses
+#pragma unroll
+  for (int z = 0; z < SETS; z++)
+#pragma unroll
+    for (int s = 0; s < 2; s++) wait_vmem_for<0>(w[z][s][0], w[z][s][1]);
+
+  // ---- outputs: lane (lq, l16) holds columns 4 lq .. + 4 of 16-column block j, rows 16 i + l16 of its wave tile
+  const int rloc = l16, cloc = (swave >> 1) * 64 + (swave & 1) * 16 + 4 * lq;
+  constexpr int JS = 32;                                     // columns from one block to the next
+  if (piece >= 0) {                                          // a tail piece leaves its partial tile, row-major [height][256]
+    float* part = g.tail_ws + (size_t)piece * g.piece_stride + (size_t)rloc * BN + cloc;
+#pragma unroll
+    for (int i = 0; i < RB; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) *reinterpret_cast<f32x4*>(part + (size_t)i * 16 * BN + j * JS) = acc[i][j];
+    return;
+  }
+  if constexpr (EPI == EPI_F32 || EPI == EPI_RESID_F32) {
+    float* out = reinterpret_cast<float*>(g.C) + (EPI == EPI_F32 ? (size_t)blockIdx.y * g.split_stride : 0) + n0 + cloc;
+#pragma unroll
+    for (int i = 0; i < RB; i++) {
+      const int row = m0 + rloc + i * 16;
+      if (row >= g.M) continue;
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)row * g.ldc + j * JS);
+        if constexpr (EPI == EPI_RESID_F32) *dst += acc[i][j]; else *dst = acc[i][j];
+      }
+    }
   } else {
-    f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + (size_t)row * g.ldc + col);
-    if constexpr (EPI == EPI_RESID_F32) *dst += sum;
-    else *dst = sum;
+    // bf16 outputs leave through the (now free) A stages as a [rows][columns] image, so that a row of the tile goes out as whole
+    // 128-byte lines; 32 bytes of padding per row spread the 8-byte writes of 16 rows over the banks
+    constexpr bool SW = EPI == EPI_SWIGLU_BF16;
+    constexpr int OC = SW ? BN / 2 : BN, RS = OC + 16;
+    static_assert(BM * RS * 2 <= ROWS_LDS, "the image fits the stages");
+    bf16* img = reinterpret_cast<bf16*>(arena);
+    bf16* outp = reinterpret_cast<bf16*>(g.C) + (SW ? (n0 >> 1) : n0);
+    __syncthreads();                                         // the stage reads of the main loop are done
+    bf16* dst = img + (size_t)rloc * RS + (SW ? swave * 16 + 4 * lq : cloc);
+#pragma unroll
+    for (int i = 0; i < RB; i++)
+#pragma unroll
+      for (int j = 0; j < (SW ? 1 : TN); j++) {
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          if constexpr (SW) {
+            const float gate = acc[i][0][e], up = acc[i][1][e];
+            o[e] = f2bf(gate / (1.f + __expf(-gate)) * up);
+          } else {
+            o[e] = f2bf(acc[i][j][e]);
+          }
+        }
+        *reinterpret_cast<bf16x4*>(dst + (size_t)i * 16 * RS + j * JS) = o;
+      }
+    __syncthreads();
+    constexpr int CPRW = OC / 8;                             // 16-byte chunks per row
+#pragma unroll
+    for (int c = 0; c < BM * CPRW / NT; c++) {
+      const int q = c * NT + tid, row = q / CPRW, cc = q % CPRW;
+      const int grow = m0 + row;
+      if (grow < g.M)
+        *reinterpret_cast<u32x4*>(outp + (size_t)grow * g.ldc + cc * 8) = *reinterpret_cast<const u32x4*>(img + (size_t)row * RS + cc * 8);
+    }
   }
+}
+
+template <int EPI>
+__global__ void __launch_bounds__(512, 2) gemm_rows_kernel(GemmArgs g) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* arena = smem + GEMM_DL_LDS_BASE;
+  int v, kbeg, kend, piece, tm, tn, m0, blocks;
+  if (!block_work<64>(g, &v, &kbeg, &kend, &piece)) return;
+  tile_coords(g, v, &tm, &tn);
+  row_range(g, tm, &m0, &blocks);
+  const int n0 = tn * 256;
+  switch (blocks) {                                          // workgroup-uniform
+    case 1: gemm_rows_body<EPI, 1>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 2: gemm_rows_body<EPI, 2>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 3: gemm_rows_body<EPI, 3>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 4: gemm_rows_body<EPI, 4>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 5: gemm_rows_body<EPI, 5>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 6: gemm_rows_body<EPI, 6>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 7: gemm_rows_body<EPI, 7>(g, arena, m0, n0, kbeg, kend, piece); break;
+    case 8: gemm_rows_body<EPI, 8>(g, arena, m0, n0, kbeg, kend, piece); break;
+    default: break;
+  }
+}
+
+// ---- the same tiles with row-major W (callers that bring their own weights; fp32 store) --------------------------
+// Both operands through LDS as in gemm_dl_kernel (two stages), waves of 128 x 64, and the 16 x 16 x 32 instruction: an element's
+// products are summed in the order of gemm_rows_kernel. A step's operands are taken in two groups of four row blocks.
+template <int WGM>
+__global__ void __launch_bounds__(WGM * 256, 2) gemm_rowmajor256_kernel(GemmArgs g) {
+  constexpr int BM = WGM * 128, BN = 256, BK = 64, NT = WGM * 256, ROWB = BK * 2, STAGE = (BM + BN) * ROWB;
+  constexpr int A_CH = BM * 8 / NT, B_CH = BN * 8 / NT;
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* arena = smem + GEMM_DL_LDS_BASE;
+  int v, kbeg, kend, piece, tm, tn;
+  if (!block_work<BK>(g, &v, &kbeg, &kend, &piece)) return;
+  tile_coords(g, v, &tm, &tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
+  const int swave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = swave >> 2, wn = swave & 3;
+
+  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.A + (size_t)m0 * g.lda);
+  const unsigned char* b_base = reinterpret_cast<const unsigned char*>(g.W + (size_t)n0 * g.ldw);
+  unsigned a_off[A_CH], b_off[B_CH];
+#pragma unroll
+  for (int j = 0; j < A_CH; j++) {
+    const int q = j * NT + tid, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
+    a_off[j] = (unsigned)(min(m0 + row, g.M - 1) - m0) * (unsigned)g.lda * 2u + ch * 16;
+  }
+#pragma unroll
+  for (int j = 0; j < B_CH; j++) {
+    const int q = j * NT + tid, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
+    b_off[j] = (unsigned)row * (unsigned)g.ldw * 2u + ch * 16;
+  }
+  auto issue = [&](int stage, int k) {
+    unsigned char* sa = arena + stage * STAGE + swave * 1024;
+#pragma unroll
+    for (int j = 0; j < A_CH; j++) lds_dma16(a_base + (size_t)k * 2, a_off[j], sa + j * NT * 16);
+#pragma unroll
+    for (int j = 0; j < B_CH; j++) lds_dma16(b_base + (size_t)k * 2, b_off[j], sa + BM * ROWB + j * NT * 16);
+  };
+  f32x4 acc[8][4];
+#pragma unroll
+  for (int i = 0; i < 8; i++)
+#pragma unroll
+    for (int j = 0; j < 4; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int koff[2];
+#pragma unroll
+  for (int s = 0; s < 2; s++) koff[s] = ((s * 4 + lq) ^ ((l16 >> 1) & 7)) * 16;
+  const int a_row = (wm * 128 + l16) * ROWB, b_row = BM * ROWB + (wn * 64 + l16) * ROWB;
+
+  const int nk = (kend - kbeg) / BK;
+  issue(0, kbeg);
+  if (nk > 1) issue(1, kbeg + BK);
+  if (nk > 1) wait_vmem<A_CH + B_CH>(); else wait_vmem<0>();
+  __syncthreads();
+  bf16x8 af[2][4], wf[2][4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    af[0][i] = *reinterpret_cast<const bf16x8*>(arena + a_row + i * 16 * ROWB + koff[0]);
+    wf[0][i] = *reinterpret_cast<const bf16x8*>(arena + b_row + i * 16 * ROWB + koff[0]);
+  }
+  for (int t = 0; t < nk; t++) {
+    const unsigned char* cur = arena + (t & 1) * STAGE;
+    const unsigned char* nxt = arena + ((t + 1) & 1) * STAGE;
+    static_for<4>([&](auto p_c) {
+      constexpr int p = decltype(p_c)::value, s = p >> 1, h = p & 1, pn = (p + 1) & 3, sn = pn >> 1, hn = pn & 1;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (pn == 0) {
+        // tile t + 1 has landed and this one's operands are in registers: its stage takes tile t + 2
+        wait_vmem<0>();
+        __syncthreads();
+        if (t + 2 < nk) issue(t & 1, kbeg + (t + 2) * BK);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      const unsigned char* src = pn == 0 ? nxt : cur;          // (after the last tile: a stage nobody uses the operands of)
+#pragma unroll
+      for (int i = 0; i < 4; i++) af[pn & 1][i] = *reinterpret_cast<const bf16x8*>(src + a_row + (hn * 4 + i) * 16 * ROWB + koff[sn]);
+      if constexpr (hn == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) wf[sn][j] = *reinterpret_cast<const bf16x8*>(src + b_row + j * 16 * ROWB + koff[sn]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+          acc[h * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s][j], af[p & 1][i], acc[h * 4 + i][j], 0, 0, 0);
+      constexpr int NR = hn == 0 ? 8 : 4;
+#pragma unroll
+      for (int x = 0; x < NR; x++) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 16 / NR, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  const int rloc = wm * 128 + l16, cloc = wn * 64 + 4 * lq;
+  float* out = piece >= 0 ? g.tail_ws + (size_t)piece * g.piece_stride + cloc
+                          : reinterpret_cast<float*>(g.C) + (size_t)blockIdx.y * g.split_stride + (size_t)m0 * g.ldc + n0 + cloc;
+  const int ld = piece >= 0 ? BN : g.ldc, rows = piece >= 0 ? BM : g.M - m0;
+#pragma unroll
+  for (int i = 0; i < 8; i++) {
+    const int row = rloc + i * 16;
+    if (row >= rows) continue;
+#pragma unroll
+    for (int j = 0; j < 4; j++) *reinterpret_cast<f32x4*>(out + (size_t)row * ld + j * 16) = acc[i][j];
+  }
+}
+
+// Adds the tail pieces of each split tile of gemm_rows_kernel in piece order and applies the epilogue. One thread per four
+// consecutive columns; blocks past the tile's height leave.
+template <int EPI>
+__global__ void __launch_bounds__(256) gemm_rows_fixup(GemmArgs g) {
+  constexpr int BN = 256;
+  const int t = blockIdx.x;                                   // tail tile
+  const int e = blockIdx.y * 256 + threadIdx.x;
+  const int r = e / (BN / 4), c = (e % (BN / 4)) * 4;
+  int tm, tn, m0, blocks;
+  tile_coords(g, g.n_full + t, &tm, &tn);
+  row_range(g, tm, &m0, &blocks);
+  const int row = m0 + r;
+  if (r >= blocks * 32 || row >= g.M) return;
+  if (EPI == EPI_SWIGLU_BF16 && ((c >> 5) & 1)) return;      // "up" columns are consumed by their gate thread
+  const float* p = g.tail_ws + (size_t)t * g.tail_f * g.piece_stride + (size_t)r * BN + c;
+  store_fixed_up<EPI>(g, p, g.piece_stride, row, tn * BN, c);
 }
 
 // How the tiles of one launch are divided when the partition holds `slots` workgroups of this
@@ -748,25 +932,42 @@ void gemm_tail_plan(int tiles, int ksteps, int slots, long long max_pieces, int*
   *n_full = full; *f = best;
 }
 
+// Whole tiles, tail pieces (stride floats each) and slices along K of a launch; returns the number of slices (gridDim.y).
+static int plan_launch(GemmArgs* g, int tiles, int splits, const GemmTail* tail, int piece_floats) {
+  constexpr int BK = 64;
+  g->group_m = 8;
+  const int ksteps = g->K / BK;
+  g->n_full = tiles; g->tail_f = 1; g->n_pieces = 0; g->piece_per_xcd = 0; g->tail_ws = nullptr; g->piece_stride = piece_floats;
+  if (tail && tail->ws && splits == 1 && g->ldc % 4 == 0) {
+    int n_full, f;
+    gemm_tail_plan(tiles, ksteps, tail->slots, (long long)(tail->ws_bytes / (piece_floats * sizeof(float))), &n_full, &f);
+    if (f > 1) {
+      g->n_full = n_full; g->tail_f = f; g->n_pieces = (tiles - n_full) * f;
+      g->piece_per_xcd = (g->n_pieces + 7) / 8;
+      g->tail_ws = tail->ws;
+    }
+  }
+  g->full_per_xcd = (g->n_full + 7) / 8;
+  const int per = (ksteps + splits - 1) / splits;
+  g->k_per_split = per * BK;
+  return (ksteps + per - 1) / per;
+}
+
 // NS: LDS stages of the main loop.
 template <int BM, int BN, int WGM, int WGN, int EPI, int NS>
 static hipError_t launch_cfg(hipStream_t s, GemmArgs g, int splits, const GemmTail* tail) {
   constexpr int NT = WGM * WGN * 64, BK = 64;
   constexpr size_t lds_dl = GEMM_DL_LDS_BASE + NS * (size_t)(BM + BN) * BK * sizeof(bf16);
-  constexpr size_t lds_wreg = GEMM_DL_LDS_BASE + 3 * (size_t)BM * BK * sizeof(bf16);    // gemm_wreg_kernel: three stages of the A tile
-  // packed W: tiles of 256 columns with wave tiles of 128 x 64 take their W operands straight from global memory
-  constexpr bool WREG = BN == 256 && WGN == 4 && BM == WGM * 128;
   // decode batches: 64-row tiles, 64 columns per wave, the W operands GEMM_SKINNY_PD tiles deep in registers
   constexpr bool SKINNY = BM == 64 && WGM == 1 && BN == WGN * 64;
   constexpr size_t lds_skinny = GEMM_DL_LDS_BASE + (size_t)(GEMM_SKINNY_PD + 2) * BM * BK * sizeof(bf16) + 1024;
   void (*kern)(GemmArgs) = nullptr;
   void (*kern_rowmajor)(GemmArgs) = nullptr;       // row-major W: the fp32-store epilogue only (callers that bring their own weights)
-  if constexpr (WREG) kern = gemm_wreg_kernel<EPI, WGM>;
-  else if constexpr (SKINNY) kern = g.stream_nt ? gemm_skinny_kernel<EPI, GEMM_SKINNY_PD, true> : gemm_skinny_kernel<EPI, GEMM_SKINNY_PD, false>;
+  if constexpr (SKINNY) kern = g.stream_nt ? gemm_skinny_kernel<EPI, GEMM_SKINNY_PD, true> : gemm_skinny_kernel<EPI, GEMM_SKINNY_PD, false>;
   else kern = gemm_dl_kernel<BM, BN, WGM, WGN, EPI, NS>;
   if constexpr (EPI == EPI_F32 && !SKINNY) kern_rowmajor = gemm_dl_kernel<BM, BN, WGM, WGN, EPI, NS, false>;
   if (!g.w_packed && !kern_rowmajor) return hipErrorInvalidValue;
-  constexpr size_t lds_packed = WREG ? lds_wreg : SKINNY ? lds_skinny : lds_dl;
+  constexpr size_t lds_packed = SKINNY ? lds_skinny : lds_dl;
   const size_t lds = !g.w_packed ? lds_dl : lds_packed;
   static std::atomic<bool> attr_set{false};        // the two phases' control threads may launch the same shape
   if (!attr_set.load()) {
@@ -782,22 +983,7 @@ static hipError_t launch_cfg(hipStream_t s, GemmArgs g, int splits, const GemmTa
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = g.N / BN;
   const int tiles = g.tiles_m * g.tiles_n;
-  g.group_m = 8;
-  const int ksteps = g.K / BK;
-  g.n_full = tiles; g.tail_f = 1; g.n_pieces = 0; g.piece_per_xcd = 0; g.tail_ws = nullptr;
-  if (tail && tail->ws && splits == 1 && g.ldc % 4 == 0) {
-    int n_full, f;
-    gemm_tail_plan(tiles, ksteps, tail->slots, (long long)(tail->ws_bytes / (BM * BN * sizeof(float))), &n_full, &f);
-    if (f > 1) {
-      g.n_full = n_full; g.tail_f = f; g.n_pieces = (tiles - n_full) * f;
-      g.piece_per_xcd = (g.n_pieces + 7) / 8;
-      g.tail_ws = tail->ws;
-    }
-  }
-  g.full_per_xcd = (g.n_full + 7) / 8;
-  const int per = (ksteps + splits - 1) / splits;
-  g.k_per_split = per * BK;
-  const int ny = (ksteps + per - 1) / per;
+  const int ny = plan_launch(&g, tiles, splits, tail, BM * BN);
   if (!g.w_packed) kern = kern_rowmajor;
   hipLaunchKernelGGL(kern, dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(NT), lds, s, g);
   if constexpr (!SKINNY) {
@@ -807,21 +993,72 @@ static hipError_t launch_cfg(hipStream_t s, GemmArgs g, int splits, const GemmTa
   return hipGetLastError();
 }
 
+// gemm_rows_kernel: the rows in row_tiles tiles of nearly equal height (0: as few as 256 rows allow).
 template <int EPI>
-static hipError_t launch_epi(hipStream_t s, int cfg, const GemmArgs& g, int splits, const GemmTail* tail) {
+static hipError_t launch_rows(hipStream_t s, GemmArgs g, int splits, const GemmTail* tail, int row_tiles, int tile_blocks) {
+  constexpr size_t lds = GEMM_DL_LDS_BASE + ROWS_LDS + 1024;
+  static std::atomic<bool> attr_set{false};        // the two phases' control threads may launch the same shape
+  if (!attr_set.load()) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_rows_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set.store(true);
+  }
+  g.row_blocks = (g.M + 31) / 32;
+  g.tile_blocks = row_tiles > 0 ? 0 : tile_blocks;
+  g.tiles_m = row_tiles > 0 ? row_tiles : (g.row_blocks + tile_blocks - 1) / tile_blocks;
+  g.tiles_n = g.N / 256;
+  const int height = row_tiles > 0 ? (g.row_blocks + row_tiles - 1) / row_tiles : std::min(tile_blocks, g.row_blocks);   // blocks of the tallest tile
+  if (height > 8 || g.tiles_m > g.row_blocks) return hipErrorInvalidValue;
+  const int tiles = g.tiles_m * g.tiles_n;
+  const int ny = plan_launch(&g, tiles, splits, tail, height * 32 * 256);
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(512), lds, s, g);
+  if (g.n_pieces > 0)
+    hipLaunchKernelGGL((gemm_rows_fixup<EPI>), dim3(tiles - g.n_full, height * 8), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+
+// Row-major W with a 256-column tile.
+template <int WGM>
+static hipError_t launch_rowmajor256(hipStream_t s, GemmArgs g, int splits, const GemmTail* tail) {
+  constexpr int BM = WGM * 128, BN = 256;
+  constexpr size_t lds = GEMM_DL_LDS_BASE + 2 * (size_t)(BM + BN) * 64 * sizeof(bf16);
+  static std::atomic<bool> attr_set{false};
+  if (!attr_set.load()) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_rowmajor256_kernel<WGM>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set.store(true);
+  }
+  g.tiles_m = (g.M + BM - 1) / BM;
+  g.tiles_n = g.N / BN;
+  const int tiles = g.tiles_m * g.tiles_n;
+  const int ny = plan_launch(&g, tiles, splits, tail, BM * BN);
+  hipLaunchKernelGGL((gemm_rowmajor256_kernel<WGM>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(WGM * 256), lds, s, g);
+  if (g.n_pieces > 0)
+    hipLaunchKernelGGL((gemm_tail_fixup<BM, BN, EPI_F32>), dim3(tiles - g.n_full, BM * BN / 1024), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+
+template <int EPI>
+static hipError_t launch_epi(hipStream_t s, int cfg, const GemmArgs& g, int splits, const GemmTail* tail, int row_tiles) {
+  if (cfg == GEMM_256x256 || cfg == GEMM_128x256) {
+    if (g.w_packed) return launch_rows<EPI>(s, g, splits, tail, cfg == GEMM_256x256 ? row_tiles : 0, cfg == GEMM_256x256 ? 8 : 4);
+    if constexpr (EPI == EPI_F32) return cfg == GEMM_256x256 ? launch_rowmajor256<2>(s, g, splits, tail) : launch_rowmajor256<1>(s, g, splits, tail);
+    return hipErrorInvalidValue;
+  }
   switch (cfg) {
     case GEMM_128x128: return launch_cfg<128, 128, 2, 2, EPI, 2>(s, g, splits, tail);
-    case GEMM_64x256: return launch_cfg<64, 256, 1, 8, EPI, 3>(s, g, splits, tail);
-    case GEMM_64x128: return launch_cfg<64, 128, 1, 4, EPI, 3>(s, g, splits, tail);
-    case GEMM_256x256: return launch_cfg<256, 256, 2, 4, EPI, 2>(s, g, splits, tail);
-    case GEMM_128x256: return launch_cfg<128, 256, 1, 4, EPI, 2>(s, g, splits, tail);
+    case GEMM_64x256: if constexpr (EPI != EPI_SWIGLU_BF16) return launch_cfg<64, 256, 1, 8, EPI, 3>(s, g, splits, tail); else break;
+    case GEMM_64x128:     // SwiGLU: wave tiles of 32 x 64, one gate/up pair
+      if constexpr (EPI == EPI_SWIGLU_BF16) return launch_cfg<64, 128, 2, 2, EPI, 3>(s, g, splits, tail);
+      else return launch_cfg<64, 128, 1, 4, EPI, 3>(s, g, splits, tail);
     case GEMM_64x256S: return launch_cfg<64, 256, 1, 4, EPI, 3>(s, g, splits, nullptr);
     case GEMM_64x320S: return launch_cfg<64, 320, 1, 5, EPI, 3>(s, g, splits, nullptr);
     case GEMM_64x384S: return launch_cfg<64, 384, 1, 6, EPI, 3>(s, g, splits, nullptr);
     case GEMM_64x448S: return launch_cfg<64, 448, 1, 7, EPI, 3>(s, g, splits, nullptr);
     case GEMM_64x512S: return launch_cfg<64, 512, 1, 8, EPI, 3>(s, g, splits, nullptr);
-    default: return hipErrorInvalidValue;
+    default: break;
   }
+  return hipErrorInvalidValue;
 }
 
 int gemm_tile_n(int cfg) {
@@ -839,34 +1076,26 @@ int gemm_wgs_per_cu(int cfg) { return cfg == GEMM_256x256 || cfg == GEMM_64x256 
 // K % 64 == 0, N % tile_n == 0, leading dimensions multiples of 8 elements, M >= 1; W packed (ldw == K) or,
 // for the fp32-store epilogue, row-major.
 // With splits > 1 (EPI_F32 only) partial sums go to C + z * split_stride. With `tail` (splits == 1)
-// the tiles of the last, partly filled wave of workgroups are cut along K (see GemmArgs).
+// the tiles of the last, partly filled wave of workgroups are cut along K (see GemmArgs). row_tiles: row tiles of a 256x256
+// launch (0: as few as 256 rows allow).
 hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, const bf16* W, int ldw,
-                     void* C, int ldc, int M, int N, int K, int splits, long long split_stride, const GemmTail* tail, bool w_packed, bool stream_nt) {
+                     void* C, int ldc, int M, int N, int K, int splits, long long split_stride, const GemmTail* tail, bool w_packed, bool stream_nt,
+                     int row_tiles) {
   if (M < 1 || K % 64 != 0 || N % gemm_tile_n(cfg) != 0 || lda % 8 != 0 || ldw % 8 != 0) return hipErrorInvalidValue;
   if (w_packed && ldw != K) return hipErrorInvalidValue;          // packed blocks are addressed by K alone
   if (splits < 1 || (splits > 1 && epi != EPI_F32)) return hipErrorInvalidValue;
-  if (cfg == GEMM_256x256 && (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16) && ldc % 8 != 0) return hipErrorInvalidValue;   // 16-byte output stores
+  // 16-byte output stores
+  if ((cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 ? 8 : 4) != 0) return hipErrorInvalidValue;
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_64x256) return hipErrorInvalidValue;   // its wave tile is one 32-column block, not a gate/up pair
-  if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not instantiated: the shape serves the O and down projections
+  if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not offered: the shape is for the O and down projections
   GemmArgs g{};
   g.A = A; g.W = W; g.C = C; g.lda = lda; g.ldw = ldw; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
   g.split_stride = split_stride; g.w_packed = w_packed ? 1 : 0; g.stream_nt = stream_nt ? 1 : 0;
   switch (epi) {
-    case EPI_BF16: return launch_epi<EPI_BF16>(s, cfg, g, splits, tail);
-    case EPI_F32: return launch_epi<EPI_F32>(s, cfg, g, splits, tail);
-    case EPI_RESID_F32: return launch_epi<EPI_RESID_F32>(s, cfg, g, splits, tail);
-    case EPI_SWIGLU_BF16:
-      switch (cfg) {   // instantiated only where the wave tile holds gate/up block pairs
-        case GEMM_256x256: return launch_cfg<256, 256, 2, 4, EPI_SWIGLU_BF16, 2>(s, g, 1, tail);
-        case GEMM_128x128: return launch_cfg<128, 128, 2, 2, EPI_SWIGLU_BF16, 2>(s, g, 1, tail);
-        case GEMM_64x256S: return launch_cfg<64, 256, 1, 4, EPI_SWIGLU_BF16, 3>(s, g, 1, nullptr);
-        case GEMM_64x320S: return launch_cfg<64, 320, 1, 5, EPI_SWIGLU_BF16, 3>(s, g, 1, nullptr);
-        case GEMM_64x384S: return launch_cfg<64, 384, 1, 6, EPI_SWIGLU_BF16, 3>(s, g, 1, nullptr);
-        case GEMM_64x448S: return launch_cfg<64, 448, 1, 7, EPI_SWIGLU_BF16, 3>(s, g, 1, nullptr);
-        case GEMM_64x512S: return launch_cfg<64, 512, 1, 8, EPI_SWIGLU_BF16, 3>(s, g, 1, nullptr);
-        case GEMM_64x128: return launch_cfg<64, 128, 2, 2, EPI_SWIGLU_BF16, 3>(s, g, 1, tail);    // wave tiles of 32 x 64: one gate/up pair
-        default: return hipErrorInvalidValue;
-      }
+    case EPI_BF16: return launch_epi<EPI_BF16>(s, cfg, g, splits, tail, row_tiles);
+    case EPI_F32: return launch_epi<EPI_F32>(s, cfg, g, splits, tail, row_tiles);
+    case EPI_RESID_F32: return launch_epi<EPI_RESID_F32>(s, cfg, g, splits, tail, row_tiles);
+    case EPI_SWIGLU_BF16: return launch_epi<EPI_SWIGLU_BF16>(s, cfg, g, 1, tail, row_tiles);
     default: return hipErrorInvalidValue;
   }
 }

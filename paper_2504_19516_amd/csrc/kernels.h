@@ -19,7 +19,7 @@ void gemm_tail_plan(int tiles, int ksteps, int slots, long long max_pieces, int*
 // the packed layout below. The row-major form exists for the fp32-store epilogue only.
 hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, const bf16* W, int ldw,
                      void* C, int ldc, int M, int N, int K, int splits, long long split_stride,
-                     const GemmTail* tail = nullptr, bool w_packed = true, bool stream_nt = false);
+                     const GemmTail* tail = nullptr, bool w_packed = true, bool stream_nt = false, int row_tiles = 0);
 
 // Packed GEMM weights: blocks of 32 rows x 64 columns (4 KiB), stored one after the other along K, then
 // along N. A block is laid out the way the matrix cores take a W operand: four pieces of 1 KiB, one per

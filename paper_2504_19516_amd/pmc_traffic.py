@@ -26,16 +26,17 @@ import re
 import subprocess
 
 COPY_BYTES = 512 << 20                     # bench.py --pmc-probe: bytes read (and bytes written) per copy launch
-GATEUP_KERNEL = "gemm_wreg_kernel"         # the 256 x 256 prefill tile; its SwiGLU instantiation is the gate/up GEMM
-# SwiGLU epilogue = first template argument 3 (the second is the tile's wave rows: 2 = 256 x 256), demangled or mangled name
-GATEUP_PATTERN = r"gemm_wreg_kernel<3, 2>|gemm_wreg_kernelILi3ELi2E"
+GATEUP_KERNEL = "gemm_"
+# the 256-column prefill tile's SwiGLU instantiation is the gate/up GEMM: epilogue = first template argument 3, demangled or mangled
+# name (gemm_wreg_kernel: its name in earlier recordings, whose second argument is the tile's wave rows)
+GATEUP_PATTERN = r"gemm_rows_kernel<3>|gemm_rows_kernelILi3E|gemm_wreg_kernel<3, 2>|gemm_wreg_kernelILi3ELi2E"
 COPY_KERNEL = "copy_kernel"
 # kernels that only the decode phase launches; one attn_decode_mfma launch = one decode layer-step.
 # (Its embedding and first RMSNorm launches share kernels with the prefill phase and are left out:
 # 64 rows, under 2 MB per step.)
 DECODE_STEP_KERNEL = "attn_decode_mfma_kernel"
 DECODE_KERNELS = (r"attn_decode_mfma_kernel", r"attn_decode_merge_kernel", r"decode_qkv_finish_kernel", r"reduce_resid_norm_kernel",
-                  r"reduce_swiglu_kernel", r"gemm_dl_kernel<64, |gemm_dl_kernelILi64E", r"gemm_skinny_kernel")
+                  r"reduce_swiglu_kernel", r"gemm_dl_kernel<64, |gemm_dl_kernelILi64E", r"gemm_skinny_kernel", r"gemm_kslice_kernel")
 
 
 def per_kernel(path, counter, queue_of=None):

@@ -123,6 +123,27 @@ def test_gemm_skinny_tiles_epilogues(sts, cfg, width, m, k):
     assert rel(sts.op_gemm(a, w, cfg, epilogue=3), ref3) <= BF16_TOL
 
 
+@pytest.mark.parametrize("m", [1, 32, 33, 96, 97, 160, 192, 224, 225, 255, 257, 400])
+@pytest.mark.parametrize("k,slots", [(64, 0), (192, 0), (320, 0), (1088, 3)])
+def test_gemm_row_tile_heights(sts, m, k, slots):
+    """The eight-wave 256-column tile has a loop per height (32 to 256 rows): every height, rows that end inside its last block, K
+    extents shorter than the operands' ring and with surplus iterations in its last round, every epilogue, and (slots) the last
+    wave of tiles cut along K."""
+    n = 512
+    a = synth.normal_bf16(71, (m, k))
+    a64 = a.astype(np.float64)
+    w = synth.normal_bf16(72, (n, k), 0.05)
+    ref = T.op_linear(a64, w.astype(np.float64))
+    assert rel(sts.op_gemm(a, w, "256x256", epilogue=0, tail_slots=slots), ref) <= BF16_TOL
+    assert rel(sts.op_gemm(a, w, "256x256", epilogue=1, tail_slots=slots), ref) <= 1e-5
+    x = np.random.default_rng(73).standard_normal((m, n)).astype(np.float32)
+    assert rel(sts.op_gemm(a, w, "256x256", epilogue=2, c_in=x, tail_slots=slots), x.astype(np.float64) + ref) <= 1e-5
+    ref3 = T.silu(ref[:, :n // 2]) * ref[:, n // 2:]
+    assert rel(sts.op_gemm(a, w, "256x256", epilogue=3, tail_slots=slots), ref3) <= BF16_TOL
+    if not slots and k > 64:
+        assert rel(sts.op_gemm(a, w, "256x256", epilogue=1, split_k=2), ref) <= 1e-5
+
+
 @pytest.mark.parametrize("cfg,m,n,slots", [("128x128", 300, 512, 8), ("128x128", 300, 512, 10), ("128x128", 300, 512, 40),
                                            ("128x128", 300, 512, 16), ("256x256", 513, 512, 4), ("256x256", 513, 512, 15),
                                            ("64x128", 64, 640, 4), ("128x256", 300, 768, 7), ("128x256", 513, 512, 8)])
