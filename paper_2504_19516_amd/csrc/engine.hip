@@ -63,7 +63,8 @@ struct Phase {
   float* X = nullptr; bf16* Xn = nullptr; bf16* QKV = nullptr; bf16* A = nullptr; bf16* H = nullptr;
   float* part = nullptr; size_t part_floats = 0; float* attn_ws = nullptr; bf16* Q = nullptr;
   float* rot = nullptr; float* ssq = nullptr;                 // decode: rotation angles of the step, shares of the rows' sums of squares
-  float* tail_ws = nullptr; size_t tail_ws_bytes = 0;         // prefill GEMM tail pieces
+  float* tail_ws = nullptr; size_t tail_ws_bytes = 0;         // prefill: GEMM tail pieces, partial attention outputs, head partial sums
+  int max_attn_extra = 0;
   bf16* Xlast_n = nullptr; float* logits = nullptr; int* next = nullptr;
   // Per-call metadata (sequence records, block tables, work items, token ids) is packed into one
   // pinned block and reaches the device in a single copy; the pointers below are views into the
@@ -553,31 +554,34 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   const sts_model_desc& d = c->d;
   int rows = 0;
   for (int i = 0; i < n_seqs; i++) rows += lens[i];
+  std::vector<int> priors(n_seqs);
+  for (int i = 0; i < n_seqs; i++) priors[i] = c->seqs[seqs[i]].len;
+  const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
+                                          (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
+  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size();
   // ---- stage metadata
-  const int mp = c->p.max_pages_per_seq, bq = attn_prefill_tile_q();
   ph.meta_used = 0;
   meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
   meta_take(ph, &ph.h_rows, &ph.d_rows, n_seqs);
-  meta_take(ph, &ph.h_items, &ph.d_items, rows / bq + n_seqs);
+  meta_take(ph, &ph.h_items, &ph.d_items, n_items);
+  AttnMerge *h_merges = nullptr, *d_merges = nullptr;
+  meta_take(ph, &h_merges, &d_merges, n_merges);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
   if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
-  int r0 = 0, n_items = 0, bt_off = 0;
+  int r0 = 0, bt_off = 0;
   for (int i = 0; i < n_seqs; i++) {
     const Seq& s = c->seqs[seqs[i]];
     ph.h_pseq[i] = PrefillSeq{r0, lens[i], s.len, bt_off, (int)s.pages.size()};
     std::memcpy(ph.h_bt + bt_off, s.pages.data(), s.pages.size() * sizeof(int));
     bt_off += (int)s.pages.size();
-    for (int q0 = 0; q0 < lens[i]; q0 += bq) ph.h_items[n_items++] = AttnItem{i, q0};
     ph.h_rows[i] = r0 + lens[i] - 1;
     r0 += lens[i];
   }
-  // heaviest query tiles first: the tail of the launch is then made of short ones
-  std::stable_sort(ph.h_items, ph.h_items + n_items, [&](const AttnItem& a, const AttnItem& b) {
-    return ph.h_pseq[a.seq].p + a.q0 > ph.h_pseq[b.seq].p + b.q0;
-  });
+  std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
+  if (n_merges > 0) std::memcpy(h_merges, attn.merges.data(), n_merges * sizeof(AttnMerge));
   hipStream_t st = ph.stream;
   HIPCK(hipEventRecord(ph.ev0, st));
   if (lb == 0) std::memcpy(ph.h_tokens, tokens, rows * sizeof(int));
@@ -593,7 +597,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     if (!(fused_embed && l == 0)) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
     KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
     KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, c->inv_freq, layer_pool(c, l), c->geo, rows, d.n_q_heads));
-    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads));
+    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
     KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd));
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
     KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
@@ -815,10 +819,13 @@ int alloc_phase(sts_ctx* c, int side) {
   STSCK(dev_alloc(c, &ph.logits, nseq * d.vocab));
   STSCK(dev_alloc(c, &ph.next, nseq));
   {
-    const size_t items = rows / attn_prefill_tile_q() + nseq + 1;
+    // prefill attention: a query tile per 128 rows, and as many again for the parts of cut key ranges
+    const size_t q_tiles = side == 0 ? rows / attn_prefill_tile_q() + nseq + 1 : 0;
+    ph.max_attn_extra = (int)q_tiles + 256;
+    const size_t items = 2 * q_tiles + 256;
     // decode attention items: a context has at most 128 chunks, and fewer than one per 4 pages (chunks hold >= 8)
     const size_t dec_items = side == 1 ? nseq * (size_t)decode_max_chunks((int)mp) : 0;
-    ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + 2 * sizeof(int)) + items * sizeof(AttnItem) + dec_items * sizeof(DecodeItem) +
+    ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + 2 * sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
                     rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
     STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes));
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes));

@@ -1,5 +1,7 @@
 // Internal (C++) interface between the engine and the gfx950 kernels. Not part of the C ABI.
 #pragma once
+#include <vector>
+
 #include "common.h"
 
 namespace sts {
@@ -53,7 +55,10 @@ struct PrefillSeq {
   int bt_off;      // offset of this sequence's block table in the block-table buffer
   int n_pages;     // valid entries in that block table
 };
-struct AttnItem { int seq; int q0; };   // one query tile of one sequence
+// One query tile of one sequence (rows from q0), or one part of its key range: 64-key tiles [kt0, kt1). part: where its partial
+// output goes, -1 if the tile is finished by its workgroup.
+struct AttnItem { int seq, q0, kt0, kt1, part; };
+struct AttnMerge { int seq, q0, part0, parts; };   // a query tile whose key range was cut: parts part0 .. part0 + parts - 1
 
 // Per-request metadata of one decode step.
 struct DecodeSeq {
@@ -105,9 +110,12 @@ hipError_t kv_read_tokens(hipStream_t s, const bf16* pool, KvGeom geo, const int
 
 // ---- attention ----------------------------------------------------------------------------
 hipError_t attn_prefill(hipStream_t s, const bf16* qkv, int ld, bf16* out, int ldo, const PrefillSeq* seqs,
-                        const AttnItem* items, int n_items, const int* block_tables, const bf16* pool,
-                        KvGeom geo, int n_q);
+                        const AttnItem* items, int n_items, const AttnMerge* merges, int n_merges, const int* block_tables, const bf16* pool,
+                        KvGeom geo, int n_q, float* part_ws);
 int attn_prefill_tile_q();
+struct AttnPlan { std::vector<AttnItem> items; std::vector<AttnMerge> merges; int parts = 0; };
+AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n_q, int slots, int max_extra, long long max_parts);
+size_t attn_prefill_part_floats(int n_q, int d);   // of one part
 size_t attn_decode_ws_floats(int n, int n_q, int d, int max_chunks);
 hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const int* multi, int n_multi,
                        const int* block_tables, const bf16* pool, KvGeom geo, int n, int n_q, int chunk_pages, int max_chunks, float* ws,

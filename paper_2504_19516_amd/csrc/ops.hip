@@ -133,20 +133,23 @@ extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* 
   bf16* dq = upload_bf16(b, q, (size_t)t * n_q * d);
   bf16* dout = b.get<bf16>((size_t)t * n_q * d);
   PrefillSeq* d_seq = b.get<PrefillSeq>(1);
-  const int bq = attn_prefill_tile_q(), n_items = (t + bq - 1) / bq;
+  // the engine's plan on a whole GPU of 256 CUs
+  const AttnPlan plan = attn_prefill_plan(1, &t, &prior, n_q, 512, 1 << 20, 256);
+  const int n_items = (int)plan.items.size(), n_merges = (int)plan.merges.size();
   AttnItem* d_items = b.get<AttnItem>(n_items);
-  if (!pool || !d_bt || !dk || !dv || !dq || !dout || !d_seq || !d_items) return STS_EHIP;
-  std::vector<AttnItem> items;
-  for (int q0 = 0; q0 < t; q0 += bq) items.push_back(AttnItem{0, q0});
+  AttnMerge* d_merges = b.get<AttnMerge>(n_merges);
+  float* part_ws = b.get<float>(plan.parts * attn_prefill_part_floats(n_q, d));
+  if (!pool || !d_bt || !dk || !dv || !dq || !dout || !d_seq || !d_items || !d_merges || !part_ws) return STS_EHIP;
   PrefillSeq sq{0, t, prior, 0, np};
   if (hipMemset(pool, 0, (size_t)n_pool_pages * geo.page_elems() * sizeof(bf16)) != hipSuccess ||
       hipMemcpy(d_bt, pages, np * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(dk, k, (size_t)total * n_kv * d * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(dv, v, (size_t)total * n_kv * d * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(d_seq, &sq, sizeof(sq), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(d_items, items.data(), n_items * sizeof(AttnItem), hipMemcpyHostToDevice) != hipSuccess) return STS_EHIP;
+      hipMemcpy(d_items, plan.items.data(), n_items * sizeof(AttnItem), hipMemcpyHostToDevice) != hipSuccess ||
+      (n_merges > 0 && hipMemcpy(d_merges, plan.merges.data(), n_merges * sizeof(AttnMerge), hipMemcpyHostToDevice) != hipSuccess)) return STS_EHIP;
   if (kv_write_tokens(nullptr, pool, geo, d_bt, 0, total, dk, dv) != hipSuccess) return STS_EHIP;
-  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, d_bt, pool, geo, n_q);
+  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
   if (e != hipSuccess) return e == hipErrorInvalidValue ? STS_EINVAL : STS_EHIP;
   int rc = download_bf16(b, out, dout, (size_t)t * n_q * d);
   if (hipDeviceSynchronize() != hipSuccess) return STS_EHIP;

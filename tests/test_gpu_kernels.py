@@ -207,6 +207,20 @@ def test_prefill_attention(sts, t, prior, nq, nkv, d):
     assert np.array_equal(got, got2)
 
 
+@pytest.mark.parametrize("nq,nkv,d,t,prior", [(4, 1, 128, 130, 5000), (2, 2, 64, 40, 3100), (8, 2, 128, 1, 4095), (2, 1, 128, 300, 6000), (1, 1, 64, 129, 17000)])
+def test_prefill_attention_cuts_long_key_ranges(sts, nq, nkv, d, t, prior):
+    """Few query tiles over many cached tokens: the key range is cut into parts whose outputs are merged (2 to 8 parts; the rows of
+    a last part that see none of its keys have no weight there)."""
+    q = synth.normal_bf16(81, (t, nq, d))
+    k = synth.normal_bf16(82, (prior + t, nkv, d))
+    v = synth.normal_bf16(83, (prior + t, nkv, d))
+    np_ = (prior + t + 15) // 16
+    pages = synth.page_permutation(84, np_ + 3)[:np_]
+    got = sts.op_attn_prefill(q, k, v, prior, pages, np_ + 3)
+    ref = T.op_causal_attention(q.astype(np.float64), k.astype(np.float64), v.astype(np.float64), prior)
+    assert rel(got, ref) <= BF16_TOL
+
+
 @pytest.mark.parametrize("nq,nkv,d,ctx", [(8, 1, 128, [700, 257, 256, 17]), (8, 2, 128, [63, 65]), (4, 4, 64, [530, 513, 511, 33])])
 def test_decode_attention_merges_many_chunks(sts, nq, nkv, d, ctx):
     """One page a chunk: 2 to 44 chunks a context, below, at and above what the merge kernel keeps in flight (16 or 32)."""
