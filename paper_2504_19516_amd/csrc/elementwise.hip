@@ -192,28 +192,48 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X,
 // Embedding rows and the first layer's RMSNorm in one pass: the row is in registers anyway, so the residual stream
 // (fp32) and its normalised bf16 copy are written together and the stream is not read back. One workgroup per row,
 // 8 elements per thread and 2048-column slab, rows of up to 8192 elements.
-// A decode step also has its rotation angles written here, once for all layers: cosines and sines of row's position in rot.
-__device__ __forceinline__ void write_rotation(float* rot, int row, int pos, const double* inv_freq, int half) {
+// The rotation angles of a launch's rows are written once for all layers: cosines and sines of row's position, [row][d].
+__device__ __forceinline__ void write_rotation(float* table, int row, int pos, const double* inv_freq, int half) {
   for (int i = threadIdx.x; i < half; i += blockDim.x) {
     double sv, cv;
     sincos((double)pos * inv_freq[i], &sv, &cv);
-    rot[(size_t)row * 2 * half + i] = (float)cv;
-    rot[(size_t)row * 2 * half + half + i] = (float)sv;
+    table[(size_t)row * 2 * half + i] = (float)cv;
+    table[(size_t)row * 2 * half + half + i] = (float)sv;
   }
 }
-__global__ void rotation_kernel(float* rot, const DecodeSeq* seqs, const double* inv_freq, int half) {
-  write_rotation(rot, blockIdx.x, seqs[blockIdx.x].cl, inv_freq, half);
+__device__ __forceinline__ int row_position(const RowRotation& r, int row) {
+  if (r.dseq) return r.dseq[row].cl;
+  int si = 0;
+  while (si + 1 < r.n_seqs && row >= r.pseq[si + 1].row0) si++;
+  return r.pseq[si].p + (row - r.pseq[si].row0);
 }
-hipError_t decode_rotation(hipStream_t s, float* rot, const DecodeSeq* seqs, const double* inv_freq, int n, int d) {
+__global__ void rotation_kernel(RowRotation rot) { write_rotation(rot.table, blockIdx.x, row_position(rot, blockIdx.x), rot.inv_freq, rot.d >> 1); }
+hipError_t row_rotation(hipStream_t s, const RowRotation& rot, int n) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(rotation_kernel, dim3(n), dim3(64), 0, s, rot, seqs, inv_freq, d >> 1);
+  hipLaunchKernelGGL(rotation_kernel, dim3(n), dim3(64), 0, s, rot);
   return hipGetLastError();
 }
-__global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int h,
-                                                         float* rot, const DecodeSeq* seqs, const double* inv_freq, int half) {
+// Metadata from pinned host memory, read over the bus by the kernel itself: a runtime copy of these few KB left the stream idle
+// for 15 to 30 us around it.
+__global__ void __launch_bounds__(256) copy_in_kernel(MetaCopy meta) {
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 16;
+  if (i < meta.bytes) *reinterpret_cast<u32x4*>(meta.dst + i) = *reinterpret_cast<const u32x4*>(meta.src + i);
+}
+hipError_t copy_in(hipStream_t s, const MetaCopy& meta) {
+  if (meta.bytes == 0) return hipSuccess;
+  hipLaunchKernelGGL(copy_in_kernel, dim3((meta.bytes + 4095) / 4096), dim3(256), 0, s, meta);
+  return hipGetLastError();
+}
+__global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int h, int n,
+                                                         RowRotation rot, MetaCopy meta) {
   constexpr int PER = 4;
   __shared__ float red[4];
   const int row = blockIdx.x;
+  if (row >= n) {                                            // the blocks behind the rows copy the metadata for the kernels after this one
+    const int i = ((row - n) * 256 + threadIdx.x) * 16;
+    if (i < meta.bytes) *reinterpret_cast<u32x4*>(meta.dst + i) = *reinterpret_cast<const u32x4*>(meta.src + i);
+    return;
+  }
   const bf16* e = emb + (size_t)tokens[row] * h;
   bf16x8 v[PER];
   float ss = 0.f;
@@ -226,7 +246,7 @@ __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, co
       for (int j = 0; j < 8; j++) { const float f = bf2f(v[i][j]); ss += f * f; }
     }
   }
-  if (rot) write_rotation(rot, row, seqs[row].cl, inv_freq, half);      // while the row is on its way
+  write_rotation(rot.table, row, row_position(rot, row), rot.inv_freq, rot.d >> 1);      // while the row is on its way
   const float w = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
   __syncthreads();
@@ -251,10 +271,10 @@ __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, co
   }
 }
 hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h,
-                           float* rot, const DecodeSeq* seqs, const double* inv_freq, int d) {
+                           const RowRotation& rot, const MetaCopy& meta) {
   if (n == 0) return hipSuccess;
   if (h > 8192 || h % 8 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(embed_norm_kernel, dim3(n), dim3(256), 0, s, X, out, emb, tokens, gain, eps, h, rot, seqs, inv_freq, d >> 1);
+  hipLaunchKernelGGL(embed_norm_kernel, dim3(n + (meta.bytes + 4095) / 4096), dim3(256), 0, s, X, out, emb, tokens, gain, eps, h, n, rot, meta);
   return hipGetLastError();
 }
 
@@ -266,24 +286,19 @@ hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* g
 }
 
 // ------------------------------------------------------------------ rotary + KV page write (prefill)
-// One workgroup per token row. cos/sin of the row's position are computed once (in double:
-// positions reach tens of thousands of radians) and applied to every head. Q is rotated in
+// One workgroup per token row; rot: the rows' cosines and sines (computed in double:
+// positions reach tens of thousands of radians). Q is rotated in
 // place; K is rotated and scattered to its page; V is scattered transposed (page_tokens = 16).
 __global__ void __launch_bounds__(256) rope_kv_prefill_kernel(bf16* qkv, int ld, const PrefillSeq* seqs, int n_seqs,
-                                                              const int* block_tables, const double* inv_freq,
+                                                              const int* block_tables, const float* rot,
                                                               bf16* pool, KvGeom geo, int n_q) {
-  __shared__ float cs[128], sn[128];
   const int row = blockIdx.x, d = geo.d, half = d >> 1;
   int si = 0;
   while (si + 1 < n_seqs && row >= seqs[si + 1].row0) si++;
   const PrefillSeq sq = seqs[si];
   const int pos = sq.p + (row - sq.row0);
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    double sv, cv;
-    sincos((double)pos * inv_freq[i], &sv, &cv);
-    cs[i] = (float)cv; sn[i] = (float)sv;
-  }
-  __syncthreads();
+  const float* cs = rot + (size_t)row * d;
+  const float* sn = cs + half;
   const int page = block_tables[sq.bt_off + pos / geo.page_tokens], slot = pos % geo.page_tokens;
   bf16* r = qkv + (size_t)row * ld;
   // eight rotation pairs (two 16-byte loads, two 16-byte stores) per work item
@@ -292,12 +307,18 @@ __global__ void __launch_bounds__(256) rope_kv_prefill_kernel(bf16* qkv, int ld,
     const int hd = t / per_head, i0 = (t % per_head) * 8;
     const bf16x8 a = *reinterpret_cast<const bf16x8*>(r + hd * d + i0);
     const bf16x8 b = *reinterpret_cast<const bf16x8*>(r + hd * d + i0 + half);
+    f32x4 c4[2], s4[2];
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      c4[q] = *reinterpret_cast<const f32x4*>(cs + i0 + 4 * q);
+      s4[q] = *reinterpret_cast<const f32x4*>(sn + i0 + 4 * q);
+    }
     bf16x8 ya, yb;
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-      const float fa = bf2f(a[e]), fb = bf2f(b[e]);
-      ya[e] = f2bf(fa * cs[i0 + e] - fb * sn[i0 + e]);
-      yb[e] = f2bf(fa * sn[i0 + e] + fb * cs[i0 + e]);
+      const float fa = bf2f(a[e]), fb = bf2f(b[e]), ce = c4[e >> 2][e & 3], se = s4[e >> 2][e & 3];
+      ya[e] = f2bf(fa * ce - fb * se);
+      yb[e] = f2bf(fa * se + fb * ce);
     }
     bf16* dst = hd < n_q ? r + hd * d : pool + ((size_t)page * geo.n_kv + (hd - n_q)) * geo.head_elems() + (size_t)slot * d;
     *reinterpret_cast<bf16x8*>(dst + i0) = ya;
@@ -329,11 +350,11 @@ __global__ void __launch_bounds__(256) rope_kv_prefill_kernel(bf16* qkv, int ld,
   }
 }
 hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const PrefillSeq* seqs, int n_seqs,
-                                 const int* block_tables, const double* inv_freq, bf16* pool, KvGeom geo,
+                                 const int* block_tables, const float* rot, bf16* pool, KvGeom geo,
                                  int n_rows, int n_q) {
   if (n_rows == 0) return hipSuccess;
   hipLaunchKernelGGL(rope_kv_prefill_kernel, dim3(n_rows), dim3(256), 0, s, qkv, ld, seqs, n_seqs, block_tables,
-                     inv_freq, pool, geo, n_q);
+                     rot, pool, geo, n_q);
   return hipGetLastError();
 }
 
@@ -497,8 +518,9 @@ hipError_t reduce_f32(hipStream_t s, float* out, const float* partials, int spli
 // ------------------------------------------------------------------ greedy sampling
 // One workgroup of 1024 threads per row; 16-byte loads, four in flight per thread. The first
 // maximum wins: a thread scans its indices in ascending order and the tree keeps the lower index
-// on equal values.
-__global__ void __launch_bounds__(1024) argmax_kernel(int* out, const float* logits, int vocab) {
+// on equal values. out is pinned host memory, and so is copy: where the caller wants small logits too, the pass that reads them
+// writes them there (a runtime copy leaves the stream idle for about 15 us).
+__global__ void __launch_bounds__(1024) argmax_kernel(int* out, const float* logits, int vocab, float* copy) {
   __shared__ float bv[1024];
   __shared__ int bi[1024];
   const float* l = logits + (size_t)blockIdx.x * vocab;
@@ -522,6 +544,8 @@ __global__ void __launch_bounds__(1024) argmax_kernel(int* out, const float* log
   } else {
     for (int c = threadIdx.x; c < vocab; c += 1024) take(l[c], c);
   }
+  if (copy)
+    for (int c = threadIdx.x * 4; c < vocab; c += 4096) *reinterpret_cast<f32x4*>(copy + (size_t)blockIdx.x * vocab + c) = *reinterpret_cast<const f32x4*>(l + c);
   bv[threadIdx.x] = best; bi[threadIdx.x] = idx;
   __syncthreads();
   for (int o = 512; o > 0; o >>= 1) {
@@ -533,9 +557,10 @@ __global__ void __launch_bounds__(1024) argmax_kernel(int* out, const float* log
   }
   if (threadIdx.x == 0) out[blockIdx.x] = bi[0] == 0x7FFFFFFF ? 0 : bi[0];     // a row without any value above -inf
 }
-hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab) {
+hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab, float* copy) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(argmax_kernel, dim3(n), dim3(1024), 0, s, out, logits, vocab);
+  if (copy && vocab % 4 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(argmax_kernel, dim3(n), dim3(1024), 0, s, out, logits, vocab, copy);
   return hipGetLastError();
 }
 

@@ -62,10 +62,10 @@ struct Phase {
   // device workspace
   float* X = nullptr; bf16* Xn = nullptr; bf16* QKV = nullptr; bf16* A = nullptr; bf16* H = nullptr;
   float* part = nullptr; size_t part_floats = 0; float* attn_ws = nullptr; bf16* Q = nullptr;
-  float* rot = nullptr; float* ssq = nullptr;                 // decode: rotation angles of the step, shares of the rows' sums of squares
+  float* rot = nullptr; float* ssq = nullptr;                 // rotation angles of the launch's rows; decode: shares of the rows' sums of squares
   float* tail_ws = nullptr; size_t tail_ws_bytes = 0;         // prefill: GEMM tail pieces, partial attention outputs, head partial sums
   int max_attn_extra = 0;
-  bf16* Xlast_n = nullptr; float* logits = nullptr; int* next = nullptr;
+  bf16* Xlast_n = nullptr; float* logits = nullptr;
   // Per-call metadata (sequence records, block tables, work items, token ids) is packed into one
   // pinned block and reaches the device in a single copy; the pointers below are views into the
   // two blocks, laid out afresh by every launch.
@@ -134,7 +134,8 @@ void meta_take(Phase& ph, T** host, T** dev, size_t count);
 template <typename T>
 int host_alloc(T** out, size_t count) {
   void* p = nullptr;
-  HIPCK(hipHostMalloc(&p, std::max<size_t>(count, 1) * sizeof(T), hipHostMallocDefault));
+  // coherent: kernels read metadata from it and store results to it, the host sees those once the stream is done
+  HIPCK(hipHostMalloc(&p, std::max<size_t>(count, 1) * sizeof(T), hipHostMallocMapped | hipHostMallocCoherent));
   *out = reinterpret_cast<T*>(p);
   return STS_OK;
 }
@@ -452,13 +453,19 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
   return STS_OK;
 }
 
+// Up to this many rows the embedding kernel reads its tokens and records from pinned host memory (one bus read each).
+constexpr int META_FUSED_ROWS = 512;
+// Logits a head's last kernel stores straight to host memory (64-byte pieces over the bus), and those that greedy sampling copies
+// on the side in whole lines; beyond, the copy engine is faster than either.
+constexpr size_t DIRECT_LOGITS_BYTES = 64 << 10, BESIDE_LOGITS_BYTES = 1 << 20;
+
 bf16* layer_pool(sts_ctx* c, int l) { return c->pool + (size_t)l * c->pool_layer_elems; }
 
-// Final norm and LM head of n rows into ph.logits. x: the residual stream, whose rows (rows idx[i] if idx is given) are normalised
+// Final norm and LM head of n rows into out. x: the residual stream, whose rows (rows idx[i] if idx is given) are normalised
 // into xn; null if xn holds them normalised already. With scale.ssq xn holds the rows scaled by the final gains, and a head that
 // applies the row factor itself needs no norm. The head runs unsplit, or with K cut over workgroups and a kernel that adds up the partial sums (a small vocabulary has too few tiles:
 // 1024 x 4096 took 33 us unsplit against 7 + 4), or as a GEMM that cuts K inside its workgroups.
-int run_head(sts_ctx* c, Phase& ph, const float* x, const int* idx, bf16* xn, RowScale scale, int n, float* scratch, size_t scratch_floats, bool nt) {
+int run_head(sts_ctx* c, Phase& ph, const float* x, const int* idx, bf16* xn, RowScale scale, int n, float* scratch, size_t scratch_floats, bool nt, float* out) {
   const int v = c->d.vocab, h = c->d.hidden;
   int cfg, one, split_cfg, splits;
   const double t_one = pick_decode_gemm(c, n, v, h, ph.cus, false, false, &cfg, &one);
@@ -471,13 +478,13 @@ int run_head(sts_ctx* c, Phase& ph, const float* x, const int* idx, bf16* xn, Ro
     scale = RowScale{nullptr, 0, 0.f};
   }
   if (kslice) {
-    KL(ph, STS_K_HEAD, kslice_f32(ph.stream, KsliceIn{xn, h, scale, c->lm, n, v, h}, ph.cus, ph.logits, v));
+    KL(ph, STS_K_HEAD, kslice_f32(ph.stream, KsliceIn{xn, h, scale, c->lm, n, v, h}, ph.cus, out, v));
   } else if (split) {
     const int ksteps = h / 64, per = (ksteps + splits - 1) / splits, used = (ksteps + per - 1) / per;   // slices the launch makes
     KL(ph, STS_K_HEAD, gemm_bf16(ph.stream, split_cfg, EPI_F32, xn, h, c->lm, h, scratch, v, n, v, h, splits, (long long)n * v, nullptr, true, nt));
-    KL(ph, STS_K_REDUCE, reduce_f32(ph.stream, ph.logits, scratch, used, (long long)n * v, (size_t)n * v));
+    KL(ph, STS_K_REDUCE, reduce_f32(ph.stream, out, scratch, used, (long long)n * v, (size_t)n * v));
   } else {
-    KL(ph, STS_K_HEAD, gemm_bf16(ph.stream, cfg, EPI_F32, xn, h, c->lm, h, ph.logits, v, n, v, h, 1, 0, nullptr, true, nt));
+    KL(ph, STS_K_HEAD, gemm_bf16(ph.stream, cfg, EPI_F32, xn, h, c->lm, h, out, v, n, v, h, 1, 0, nullptr, true, nt));
   }
   return STS_OK;
 }
@@ -585,18 +592,26 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   hipStream_t st = ph.stream;
   HIPCK(hipEventRecord(ph.ev0, st));
   if (lb == 0) std::memcpy(ph.h_tokens, tokens, rows * sizeof(int));
-  HIPCK(hipMemcpyAsync(ph.d_meta, ph.h_meta, ph.meta_used, hipMemcpyHostToDevice, st));
   const int h = d.hidden;
   const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
-  if (fused_embed) KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h));
-  else if (lb == 0) KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, rows, h));
+  const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
+  // few rows: the embedding kernel reads tokens and sequence records from host memory itself and copies the metadata on the side
+  const bool fused_meta = fused_embed && rows <= META_FUSED_ROWS;
+  RowRotation rot{ph.rot, nullptr, fused_meta ? ph.h_pseq : ph.d_pseq, n_seqs, c->inv_freq, d.head_dim};
+  if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
+  if (fused_embed) {
+    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
+  } else if (lb == 0) {
+    KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, rows, h));
+    KL(ph, STS_K_ROPE, row_rotation(st, rot, rows));
+  }
   auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
   const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
   for (int l = lb; l < le; l++) {
     const LayerW& w = c->layers[l];
     if (!(fused_embed && l == 0)) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
     KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
-    KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, c->inv_freq, layer_pool(c, l), c->geo, rows, d.n_q_heads));
+    KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
     KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
     KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd));
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
@@ -604,8 +619,10 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp));
   }
   if (le == d.n_layers && want_logits) {
-    STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false));
-    HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, (size_t)n_seqs * d.vocab * sizeof(float), hipMemcpyDeviceToHost, st));
+    const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);
+    const bool direct = bytes <= DIRECT_LOGITS_BYTES;        // the head's last kernel stores to host memory
+    STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false, direct ? ph.h_logits : ph.logits));
+    if (!direct) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
   ph.ran = true; ph.rows = rows;
@@ -726,14 +743,17 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   for (int i = 0; i < n; i++) if (ph.h_dseq[i].n_pages > chunk_pages) h_multi[n_multi++] = i;
   hipStream_t st = ph.stream;
   HIPCK(hipEventRecord(ph.ev0, st));
-  HIPCK(hipMemcpyAsync(ph.d_meta, ph.h_meta, ph.meta_used, hipMemcpyHostToDevice, st));
   const int h = d.hidden;
+  const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
+  const bool fused_meta = h <= 8192 && n <= META_FUSED_ROWS;
+  RowRotation rot{ph.rot, fused_meta ? ph.h_dseq : ph.d_dseq, nullptr, 0, c->inv_freq, d.head_dim};
+  if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
   if (h <= 8192) {
-    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h, ph.rot, ph.d_dseq, c->inv_freq, d.head_dim));
+    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
   } else {
     KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, n, h));
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, c->layers[0].g1, d.rms_eps, n, h));
-    KL(ph, STS_K_ROPE, decode_rotation(st, ph.rot, ph.d_dseq, c->inv_freq, n, d.head_dim));
+    KL(ph, STS_K_ROPE, row_rotation(st, rot, n));
   }
   // On a large partition the decode streams (K and V, the weights of the skinny tiles) are fetched with the non-temporal
   // hint: measured on a 6-layer model, the layer-step is 6 % shorter on 256 CUs (attention 72 -> 63 us), 3 % on 128,
@@ -777,12 +797,12 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   }
   if (want_logits || want_next) {
     // (the last reduce kernel of the split form has written Xn normalised)
-    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt_w));
-    if (want_next) {
-      KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.next, ph.logits, n, d.vocab));
-      HIPCK(hipMemcpyAsync(ph.h_next, ph.next, n * sizeof(int), hipMemcpyDeviceToHost, st));
-    }
-    if (want_logits) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, (size_t)n * d.vocab * sizeof(float), hipMemcpyDeviceToHost, st));
+    const size_t bytes = (size_t)n * d.vocab * sizeof(float);
+    // small logits reach host memory from the kernel that reads them last, large ones by a copy
+    const bool direct = want_logits && !want_next && bytes <= DIRECT_LOGITS_BYTES, beside = want_logits && want_next && bytes <= BESIDE_LOGITS_BYTES;
+    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt_w, direct ? ph.h_logits : ph.logits));
+    if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_next, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
+    if (want_logits && !direct && !beside) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
   ph.ran = true; ph.rows = n;
@@ -817,7 +837,7 @@ int alloc_phase(sts_ctx* c, int side) {
   STSCK(dev_alloc(c, &ph.H, rows * d.mlp));
   STSCK(dev_alloc(c, &ph.Xlast_n, nseq * d.hidden));
   STSCK(dev_alloc(c, &ph.logits, nseq * d.vocab));
-  STSCK(dev_alloc(c, &ph.next, nseq));
+  STSCK(dev_alloc(c, &ph.rot, rows * d.head_dim));
   {
     // prefill attention: a query tile per 128 rows, and as many again for the parts of cut key ranges
     const size_t q_tiles = side == 0 ? rows / attn_prefill_tile_q() + nseq + 1 : 0;
@@ -827,8 +847,8 @@ int alloc_phase(sts_ctx* c, int side) {
     const size_t dec_items = side == 1 ? nseq * (size_t)decode_max_chunks((int)mp) : 0;
     ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + 2 * sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
                     rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
-    STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes));
-    STSCK(host_alloc(&ph.h_meta, ph.meta_bytes));
+    STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes + 16));      // copied in 16-byte pieces
+    STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));
   }
   STSCK(host_alloc(&ph.h_logits, nseq * d.vocab));
   STSCK(host_alloc(&ph.h_next, nseq));
@@ -842,7 +862,6 @@ int alloc_phase(sts_ctx* c, int side) {
     const size_t max_chunks = decode_max_chunks((int)mp);
     ph.part_floats = 8 * rows * widest;
     STSCK(dev_alloc(c, &ph.part, ph.part_floats));
-    STSCK(dev_alloc(c, &ph.rot, rows * d.head_dim));
     STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
     STSCK(dev_alloc(c, &ph.Q, rows * c->qd));
     STSCK(dev_alloc(c, &ph.attn_ws, attn_decode_ws_floats((int)rows, d.n_q_heads, d.head_dim, (int)max_chunks)));

@@ -80,15 +80,21 @@ hipError_t export_weight(hipStream_t s, float* dst, const bf16* src, int ld, int
                          int row_offset, int interleave_block, int interleave_phase, int packed);
 hipError_t fill_f32(hipStream_t s, float* dst, float v, size_t n);
 hipError_t embed_rows(hipStream_t s, float* X, const bf16* emb, const int* tokens, int n, int h);
-// embedding rows into the fp32 residual stream X and, in the same pass, their RMSNorm into out (bf16); h <= 8192
-// (a decode step passes rot too: the rotation angles of its requests' positions, [n][d / 2 cosines | d / 2 sines])
+// Rotation angles of a launch's rows, written to table [row][d / 2 cosines | d / 2 sines]: positions from dseq (one row per decode
+// request) or pseq.
+struct RowRotation { float* table; const DecodeSeq* dseq; const PrefillSeq* pseq; int n_seqs; const double* inv_freq; int d; };
+hipError_t row_rotation(hipStream_t s, const RowRotation& rot, int n);
+// Metadata in pinned host memory to the device (bytes rounded up to 16 must be readable and writable).
+struct MetaCopy { const unsigned char* src; unsigned char* dst; int bytes; };
+hipError_t copy_in(hipStream_t s, const MetaCopy& meta);
+// embedding rows into the fp32 residual stream X and, in the same pass, their RMSNorm into out (bf16); h <= 8192; the rows'
+// rotation angles; and the metadata copy (bytes 0: none)
 hipError_t embed_norm_rows(hipStream_t s, float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int n, int h,
-                           float* rot = nullptr, const DecodeSeq* seqs = nullptr, const double* inv_freq = nullptr, int d = 0);
-hipError_t decode_rotation(hipStream_t s, float* rot, const DecodeSeq* seqs, const double* inv_freq, int n, int d);
+                           const RowRotation& rot, const MetaCopy& meta);
 // rows idx[i] of X if idx is given
 hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* gain, float eps, int n, int h, const int* idx = nullptr);
 hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const PrefillSeq* seqs, int n_seqs,
-                                 const int* block_tables, const double* inv_freq, bf16* pool, KvGeom geo,
+                                 const int* block_tables, const float* rot, bf16* pool, KvGeom geo,
                                  int n_rows, int n_q);
 hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, long long split_stride, int ld,
                              const DecodeSeq* seqs, const int* block_tables, const float* rot,
@@ -98,7 +104,8 @@ hipError_t reduce_resid_norm(hipStream_t s, float* X, const float* partials, int
 hipError_t reduce_swiglu(hipStream_t s, bf16* H, const float* partials, int splits, long long split_stride,
                          int n, int mlp);
 hipError_t reduce_f32(hipStream_t s, float* out, const float* partials, int splits, long long split_stride, size_t n);
-hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab);
+// copy: the logits again (pinned host memory), or null
+hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab, float* copy = nullptr);
 hipError_t copy_probe(hipStream_t s, void* dst, const void* src, size_t bytes, int grid);
 hipError_t read_probe(hipStream_t s, const void* src, size_t bytes, unsigned* sink, int grid);    // the read half alone; sink: 4 bytes of device memory
 hipError_t kv_fill_random(hipStream_t s, bf16* pool, KvGeom geo, const int* block_table, int pos0, int n,
