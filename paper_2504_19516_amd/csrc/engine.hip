@@ -285,12 +285,10 @@ PrefillGemm pick_prefill_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, 
   return best;
 }
 // A prefill GEMM on the phase's partition, the last wave of tiles cut along K.
-hipError_t prefill_gemm(const Phase& ph, const PrefillGemm& gm, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k) {
-  const GemmTail tail{gemm_wgs_per_cu(gm.cfg) * ph.cus, ph.tail_ws, ph.tail_ws_bytes};
+hipError_t prefill_gemm(const Phase& ph, const PrefillGemm& gm, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k, ResidNorm* norm = nullptr) {
+  const GemmTail tail{gemm_wgs_per_cu(gm.cfg) * ph.cus, ph.tail_ws, ph.tail_ws_bytes, norm};
   return gemm_bf16(ph.stream, gm.cfg, epi, A, lda, W, ldw, C, ldc, m, n, k, 1, 0, &tail, true, false, gm.row_tiles);
 }
-int plan_splits(double rate_256, double partial_bw, int cfg, int m, int n, int k, int cus);
-int pick_splits(const sts_ctx* ctx, int cfg, int m, int n, int k, int cus) { return plan_splits(ctx->rate_256, ctx->partial_bw, cfg, m, n, k, cus); }
 int plan_splits(double rate_256, double partial_bw, int cfg, int m, int n, int k, int cus) {
   const int tiles = ((m + gemm_tile_m(cfg) - 1) / gemm_tile_m(cfg)) * (n / gemm_tile_n(cfg));
   const int slots = gemm_wgs_per_cu(cfg) * std::max(cus, 8);
@@ -607,16 +605,19 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   }
   auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
   const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
+  bool normed = fused_embed;                                 // Xn holds this layer's input already
   for (int l = lb; l < le; l++) {
     const LayerW& w = c->layers[l];
-    if (!(fused_embed && l == 0)) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
+    ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
+    if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
     KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
     KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
     KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
-    KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd));
-    KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
+    KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
+    if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
     KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
-    KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp));
+    KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp, l + 1 < le ? &next : nullptr));
+    normed = next.done;
   }
   if (le == d.n_layers && want_logits) {
     const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);

@@ -15,7 +15,9 @@ int gemm_tile_m(int cfg);
 int gemm_tile_n(int cfg);
 int gemm_wgs_per_cu(int cfg);                       // resident workgroups per CU of this configuration
 // Tail splitting: `slots` = workgroups the stream's CU partition holds at once, `ws` = fp32 scratch.
-struct GemmTail { int slots; float* ws; size_t ws_bytes; };
+// norm: RMSNorm wanted of the finished rows of C (out: [M, N] bf16); `done` is set if the launch's last kernel writes it.
+struct ResidNorm { bf16* out; const float* gain; float eps; bool done; };
+struct GemmTail { int slots; float* ws; size_t ws_bytes; ResidNorm* norm = nullptr; };
 void gemm_tail_plan(int tiles, int ksteps, int slots, long long max_pieces, int* n_full, int* f);
 // W is either row-major [N, ldw] or (w_packed, the engine's weights; needs ldw == K) in
 // the packed layout below. The row-major form exists for the fp32-store epilogue only.

@@ -698,3 +698,34 @@ def test_decode_gemms_that_finish_their_output(ragged_case, n, cus):
     for a, b in zip(eng.kv_read(0, seqs[n - 1], pos, 1), eng.kv_read(0, again[0], pos, 1)):
         assert rel(a, b) <= 2.0 ** -7
     free_all(eng, seqs + again)
+
+
+@pytest.fixture(scope="module")
+def wide_rows(sts):
+    """Three layers of hidden 1280 (five 256-column tiles; the norm's last 256 elements of its second 1024 are past the row)."""
+    desc = synth.ModelDesc(3, 1280, 8, 2, 128, 2048, 640, 16, 1.0e4, 1.0e-5, "bf16")
+    w = synth.make_weights(desc, 78)
+    eng = new_engine(sts, desc, weight_seed=78)
+    eng.load_all(w)
+    yield desc, w, eng
+    eng.close()
+
+
+@pytest.mark.parametrize("cus,rows", [(256, 1), (256, 33), (256, 300), (64, 97), (64, 289), (8, 65)])
+def test_prefill_rows_finished_and_normalised_in_one_kernel(wide_rows, cus, rows):
+    """Residual GEMMs whose last wave of tiles is cut along K leave the sum of the pieces, the residual stream and its RMSNorm to
+    one kernel, also where only the last wave's tiles are cut (8 CUs). Six norm kernels run without it: five in the layers, the head's."""
+    desc, w, eng = wide_rows
+    tok = synth.tokens(800 + rows, rows, desc.vocab)
+    eng.set_partition(cus, 256)
+    eng.kernel_timing(True)
+    eng.kernel_times(0, reset=True)
+    s = eng.seq_create()
+    got = eng.prefill_append(s, tok)
+    norms = eng.kernel_times(0, reset=True)["norm"][1]
+    eng.kernel_timing(False)
+    orc = T.Oracle(desc, w, 24)
+    orc.kv.add_sequence(0, list(range((rows + 15) // 16)))
+    assert rel(got, orc.prefill_append(0, tok)) <= TOL
+    assert (norms < 6) == (rows > 33)                        # up to 64 rows the tiles are 64 x 128 or uncut
+    free_all(eng, [s])
