@@ -267,57 +267,59 @@ __global__ void __launch_bounds__(256, 2) attn_decode_mfma_kernel(const bf16* __
   }
 }
 
-// Merge the chunks of one (request, query head): out = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m).
-// Bound by memory latency, not by its few hundred KB: a workgroup's chunks are dealt to groups of D / 2 lanes (4 or 8 of them,
-// two elements a lane), each keeps four chunks' loads in flight and rescales as its maximum grows, and the groups meet in LDS.
-// One thread per element walking its chunks took 6.4 us for one request of 9 chunks and 12.1 for 24 requests of 64 heads (now 4.3
-// and 5.0, which is what a kernel of a few memory round trips takes here).
+// Merge the chunks of one (request, query head): out = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m), one maximum, chunks added in
+// their order: how chunks share the threads of a workgroup does not show in the result.
+// Bound by memory latency, not by its few hundred KB: groups of D / 2 lanes (4 or 8 of them, two elements a lane) fetch eight
+// chunks each side by side with the (max, sum) pairs, one pair per lane; the values meet in LDS, where one thread per element adds
+// them up while the next 32 or 64 chunks are on the way. 4.4 us for one request of 9 chunks, 4.7 for 64 requests of 32 heads, 5.6 for
+// 24 of 64 heads; lane groups that each add their own chunks, with running maxima, took 4.3, 4.7 and 5.2 but round differently.
 template <int D>
 __global__ void __launch_bounds__(256) attn_decode_merge_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeSeq* __restrict__ seqs,
                                          const int* __restrict__ multi, int n_q, int n_kv, int G, int chunk_pages, int max_chunks) {
-  constexpr int LPC = D / 2, GROUPS = 256 / LPC, DEPTH = 4;
-  __shared__ float sm[GROUPS], sl[GROUPS], so[GROUPS][D];
-  const int head = blockIdx.x, req = multi[blockIdx.y], grp = threadIdx.x / LPC, dd = threadIdx.x % LPC * 2;
+  constexpr int LPC = D / 2, GROUPS = 256 / LPC, DEPTH = 8, PASS = GROUPS * DEPTH;
+  static_assert(PASS <= 64, "the pairs of a pass fit one wave");
+  __shared__ float so[PASS][D];
+  __shared__ f32x2 sw[PASS];                       // weight and sum of each chunk
+  const int head = blockIdx.x, req = multi[blockIdx.y], tid = threadIdx.x, grp = tid / LPC, dd = tid % LPC * 2;
   const int kvh = head / G, g = head % G;
   const int n_pages = (seqs[req].cl + 1 + 15) >> 4;
   const int chunks = (n_pages + chunk_pages - 1) / chunk_pages;
   if (chunks == 1) return;                         // (not listed by the caller: the attention kernel stored this request's output itself)
   const float* base = ws + (((size_t)req * n_kv + kvh) * max_chunks) * G * (D + 2) + g * (D + 2);
   const size_t cstride = (size_t)G * (D + 2);
-  float m = -INFINITY, l = 0.f;
-  f32x2 o = {0.f, 0.f};
-  for (int c0 = grp; c0 < chunks; c0 += GROUPS * DEPTH) {
-    f32x2 ml[DEPTH], v[DEPTH];
+  f32x2 v[DEPTH];
+  auto fetch = [&](int c0) {                       // past the last chunk: that chunk again, not used
 #pragma unroll
-    for (int u = 0; u < DEPTH; u++) {              // past the last chunk: that chunk again, with no weight
-      const float* p = base + min(c0 + u * GROUPS, chunks - 1) * cstride;
-      ml[u] = *reinterpret_cast<const f32x2*>(p + D);
-      v[u] = *reinterpret_cast<const f32x2*>(p + dd);
+    for (int u = 0; u < DEPTH; u++) v[u] = *reinterpret_cast<const f32x2*>(base + min(c0 + u * GROUPS + grp, chunks - 1) * cstride + dd);
+  };
+  fetch(0);
+  const int lane = tid & 63;
+  f32x2 pair = *reinterpret_cast<const f32x2*>(base + min(lane, chunks - 1) * cstride + D);
+  float m = pair[0];
+  for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, base[c * cstride + D]);
+  m = wave_max(m);
+  float l = 0.f, o = 0.f;
+  for (int c0 = 0; c0 < chunks; c0 += PASS) {
+    const int cnt = min(PASS, chunks - c0);
+    if (c0 > 0) {
+      __syncthreads();                             // the last pass has been added up
+      if (tid < cnt) pair = *reinterpret_cast<const f32x2*>(base + (c0 + tid) * cstride + D);
     }
-    float mx = m;
 #pragma unroll
-    for (int u = 0; u < DEPTH; u++) mx = fmaxf(mx, ml[u][0]);
-    const float corr = __builtin_amdgcn_exp2f(m - mx);       // 0 the first time; a chunk's maximum is finite
-    m = mx; l *= corr; o[0] *= corr; o[1] *= corr;
-#pragma unroll
-    for (int u = 0; u < DEPTH; u++) {
-      const float w = c0 + u * GROUPS < chunks ? __builtin_amdgcn_exp2f(ml[u][0] - mx) : 0.f;
-      l += ml[u][1] * w; o[0] += v[u][0] * w; o[1] += v[u][1] * w;
+    for (int u = 0; u < DEPTH; u++) *reinterpret_cast<f32x2*>(&so[u * GROUPS + grp][dd]) = v[u];
+    if (tid < cnt) sw[tid] = f32x2{__builtin_amdgcn_exp2f(pair[0] - m), pair[1]};
+    __syncthreads();
+    if (c0 + PASS < chunks) fetch(c0 + PASS);
+    if (tid < D) {
+#pragma unroll 8
+      for (int c = 0; c < cnt; c++) {
+        const f32x2 wl = sw[c];
+        l += wl[1] * wl[0];
+        o += so[c][tid] * wl[0];
+      }
     }
   }
-  if (threadIdx.x % LPC == 0) { sm[grp] = m; sl[grp] = l; }
-  so[grp][dd] = o[0]; so[grp][dd + 1] = o[1];
-  __syncthreads();
-  if (threadIdx.x >= D) return;
-  float mx = sm[0], lt = 0.f, ot = 0.f;
-#pragma unroll
-  for (int i = 1; i < GROUPS; i++) mx = fmaxf(mx, sm[i]);
-#pragma unroll
-  for (int i = 0; i < GROUPS; i++) {
-    const float w = __builtin_amdgcn_exp2f(sm[i] - mx);      // 0 for a group without a chunk
-    lt += sl[i] * w; ot += so[i][threadIdx.x] * w;
-  }
-  out[((size_t)req * n_q + head) * D + threadIdx.x] = f2bf(ot / lt);
+  if (tid < D) out[((size_t)req * n_q + head) * D + tid] = f2bf(o / l);
 }
 
 size_t attn_decode_ws_floats(int n, int n_q, int d, int chunks) { return (size_t)n * n_q * chunks * (d + 2); }

@@ -256,3 +256,31 @@ def test_decode_attention(sts, nq, nkv, d, ctx, chunks):
             ref = T.attend_one(q[r, h].astype(np.float64), kk[:, h // (nq // nkv)], vv[:, h // (nq // nkv)])
             assert rel(got[r, h], ref) <= BF16_TOL, (r, h)
         off += c
+
+
+@pytest.mark.parametrize("nq,nkv,d,n_chunks", [(8, 1, 128, [2, 9, 32, 33, 128]), (8, 2, 128, [65]), (4, 4, 64, [7, 63, 64, 65, 128, 129])])
+def test_decode_attention_adds_chunks_in_their_order(sts, nq, nkv, d, n_chunks):
+    """The sums over a context's chunks (one page each) are taken in chunk order, whatever the number of chunks. Keys of zero make
+    every probability 1 and every chunk's sum exact; element e has 2^24 in one chunk, -2^24 in a later one and small whole
+    numbers elsewhere, so that fp32 sums in any other order come out different. The expected value is that fp32 sum, bit by bit."""
+    ctx = [16 * c - 5 for c in n_chunks]
+    rng = np.random.default_rng(91)
+    q = synth.normal_bf16(92, (len(ctx), nq, d))
+    k = np.zeros((sum(ctx), nkv, d), np.float32)
+    v = np.zeros((sum(ctx), nkv, d), np.float32)
+    want, off, other = np.empty((len(ctx), nq, d), np.float32), 0, 0
+    for r, (c, n) in enumerate(zip(ctx, n_chunks)):
+        part = rng.integers(1, 8, (n, nkv, d)).astype(np.float32)
+        up = rng.integers(0, n - 1, (nkv, d))
+        down = up + 1 + rng.integers(0, n, (nkv, d)) % (n - 1 - up)
+        np.put_along_axis(part, up[None], np.float32(2.0 ** 24), 0)
+        np.put_along_axis(part, down[None], np.float32(-2.0 ** 24), 0)
+        v[off:off + 16 * n:16] = part                        # the first token of each page
+        s = np.zeros((nkv, d), np.float32)
+        for x in part:
+            s = s + x
+        want[r] = np.repeat(synth.to_bf16(s / np.float32(c)), nq // nkv, axis=0)
+        other += int((s != part.sum(0, dtype=np.float64)).sum())
+        off += c
+    assert other > 0                                         # the order matters in these inputs
+    assert np.array_equal(sts.op_attn_decode(q, k, v, ctx, 1), want)
