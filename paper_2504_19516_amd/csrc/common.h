@@ -30,6 +30,13 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// One rotation pair (a, b) by the angle with cosine c and sine s. The fused multiply-adds are written out: every kernel that
+// rotates rounds alike, whatever order the compiler would have picked for it.
+__device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, float* ya, float* yb) {
+  *ya = fmaf(a, c, -(b * s));
+  *yb = fmaf(b, c, a * s);
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave writes at
 // lds_dst + 16 * l (lds_dst must be wave-uniform); completion is counted by vmcnt. Buffers filled
 // this way are kept 1 KB above LDS address 0.

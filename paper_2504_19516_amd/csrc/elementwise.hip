@@ -316,9 +316,10 @@ __global__ void __launch_bounds__(256) rope_kv_prefill_kernel(bf16* qkv, int ld,
     bf16x8 ya, yb;
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-      const float fa = bf2f(a[e]), fb = bf2f(b[e]), ce = c4[e >> 2][e & 3], se = s4[e >> 2][e & 3];
-      ya[e] = f2bf(fa * ce - fb * se);
-      yb[e] = f2bf(fa * se + fb * ce);
+      float ra, rb;
+      rotate_pair(bf2f(a[e]), bf2f(b[e]), c4[e >> 2][e & 3], s4[e >> 2][e & 3], &ra, &rb);
+      ya[e] = f2bf(ra);
+      yb[e] = f2bf(rb);
     }
     bf16* dst = hd < n_q ? r + hd * d : pool + ((size_t)page * geo.n_kv + (hd - n_q)) * geo.head_elems() + (size_t)slot * d;
     *reinterpret_cast<bf16x8*>(dst + i0) = ya;
@@ -416,9 +417,10 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         // the projection's result is rounded to bf16 before the rotation, as in the prefill path
-        const float fa = bf2f(f2bf(a[e])), fb = bf2f(f2bf(b[e]));
-        ya[e] = f2bf(fa * cs[e] - fb * sn[e]);
-        yb[e] = f2bf(fa * sn[e] + fb * cs[e]);
+        float ra, rb;
+        rotate_pair(bf2f(f2bf(a[e])), bf2f(f2bf(b[e])), cs[e], sn[e], &ra, &rb);
+        ya[e] = f2bf(ra);
+        yb[e] = f2bf(rb);
       }
       bf16* dst = hd < n_q ? q_out + (size_t)row * n_q * d + hd * d
                            : pool + ((size_t)page * geo.n_kv + (hd - n_q)) * geo.head_elems() + (size_t)slot * d;

@@ -231,9 +231,10 @@ __global__ void __launch_bounds__(NW * 64, 4) gemm_kslice_kernel(KsArgs g) {
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         // the projection's result is rounded to bf16 before the rotation, as in the prefill path
-        const float fa = bf2f(f2bf(a4[e])), fb = bf2f(f2bf(b4[e]));
-        ya[e] = f2bf(fa * cs[e] - fb * sn[e]);
-        yb[e] = f2bf(fa * sn[e] + fb * cs[e]);
+        float ra, rb;
+        rotate_pair(bf2f(f2bf(a4[e])), bf2f(f2bf(b4[e])), cs[e], sn[e], &ra, &rb);
+        ya[e] = f2bf(ra);
+        yb[e] = f2bf(rb);
       }
       bf16* dst = head < g.n_q ? g.q_out + (size_t)row * g.n_q * d + head * d
                                : g.pool + ((size_t)page * g.geo.n_kv + (head - g.n_q)) * g.geo.head_elems() + (size_t)slot * d;

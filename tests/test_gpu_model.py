@@ -729,3 +729,45 @@ def test_prefill_rows_finished_and_normalised_in_one_kernel(wide_rows, cus, rows
     assert rel(got, orc.prefill_append(0, tok)) <= TOL
     assert (norms < 6) == (rows > 33)                        # up to 64 rows the tiles are 64 x 128 or uncut
     free_all(eng, [s])
+
+
+def test_rotated_keys_are_rounded_alike_by_every_kernel(sts):
+    """Cached K of prefill (8192 tokens) and of decode steps (16 steps of 224 requests, and of 8: the split and the finishing
+    GEMM form) against the documented rounding, bit by bit: bf16(fma(a, c, -(b s))) and bf16(fma(b, c, a s)) of the bf16
+    projections a, b. Embeddings of +-1 make the normalised rows +-1 exactly, one weight per K row makes the projections that weight, up
+    to the sign. The other order of the second product moves about one element in 10^5."""
+    n_kv, d, hid, vocab = 8, 128, 512, 256
+    desc = synth.ModelDesc(1, hid, 8, n_kv, d, 256, vocab, 16, 1.0e4, 1.0e-5, "bf16")
+    w = synth.make_weights(desc, 79)
+    rng = np.random.default_rng(79)
+    w["emb"] = np.where(rng.random((vocab, hid)) < 0.5, -1, 1).astype(np.float32)
+    col, val = rng.integers(0, hid, n_kv * d), synth.normal_bf16(79, n_kv * d)
+    w["layers"][0]["wk"] = np.zeros((n_kv * d, hid), np.float32)
+    w["layers"][0]["wk"][np.arange(n_kv * d), col] = val
+
+    def expect(tok, pos):
+        x = (w["emb"][np.asarray(tok)][:, col] * val).reshape(-1, n_kv, d)
+        a, b = x[:, :, :d // 2].astype(np.float64), x[:, :, d // 2:].astype(np.float64)
+        ang = np.asarray(pos, np.float64)[:, None] * (1.0e4 ** (-2.0 * np.arange(d // 2) / d))[None]
+        c, s = (f(ang).astype(np.float32).astype(np.float64)[:, None, :] for f in (np.cos, np.sin))
+        ya = (a * c - (b * s).astype(np.float32)).astype(np.float32)         # a c is exact in 64 bits
+        yb = (b * c + (a * s).astype(np.float32)).astype(np.float32)
+        return synth.to_bf16(np.concatenate([ya, yb], axis=2))
+
+    eng = new_engine(sts, desc, max_prefill_tokens=8192, max_decode_batch=224, max_seqs=232, kv_pool_pages=1600, max_pages_per_seq=520)
+    eng.load_all(w)
+    s = eng.seq_create()
+    tok = synth.tokens(801, 8192, vocab)
+    eng.prefill_append(s, tok)
+    assert np.array_equal(eng.kv_read(0, s, 0, 8192)[0].reshape(8192, n_kv, d), expect(tok, np.arange(8192)))
+    eng.seq_free(s)
+    for n in (224, 8):
+        lens = synth.uniform_lengths(82, n, 1, 60)
+        seqs = gpu_contexts(eng, [synth.tokens(900 + i, int(c), vocab) for i, c in enumerate(lens)])
+        for step in range(16):
+            tok = synth.tokens(1000 + step, n, vocab)
+            eng.decode_step(seqs, tok)
+            got = np.concatenate([eng.kv_read(0, q, int(c) + step, 1)[0] for q, c in zip(seqs, lens)]).reshape(n, n_kv, d)
+            assert np.array_equal(got, expect(tok, lens + step)), (n, step)
+        free_all(eng, seqs)
+    eng.close()
