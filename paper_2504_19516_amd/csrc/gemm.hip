@@ -13,7 +13,7 @@
 // operand reads of the next 16-wide step are slotted between the MFMAs of the current one. It runs
 // the 128x128 tiles with 4 waves (two workgroups per CU) for prefill, the 64x128 (4 waves, two per
 // CU) and 64x256 (8 waves) tiles with split-K for decode batches, and row-major W of callers that
-// bring their own weights (256-column tiles of those: gemm_rowmajor256_kernel).
+// bring their own weights.
 // gemm_skinny_kernel: decode batches of up to 64 rows -- tiles of 256 to 512 columns, the W operands three K tiles deep in
 // registers.
 // Epilogues: bf16 store, fp32 store (split-K partial sums), fp32 residual add, SwiGLU on interleaved
@@ -789,9 +789,11 @@ __global__ void __launch_bounds__(512, 2) gemm_rows_kernel(GemmArgs g) {
   }
 }
 
-// ---- the same tiles with row-major W (callers that bring their own weights; fp32 store) --------------------------
-// Both operands through LDS as in gemm_dl_kernel (two stages), waves of 128 x 64, and the 16 x 16 x 32 instruction: an element's
-// products are summed in the order of gemm_rows_kernel. A step's operands are taken in two groups of four row blocks.
+// ---- the same tiles with row-major W (callers that bring their own weights; fp32 store), many of them ---------------
+// Both operands through LDS in two stages, waves of 128 x 64, and the 16 x 16 x 32 instruction, whose chain along K gives bit for
+// bit what the 32 x 32 x 16 one gives. It holds a higher clock where the chip is full for long (see gemm_rows_kernel) but waits
+// for a whole stage at each barrier: gemm_dl_kernel's tiles are faster where every CU has one (launch_rowmajor256). A step's
+// operands are taken in two groups of four row blocks.
 template <int WGM>
 __global__ void __launch_bounds__(WGM * 256, 2) gemm_rowmajor256_kernel(GemmArgs g) {
   constexpr int BM = WGM * 128, BN = 256, BK = 64, NT = WGM * 256, ROWB = BK * 2, STAGE = (BM + BN) * ROWB;
@@ -1088,22 +1090,31 @@ static hipError_t launch_rows(hipStream_t s, GemmArgs g, int splits, const GemmT
   return hipGetLastError();
 }
 
-// Row-major W with a 256-column tile.
+// Row-major W with a 256-column tile (fp32 store). Fewer workgroups than a GPU has CUs: gemm_dl_kernel; else gemm_rowmajor256_kernel,
+// if its 16-byte stores are aligned. Both give the same bits. 520 x 4096 x 4096 77 us against 83, 223 rows in four slices 30 against 35,
+// 2048 x 4096 x 14336 (128 tiles) 314 against 316; 2048 x 4096 x 4096 in 256 tiles of 128 rows 66.7 against 65.3, 4096 x 28672 x 4096
+// (1792 tiles) 798 against 757.
 template <int WGM>
 static hipError_t launch_rowmajor256(hipStream_t s, GemmArgs g, int splits, const GemmTail* tail) {
   constexpr int BM = WGM * 128, BN = 256;
   constexpr size_t lds = GEMM_DL_LDS_BASE + 2 * (size_t)(BM + BN) * 64 * sizeof(bf16);
+  void (*const few)(GemmArgs) = gemm_dl_kernel<BM, BN, WGM, 4, EPI_F32, 2, false>;
+  void (*const many)(GemmArgs) = gemm_rowmajor256_kernel<WGM>;
   static std::atomic<bool> attr_set{false};
   if (!attr_set.load()) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_rowmajor256_kernel<WGM>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    for (void (*k)(GemmArgs) : {few, many}) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
+    }
     attr_set.store(true);
   }
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = g.N / BN;
   const int tiles = g.tiles_m * g.tiles_n;
   const int ny = plan_launch(&g, tiles, splits, tail, BM * BN);
-  hipLaunchKernelGGL((gemm_rowmajor256_kernel<WGM>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(WGM * 256), lds, s, g);
+  const bool aligned = reinterpret_cast<uintptr_t>(g.C) % 16 == 0 && g.ldc % 4 == 0 && g.split_stride % 4 == 0;
+  const bool full = (long long)g.n_full * ny + g.n_pieces >= 256;
+  hipLaunchKernelGGL(full && aligned ? many : few, dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(WGM * 256), lds, s, g);
   if (g.n_pieces > 0)
     hipLaunchKernelGGL((gemm_tail_fixup<BM, BN, EPI_F32>), dim3(tiles - g.n_full, BM * BN / 1024), dim3(256), 0, s, g);
   return hipGetLastError();
@@ -1156,7 +1167,7 @@ hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, co
   if (w_packed && ldw != K) return hipErrorInvalidValue;          // packed blocks are addressed by K alone
   if (splits < 1 || (splits > 1 && epi != EPI_F32)) return hipErrorInvalidValue;
   // 16-byte output stores
-  if ((cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 ? 8 : 4) != 0) return hipErrorInvalidValue;
+  if (w_packed && (cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 ? 8 : 4) != 0) return hipErrorInvalidValue;
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_64x256) return hipErrorInvalidValue;   // its wave tile is one 32-column block, not a gate/up pair
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not offered: the shape is for the O and down projections
   GemmArgs g{};

@@ -61,6 +61,10 @@ CASES = [
     [(150, 1024, 2048, "64x128", 4, 0), (37, 512, 1024, "64x128", 3, 0)],
     [(300, 1024, 1024, "128x128", 1, 20), (130, 512, 512, "128x128", 1, 6)],
     [(520, 1024, 1024, "256x256", 1, 10), (64, 256, 512, "64x128", 8, 0)],
+    [(223, 512, 4096, "256x256", 2, 0), (200, 512, 1088, "256x256", 1, 0)],
+    [(300, 768, 1088, "128x256", 1, 7), (33, 512, 192, "128x256", 1, 0)],
+    # as many workgroups as the GPU has CUs, and one fewer row of them
+    [(2048, 4096, 192, "128x256", 1, 0), (1900, 4096, 192, "128x256", 1, 0)],
 ]
 
 
@@ -82,6 +86,27 @@ def test_noalloc_gemm_equals_the_allocating_entry_point(pair):
             assert np.isfinite(got).all()
             assert rel(got, want) <= TOL_ACC, (m, n, k, tile, split_k, tail_slots)
             assert np.array_equal(got, want)                                 # same kernels, same summation order
+    finally:
+        hip.free_all()
+
+
+@pytest.mark.parametrize("tile,m,n", [("256x256", 300, 512), ("128x256", 300, 512), ("128x128", 300, 512), ("64x128", 300, 512),
+                                      ("128x256", 2048, 4096)])
+def test_noalloc_gemm_output_at_any_float(tile, m, n):
+    """Whole tiles of row-major weights are stored float by float: the output need not be aligned to more than a float."""
+    from paper_2504_19516_amd import sts
+    sts.lib()
+    hip = Hip()
+    try:
+        k = 192
+        a, w = synth.normal_bf16(300, (m, k)), synth.normal_bf16(301, (n, k), 0.05)
+        a_dev, w_dev = hip.upload(synth.bf16_bits(a)), hip.upload(synth.bf16_bits(w))
+        c_dev = hip.upload(np.full(m * n + 2, 7.0, np.float32))
+        sts.op_gemm_noalloc(a_dev, w_dev, c_dev + 4, m, n, k, tile, 1, 0)
+        hip.sync()
+        got = hip.download(c_dev, (m * n + 2,), np.float32)
+        assert got[0] == 7.0 and got[-1] == 7.0
+        assert np.array_equal(got[1:-1].reshape(m, n), sts.op_gemm(a, w, tile, epilogue=1))
     finally:
         hip.free_all()
 
