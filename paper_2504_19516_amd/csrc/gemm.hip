@@ -1079,7 +1079,8 @@ static hipError_t launch_rows(hipStream_t s, GemmArgs g, int splits, const GemmT
   const int height = row_tiles > 0 ? (g.row_blocks + row_tiles - 1) / row_tiles : std::min(tile_blocks, g.row_blocks);   // blocks of the tallest tile
   if (height > 8 || g.tiles_m > g.row_blocks) return hipErrorInvalidValue;
   const int tiles = g.tiles_m * g.tiles_n;
-  const int ny = plan_launch(&g, tiles, splits, tail, height * 32 * 256);
+  // row_tiles == 0: pieces of whole tiles, so that the cut is that of the row-major form
+  const int ny = plan_launch(&g, tiles, splits, tail, (row_tiles > 0 ? height : tile_blocks) * 32 * 256);
   hipLaunchKernelGGL((gemm_rows_kernel<EPI>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(512), lds, s, g);
   if (EPI == EPI_RESID_F32 && g.n_pieces > 0 && tail->norm && g.N <= FIXUP_NORM_MAX_N) {
     ResidNorm& r = *tail->norm;

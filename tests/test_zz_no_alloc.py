@@ -61,7 +61,9 @@ CASES = [
     [(150, 1024, 2048, "64x128", 4, 0), (37, 512, 1024, "64x128", 3, 0)],
     [(300, 1024, 1024, "128x128", 1, 20), (130, 512, 512, "128x128", 1, 6)],
     [(520, 1024, 1024, "256x256", 1, 10), (64, 256, 512, "64x128", 8, 0)],
-    [(223, 512, 4096, "256x256", 2, 0), (200, 512, 1088, "256x256", 1, 0)],
+    # fewer rows than the tile: the last wave is cut alike (here not at all: three pieces a tile are more than the slots)
+    [(130, 2048, 1024, "256x256", 1, 15), (223, 512, 4096, "256x256", 2, 0)],
+    [(200, 512, 1088, "256x256", 1, 0), (129, 1024, 576, "256x256", 1, 5)],
     [(300, 768, 1088, "128x256", 1, 7), (33, 512, 192, "128x256", 1, 0)],
     # as many workgroups as the GPU has CUs, and one fewer row of them
     [(2048, 4096, 192, "128x256", 1, 0), (1900, 4096, 192, "128x256", 1, 0)],
