@@ -382,6 +382,7 @@ double plan_decode_gemm(const StreamRates& r, int m, int n, int k, int cus, bool
 // activations of the whole K, whose 16-byte pieces cost about twice their bytes. Measured against it: 28672 x 4096 at 1 / 16 rows
 // 37 / 41 us on 256 CUs (38 / 38 estimated), 46 / 62 on 128 (42 / 65), 153 / 220 on 32 (140 / 260).
 double kslice_time(const sts_ctx* ctx, int epi, int m, int n, int k, int cus) {
+  if (!kslice_covers(n, k)) return HUGE_VAL;         // a vocabulary of 2^23 at hidden 256, 262144 at 8192: the tile forms take those
   const int c = std::max(cus, 8), cols = kslice_cols(epi, n, c), wgs = n / cols;
   const double per_cu = wgs <= c ? 1.0 : (double)wgs / c;
   return std::max(2.0 * n * k / (0.95 * ctx->stream_bw_gpu), per_cu * 2.0 * k * (cols + 2 * m) / (0.93 * ctx->stream_bw_cu)) + 2.5e-6;

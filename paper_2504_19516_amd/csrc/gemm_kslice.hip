@@ -253,7 +253,7 @@ hipError_t launch_ks(hipStream_t s, const KsArgs& g, int grid) {
 // Byte offsets into W and the activations are 32 bits wide; a workgroup reads rows up to M - 1 of A only.
 bool fill(KsArgs* g, const KsliceIn& in) {
   if (!in.A || !in.W || in.M < 1 || in.M > KSLICE_MAX_ROWS || in.N < 64 || in.N % 64 != 0 || in.K < 64 || in.K % 64 != 0 || in.lda % 8 != 0 || in.lda < in.K) return false;
-  if ((unsigned long long)in.N * in.K * 2 >= (1ull << 32) || (in.scale.ssq && in.scale.parts < 1)) return false;
+  if (!kslice_covers(in.N, in.K) || (in.scale.ssq && in.scale.parts < 1)) return false;
   *g = KsArgs{};
   g->A = in.A; g->W = in.W; g->lda = in.lda; g->M = in.M; g->N = in.N; g->K = in.K;
   g->ssq = in.scale.ssq; g->ssq_parts = in.scale.parts; g->eps = in.scale.eps;

@@ -134,6 +134,8 @@ int attn_decode_max_chunk_tokens();
 // ---- decode GEMMs that finish their own output (gemm_kslice.hip) ----------------------------
 enum KsliceEpilogue { KS_F32 = 0, KS_RESID = 1, KS_SWIGLU = 2, KS_QKV = 3 };
 constexpr int KSLICE_MAX_ROWS = 16;
+// Sizes the form takes: its byte offsets into W are 32 bits wide. A plan asks before it compares times.
+inline bool kslice_covers(int n, int k) { return (unsigned long long)n * k * 2 < (1ull << 32); }
 // Row factor of a GEMM's activations: 1 / sqrt(sum of `parts` shares of the row's sum of squares / K + eps); none if ssq is null.
 struct RowScale { const float* ssq; int parts; float eps; };
 // A [M, lda] row-major, W [N, K] in the packed layout.

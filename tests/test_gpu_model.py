@@ -771,3 +771,23 @@ def test_rotated_keys_are_rounded_alike_by_every_kernel(sts):
             assert np.array_equal(got, expect(tok, lens + step)), (n, step)
         free_all(eng, seqs)
     eng.close()
+
+
+@pytest.mark.parametrize("vocab", [2 ** 23, 2 ** 23 - 128])
+def test_head_of_four_gib(sts, vocab):
+    """An LM head of 2^32 bytes, which the GEMM that finishes its own output does not take (32-bit offsets), and the largest it does:
+    prefill and decode of one request against the oracle, on the first and the last 1024 rows of the vocabulary (weights are drawn
+    by position, so a model with those rows alone has the same ones)."""
+    seed, d = 91, lambda v: synth.ModelDesc(1, 256, 4, 1, 64, 256, v, 16, 1.0e4, 1.0e-5, "bf16")
+    w = synth.make_weights(d(1024), seed)
+    lm_end = synth.weight_slice(seed, synth.tensor_id("lm"), (vocab - 1024) * 256, 1024 * 256, True).reshape(1024, 256)
+    prompt, tok = synth.tokens(92, 40, 1024), synth.tokens(93, 1, 1024)
+    eng = new_engine(sts, d(vocab), weight_seed=seed, max_prefill_seqs=1, max_decode_batch=1)
+    s = eng.seq_create()
+    got = [eng.prefill_append(s, prompt).reshape(-1), eng.decode_step([s], tok)[0].reshape(-1)]
+    eng.close()
+    for lm, rows in ((w["lm"], slice(0, 1024)), (lm_end, slice(vocab - 1024, vocab))):
+        orc = T.Oracle(d(1024), dict(w, lm=lm), 8)
+        orc.kv.add_sequence(0, [0, 1, 2])
+        ref = [orc.prefill_append(0, prompt).reshape(-1), orc.decode_step([0], tok).reshape(-1)]
+        assert rel(got[0][rows], ref[0]) <= TOL and rel(got[1][rows], ref[1]) <= TOL
