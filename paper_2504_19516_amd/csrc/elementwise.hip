@@ -201,13 +201,7 @@ __device__ __forceinline__ void write_rotation(float* table, int row, int pos, c
     table[(size_t)row * 2 * half + half + i] = (float)sv;
   }
 }
-__device__ __forceinline__ int row_position(const RowRotation& r, int row) {
-  if (r.dseq) return r.dseq[row].cl;
-  int si = 0;
-  while (si + 1 < r.n_seqs && row >= r.pseq[si + 1].row0) si++;
-  return r.pseq[si].p + (row - r.pseq[si].row0);
-}
-__global__ void rotation_kernel(RowRotation rot) { write_rotation(rot.table, blockIdx.x, row_position(rot, blockIdx.x), rot.inv_freq, rot.d >> 1); }
+__global__ void rotation_kernel(RowRotation rot) { write_rotation(rot.table, blockIdx.x, rot.pos[blockIdx.x], rot.inv_freq, rot.d >> 1); }
 hipError_t row_rotation(hipStream_t s, const RowRotation& rot, int n) {
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(rotation_kernel, dim3(n), dim3(64), 0, s, rot);
@@ -246,7 +240,7 @@ __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, co
       for (int j = 0; j < 8; j++) { const float f = bf2f(v[i][j]); ss += f * f; }
     }
   }
-  write_rotation(rot.table, row, row_position(rot, row), rot.inv_freq, rot.d >> 1);      // while the row is on its way
+  write_rotation(rot.table, row, rot.pos[row], rot.inv_freq, rot.d >> 1);      // while the row is on its way
   const float w = wave_sum(ss);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = w;
   __syncthreads();

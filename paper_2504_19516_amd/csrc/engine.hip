@@ -70,10 +70,10 @@ struct Phase {
   // pinned block and reaches the device in a single copy; the pointers below are views into the
   // two blocks, laid out afresh by every launch.
   unsigned char* h_meta = nullptr; unsigned char* d_meta = nullptr; size_t meta_bytes = 0, meta_used = 0;
-  int* d_tokens = nullptr; int* d_bt = nullptr; int* d_rows = nullptr;
+  int* d_tokens = nullptr; int* d_pos = nullptr; int* d_bt = nullptr; int* d_rows = nullptr;
   PrefillSeq* d_pseq = nullptr; DecodeSeq* d_dseq = nullptr; AttnItem* d_items = nullptr; DecodeItem* d_ditems = nullptr;
   // pinned staging
-  int* h_tokens = nullptr; int* h_bt = nullptr; int* h_rows = nullptr;
+  int* h_tokens = nullptr; int* h_pos = nullptr; int* h_bt = nullptr; int* h_rows = nullptr;
   PrefillSeq* h_pseq = nullptr; DecodeSeq* h_dseq = nullptr; AttnItem* h_items = nullptr; DecodeItem* h_ditems = nullptr;
   float* h_logits = nullptr; int* h_next = nullptr;
   int rows = 0;                               // rows of the last call
@@ -452,7 +452,7 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
   return STS_OK;
 }
 
-// Up to this many rows the embedding kernel reads its tokens and records from pinned host memory (one bus read each).
+// Up to this many rows the embedding kernel reads its tokens and positions from pinned host memory (one bus read each).
 constexpr int META_FUSED_ROWS = 512;
 // Logits a head's last kernel stores straight to host memory (64-byte pieces over the bus), and those that greedy sampling copies
 // on the side in whole lines; beyond, the copy engine is faster than either.
@@ -573,6 +573,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   AttnMerge *h_merges = nullptr, *d_merges = nullptr;
   meta_take(ph, &h_merges, &d_merges, n_merges);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
+  meta_take(ph, &ph.h_pos, &ph.d_pos, lb == 0 ? rows : 0);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
@@ -584,6 +585,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     std::memcpy(ph.h_bt + bt_off, s.pages.data(), s.pages.size() * sizeof(int));
     bt_off += (int)s.pages.size();
     ph.h_rows[i] = r0 + lens[i] - 1;
+    for (int j = 0; lb == 0 && j < lens[i]; j++) ph.h_pos[r0 + j] = s.len + j;
     r0 += lens[i];
   }
   std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
@@ -594,9 +596,9 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   const int h = d.hidden;
   const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
   const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
-  // few rows: the embedding kernel reads tokens and sequence records from host memory itself and copies the metadata on the side
+  // few rows: the embedding kernel reads tokens and positions from host memory itself and copies the metadata on the side
   const bool fused_meta = fused_embed && rows <= META_FUSED_ROWS;
-  RowRotation rot{ph.rot, nullptr, fused_meta ? ph.h_pseq : ph.d_pseq, n_seqs, c->inv_freq, d.head_dim};
+  RowRotation rot{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
   if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
   if (fused_embed) {
     KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
@@ -702,6 +704,7 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   ph.meta_used = 0;
   meta_take(ph, &ph.h_dseq, &ph.d_dseq, n);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, n);
+  meta_take(ph, &ph.h_pos, &ph.d_pos, n);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n; i++) bt_entries += (c->seqs[seqs[i]].len + 1 + pt - 1) / pt;
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
@@ -715,6 +718,7 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
     bt_off += np;
     max_pages = std::max(max_pages, np);
     ph.h_tokens[i] = in_tokens[i];
+    ph.h_pos[i] = s.len;
   }
   std::vector<int> np_list(n);
   for (int i = 0; i < n; i++) np_list[i] = ph.h_dseq[i].n_pages;
@@ -748,7 +752,7 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   const int h = d.hidden;
   const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
   const bool fused_meta = h <= 8192 && n <= META_FUSED_ROWS;
-  RowRotation rot{ph.rot, fused_meta ? ph.h_dseq : ph.d_dseq, nullptr, 0, c->inv_freq, d.head_dim};
+  RowRotation rot{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
   if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
   if (h <= 8192) {
     KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
@@ -848,7 +852,7 @@ int alloc_phase(sts_ctx* c, int side) {
     // decode attention items: a context has at most 128 chunks, and fewer than one per 4 pages (chunks hold >= 8)
     const size_t dec_items = side == 1 ? nseq * (size_t)decode_max_chunks((int)mp) : 0;
     ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + 2 * sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
-                    rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
+                    2 * rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
     STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes + 16));      // copied in 16-byte pieces
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));
   }

@@ -82,9 +82,9 @@ hipError_t export_weight(hipStream_t s, float* dst, const bf16* src, int ld, int
                          int row_offset, int interleave_block, int interleave_phase, int packed);
 hipError_t fill_f32(hipStream_t s, float* dst, float v, size_t n);
 hipError_t embed_rows(hipStream_t s, float* X, const bf16* emb, const int* tokens, int n, int h);
-// Rotation angles of a launch's rows, written to table [row][d / 2 cosines | d / 2 sines]: positions from dseq (one row per decode
-// request) or pseq.
-struct RowRotation { float* table; const DecodeSeq* dseq; const PrefillSeq* pseq; int n_seqs; const double* inv_freq; int d; };
+// Rotation angles of a launch's rows, written to table [row][d / 2 cosines | d / 2 sines]. pos: each row's position (device or pinned
+// host memory: one read a row).
+struct RowRotation { float* table; const int* pos; const double* inv_freq; int d; };
 hipError_t row_rotation(hipStream_t s, const RowRotation& rot, int n);
 // Metadata in pinned host memory to the device (bytes rounded up to 16 must be readable and writable).
 struct MetaCopy { const unsigned char* src; unsigned char* dst; int bytes; };

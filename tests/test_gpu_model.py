@@ -791,3 +791,27 @@ def test_head_of_four_gib(sts, vocab):
         orc.kv.add_sequence(0, [0, 1, 2])
         ref = [orc.prefill_append(0, prompt).reshape(-1), orc.decode_step([0], tok).reshape(-1)]
         assert rel(got[0][rows], ref[0]) <= TOL and rel(got[1][rows], ref[1]) <= TOL
+
+
+def test_embedding_time_does_not_depend_on_the_number_of_prompts(sts):
+    """512 rows are embedded in about the same time whether they are one prompt or 64: a row's position is read, not looked for
+    among the prompts (which took a bus read per prompt before it). Positions themselves: the logits of the two batches agree."""
+    desc = synth.tiny_model("bf16")
+    eng = new_engine(sts, desc, max_prefill_seqs=64, max_seqs=72)
+    tok = synth.tokens(821, 512, desc.vocab)
+    best = {}
+    for n in (1, 64):
+        parts = np.split(tok, n)
+        for _ in range(6):
+            seqs = [eng.seq_create() for _ in parts]
+            eng.kernel_timing(True)
+            eng.kernel_times(0, reset=True)
+            got = eng.prefill_batch(seqs, parts)
+            t = eng.kernel_times(0, reset=True)["embed"][0]
+            eng.kernel_timing(False)
+            free_all(eng, seqs)
+            best[n] = min(best.get(n, t), t)
+    assert best[64] <= 2 * best[1], best
+    s = eng.seq_create()
+    assert rel(eng.prefill_append(s, parts[-1]), got[-1]) <= TOL
+    eng.close()
