@@ -65,11 +65,11 @@ class Profile:
     use_waveq: int = 1
     tail_cut: int = 0                  # > 0: the GEMMs cut the tiles of a partly filled last wave along K, into at most this many pieces
     # measured rates the GPU library's tile choice reads from the same file; the estimator does not use them:
-    # GFLOP/s per busy CU of the 128x128, 256x256 and 128x256 GEMM tiles, MB/s per CU for partial tiles written and read back
+    # GFLOP/s per busy CU of the 128x128 and 256x256 GEMM tiles, MB/s per CU for partial tiles written and read back
     gemm_rate_128: int = 3500
     gemm_rate_256: int = 4800
-    gemm_rate_128x256: int = 5000
-    gemm_fixed_128x256: int = 25000    # ns: start-up and epilogue of that tile, which runs one per CU
+    gemm_rate_128x256: int = 5000      # (this one and the next: fields of the format that nothing reads)
+    gemm_fixed_128x256: int = 25000
     partial_bw_cu: int = 20000
     # MB/s of a plain read-only stream, per CU of a 32-CU partition and of the whole GPU (the GPU library plans its decode GEMMs with them)
     stream_bw_cu: int = 59000

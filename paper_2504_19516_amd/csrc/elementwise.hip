@@ -189,9 +189,6 @@ __global__ void __launch_bounds__(256) rmsnorm_kernel(bf16* out, const float* X,
     }
   }
 }
-// Embedding rows and the first layer's RMSNorm in one pass: the row is in registers anyway, so the residual stream
-// (fp32) and its normalised bf16 copy are written together and the stream is not read back. One workgroup per row,
-// 8 elements per thread and 2048-column slab, rows of up to 8192 elements.
 // The rotation angles of a launch's rows are written once for all layers: cosines and sines of row's position, [row][d].
 __device__ __forceinline__ void write_rotation(float* table, int row, int pos, const double* inv_freq, int half) {
   for (int i = threadIdx.x; i < half; i += blockDim.x) {
@@ -218,6 +215,9 @@ hipError_t copy_in(hipStream_t s, const MetaCopy& meta) {
   hipLaunchKernelGGL(copy_in_kernel, dim3((meta.bytes + 4095) / 4096), dim3(256), 0, s, meta);
   return hipGetLastError();
 }
+// Embedding rows and the first layer's RMSNorm in one pass: the row is in registers anyway, so the residual stream
+// (fp32) and its normalised bf16 copy are written together and the stream is not read back. One workgroup per row,
+// 8 elements per thread and 2048-column slab, rows of up to 8192 elements.
 __global__ void __launch_bounds__(256) embed_norm_kernel(float* X, bf16* out, const bf16* emb, const int* tokens, const float* gain, float eps, int h, int n,
                                                          RowRotation rot, MetaCopy meta) {
   constexpr int PER = 4;

@@ -66,9 +66,9 @@ struct Phase {
   float* tail_ws = nullptr; size_t tail_ws_bytes = 0;         // prefill: GEMM tail pieces, partial attention outputs, head partial sums
   int max_attn_extra = 0;
   bf16* Xlast_n = nullptr; float* logits = nullptr;
-  // Per-call metadata (sequence records, block tables, work items, token ids) is packed into one
-  // pinned block and reaches the device in a single copy; the pointers below are views into the
-  // two blocks, laid out afresh by every launch.
+  // Per-call metadata (sequence records, block tables, work items, token ids, positions) is packed into one pinned
+  // block, which a kernel copies to the device (the embedding kernel on the side, or copy_in); the pointers below are views
+  // into the two blocks, laid out afresh by every launch.
   unsigned char* h_meta = nullptr; unsigned char* d_meta = nullptr; size_t meta_bytes = 0, meta_used = 0;
   int* d_tokens = nullptr; int* d_pos = nullptr; int* d_bt = nullptr; int* d_rows = nullptr;
   PrefillSeq* d_pseq = nullptr; DecodeSeq* d_dseq = nullptr; AttnItem* d_items = nullptr; DecodeItem* d_ditems = nullptr;
@@ -111,9 +111,9 @@ struct sts_ctx {
   void* probe_src = nullptr; void* probe_dst = nullptr; size_t probe_bytes = 0;
   std::vector<void*> allocs;
   std::vector<hipStream_t> used_streams;       // every pooled stream this ctx ever selected (guarded by part_mu)
-  // what the tile choice of the prefill GEMMs assumes about the part (sts_set_tile_model): TFLOP/s per busy CU of
-  // the 128x128 tiles (two workgroups per CU) and of the 256x256 tiles (one), bytes/s per CU for partial tiles
-  double rate_128 = 3.5, rate_256 = 4.8, rate_128x256 = 5.0, fixed_128x256 = 25e-6, partial_bw = 20e9;
+  // what the choice of GEMM tiles assumes about the part (sts_set_tile_model): TFLOP/s per busy CU of the 128x128
+  // tiles (two workgroups per CU) and of the 256x256 tiles (one), bytes/s per CU for partial tiles
+  double rate_128 = 3.5, rate_256 = 4.8, partial_bw = 20e9;
   double stream_bw_cu = 59e9, stream_bw_gpu = 6.4e12;          // read-only streams: bytes/s per CU of a 32-CU partition, bytes/s of the whole GPU
 };
 
@@ -246,7 +246,7 @@ int pick_cfg(int m, int n, int k, int cus) {
 // estimated time, which is where wave quantisation (paper Section 2.2.1) enters -- complete
 // waves of workgroups at the tile's busy-CU rate, then the last wave, whole or cut along K.
 // Rates are measured busy-CU throughputs in TFLOP/s per CU: 128x128 tiles run two workgroups
-// per CU, the 256-column tiles (8 waves) one. The latter come in heights of 32 to 256 rows: the rows
+// per CU, the 256-column tiles (8 waves) one; rate_256 is that of the tallest. The latter come in heights of 32 to 256 rows: the rows
 // are dealt to any number of row tiles, so that they fill whole waves of workgroups.
 struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; };
 // Time of a 256-column tile of 32 (h + 1) rows against one of 256. Measured on 256 CUs at K = 4096 and 14336, weights from HBM and
@@ -452,10 +452,16 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
   return STS_OK;
 }
 
-// Up to this many rows the embedding kernel reads its tokens and positions from pinned host memory (one bus read each).
+// Up to this many rows the embedding kernel reads its tokens and positions from pinned host memory (one bus read each) instead
+// of waiting for a kernel that copies them. With 8B rows, both kernels / the one: 13.3 / 9.2 us at 64 rows, 17.4 / 12.8 at 512 on 256 CUs and
+// 21.3 / 19.3 on 64; at 1024 rows 19.6 / 15.1 on 256 CUs but 29.5 / 31.3 on 64, whose few workgroups wait for the bus in turn
+// (8192 rows: 50 / 56 and 114 / 188).
 constexpr int META_FUSED_ROWS = 512;
-// Logits a head's last kernel stores straight to host memory (64-byte pieces over the bus), and those that greedy sampling copies
-// on the side in whole lines; beyond, the copy engine is faster than either.
+// Logits a head's last kernel stores straight to host memory, and those that greedy sampling copies there on the side; larger ones
+// go by a runtime copy. A copy of more than 16 KiB leaves the stream idle for about 15 us (one layer, 16 rows of 1024: 124 us
+// against 109; with tokens, 256 rows 291 against 277). The lines lie where logits stop being small beside a step of real depth, not where
+// the copy becomes the faster way, which on an idle bus it does not: 4 MB (8 rows of 128256) 335 against 296 us stored by the
+// head, 342 against 335 by the sampling; 32 MB 892 against 810, and 903 against 904.
 constexpr size_t DIRECT_LOGITS_BYTES = 64 << 10, BESIDE_LOGITS_BYTES = 1 << 20;
 
 bf16* layer_pool(sts_ctx* c, int l) { return c->pool + (size_t)l * c->pool_layer_elems; }
@@ -1388,8 +1394,7 @@ extern "C" int sts_set_tile_model(sts_ctx* c, int64_t gemm_rate_128, int64_t gem
                                   int64_t partial_bw_cu) {
   if (!c || gemm_rate_128 < 1 || gemm_rate_256 < 1 || gemm_rate_128x256 < 1 || gemm_fixed_128x256 < 0 || partial_bw_cu < 1) return STS_EINVAL;
   if (c->pend_prefill || c->pend_decode) return STS_ESTATE;
-  c->rate_128 = gemm_rate_128 * 1e-3; c->rate_256 = gemm_rate_256 * 1e-3; c->rate_128x256 = gemm_rate_128x256 * 1e-3;
-  c->fixed_128x256 = gemm_fixed_128x256 * 1e-9; c->partial_bw = partial_bw_cu * 1e6;
+  c->rate_128 = gemm_rate_128 * 1e-3; c->rate_256 = gemm_rate_256 * 1e-3; c->partial_bw = partial_bw_cu * 1e6;
   return STS_OK;
 }
 extern "C" int sts_set_stream_model(sts_ctx* c, int64_t stream_bw_cu, int64_t stream_bw_gpu) {

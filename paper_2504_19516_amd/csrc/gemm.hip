@@ -569,7 +569,7 @@ __device__ __forceinline__ void load_w16x16(bf16x8& dst, const unsigned char* ba
 //
 // Bound by power on a full GPU: the 32 x 32 x 16 instruction kept the matrix cores busier (77 % of the cycles against 65 %) but
 // at 1.47 GHz, where 16 x 16 x 32, which moves half the accumulator registers per product, holds 1.90 GHz (8192 x 28672 x 4096 on
-// 256 CUs: 1434 -> 1392 us). The W block is the first operand, so a lane holds four consecutive output columns: fp32 results
+// 256 CUs: 1434 -> 1408 us). The W block is the first operand, so a lane holds four consecutive output columns: fp32 results
 // leave in 16-byte pieces.
 //
 // Order of a wave's vector-memory operations (they complete in order): iteration t queues the ACH A loads of tile t + SETS, then after
@@ -1149,10 +1149,8 @@ int gemm_tile_n(int cfg) {
   return cfg == GEMM_256x256 || cfg == GEMM_64x256 || cfg == GEMM_128x256 ? 256 : 128;
 }
 int gemm_tile_m(int cfg) { return cfg == GEMM_256x256 ? 256 : cfg == GEMM_128x128 || cfg == GEMM_128x256 ? 128 : 64; }
-// Workgroups per CU the launch plan counts: the 8-wave tiles fill a CU, the 4-wave tiles share it in pairs. The 128x256
-// tile (4 waves, wave tiles of 128 x 64) is planned one per CU although two fit: it is the shape for launches with little
-// more than one tile per CU, where the whole tiles take one slot of every CU and the K pieces of the surplus tiles run
-// beside them in the second.
+// Workgroups per CU the launch plan counts: the 8-wave tiles fill a CU (the 256-column ones also by their LDS), the 4-wave
+// tiles share it in pairs.
 int gemm_wgs_per_cu(int cfg) { return cfg == GEMM_256x256 || cfg == GEMM_64x256 || cfg == GEMM_128x256 || cfg > GEMM_64x256S ? 1 : 2; }
 
 // C = A * W^T with the chosen tile configuration and epilogue. Requirements (checked):
@@ -1170,7 +1168,7 @@ hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, co
   // 16-byte output stores
   if (w_packed && (cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 ? 8 : 4) != 0) return hipErrorInvalidValue;
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_64x256) return hipErrorInvalidValue;   // its wave tile is one 32-column block, not a gate/up pair
-  if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not offered: the shape is for the O and down projections
+  if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not offered (the engine itself never takes this shape: its row tiles have any height)
   GemmArgs g{};
   g.A = A; g.W = W; g.C = C; g.lda = lda; g.ldw = ldw; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
   g.split_stride = split_stride; g.w_packed = w_packed ? 1 : 0; g.stream_nt = stream_nt ? 1 : 0;

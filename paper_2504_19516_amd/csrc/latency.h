@@ -22,9 +22,8 @@ struct Profile {
   int64_t tile_m = 256, tile_n = 256, tile_q = 128, wgs_per_cu = 1, use_waveq = 1;
   int64_t tail_cut = 0;                // > 0: GEMMs cut a partly filled last wave along K into at most this many pieces
   // Measured on the part by the offline profiler and read by the engine's tile choice (not by the estimator):
-  // GFLOP/s per busy CU of the 128x128, the 256x256 and the 128x256 GEMM tiles, MB/s per CU for partial tiles written and
-  // read back. The 128x256 tile runs one per CU, so its start-up and epilogue are not hidden behind another workgroup:
-  // its time is gemm_fixed_128x256 ns plus the flops at gemm_rate_128x256.
+  // GFLOP/s per busy CU of the 128x128 and the 256x256 GEMM tiles, MB/s per CU for partial tiles written and read back.
+  // gemm_rate_128x256 and gemm_fixed_128x256 (GFLOP/s and ns of a 128x256 tile) are fields of the format that nothing reads.
   int64_t gemm_rate_128 = 3500, gemm_rate_256 = 4800, gemm_rate_128x256 = 5000, gemm_fixed_128x256 = 25000, partial_bw_cu = 20000;
   // MB/s of a plain read-only stream: per CU of a 32-CU partition, and of the whole GPU (the decode GEMM planner's rates)
   int64_t stream_bw_cu = 59000, stream_bw_gpu = 6400000;

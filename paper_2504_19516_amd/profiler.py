@@ -47,7 +47,8 @@ class Profiler:
         self.hw = dict(n_cu=self.n_cu, granule=granule, c_peak=2_500_000, d_peak=8_000, n_d=self.n_cu, tile_m=128, tile_n=128,
                        tile_q=128, wgs_per_cu=2, use_waveq=1, tail_cut=16,
                        gemm_rate_128=3500, gemm_rate_256=4800, gemm_rate_128x256=5000, gemm_fixed_128x256=25000, partial_bw_cu=20000,
-                       stream_bw_cu=59000, stream_bw_gpu=6400000)      # the library's defaults until measured
+                       stream_bw_cu=59000, stream_bw_gpu=6400000)      # the library's defaults until measured (of the 128x256 tile: fields
+        #                                                         of the format that nothing reads)
         self.max_tokens = max_tokens
         self.grids = {}
 
@@ -163,20 +164,6 @@ class Profiler:
             rate = 2 * m * n * d.hidden / ns / cus             # GFLOP/s per busy CU
             self.hw[key] = int(rate)
             log(f"{name} tiles, {m} x {n} x {d.hidden} on {cus} CUs ({waves} whole waves): {ns / 1e3:.1f} us -> {rate / 1e3:.2f} TFLOP/s per busy CU")
-        # 128x256 tiles run one per CU (the O and down projections: little more than one tile per CU), so a tile's start-up
-        # and residual epilogue are exposed: time one wave of tiles of both projections and fit fixed + flops / rate
-        rows = m // 128 if m else 0
-        if rows and cus % rows == 0 and cus // rows * 256 <= d.hidden:
-            n = cus // rows * 256
-            qd = d.n_q_heads * d.head_dim
-            t_o = self.eng.probe_gemm(cus, "128x256", m, n, iters=20, product="o") / 20
-            t_d = self.eng.probe_gemm(cus, "128x256", m, n, iters=20, product="down") / 20
-            if d.mlp > qd and t_d > t_o:
-                rate = 2 * 128 * 256 * (d.mlp - qd) / (t_d - t_o)              # flop/ns = GFLOP/s of one CU
-                fixed = max(0.0, t_o - 2 * 128 * 256 * qd / rate)
-                self.hw["gemm_rate_128x256"], self.hw["gemm_fixed_128x256"] = int(rate), int(fixed)
-                log(f"128x256 tiles, one per CU on {cus} CUs, {m} x {n}: K = {qd} {t_o / 1e3:.1f} us, K = {d.mlp} {t_d / 1e3:.1f} us -> "
-                    f"{fixed / 1e3:.1f} us + flops at {rate / 1e3:.2f} TFLOP/s per CU")
         self.hw["partial_bw_cu"] = int(bws[cus] / cus * 1e3)
         log(f"partial tiles: {self.hw['partial_bw_cu'] / 1e3:.1f} GB/s per CU (copy probe on {cus} CUs)")
         self.eng.set_tile_model(self.hw["gemm_rate_128"], self.hw["gemm_rate_256"], self.hw["gemm_rate_128x256"], self.hw["gemm_fixed_128x256"],

@@ -304,8 +304,8 @@ class Engine:
         _ck(lib().sts_set_partition(self._ctx, prefill_cus, decode_cus), "sts_set_partition")
 
     def set_tile_model(self, gemm_rate_128, gemm_rate_256, gemm_rate_128x256, gemm_fixed_128x256, partial_bw_cu):
-        """GFLOP/s per busy CU of the three prefill tile shapes, the fixed ns of a 128x256 tile and MB/s per CU for partial
-        tiles (Profile.tile_model())."""
+        """GFLOP/s per busy CU of the 128x128 and 256x256 tiles and MB/s per CU for partial tiles (Profile.tile_model(); the
+        figures of the 128x256 tile are fields of the profile that nothing reads)."""
         _ck(lib().sts_set_tile_model(self._ctx, C.c_int64(int(gemm_rate_128)), C.c_int64(int(gemm_rate_256)), C.c_int64(int(gemm_rate_128x256)),
                                      C.c_int64(int(gemm_fixed_128x256)), C.c_int64(int(partial_bw_cu))), "sts_set_tile_model")
 
