@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_kernel(const bf16* __rest
 }
 
 // Adds up the parts of one query tile's key range: out = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m), parts in order. One thread
-// per four elements; bound by the fp32 parts it reads. A part all of whose keys a row may not see has m = -inf and no weight.
+// per four elements; bound by the fp32 parts it reads. Every row sees keys of every part (attn_prefill_plan), so m is finite.
 template <int D>
 __global__ void __launch_bounds__(256) attn_prefill_merge_kernel(bf16* __restrict__ out, int ldo, const PrefillSeq* __restrict__ seqs,
                                                                  const AttnMerge* __restrict__ merges, int n_q, const float* __restrict__ part_ws) {
@@ -287,8 +287,9 @@ int attn_prefill_tile_q() { return BQ; }
 size_t attn_prefill_part_floats(int n_q, int d) { return (size_t)n_q * BQ * (d + 2); }
 
 // The launch's work: query tiles of every sequence, longest key range first (the tail of the launch is then made of short
-// ones). A key range is cut into parts of what one workgroup slot of the partition (two per CU) gets of an even deal, and no
-// shorter than 32 tiles (2048 keys: a part costs fp32 outputs written and read back, about an eighth of that work). So ranges
+// ones). A key range is cut into the number of parts (up to 8) that brings them nearest to what one workgroup slot of the
+// partition (two per CU) gets of an even deal, or to 32 tiles (2048 keys: a part costs fp32 outputs written and read back, about
+// an eighth of that work) where that is less; a part has at least 24 tiles, more keys than a query tile has rows. So ranges
 // are cut only where a few long ones leave slots empty: 1024 new tokens over 15 000 cached ones, 32 heads on 256 CUs, two parts
 // (406 -> 274 + 10 us a layer); a 2048-token prompt or 8192 rows on their own are not. At most `max_extra` items more than query tiles and
 // `max_parts` parts.

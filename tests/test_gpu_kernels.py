@@ -209,8 +209,7 @@ def test_prefill_attention(sts, t, prior, nq, nkv, d):
 
 @pytest.mark.parametrize("nq,nkv,d,t,prior", [(4, 1, 128, 130, 5000), (2, 2, 64, 40, 3100), (8, 2, 128, 1, 4095), (2, 1, 128, 300, 6000), (1, 1, 64, 129, 17000)])
 def test_prefill_attention_cuts_long_key_ranges(sts, nq, nkv, d, t, prior):
-    """Few query tiles over many cached tokens: the key range is cut into parts whose outputs are merged (2 to 8 parts; the rows of
-    a last part that see none of its keys have no weight there)."""
+    """Few query tiles over many cached tokens: the key range is cut into parts whose outputs are merged (2 to 8 parts)."""
     q = synth.normal_bf16(81, (t, nq, d))
     k = synth.normal_bf16(82, (prior + t, nkv, d))
     v = synth.normal_bf16(83, (prior + t, nkv, d))
@@ -284,3 +283,17 @@ def test_decode_attention_adds_chunks_in_their_order(sts, nq, nkv, d, n_chunks):
         off += c
     assert other > 0                                         # the order matters in these inputs
     assert np.array_equal(sts.op_attn_decode(q, k, v, ctx, 1), want)
+
+
+def test_prefill_attention_with_no_room_for_more_parts(sts):
+    """34 query tiles that would take 8 parts each, and room for 256: the first 32 are cut, the last two (16 and 17 thousand keys) are
+    not. Rows of the first tile, of the last cut and the first uncut one, and the last row."""
+    t, prior, d = 33 * 128 + 1, 16000, 64
+    q = synth.normal_bf16(94, (t, 1, d))
+    k = synth.normal_bf16(95, (prior + t, 1, d))
+    v = synth.normal_bf16(96, (prior + t, 1, d))
+    np_ = (prior + t + 15) // 16
+    got = sts.op_attn_prefill(q, k, v, prior, synth.page_permutation(97, np_), np_)
+    for a, b in ((0, 40), (31 * 128 + 100, 32 * 128 + 40), (t - 30, t)):
+        ref = T.op_causal_attention(q[a:b].astype(np.float64), k[:prior + b].astype(np.float64), v[:prior + b].astype(np.float64), prior + a)
+        assert rel(got[a:b], ref) <= BF16_TOL, (a, b)

@@ -815,3 +815,52 @@ def test_embedding_time_does_not_depend_on_the_number_of_prompts(sts):
     s = eng.seq_create()
     assert rel(eng.prefill_append(s, parts[-1]), got[-1]) <= TOL
     eng.close()
+
+
+def test_prefill_attention_parts_limited_by_the_work_list(sts):
+    """One head, 50 query tiles over 17 000 cached tokens: 350 parts more than query tiles would be made and 308 fit the work list, so
+    the last tiles stay whole. The logits are those of a small partition, where nothing is cut."""
+    desc = synth.ModelDesc(1, 256, 1, 1, 128, 256, 1024, 16, 1.0e4, 1.0e-5, "bf16")
+    t, prior = 6400, 17000
+    eng = new_engine(sts, desc, max_prefill_tokens=t, max_prefill_seqs=1, kv_pool_pages=1500, max_pages_per_seq=1480)
+    tok, got = synth.tokens(831, t, 1024), []
+    for cus in (256, 8):
+        eng.set_partition(cus, 256)
+        s = eng.seq_create()
+        eng.kv_fill_random(s, prior, 832)
+        got.append(eng.prefill_append(s, tok).reshape(-1))
+        free_all(eng, [s])
+    eng.close()
+    assert rel(got[0], got[1]) <= TOL
+
+
+def test_results_at_the_lines_between_stored_and_copied(sts, tiny):
+    """Logits of 64 KiB (16 rows of 1024) and a row more, of 1 MiB and a row more: stored by the head, by the sampling or copied, they
+    are the same numbers. Prompts of 512 and 513 rows (tokens and positions read from host memory, or copied first) match the oracle."""
+    desc, w = tiny
+    eng = new_engine(sts, desc, max_prefill_tokens=513, max_prefill_seqs=17, max_decode_batch=257, max_seqs=280, kv_pool_pages=900)
+    lens = synth.uniform_lengths(841, 257, 1, 30)
+    toks = [synth.tokens(842 + i, int(c), desc.vocab) for i, c in enumerate(lens)]
+    seqs, nxt = gpu_contexts(eng, toks), synth.tokens(843, 257, desc.vocab)
+    for n in (16, 17, 256, 257):
+        a, _ = eng.decode_step(seqs[:n], nxt[:n], want_logits=True, want_next=False)
+        for s, c in zip(seqs[:n], lens):
+            eng.seq_truncate(s, int(c))
+        b, g = eng.decode_step(seqs[:n], nxt[:n], want_logits=True, want_next=True)
+        for s, c in zip(seqs[:n], lens):
+            eng.seq_truncate(s, int(c))
+        assert np.array_equal(a, b) and np.array_equal(g, a.argmax(1)), n
+    free_all(eng, seqs)
+    for n in (16, 17):
+        seqs = [eng.seq_create() for _ in range(n)]
+        got = eng.prefill_batch(seqs, toks[:n])
+        one = eng.seq_create()
+        assert rel(got[n - 1], eng.prefill_append(one, toks[n - 1]).reshape(-1)) <= TOL
+        free_all(eng, seqs + [one])
+    for rows in (512, 513):
+        tok, s = synth.tokens(844, rows, desc.vocab), eng.seq_create()
+        orc = T.Oracle(desc, w, 40)
+        orc.kv.add_sequence(0, list(range(33)))
+        assert rel(eng.prefill_append(s, tok), orc.prefill_append(0, tok)) <= TOL
+        eng.seq_free(s)
+    eng.close()
