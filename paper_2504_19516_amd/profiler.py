@@ -255,7 +255,8 @@ class Profiler:
             log(f"alpha_prefill pm={pm}: {[round(v / PPM, 3) for v in row]}")
         self.grids["alpha_prefill"] = ([list(pms), list(tokens)], vals)
 
-    def calibrate_decode(self, dms=(32, 64, 128, 256), batches=(8, 64, 224), mean_ctx=(256, 2048), log=print):
+    def calibrate_decode(self, dms=(32, 64, 128, 256), batches=(8, 16, 17, 64, 224), mean_ctx=(256, 2048), log=print):
+        """16 and 17 requests: a sample on either side of the line where the decode GEMMs change their form."""
         vals = np.zeros((len(dms), len(batches), len(mean_ctx)), dtype=np.int64)
         ctx_axis = None
         for bi, b in enumerate(batches):
