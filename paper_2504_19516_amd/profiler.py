@@ -44,7 +44,8 @@ class Profiler:
                               max_prefill_seqs=4, max_decode_batch=max_batch, max_seqs=max_batch + 8,
                               max_pages_per_seq=(max_ctx + 128) // 16)
         self.n_cu = self.eng.get_partition()[2]
-        self.hw = dict(n_cu=self.n_cu, granule=granule, c_peak=2_500_000, d_peak=8_000, n_d=self.n_cu, tile_m=128, tile_n=128,
+        # tile_m: what the prefill GEMMs pad rows to, blocks of 32
+        self.hw = dict(n_cu=self.n_cu, granule=granule, c_peak=2_500_000, d_peak=8_000, n_d=self.n_cu, tile_m=32, tile_n=128,
                        tile_q=128, wgs_per_cu=2, use_waveq=1, tail_cut=16,
                        gemm_rate_128=3500, gemm_rate_256=4800, gemm_rate_128x256=5000, gemm_fixed_128x256=25000, partial_bw_cu=20000,
                        stream_bw_cu=59000, stream_bw_gpu=6400000)      # the library's defaults until measured (of the 128x256 tile: fields
@@ -239,7 +240,7 @@ class Profiler:
         text = profile_text(self.hw, {k: v for k, v in self.grids.items() if k == "bw"})
         return sts.Profile(text=text).query(self.desc, es, roofline=True)
 
-    def calibrate_prefill(self, pms=(32, 64, 96, 128, 160, 192, 224, 256), tokens=(256, 512, 1024, 2048, 4096, 8192), log=print):
+    def calibrate_prefill(self, pms=(32, 64, 96, 128, 160, 192, 224, 256), tokens=(64, 128, 256, 512, 1024, 2048, 4096, 8192), log=print):
         vals = []
         for pm in pms:
             row = []
@@ -342,8 +343,10 @@ def sample_count_study(profiler: Profiler, heldout, log=print):
     npm, nt = len(gp[0][0]), len(gp[0][1])
     ndm, nb, nc = len(gd[0][0]), len(gd[0][1]), len(gd[0][2])
     every = lambda n, k: sorted(set(list(range(0, n, k)) + [n - 1]))
-    p_sets = [("ends of the CU axis, tokens <= %d" % gp[0][1][min(2, nt - 1)], [[0, npm - 1], list(range(min(3, nt)))]),
-              ("every other CU count, tokens <= %d" % gp[0][1][min(3, nt - 1)], [every(npm, 2), list(range(min(4, nt)))]),
+    t0 = next((i for i, t in enumerate(gp[0][1]) if t >= 256), 0)         # the subsets leave the shortest prompts out
+    first = lambda n: list(range(t0, min(t0 + n, nt)))
+    p_sets = [("ends of the CU axis, tokens %d to %d" % (gp[0][1][t0], gp[0][1][first(3)[-1]]), [[0, npm - 1], first(3)]),
+              ("every other CU count, tokens %d to %d" % (gp[0][1][t0], gp[0][1][first(4)[-1]]), [every(npm, 2), first(4)]),
               ("full grid", [list(range(npm)), list(range(nt))])]
     d_sets = [("ends of the CU and batch axes", [[0, ndm - 1], sorted({0, nb - 1}), list(range(nc))]),
               ("full grid", [list(range(ndm)), list(range(nb)), list(range(nc))])]
