@@ -567,10 +567,10 @@ __device__ __forceinline__ void load_w16x16(bf16x8& dst, const unsigned char* ba
 // tiles of 128 x 4096 x 14336 236 -> 186. The price is LDS traffic (288 KB per K tile instead of 160), which the LDS still delivers
 // in the tile's matrix-core time. Four K tiles ahead pay on short tiles (54 us against 62 with two), two on tall ones.
 //
-// Bound by power on a full GPU: the 32 x 32 x 16 instruction kept the matrix cores busier (77 % of the cycles against 65 %) but
-// at 1.47 GHz, where 16 x 16 x 32, which moves half the accumulator registers per product, holds 1.90 GHz (8192 x 28672 x 4096 on
-// 256 CUs: 1434 -> 1408 us). The W block is the first operand, so a lane holds four consecutive output columns: fp32 results
-// leave in 16-byte pieces.
+// Bound by power on a full GPU: the 32 x 32 x 16 instruction kept the matrix cores busier (76 % of the cycles against 68 %) but
+// at 1.65 GHz, where 16 x 16 x 32, which moves half the accumulator registers per product, holds 1.89 GHz (8192 x 28672 x 4096 on
+// 256 CUs: 1464 -> 1435 us). Both give the same bits. The W block is the first operand, so a lane holds four consecutive
+// output columns: fp32 results leave in 16-byte pieces.
 //
 // Order of a wave's vector-memory operations (they complete in order): iteration t queues the ACH A loads of tile t + SETS, then after
 // step s the TN W loads of (tile t + SETS, step s); the prologue queues the first SETS tiles in the same order. When step s
