@@ -268,42 +268,65 @@ __global__ void __launch_bounds__(256, 2) attn_decode_mfma_kernel(const bf16* __
 }
 
 // Merge the chunks of one (request, query head): out = sum_c o_c 2^(m_c - m) / sum_c l_c 2^(m_c - m), one maximum, chunks added in
-// their order: how chunks share the threads of a workgroup does not show in the result.
-// Bound by memory latency, not by its few hundred KB: groups of D / 2 lanes (4 or 8 of them, two elements a lane) fetch eight
-// chunks each side by side with the (max, sum) pairs, one pair per lane; the values meet in LDS, where one thread per element adds
-// them up while the next 32 or 64 chunks are on the way. 4.4 us for one request of 9 chunks, 4.7 for 64 requests of 32 heads, 5.6 for
-// 24 of 64 heads; lane groups that each add their own chunks, with running maxima, took 4.3, 4.7 and 5.2 but round differently.
-template <int D>
-__global__ void __launch_bounds__(256) attn_decode_merge_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeSeq* __restrict__ seqs,
-                                         const int* __restrict__ multi, int n_q, int n_kv, int G, int chunk_pages, int max_chunks) {
-  constexpr int LPC = D / 2, GROUPS = 256 / LPC, DEPTH = 8, PASS = GROUPS * DEPTH;
+// their order, so both forms below give the same bits. Bound by memory latency and by cold instruction fetches, not by their few
+// hundred KB: the (max, sum) pairs are read one per lane, strides are known at compile time, the chunk count comes from the host.
+//
+// Up to MERGE_DIRECT_CHUNKS chunks in the launch's longest context: one thread per element with the loads of all chunks under way.
+// Device time of decode steps with both forms / with the other form alone: 64 requests, 8 layers 1451 / 1461 us, 223 requests, 4
+// layers 1376 / 1382, 4 requests, 32 layers 3156 / 3161; up to 32 chunks this way: 1453, 1376, 3164 (one request of 4000 tokens, 32 chunks,
+// 384 against 382). Groups of lanes that each add their own chunks with running maxima took 1455, 1376 and 3149, but round differently.
+constexpr int MERGE_DIRECT_CHUNKS = 16;
+template <int D, int G>
+__global__ void __launch_bounds__(D) attn_decode_merge_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeMerge* __restrict__ multi,
+                                                              int n_q, int n_kv, int max_chunks) {
+  constexpr int CS = G * (D + 2);
+  const DecodeMerge mg = multi[blockIdx.y];
+  const int head = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const float* base = ws + (((size_t)mg.seq * n_kv + head / G) * max_chunks) * CS + head % G * (D + 2);
+  float x[MERGE_DIRECT_CHUNKS];
+#pragma unroll
+  for (int c = 0; c < MERGE_DIRECT_CHUNKS; c++)
+    if (c < mg.chunks) x[c] = base[c * CS + tid];
+  const f32x2 pair = *reinterpret_cast<const f32x2*>(base + min(lane, mg.chunks - 1) * CS + D);
+  const float w = __builtin_amdgcn_exp2f(pair[0] - wave_max(pair[0]));
+  float l = 0.f, o = 0.f;
+#pragma unroll
+  for (int c = 0; c < MERGE_DIRECT_CHUNKS; c++)
+    if (c < mg.chunks) {
+      const float wc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), c));
+      l += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(pair[1]), c)) * wc;
+      o += x[c] * wc;
+    }
+  out[((size_t)mg.seq * n_q + head) * D + tid] = f2bf(o / l);
+}
+// More chunks: groups of D / 2 lanes (4 or 8 of them, two elements a lane) fetch eight chunks each side by side; the values meet in
+// LDS, where one thread per element adds them up while the next 32 or 64 chunks are on the way.
+template <int D, int G>
+__global__ void __launch_bounds__(256) attn_decode_merge_many_kernel(bf16* __restrict__ out, const float* __restrict__ ws, const DecodeMerge* __restrict__ multi,
+                                                                     int n_q, int n_kv, int max_chunks) {
+  constexpr int CS = G * (D + 2), LPC = D / 2, GROUPS = 256 / LPC, DEPTH = 8, PASS = GROUPS * DEPTH;
   static_assert(PASS <= 64, "the pairs of a pass fit one wave");
   __shared__ float so[PASS][D];
   __shared__ f32x2 sw[PASS];                       // weight and sum of each chunk
-  const int head = blockIdx.x, req = multi[blockIdx.y], tid = threadIdx.x, grp = tid / LPC, dd = tid % LPC * 2;
-  const int kvh = head / G, g = head % G;
-  const int n_pages = (seqs[req].cl + 1 + 15) >> 4;
-  const int chunks = (n_pages + chunk_pages - 1) / chunk_pages;
-  if (chunks == 1) return;                         // (not listed by the caller: the attention kernel stored this request's output itself)
-  const float* base = ws + (((size_t)req * n_kv + kvh) * max_chunks) * G * (D + 2) + g * (D + 2);
-  const size_t cstride = (size_t)G * (D + 2);
+  const DecodeMerge mg = multi[blockIdx.y];
+  const int head = blockIdx.x, chunks = mg.chunks, tid = threadIdx.x, lane = tid & 63, grp = tid / LPC, dd = tid % LPC * 2;
+  const float* base = ws + (((size_t)mg.seq * n_kv + head / G) * max_chunks) * CS + head % G * (D + 2);
   f32x2 v[DEPTH];
   auto fetch = [&](int c0) {                       // past the last chunk: that chunk again, not used
 #pragma unroll
-    for (int u = 0; u < DEPTH; u++) v[u] = *reinterpret_cast<const f32x2*>(base + min(c0 + u * GROUPS + grp, chunks - 1) * cstride + dd);
+    for (int u = 0; u < DEPTH; u++) v[u] = *reinterpret_cast<const f32x2*>(base + min(c0 + u * GROUPS + grp, chunks - 1) * CS + dd);
   };
   fetch(0);
-  const int lane = tid & 63;
-  f32x2 pair = *reinterpret_cast<const f32x2*>(base + min(lane, chunks - 1) * cstride + D);
+  f32x2 pair = *reinterpret_cast<const f32x2*>(base + min(lane, chunks - 1) * CS + D);
   float m = pair[0];
-  for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, base[c * cstride + D]);
+  for (int c = lane + 64; c < chunks; c += 64) m = fmaxf(m, base[c * CS + D]);
   m = wave_max(m);
   float l = 0.f, o = 0.f;
   for (int c0 = 0; c0 < chunks; c0 += PASS) {
     const int cnt = min(PASS, chunks - c0);
     if (c0 > 0) {
       __syncthreads();                             // the last pass has been added up
-      if (tid < cnt) pair = *reinterpret_cast<const f32x2*>(base + (c0 + tid) * cstride + D);
+      if (tid < cnt) pair = *reinterpret_cast<const f32x2*>(base + (c0 + tid) * CS + D);
     }
 #pragma unroll
     for (int u = 0; u < DEPTH; u++) *reinterpret_cast<f32x2*>(&so[u * GROUPS + grp][dd]) = v[u];
@@ -319,7 +342,7 @@ __global__ void __launch_bounds__(256) attn_decode_merge_kernel(bf16* __restrict
       }
     }
   }
-  if (tid < D) out[((size_t)req * n_q + head) * D + tid] = f2bf(o / l);
+  if (tid < D) out[((size_t)mg.seq * n_q + head) * D + tid] = f2bf(o / l);
 }
 
 size_t attn_decode_ws_floats(int n, int n_q, int d, int chunks) { return (size_t)n * n_q * chunks * (d + 2); }
@@ -338,12 +361,13 @@ static void launch_decode_kernel(hipStream_t s, const bf16* q, bf16* out, const 
 }
 
 template <int D, int G>
-static void launch_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const int* multi, int n_multi,
+static void launch_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const DecodeMerge* multi, int n_multi,
                           const int* bt, const bf16* pool, KvGeom geo, int n_q, int chunk_pages, int max_chunks, float* ws, float sc, bool stream_nt) {
   if (stream_nt) launch_decode_kernel<D, G, true>(s, q, out, seqs, items, n_items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
   else launch_decode_kernel<D, G, false>(s, q, out, seqs, items, n_items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
-  if (n_multi > 0)
-    hipLaunchKernelGGL(attn_decode_merge_kernel<D>, dim3(n_q, n_multi), dim3(256), 0, s, out, ws, seqs, multi, n_q, geo.n_kv, G, chunk_pages, max_chunks);
+  if (n_multi == 0) return;
+  if (max_chunks <= MERGE_DIRECT_CHUNKS) hipLaunchKernelGGL((attn_decode_merge_kernel<D, G>), dim3(n_q, n_multi), dim3(D), 0, s, out, ws, multi, n_q, geo.n_kv, max_chunks);
+  else hipLaunchKernelGGL((attn_decode_merge_many_kernel<D, G>), dim3(n_q, n_multi), dim3(256), 0, s, out, ws, multi, n_q, geo.n_kv, max_chunks);
 }
 
 // q, out: [n, n_q * d] bf16 (q already rotated). A context is cut into chunks of `chunk_pages`
@@ -352,7 +376,7 @@ static void launch_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeS
 // that exists, n_items of them (device memory). multi: the n_multi requests whose context has more than
 // one chunk (device memory; only these need the merge kernel, and with none of them it is not launched).
 // ws: attn_decode_ws_floats(n, n_q, d, max_chunks). stream_nt: fetch K and V with the non-temporal hint.
-hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const int* multi, int n_multi,
+hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const DecodeMerge* multi, int n_multi,
                        const int* block_tables, const bf16* pool, KvGeom geo, int n, int n_q, int chunk_pages, int max_chunks, float* ws, bool stream_nt) {
   if (n == 0 || n_items == 0) return hipSuccess;
   if (n_multi < 0 || n_multi > n || (n_multi > 0 && !multi)) return hipErrorInvalidValue;

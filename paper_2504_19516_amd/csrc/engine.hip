@@ -750,10 +750,12 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
     std::stable_sort(ph.h_ditems, ph.h_ditems + n_items, [&](const DecodeItem& a, const DecodeItem& b) { return chunk_len(a) > chunk_len(b); });
   }
   // requests whose context has more than one chunk: only they need the merge kernel
-  int *h_multi = nullptr, *d_multi = nullptr, n_multi = 0;
+  DecodeMerge *h_multi = nullptr, *d_multi = nullptr;
+  int n_multi = 0;
   meta_take(ph, &h_multi, &d_multi, (size_t)n);
   if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
-  for (int i = 0; i < n; i++) if (ph.h_dseq[i].n_pages > chunk_pages) h_multi[n_multi++] = i;
+  for (int i = 0; i < n; i++)
+    if (ph.h_dseq[i].n_pages > chunk_pages) h_multi[n_multi++] = DecodeMerge{i, (ph.h_dseq[i].n_pages + chunk_pages - 1) / chunk_pages};
   hipStream_t st = ph.stream;
   HIPCK(hipEventRecord(ph.ev0, st));
   const int h = d.hidden;
@@ -858,7 +860,7 @@ int alloc_phase(sts_ctx* c, int side) {
     const size_t items = 2 * q_tiles + 256;
     // decode attention items: a context has at most 128 chunks, and fewer than one per 4 pages (chunks hold >= 8)
     const size_t dec_items = side == 1 ? nseq * (size_t)decode_max_chunks((int)mp) : 0;
-    ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + 2 * sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
+    ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + sizeof(DecodeMerge) + sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
                     2 * rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
     STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes + 16));      // copied in 16-byte pieces
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));

@@ -72,6 +72,7 @@ struct DecodeSeq {
 // One context chunk of one decode request, with what its workgroup needs to start: a single
 // 16-byte load instead of a chain through the per-request record.
 struct DecodeItem { int seq; int chunk; int cl; int bt_off; };
+struct DecodeMerge { int seq; int chunks; };           // a request whose context has more than one chunk
 
 // ---- element-wise / small kernels ---------------------------------------------------------
 hipError_t init_weight(hipStream_t s, bf16* dst, int ld, uint64_t seed, uint64_t tensor_id, int rows, int cols,
@@ -126,7 +127,7 @@ struct AttnPlan { std::vector<AttnItem> items; std::vector<AttnMerge> merges; in
 AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n_q, int slots, int max_extra, long long max_parts);
 size_t attn_prefill_part_floats(int n_q, int d);   // of one part
 size_t attn_decode_ws_floats(int n, int n_q, int d, int max_chunks);
-hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const int* multi, int n_multi,
+hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const DecodeMerge* multi, int n_multi,
                        const int* block_tables, const bf16* pool, KvGeom geo, int n, int n_q, int chunk_pages, int max_chunks, float* ws,
                        bool stream_nt = false);
 int attn_decode_max_chunk_tokens();

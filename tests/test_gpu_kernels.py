@@ -257,9 +257,10 @@ def test_decode_attention(sts, nq, nkv, d, ctx, chunks):
         off += c
 
 
-@pytest.mark.parametrize("nq,nkv,d,n_chunks", [(8, 1, 128, [2, 9, 32, 33, 128]), (8, 2, 128, [65]), (4, 4, 64, [7, 63, 64, 65, 128, 129])])
+@pytest.mark.parametrize("nq,nkv,d,n_chunks", [(8, 1, 128, [2, 9, 16]), (8, 1, 128, [3, 17]), (8, 1, 128, [2, 9, 32, 33, 128]), (8, 2, 128, [65]), (4, 4, 64, [7, 16]),
+                                               (4, 4, 64, [7, 17, 63, 64, 65, 128, 129]), (4, 1, 64, [5, 2])])
 def test_decode_attention_adds_chunks_in_their_order(sts, nq, nkv, d, n_chunks):
-    """The sums over a context's chunks (one page each) are taken in chunk order, whatever the number of chunks. Keys of zero make
+    """The sums over a context's chunks (one page each) are taken in chunk order, whatever the number of chunks (16 and 17: two forms). Keys of zero make
     every probability 1 and every chunk's sum exact; element e has 2^24 in one chunk, -2^24 in a later one and small whole
     numbers elsewhere, so that fp32 sums in any other order come out different. The expected value is that fp32 sum, bit by bit."""
     ctx = [16 * c - 5 for c in n_chunks]
