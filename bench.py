@@ -314,7 +314,7 @@ def main():
                                                 "decode_ms": round(ov_td / 1e6, 4)},
                    "slo_per_layer_ms": {"ttft": ttft_budget / 1e6, "tpot": tpot_budget / 1e6},
                    "sweep": sweep},
-        "roofline": {"bound": "mfma", "kernel": "prefill gate/up GEMM (gemm_rows_kernel<SwiGLU>: 256-column tiles, 8 waves, activations through LDS, packed weights straight into registers)",
+        "roofline": {"bound": "mfma", "kernel": "prefill gate/up GEMM (gemm_rows_kernel<SwiGLU>: 256-column tiles, 4 waves, activations through LDS, packed weights straight into registers)",
                      "achieved": achieved / 1e12, "peak": PEAK_BF16 / 1e12, "unit": "TFLOP/s", "frac": achieved / PEAK_BF16,
                      "traffic": stored_traffic(pm), "traffic_source": traffic_source(), "avg_launch_ms": gu_avg_s * 1e3, "partition_cus": pm,
                      "frac_of_partition_peak": achieved / (PEAK_BF16 * pm / 256),

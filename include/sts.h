@@ -244,7 +244,7 @@ int64_t sts_weight_packed_index(int32_t row, int32_t col, int32_t ld);
  * workgroups at once -- the tiles of the last, partly filled wave (Section 2.2.1) are cut along
  * K into pieces that fill the wave, and a second kernel sums the pieces. 0 = whole tiles only. */
 enum { STS_GEMM_128x128 = 0 /* 4 waves, two workgroups per CU */, STS_GEMM_64x256 /* 8 waves */, STS_GEMM_64x128 /* 4 waves, two per CU */,
-       STS_GEMM_256x256 /* 8 waves; the last row tile is cut to its rows in blocks of 32 */,
+       STS_GEMM_256x256 /* 4 waves, a CU each; the last row tile is cut to its rows in blocks of 32 */,
        STS_GEMM_128x256 /* the same with at most 128 rows a tile; no SwiGLU epilogue */,
        /* decode batches: 64-row tiles of 4 to 8 waves, 64 columns per wave, the weights of the library's packed
           layout streamed straight into registers (no row-major form: sts_op_gemm_noalloc rejects them; whole tiles

@@ -246,7 +246,7 @@ int pick_cfg(int m, int n, int k, int cus) {
 // estimated time, which is where wave quantisation (paper Section 2.2.1) enters -- complete
 // waves of workgroups at the tile's busy-CU rate, then the last wave, whole or cut along K.
 // Rates are measured busy-CU throughputs in TFLOP/s per CU: 128x128 tiles run two workgroups
-// per CU, the 256-column tiles (8 waves) one; rate_256 is that of the tallest. The latter come in heights of 32 to 256 rows: the rows
+// per CU, the 256-column tiles one; rate_256 is that of the tallest. The latter come in heights of 32 to 256 rows: the rows
 // are dealt to any number of row tiles, so that they fill whole waves of workgroups.
 struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; };
 // Time of a 256-column tile of 32 (h + 1) rows against one of 256. Measured on 256 CUs at K = 4096 and 14336, weights from HBM and

@@ -4,7 +4,7 @@
 // holds 8 consecutive k of one A row (or one W row). A workgroup owns a BM x BN tile and each of
 // its waves accumulates a (BM/WGM) x (BN/WGN) sub-tile in 32x32 MFMA blocks.
 //
-// Main loops. gemm_rows_kernel: the prefill tiles of 256 columns and any multiple of 32 rows up to 256 (8 waves); only
+// Main loops. gemm_rows_kernel: the prefill tiles of 256 columns and any multiple of 32 rows up to 256 (4 waves); only
 // the activation tile goes through LDS, the W operands go from the packed weight layout straight into registers.
 // gemm_dl_kernel: K tiles of 64 of both operands go global -> LDS directly (no
 // staging registers, no LDS store instructions): activations into 128-byte rows whose 16-byte chunks
@@ -545,40 +545,34 @@ __global__ void __launch_bounds__(256) gemm_tail_fixup(GemmArgs g) {
   store_fixed_up<EPI>(g, g.tail_ws + (size_t)t * g.tail_f * (BM * BN) + (size_t)r * BN + c, BM * BN, row, tn * BN, c);
 }
 
-// The operand of a 16 x 16 x 32 step: 32-wide step 0 or 1 of a packed block.
-__device__ __forceinline__ void load_w16x16(bf16x8& dst, const unsigned char* base, unsigned lane_off, int step) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  if (step == 0) asm volatile("global_load_dwordx4 %0, %1, %2" : "=v"(dst) : "v"(lane_off), "s"(base) : "memory");
-  else asm volatile("global_load_dwordx4 %0, %1, %2 offset:2048" : "=v"(dst) : "v"(lane_off), "s"(base) : "memory");
-#endif
-}
-
-// ---- the 256-column prefill tiles of eight waves: row tiles of any multiple of 32 rows up to 256 -------------------
+// ---- the 256-column prefill tiles: row tiles of any multiple of 32 rows up to 256 -----------------------------------
 // A launch's rows are cut into `tiles_m` row tiles of nearly equal height in blocks of 32 (row_range), and a workgroup runs
 // the loop compiled for its height: nothing is computed for padding beyond the last block, and the number of row tiles is
 // free to make whole waves of workgroups (Section 2.2.1): 2048 x 4096 outputs on 224 CUs are 14 x 16 tiles of at most 160 rows,
 // one per CU, where 256-row tiles leave 96 CUs idle or cut along K. T = 301 rows run as two tiles of 160.
 //
-// Eight waves, each all rows x 32 columns in 16 x 16 matrix-core blocks. Only the activation tile goes through LDS (SETS + 1
-// stages, read by every wave); a wave reads its own columns' W operands from the packed layout straight into registers, SETS K tiles
-// ahead. What this split is after is bytes: with all CUs busy the L2s give a CU about 57 GB/s, and two rows of four waves,
-// which load every W block twice (96 KB per 64-wide K tile of 256 x 256, against 64 here), ran at exactly that rate --
-// 28672 x 4096, two row tiles, weights from HBM: 82 / 89 / 93 / 110 us at heights 32 / 128 / 160 / 256, now 54 / 73 / 83 / 109; 14 row
-// tiles of 128 x 4096 x 14336 236 -> 186. The price is LDS traffic (288 KB per K tile instead of 160), which the LDS still delivers
-// in the tile's matrix-core time. Four K tiles ahead pay on short tiles (54 us against 62 with two), two on tall ones.
+// Four waves, one per SIMD, each all rows x 64 columns in 16 x 16 matrix-core blocks. Only the activation tile goes through LDS
+// (four stages, read by every wave); a wave reads its own columns' W operands from the packed layout straight into registers, two
+// K tiles ahead, so no W byte is loaded twice. A wave has the SIMD's 512 registers: 256 of sums, 64 of W operands, 32 of row blocks.
 //
-// Bound by power on a full GPU: the 32 x 32 x 16 instruction kept the matrix cores busier (76 % of the cycles against 68 %) but
-// at 1.65 GHz, where 16 x 16 x 32, which moves half the accumulator registers per product, holds 1.89 GHz (8192 x 28672 x 4096 on
-// 256 CUs: 1464 -> 1435 us). Both give the same bits. The W block is the first operand, so a lane holds four consecutive
-// output columns: fp32 results leave in 16-byte pieces.
+// What bounds it: nothing stands in for a wave that waits, so everything but the matrix instructions has to fit into
+// their shadow. They take 16 cycles each and 4 to issue, so one other instruction fits behind each, not a run of them: a K tile is
+// dealt out in units of one row block (four matrix instructions) with that unit's LDS read, at most one vector-memory
+// operation and the pointer arithmetic each between two of them (RowsPlan). 256 rows: 2160 to 2220 cycles per K tile of 2048 matrix-core
+// cycles; with the reads and loads of four row blocks in a run 2670, with eight waves of 32 columns, whose LDS reads are
+// twice as many, 68 % busy. The clock falls as the matrix cores get busier (1.7 GHz at 256 rows on a full GPU: power), so the rate gains
+// less than the cycles. Against eight waves, 256 CUs: 8192 x 28672 x 4096 1424 -> 1263 us (1.52 PFLOP/s), 8192 x 4096 x 14336 756 -> 657, 3980 x 28672 x
+// 4096 730 -> 638, 700 x 57344 x 8192 588 -> 513; two row tiles of 28672 x 4096 at heights 32 / 96 / 128 / 160 / 192 / 256: 36 / 48 / 59 / 74 / 84 / 109 us
+// before, 36 / 43 / 49 / 63 / 73 / 93 now. The W block is the first operand, so a lane holds four consecutive output columns: fp32
+// results leave in 16-byte pieces. The 32 x 32 x 16 instruction gives the same bits but moves twice the accumulator registers per
+// product, which costs clock.
 //
-// Order of a wave's vector-memory operations (they complete in order): iteration t queues the ACH A loads of tile t + SETS, then after
-// step s the TN W loads of (tile t + SETS, step s); the prologue queues the first SETS tiles in the same order. When step s
-// of tile t waits for its operands, WAIT = TN + ACH + (SETS - 1)(ACH + 2 TN) operations were queued after them, in every iteration: the
-// last ones re-read the last K tile into stages and registers nobody uses. At the barrier of iteration t the A loads of tile
-// t + 1 must have landed: WAIT - ACH operations are younger. Tile t + SETS goes into the stage that tile t - 1 left at the
-// last barrier (SETS + 1 stages). Waves without a full share of the A tile's 1 KiB pieces queue loads of its first bytes into
-// a spare KiB, so that all count alike.
+// Order of a wave's vector-memory operations (they complete in order): the first half of tile t queues the step-1 W operands of
+// tile t + 1 and the first pieces of the A tile t + 2, the second half the step-0 W operands of tile t + 2 and the other pieces, in
+// every iteration (the last ones re-read the last K tile into stages and registers nobody uses). RowsPlan counts
+// what was queued behind the operands a step waits for (WAIT0, WAIT1), and behind the A pieces of tile t + 1 at the barrier that publishes
+// them (WAITB). Pieces go into the stage that tile t - 2 left: its operands were multiplied, hence read, before the last barrier.
+// A number of K tiles that SETS does not divide starts with null tiles (zero operands add nothing), so that the loop has one exit.
 constexpr int ROWS_LDS = 136 * 1024;              // A stages of a gemm_rows_kernel workgroup (or its output image)
 __device__ __forceinline__ void row_range(const GemmArgs& g, int tm, int* row0, int* blocks) {
   const int b0 = g.tile_blocks ? tm * g.tile_blocks : (int)((long long)tm * g.row_blocks / g.tiles_m);
@@ -591,34 +585,107 @@ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
+// One product of the 256-column tiles. Written in assembly so that the sum stays where it is: left to itself the compiler gives
+// the result a register quad of its own and copies 256 accumulators per K tile. AG: the sum lives in an accumulation register.
+template <bool AG>
+__device__ __forceinline__ void mma16(f32x4& c, const bf16x8& a, const bf16x8& b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (AG) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+#endif
+}
+// The compiler does not know that mma16 takes time: before the sums are read otherwise, wait, then tie every one of them to that point.
+__device__ __forceinline__ void mma16_settle() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+#endif
+}
+template <bool AG>
+__device__ __forceinline__ void mma16_settled(f32x4& c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if constexpr (AG) asm volatile("" : "+a"(c)); else asm volatile("" : "+v"(c));
+#endif
+}
+// Wait until at most N vector-memory operations of this wave are outstanding; the four operands are valid afterwards.
+template <int N>
+__device__ __forceinline__ void wait_vmem_for4(bf16x8 (&w)[4]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  asm volatile("s_waitcnt vmcnt(%4)" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]) : "n"(N) : "memory");
+#endif
+}
+template <int OFF>
+__device__ __forceinline__ void load_w_off(bf16x8& dst, const unsigned char* base, unsigned lane_off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
+#endif
+}
+// lds_dma16 in two parts, so that a matrix instruction can stand in the wait state between them (dma_m0_idle where none does).
+template <int OFF>
+__device__ __forceinline__ void dma_m0(unsigned lds_base) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "scc", "memory");
+#endif
+}
+__device__ __forceinline__ void dma_m0_idle() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 0");
+#endif
+}
+__device__ __forceinline__ void dma_load(const unsigned char* base, unsigned lane_off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
+#endif
+}
+
+// A K tile of one wave: U units of one 16-row block each. A half of the units is one 32-wide step; its vector-memory operations -- four W
+// loads and its share of the A pieces, alternating -- are dealt over its units.
+template <int TM>
+struct RowsPlan {
+  static constexpr int SETS = 2;                                          // K tiles of W operands in registers
+  static constexpr int AGPR_BLOCKS = 13;                                  // of 16; the rest leaves the register allocator room
+  static constexpr int RB = 2 * TM, U = 2 * RB;                           // row blocks of a step, units of a K tile
+  static constexpr int ACH = TM, D0 = ACH / 2, D1 = ACH - D0;             // A pieces a wave queues per K tile, and in each half of it
+  static constexpr int PER = ACH + 8;                                     // vector-memory operations of a K tile
+  static constexpr int R = 8, D = U - 2 < 6 ? 2 : 6;                      // row blocks in registers, and how many units ahead one is read
+  static constexpr int after_w(int nd) { return nd > 3 ? nd - 3 : 0; }    // DMAs of a half behind its last W load
+  static constexpr int after_d(int nd) { return nd < 4 ? 4 - nd : 0; }    // W loads of a half behind its last DMA
+  // operation k of a half with nd DMAs: W load (true) or DMA, and its number among its kind
+  static constexpr bool is_w(int k, int nd) { return k < 2 * nd && k < 8 ? k % 2 == 0 : (nd < 4 ? true : false); }
+  static constexpr int num(int k, int nd) { int n = 0; for (int i = 0; i < k; i++) n += is_w(i, nd) == is_w(k, nd); return n; }
+  static constexpr int unit_of(int k, int nd) { return k * RB / (4 + nd); }   // unit of the half it goes out in
+  static constexpr int upto(int u, int nd) { int n = 0; for (int k = 0; k < 4 + nd; k++) n += unit_of(k, nd) < u; return n; }
+  // operations queued behind the W operands of step 0 and of step 1 when that step begins, and behind the last A piece of the next
+  // tile at the barrier
+  static constexpr int WAIT0 = after_w(D1) + (SETS - 1) * PER, WAIT1 = after_w(D0) + (SETS - 1) * PER;
+  static constexpr int UB = U - D;                                        // the barrier stands before the reads of this unit
+  static constexpr int WAITB = after_d(D1) + (SETS - 2) * PER + (UB >= RB ? 4 + D0 + upto(UB - RB, D1) : upto(UB, D0));
+  static_assert(WAIT0 < 64 && WAIT1 < 64 && WAITB < 64 && WAITB >= 0, "vmcnt is a 6-bit counter");
+  static_assert(SETS * U % R == 0 && D + 2 <= R && D <= RB * 2 - 2, "the row blocks' registers turn over whole within the loop");
+};
+
+typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
+__device__ __forceinline__ bf16x8 lds_read16(lds_cptr p) { return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p); }
 template <int EPI, int TM>
 __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char* arena, int m0, int n0, int kbeg, int kend, int piece) {
-  constexpr int BM = 32 * TM, BN = 256, BK = 64, NT = 512, TN = 2, RB = 2 * TM;
-  constexpr int SETS = TM > 4 ? 2 : 4, NS = SETS + 1;
-  constexpr int ROWB = BK * 2, STAGE = BM * ROWB, PIECES = STAGE / 1024, ACH = (PIECES + 7) / 8;
-  constexpr int WAIT = TN + ACH + (SETS - 1) * (ACH + 2 * TN);
-  static_assert(NS * STAGE <= ROWS_LDS && WAIT < 64, "the stages fit the launch's LDS, the waits vmcnt");
+  using P = RowsPlan<TM>;
+  constexpr int BM = 32 * TM, BN = 256, BK = 64, NT = 256, TN = 4, RB = P::RB, U = P::U, D = P::D, R = P::R, SETS = P::SETS;
+  constexpr int NS = SETS + 2;                               // A stages
+  constexpr int ROWB = BK * 2, STAGE = BM * ROWB, ACH = TM;
+  static_assert(NS * STAGE <= ROWS_LDS, "the stages fit the launch's LDS");
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
   const int swave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.A + (size_t)m0 * g.lda);
   unsigned a_off[ACH];
 #pragma unroll
   for (int j = 0; j < ACH; j++) {
-    const int q = (j * 8 + swave) * 64 + lane, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
-    a_off[j] = j * 8 + swave < PIECES ? (unsigned)(min(m0 + row, g.M - 1) - m0) * (unsigned)g.lda * 2u + ch * 16 : 0u;
+    const int q = (j * 4 + swave) * 64 + lane, row = q >> 3, ch = (q & 7) ^ ((row >> 1) & 7);
+    a_off[j] = (unsigned)(min(m0 + row, g.M - 1) - m0) * (unsigned)g.lda * 2u + ch * 16;
   }
-  auto issue_a = [&](int stage, int k) {
-    const unsigned char* ak = a_base + (size_t)k * 2;
-#pragma unroll
-    for (int j = 0; j < ACH; j++)
-      lds_dma16(ak, a_off[j], j * 8 + swave < PIECES ? arena + stage * STAGE + (j * 8 + swave) * 1024 : arena + ROWS_LDS);
-  };
-  // A wave's 32 columns are one half (16 columns) of each of two neighbouring 32-column blocks -- a gate block and its up
-  // block in the SwiGLU form. Operand of block j, step s: 256 bytes out of each quarter of a 2 KiB half of the block's 4 KiB.
-  const size_t wrow = (size_t)(g.K >> 6) * 4096;
-  const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.W) + (size_t)((n0 >> 5) + (swave & ~1)) * wrow;
-  const unsigned w_lane = (unsigned)((lq >> 1) * 1024 + (lq & 1) * 512 + l16 * 16 + (swave & 1) * 256);
+  // A wave's 64 columns are two neighbouring 32-column blocks -- a gate block and its up block in the SwiGLU form -- in halves of 16.
+  // Operand of a half, step s: 256 bytes out of each quarter of a 2 KiB half of the block's 4 KiB.
+  const unsigned wrow = (unsigned)(g.K >> 6) * 4096u;
+  const unsigned w_lane0 = (unsigned)((lq >> 1) * 1024 + (lq & 1) * 512 + l16 * 16), w_lane1 = w_lane0 + wrow;
   bf16x8 w[SETS][2][TN];
 #pragma unroll
   for (int z = 0; z < SETS; z++)
@@ -628,9 +695,21 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
       for (int j = 0; j < TN; j++)
 #pragma unroll
         for (int e = 0; e < 8; e++) w[z][s][j][e] = 0;
-  auto load_w = [&](int z, int s, const unsigned char* wk) {
-#pragma unroll
-    for (int j = 0; j < TN; j++) load_w16x16(w[z][s][j], wk + j * wrow, w_lane, s);
+  // the loop takes a multiple of SETS tiles: `lead` null tiles (zero operands) first
+  const int nk = (kend - kbeg) / BK, lead = (SETS - nk % SETS) % SETS, nt = nk + lead;
+  const unsigned char* ap = reinterpret_cast<const unsigned char*>(g.A + (size_t)m0 * g.lda) + (size_t)kbeg * 2;   // A of the tile whose pieces are queued
+  const unsigned char* wp = reinterpret_cast<const unsigned char*>(g.W) + (size_t)((n0 >> 5) + swave * 2) * wrow + (size_t)(kbeg >> 6) * 4096;
+  const unsigned arena_lds = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)arena + swave * 1024;
+  // operation k of half h of a tile: W operands (set z, step 1 - h) or a piece of A; in two parts, the first sets m0
+  auto vm_first = [&](auto h_c, auto k_c, unsigned stage) {
+    constexpr int h = decltype(h_c)::value, k = decltype(k_c)::value, nd = h ? P::D1 : P::D0, n = P::num(k, nd);
+    if constexpr (!P::is_w(k, nd)) { constexpr int j = h ? P::D0 + n : n; dma_m0<j * 4096>(stage); }
+  };
+  auto vm_op = [&](auto h_c, auto k_c, auto z_c) {
+    constexpr int h = decltype(h_c)::value, k = decltype(k_c)::value, z = decltype(z_c)::value, nd = h ? P::D1 : P::D0, s = 1 - h;
+    constexpr int n = P::num(k, nd);
+    if constexpr (P::is_w(k, nd)) load_w_off<(n & 1) * 256 + s * 2048>(w[z][s][n], wp, n >> 1 ? w_lane1 : w_lane0);
+    else { constexpr int j = h ? P::D0 + n : n; dma_load(ap, a_off[j]); }
   };
 
   f32x4 acc[RB][TN];
@@ -638,125 +717,181 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
   for (int i = 0; i < RB; i++)
 #pragma unroll
     for (int j = 0; j < TN; j++) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  int koff[2];
-#pragma unroll
-  for (int s = 0; s < 2; s++) koff[s] = ((s * 4 + lq) ^ ((l16 >> 1) & 7)) * 16;
-  const int a_row = l16 * ROWB;
 
-  const int nk = (kend - kbeg) / BK;
-  auto tile_k = [&](int t) { return kbeg + min(t, nk - 1) * BK; };
-#pragma unroll
-  for (int z = 0; z < SETS; z++) {
-    issue_a(z, tile_k(z));
-    const unsigned char* wk = w_base + (size_t)(tile_k(z) >> 6) * 4096;
-    load_w(z, 0, wk);
-    load_w(z, 1, wk);
-  }
-  wait_vmem<WAIT - ACH + TN>();                              // A(0) has landed
-  __syncthreads();
-  // A step's RB row blocks are taken in groups of up to four: a group's operands are read while the group before it is
-  // multiplied.
-  constexpr int G = (RB + 3) / 4, GROUPS = 2 * G;
-  bf16x8 af[2][4];
-#pragma unroll
-  for (int i = 0; i < (RB < 4 ? RB : 4); i++) af[0][i] = *reinterpret_cast<const bf16x8*>(arena + a_row + i * 16 * ROWB + koff[0]);
-
-  int cur = 0;
-  auto tile = [&](int t, auto z_c) {
-    constexpr int z = decltype(z_c)::value;                  // register set of tile t: t % SETS
-    const bool live = t < nk;                                // the surplus tiles of the last round only keep the queue's shape
-    const int nxt = cur + 1 == NS ? 0 : cur + 1;
-    const unsigned char* Ac = arena + cur * STAGE + a_row;
-    const unsigned char* An = arena + nxt * STAGE + a_row;
-    const int ka = tile_k(t + SETS);
-    const unsigned char* wk = w_base + (size_t)(ka >> 6) * 4096;
-    __builtin_amdgcn_sched_barrier(0);
-    issue_a(cur == 0 ? NS - 1 : cur - 1, ka);
-    static_for<GROUPS>([&](auto p_c) {
-      constexpr int p = decltype(p_c)::value, s = p / G, h = p % G, cnt = RB - h * 4 < 4 ? RB - h * 4 : 4;
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (h == 0) {
-        wait_vmem_for<WAIT>(w[z][s][0], w[z][s][1]);
+  // queue the first SETS tiles in the loop's order
+  static_for<SETS>([&](auto z_c) {
+    constexpr int z = decltype(z_c)::value;
+    const unsigned stage = arena_lds + z * STAGE;
+    static_for<4 + P::D0>([&](auto k_c) {
+      constexpr int k = decltype(k_c)::value;
+      if constexpr (z > 0 || !P::is_w(k, P::D0)) {
+        vm_first(std::integral_constant<int, 0>{}, k_c, stage);
+        dma_m0_idle();
+        vm_op(std::integral_constant<int, 0>{}, k_c, std::integral_constant<int, (z + SETS - 1) % SETS>{});
       }
-      constexpr int pn = p + 1 == GROUPS ? 0 : p + 1, sn = pn / G, hn = pn % G, cntn = RB - hn * 4 < 4 ? RB - hn * 4 : 4;
-      if constexpr (pn == 0) {
-        wait_vmem<WAIT - ACH>();                             // publish tile t + 1, retire this one
-        __syncthreads();
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      const unsigned char* src = pn == 0 ? An : Ac;
+    });
+    if (z > lead) wp += 4096;
+    static_for<4 + P::D1>([&](auto k_c) {
+      vm_first(std::integral_constant<int, 1>{}, k_c, stage);
+      dma_m0_idle();
+      vm_op(std::integral_constant<int, 1>{}, k_c, z_c);
+    });
+    if (z >= lead) ap += z - lead + 1 < nk ? 128 : 0;
+  });
+  if (lead > 0) {                                            // the null tiles' operands and stages
+    wait_vmem<0>();
+    __syncthreads();                                         // every wave's pieces have landed
+    static_for<SETS>([&](auto z_c) {
+      constexpr int z = decltype(z_c)::value;
+      static_for<2>([&](auto s_c) { constexpr int s = decltype(s_c)::value; wait_vmem_for4<0>(w[z][s]); });
+      if (z < lead) {
 #pragma unroll
-      for (int i = 0; i < cntn; i++) af[(p + 1) & 1][i] = *reinterpret_cast<const bf16x8*>(src + (hn * 4 + i) * 16 * ROWB + koff[sn]);
-      if (live) {
-#pragma unroll
-        for (int i = 0; i < cnt; i++)
+        for (int s = 0; s < 2; s++)
 #pragma unroll
           for (int j = 0; j < TN; j++)
-            acc[h * 4 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[z][s][j], af[p & 1][i], acc[h * 4 + i][j], 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 8; e++) w[z][s][j][e] = 0;
+        for (int c = tid; c < STAGE / 16; c += NT) *reinterpret_cast<u32x4*>(arena + z * STAGE + c * 16) = u32x4{0u, 0u, 0u, 0u};
       }
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (h == G - 1) load_w(z, s, wk);
     });
-    cur = nxt;
+  }
+  wait_vmem<P::after_d(P::D1) + (SETS - 1) * P::PER>();      // A(0) has landed
+  __syncthreads();
+  const int koff0 = (lq ^ ((l16 >> 1) & 7)) * 16;            // step 1's chunk: koff0 ^ 64
+  lds_cptr base0 = (lds_cptr)(arena + l16 * ROWB + koff0), base1 = (lds_cptr)(arena + l16 * ROWB + (koff0 ^ 64));
+  bf16x8 af[R];
+  static_for<D>([&](auto u_c) {
+    constexpr int u = decltype(u_c)::value;
+    af[u] = lds_read16((u / RB ? base1 : base0) + (u % RB) * 16 * ROWB);
+  });
+  // a unit per row block: its four products, between them the read of the block D units ahead and a vector-memory operation
+  unsigned cur = 0, into = SETS * STAGE;                     // stages of the tile in hand and of the tile whose pieces are queued (bytes)
+  lds_cptr rd0 = base0, rd1 = base1;
+  auto tile = [&](int t, auto z_c) {
+    constexpr int z = decltype(z_c)::value, zp = (z + SETS - 1) % SETS;
+    lds_cptr nx0 = rd0, nx1 = rd1;
+    const unsigned stage = arena_lds + into;
+    static_for<U>([&](auto u_c) {
+      constexpr int u = decltype(u_c)::value, s = u / RB, i = u % RB, nd = s ? P::D1 : P::D0;
+      constexpr std::integral_constant<int, s> s_c{};
+      constexpr std::integral_constant<int, s ? z : zp> zz{};
+      constexpr int n_ops = P::upto(i + 1, nd) - P::upto(i, nd), k0 = P::upto(i, nd);
+      constexpr bool AG = i < P::AGPR_BLOCKS;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (u == 0) wait_vmem_for4<P::WAIT0>(w[z][0]);
+      if constexpr (u == RB) wait_vmem_for4<P::WAIT1>(w[z][1]);
+      if constexpr (u == P::UB) {
+        wait_vmem<P::WAITB>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      mma16<AG>(acc[i][0], w[z][s][0], af[(z * U + u) % R]);
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int un = (u + D) % U;
+      af[(z * U + u + D) % R] = lds_read16((u + D >= U ? (un / RB ? nx1 : nx0) : (un / RB ? rd1 : rd0)) + (un % RB) * 16 * ROWB);
+      __builtin_amdgcn_sched_barrier(0);
+      mma16<AG>(acc[i][1], w[z][s][1], af[(z * U + u) % R]);
+      if constexpr (n_ops > 0) vm_first(s_c, std::integral_constant<int, k0>{}, stage);
+      mma16<AG>(acc[i][2], w[z][s][2], af[(z * U + u) % R]);
+      if constexpr (n_ops > 0) vm_op(s_c, std::integral_constant<int, k0>{}, zz);
+      mma16<AG>(acc[i][3], w[z][s][3], af[(z * U + u) % R]);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<n_ops>([&](auto k_c) {
+        constexpr int k = k0 + decltype(k_c)::value;
+        if constexpr (k > k0) {
+          vm_first(s_c, std::integral_constant<int, k>{}, stage);
+          dma_m0_idle();
+          vm_op(s_c, std::integral_constant<int, k>{}, zz);
+        }
+      });
+      if constexpr (u == RB - 1) wp += t + SETS < nt ? 4096 : 0;                // W of tile t + SETS from here on
+      if constexpr (u == U - 1) ap += t + SETS + 1 < nt ? 128 : 0;
+      if constexpr (u == P::UB - 2) cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+      if constexpr (u == P::UB - 1) { nx0 = base0 + cur; nx1 = base1 + cur; }
+      if constexpr (u == U - 1) into = into + STAGE == NS * STAGE ? 0 : into + STAGE;
+    });
+    rd0 = nx0; rd1 = nx1;
   };
-  for (int t = 0; t < nk; t += SETS) static_for<SETS>([&](auto z_c) { tile(t + decltype(z_c)::value, z_c); });
-  // the surplus loads of the last iterations must not land in registers the epilogue reuses
+  for (int t = 0; t < nt; t += SETS) static_for<SETS>([&](auto z_c) { tile(t + decltype(z_c)::value, z_c); });
+  mma16_settle();
+  static_for<RB * TN>([&](auto q) {
+    constexpr int i = decltype(q)::value / TN, j = decltype(q)::value % TN;
+    mma16_settled<(i < P::AGPR_BLOCKS)>(acc[i][j]);
+  });
+  // the surplus loads of the last iterations must not land in registers or stages the epilogue reuses
 #pragma unroll
   for (int z = 0; z < SETS; z++)
 #pragma unroll
-    for (int s = 0; s < 2; s++) wait_vmem_for<0>(w[z][s][0], w[z][s][1]);
+    for (int s = 0; s < 2; s++) wait_vmem_for4<0>(w[z][s]);
 
-  // ---- outputs: lane (lq, l16) holds columns 4 lq .. + 4 of 16-column block j, rows 16 i + l16 of its wave tile
-  const int rloc = l16, cloc = (swave >> 1) * 64 + (swave & 1) * 16 + 4 * lq;
-  constexpr int JS = 32;                                     // columns from one block to the next
+  // ---- outputs: lane (lq, l16) holds columns 4 lq .. + 4 of 16-column block j, rows 16 i + l16 of its wave tile. A few row blocks at
+  // a time: all at once the compiler spills.
+  const int rloc = l16, cloc = swave * 64 + 4 * lq;          // column block j: + 16 j
   if (piece >= 0) {                                          // a tail piece leaves its partial tile, row-major [height][256]
     float* part = g.tail_ws + (size_t)piece * g.piece_stride + (size_t)rloc * BN + cloc;
 #pragma unroll
     for (int i = 0; i < RB; i++)
 #pragma unroll
-      for (int j = 0; j < TN; j++) *reinterpret_cast<f32x4*>(part + (size_t)i * 16 * BN + j * JS) = acc[i][j];
+      for (int j = 0; j < TN; j++) *reinterpret_cast<f32x4*>(part + (size_t)i * 16 * BN + j * 16) = acc[i][j];
     return;
   }
   if constexpr (EPI == EPI_F32 || EPI == EPI_RESID_F32) {
     float* out = reinterpret_cast<float*>(g.C) + (EPI == EPI_F32 ? (size_t)blockIdx.y * g.split_stride : 0) + n0 + cloc;
 #pragma unroll
-    for (int i = 0; i < RB; i++) {
-      const int row = m0 + rloc + i * 16;
-      if (row >= g.M) continue;
+    for (int i0 = 0; i0 < RB; i0 += 2) {
+      f32x4 old[2][TN];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < TN; j++) {
-        f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)row * g.ldc + j * JS);
-        if constexpr (EPI == EPI_RESID_F32) *dst += acc[i][j]; else *dst = acc[i][j];
+      for (int i = i0; i < i0 + 2; i++) {
+        const int row = min(m0 + rloc + i * 16, g.M - 1);
+        if constexpr (EPI == EPI_RESID_F32) {
+#pragma unroll
+          for (int j = 0; j < TN; j++) old[i - i0][j] = *reinterpret_cast<const f32x4*>(out + (size_t)row * g.ldc + j * 16);
+        }
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = i0; i < i0 + 2; i++) {
+        const int row = m0 + rloc + i * 16;
+        if (row >= g.M) continue;
+#pragma unroll
+        for (int j = 0; j < TN; j++) {
+          f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)row * g.ldc + j * 16);
+          if constexpr (EPI == EPI_RESID_F32) *dst = old[i - i0][j] + acc[i][j]; else *dst = acc[i][j];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   } else {
-    // bf16 outputs leave through the (now free) A stages as a [rows][columns] image, so that a row of the tile goes out as whole
-    // 128-byte lines; 32 bytes of padding per row spread the 8-byte writes of 16 rows over the banks
     constexpr bool SW = EPI == EPI_SWIGLU_BF16;
     constexpr int OC = SW ? BN / 2 : BN, RS = OC + 16;
+    // bf16 outputs leave through the (now free) A stages as a [rows][columns] image, so that a row of the tile goes out as whole
+    // 128-byte lines; 32 bytes of padding per row spread the 8-byte writes of 16 rows over the banks
     static_assert(BM * RS * 2 <= ROWS_LDS, "the image fits the stages");
     bf16* img = reinterpret_cast<bf16*>(arena);
     bf16* outp = reinterpret_cast<bf16*>(g.C) + (SW ? (n0 >> 1) : n0);
     __syncthreads();                                         // the stage reads of the main loop are done
-    bf16* dst = img + (size_t)rloc * RS + (SW ? swave * 16 + 4 * lq : cloc);
+    bf16* dst = img + (size_t)rloc * RS + (SW ? swave * 32 + 4 * lq : cloc);
 #pragma unroll
-    for (int i = 0; i < RB; i++)
+    for (int i = 0; i < RB; i++) {
+      if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int j = 0; j < (SW ? 1 : TN); j++) {
+      for (int j = 0; j < (SW ? 2 : TN); j++) {
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           if constexpr (SW) {
-            const float gate = acc[i][0][e], up = acc[i][1][e];
+            const float gate = acc[i][j][e], up = acc[i][j + 2][e];
             o[e] = f2bf(gate / (1.f + __expf(-gate)) * up);
           } else {
             o[e] = f2bf(acc[i][j][e]);
           }
         }
-        *reinterpret_cast<bf16x4*>(dst + (size_t)i * 16 * RS + j * JS) = o;
+        *reinterpret_cast<bf16x4*>(dst + (size_t)i * 16 * RS + j * 16) = o;
       }
+    }
     __syncthreads();
-    constexpr int CPRW = OC / 8;                             // 16-byte chunks per row
+    constexpr int CPRW = OC / 8;
 #pragma unroll
     for (int c = 0; c < BM * CPRW / NT; c++) {
       const int q = c * NT + tid, row = q / CPRW, cc = q % CPRW;
@@ -768,7 +903,7 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
 }
 
 template <int EPI>
-__global__ void __launch_bounds__(512, 2) gemm_rows_kernel(GemmArgs g) {
+__global__ void __launch_bounds__(256, 1) gemm_rows_kernel(GemmArgs g) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* arena = smem + GEMM_DL_LDS_BASE;
   int v, kbeg, kend, piece, tm, tn, m0, blocks;
@@ -1065,7 +1200,7 @@ static hipError_t launch_cfg(hipStream_t s, GemmArgs g, int splits, const GemmTa
 // gemm_rows_kernel: the rows in row_tiles tiles of nearly equal height (0: as few as 256 rows allow).
 template <int EPI>
 static hipError_t launch_rows(hipStream_t s, GemmArgs g, int splits, const GemmTail* tail, int row_tiles, int tile_blocks) {
-  constexpr size_t lds = GEMM_DL_LDS_BASE + ROWS_LDS + 1024;
+  constexpr size_t lds = GEMM_DL_LDS_BASE + ROWS_LDS;
   static std::atomic<bool> attr_set{false};        // the two phases' control threads may launch the same shape
   if (!attr_set.load()) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_rows_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1081,7 +1216,7 @@ static hipError_t launch_rows(hipStream_t s, GemmArgs g, int splits, const GemmT
   const int tiles = g.tiles_m * g.tiles_n;
   // row_tiles == 0: pieces of whole tiles, so that the cut is that of the row-major form
   const int ny = plan_launch(&g, tiles, splits, tail, (row_tiles > 0 ? height : tile_blocks) * 32 * 256);
-  hipLaunchKernelGGL((gemm_rows_kernel<EPI>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(512), lds, s, g);
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI>), dim3((g.full_per_xcd + g.piece_per_xcd) * 8, ny), dim3(256), lds, s, g);
   if (EPI == EPI_RESID_F32 && g.n_pieces > 0 && tail->norm && g.N <= FIXUP_NORM_MAX_N) {
     ResidNorm& r = *tail->norm;
     hipLaunchKernelGGL(gemm_rows_fixup_norm, dim3(g.M), dim3(256), 0, s, g, r.out, r.gain, r.eps);
@@ -1149,7 +1284,7 @@ int gemm_tile_n(int cfg) {
   return cfg == GEMM_256x256 || cfg == GEMM_64x256 || cfg == GEMM_128x256 ? 256 : 128;
 }
 int gemm_tile_m(int cfg) { return cfg == GEMM_256x256 ? 256 : cfg == GEMM_128x128 || cfg == GEMM_128x256 ? 128 : 64; }
-// Workgroups per CU the launch plan counts: the 8-wave tiles fill a CU (the 256-column ones also by their LDS), the 4-wave
+// Workgroups per CU the launch plan counts: the 8-wave tiles and the 256-column ones (by their LDS) fill a CU, the other 4-wave
 // tiles share it in pairs.
 int gemm_wgs_per_cu(int cfg) { return cfg == GEMM_256x256 || cfg == GEMM_64x256 || cfg == GEMM_128x256 || cfg > GEMM_64x256S ? 1 : 2; }
 

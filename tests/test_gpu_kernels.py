@@ -126,7 +126,7 @@ def test_gemm_skinny_tiles_epilogues(sts, cfg, width, m, k):
 @pytest.mark.parametrize("m", [1, 32, 33, 96, 97, 160, 192, 224, 225, 255, 257, 400])
 @pytest.mark.parametrize("k,slots", [(64, 0), (192, 0), (320, 0), (1088, 3)])
 def test_gemm_row_tile_heights(sts, m, k, slots):
-    """The eight-wave 256-column tile has a loop per height (32 to 256 rows): every height, rows that end inside its last block, K
+    """The 256-column tile has a loop per height (32 to 256 rows): every height, rows that end inside its last block, K
     extents shorter than the operands' ring and with surplus iterations in its last round, every epilogue, and (slots) the last
     wave of tiles cut along K."""
     n = 512
@@ -142,6 +142,22 @@ def test_gemm_row_tile_heights(sts, m, k, slots):
     assert rel(sts.op_gemm(a, w, "256x256", epilogue=3, tail_slots=slots), ref3) <= BF16_TOL
     if not slots and k > 64:
         assert rel(sts.op_gemm(a, w, "256x256", epilogue=1, split_k=2), ref) <= 1e-5
+
+
+@pytest.mark.parametrize("m,k", [(40, 64), (161, 192), (256, 320), (256, 256)])
+def test_gemm_row_tiles_keep_infinities_to_their_row(sts, m, k):
+    """An odd number of K tiles starts with a null tile of zero operands: it must not meet the activations, an infinity of which
+    would make it NaN. One row's only non-zero is an infinity, another holds a NaN; every other row is as without them."""
+    n = 256
+    a, w = synth.normal_bf16(74, (m, k)), synth.normal_bf16(75, (n, k), 0.05)
+    a[3], a[m - 1] = 0.0, 0.0
+    clean = sts.op_gemm(a, w, "256x256", epilogue=1)
+    a[3, 5], a[m - 1, k - 1] = np.inf, np.nan
+    got = sts.op_gemm(a, w, "256x256", epilogue=1)
+    assert np.array_equal(got[3], np.where(w[:, 5] > 0, np.inf, -np.inf)) and np.isnan(got[m - 1]).all()
+    rest = np.ones(m, bool)
+    rest[[3, m - 1]] = False
+    assert np.array_equal(got[rest], clean[rest])
 
 
 @pytest.mark.parametrize("cfg,m,n,slots", [("128x128", 300, 512, 8), ("128x128", 300, 512, 10), ("128x128", 300, 512, 40),
