@@ -580,6 +580,15 @@ __device__ __forceinline__ void row_range(const GemmArgs& g, int tm, int* row0, 
   *row0 = b0 * 32; *blocks = b1 - b0;
 }
 
+// gate / (1 + exp(-gate)) * up. The quotient by a reciprocal and a correction step: as near as the division (which takes ten
+// instructions) but for the rounding of the product. The bound keeps the correction finite where exp overflows: the reciprocal is 0 there.
+__device__ __forceinline__ float silu_mul(float gate, float up) {
+  const float d = 1.f + fminf(__expf(-gate), 1e38f);
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.f), r, r);
+  return gate * r * up;
+}
+
 template <typename F, int... P>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, P...>) { (f(std::integral_constant<int, P>{}), ...); }
 template <int N, typename F>
@@ -824,72 +833,93 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
 #pragma unroll
     for (int s = 0; s < 2; s++) wait_vmem_for4<0>(w[z][s]);
 
-  // ---- outputs: lane (lq, l16) holds columns 4 lq .. + 4 of 16-column block j, rows 16 i + l16 of its wave tile. A few row blocks at
-  // a time: all at once the compiler spills.
+  // ---- outputs: lane (lq, l16) holds columns 4 lq .. + 4 of 16-column block j, rows 16 i + l16 of its wave tile. They leave
+  // through the (now free) A stages as a [rows][columns] image, so that rows go out whole.
   const int rloc = l16, cloc = swave * 64 + 4 * lq;          // column block j: + 16 j
+  // A row block's sums are read where they are stored, not earlier: all at once, or ahead of a branch, the compiler spills.
+  auto take_row_block = [&](auto i_c) {
+    constexpr int i = decltype(i_c)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    mma16_settled<(i < P::AGPR_BLOCKS)>(acc[i][0]);
+    mma16_settled<(i < P::AGPR_BLOCKS)>(acc[i][1]);
+    mma16_settled<(i < P::AGPR_BLOCKS)>(acc[i][2]);
+    mma16_settled<(i < P::AGPR_BLOCKS)>(acc[i][3]);
+  };
+  // fp32 rows, up to 128 at a time: each wave takes a quarter of them, a row (1 KiB) per instruction. ADD: to what is there, the rows of
+  // the next eight under way. Bound by memory, all workgroups of a wave of them at once: 256 rows of the residual stream 45 us straight
+  // from the accumulators (64 bytes of a row in each of 16 rows per instruction), 24 this way; the projection of 8192 x 4096 x 4096 231 -> 220 us,
+  // 8192 x 4096 x 14336 663 -> 649, 3980 x 4096 x 4096 108 -> 103, 2048 rows on tiles of 128 62 -> 57.
+  auto store_f32 = [&](auto add_c, float* out, int ld, int rows) {
+    constexpr bool ADD = decltype(add_c)::value;
+    constexpr int HB = RB < 8 ? RB : 8, RSF = BN + 4;        // row blocks of a pass; floats of an image row
+    static_assert(HB * 16 * RSF * 4 <= ROWS_LDS, "the image fits the stages");
+    float* img = reinterpret_cast<float*>(arena);
+    float* col = out + lane * 4;
+    static_for<(RB + HB - 1) / HB>([&](auto h_c) {
+      constexpr int h = decltype(h_c)::value, cnt = RB - h * HB < HB ? RB - h * HB : HB, RPW = cnt * 4;
+      const int r0 = h * HB * 16 + swave * RPW;              // this wave's rows of the pass
+      f32x4 old[8];
+      auto fetch = [&](int q) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) old[i] = *reinterpret_cast<const f32x4*>(col + (size_t)min(r0 + q + i, rows - 1) * ld);
+      };
+      if constexpr (ADD) fetch(0);
+      __syncthreads();                                       // the stage reads of the main loop, or of the pass before, are done
+      static_for<cnt>([&](auto i_c) {
+        constexpr int i = decltype(i_c)::value;
+        take_row_block(std::integral_constant<int, h * HB + i>{});
+#pragma unroll
+        for (int j = 0; j < TN; j++) *reinterpret_cast<f32x4*>(img + (i * 16 + rloc) * RSF + cloc + j * 16) = acc[h * HB + i][j];
+      });
+      __syncthreads();
+      for (int q = 0; q < RPW; q += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) v[i] = *reinterpret_cast<const f32x4*>(img + (swave * RPW + q + i) * RSF + lane * 4);
+        if constexpr (ADD) {
+#pragma unroll
+          for (int i = 0; i < 8; i++) v[i] = old[i] + v[i];
+          if (q + 8 < RPW) fetch(q + 8);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i++)
+          if (r0 + q + i < rows) *reinterpret_cast<f32x4*>(col + (size_t)(r0 + q + i) * ld) = v[i];
+      }
+    });
+  };
   if (piece >= 0) {                                          // a tail piece leaves its partial tile, row-major [height][256]
-    float* part = g.tail_ws + (size_t)piece * g.piece_stride + (size_t)rloc * BN + cloc;
-#pragma unroll
-    for (int i = 0; i < RB; i++)
-#pragma unroll
-      for (int j = 0; j < TN; j++) *reinterpret_cast<f32x4*>(part + (size_t)i * 16 * BN + j * 16) = acc[i][j];
+    store_f32(std::integral_constant<bool, false>{}, g.tail_ws + (size_t)piece * g.piece_stride, BN, BM);
     return;
   }
   if constexpr (EPI == EPI_F32 || EPI == EPI_RESID_F32) {
-    float* out = reinterpret_cast<float*>(g.C) + (EPI == EPI_F32 ? (size_t)blockIdx.y * g.split_stride : 0) + n0 + cloc;
-#pragma unroll
-    for (int i0 = 0; i0 < RB; i0 += 2) {
-      f32x4 old[2][TN];
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = i0; i < i0 + 2; i++) {
-        const int row = min(m0 + rloc + i * 16, g.M - 1);
-        if constexpr (EPI == EPI_RESID_F32) {
-#pragma unroll
-          for (int j = 0; j < TN; j++) old[i - i0][j] = *reinterpret_cast<const f32x4*>(out + (size_t)row * g.ldc + j * 16);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = i0; i < i0 + 2; i++) {
-        const int row = m0 + rloc + i * 16;
-        if (row >= g.M) continue;
-#pragma unroll
-        for (int j = 0; j < TN; j++) {
-          f32x4* dst = reinterpret_cast<f32x4*>(out + (size_t)row * g.ldc + j * 16);
-          if constexpr (EPI == EPI_RESID_F32) *dst = old[i - i0][j] + acc[i][j]; else *dst = acc[i][j];
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    float* out = reinterpret_cast<float*>(g.C) + (EPI == EPI_F32 ? (size_t)blockIdx.y * g.split_stride : 0) + (size_t)m0 * g.ldc + n0;
+    store_f32(std::integral_constant<bool, EPI == EPI_RESID_F32>{}, out, g.ldc, min(BM, g.M - m0));
   } else {
     constexpr bool SW = EPI == EPI_SWIGLU_BF16;
     constexpr int OC = SW ? BN / 2 : BN, RS = OC + 16;
-    // bf16 outputs leave through the (now free) A stages as a [rows][columns] image, so that a row of the tile goes out as whole
-    // 128-byte lines; 32 bytes of padding per row spread the 8-byte writes of 16 rows over the banks
+    // whole 128-byte lines of bf16; 32 bytes of padding per row spread the 8-byte writes of 16 rows over the banks
     static_assert(BM * RS * 2 <= ROWS_LDS, "the image fits the stages");
     bf16* img = reinterpret_cast<bf16*>(arena);
     bf16* outp = reinterpret_cast<bf16*>(g.C) + (SW ? (n0 >> 1) : n0);
     __syncthreads();                                         // the stage reads of the main loop are done
     bf16* dst = img + (size_t)rloc * RS + (SW ? swave * 32 + 4 * lq : cloc);
-#pragma unroll
-    for (int i = 0; i < RB; i++) {
-      if (i % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+    static_for<RB>([&](auto i_c) {
+      constexpr int i = decltype(i_c)::value;
+      take_row_block(i_c);
 #pragma unroll
       for (int j = 0; j < (SW ? 2 : TN); j++) {
         bf16x4 o;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           if constexpr (SW) {
-            const float gate = acc[i][j][e], up = acc[i][j + 2][e];
-            o[e] = f2bf(gate / (1.f + __expf(-gate)) * up);
+            o[e] = f2bf(silu_mul(acc[i][j][e], acc[i][j + 2][e]));
           } else {
             o[e] = f2bf(acc[i][j][e]);
           }
         }
         *reinterpret_cast<bf16x4*>(dst + (size_t)i * 16 * RS + j * 16) = o;
       }
-    }
+    });
     __syncthreads();
     constexpr int CPRW = OC / 8;
 #pragma unroll
