@@ -70,10 +70,10 @@ struct Phase {
   // block, which a kernel copies to the device (the embedding kernel on the side, or copy_in); the pointers below are views
   // into the two blocks, laid out afresh by every launch.
   unsigned char* h_meta = nullptr; unsigned char* d_meta = nullptr; size_t meta_bytes = 0, meta_used = 0;
-  int* d_tokens = nullptr; int* d_pos = nullptr; int* d_bt = nullptr; int* d_rows = nullptr;
+  int* d_tokens = nullptr; int* d_pos = nullptr; int* d_place = nullptr; int* d_bt = nullptr; int* d_rows = nullptr;
   PrefillSeq* d_pseq = nullptr; DecodeSeq* d_dseq = nullptr; AttnItem* d_items = nullptr; DecodeItem* d_ditems = nullptr;
   // pinned staging
-  int* h_tokens = nullptr; int* h_pos = nullptr; int* h_bt = nullptr; int* h_rows = nullptr;
+  int* h_tokens = nullptr; int* h_pos = nullptr; int* h_place = nullptr; int* h_bt = nullptr; int* h_rows = nullptr;
   PrefillSeq* h_pseq = nullptr; DecodeSeq* h_dseq = nullptr; AttnItem* h_items = nullptr; DecodeItem* h_ditems = nullptr;
   float* h_logits = nullptr; int* h_next = nullptr;
   int rows = 0;                               // rows of the last call
@@ -286,9 +286,9 @@ PrefillGemm pick_prefill_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, 
   return best;
 }
 // A prefill GEMM on the phase's partition, the last wave of tiles cut along K.
-hipError_t prefill_gemm(const Phase& ph, const PrefillGemm& gm, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k, ResidNorm* norm = nullptr) {
+hipError_t prefill_gemm(const Phase& ph, const PrefillGemm& gm, int epi, const bf16* A, int lda, const bf16* W, int ldw, void* C, int ldc, int m, int n, int k, ResidNorm* norm = nullptr, const QkvOut* qkv = nullptr) {
   const GemmTail tail{gemm_wgs_per_cu(gm.cfg) * ph.cus, ph.tail_ws, ph.tail_ws_bytes, norm};
-  return gemm_bf16(ph.stream, gm.cfg, epi, A, lda, W, ldw, C, ldc, m, n, k, 1, 0, &tail, true, false, gm.row_tiles);
+  return gemm_bf16(ph.stream, gm.cfg, epi, A, lda, W, ldw, C, ldc, m, n, k, 1, 0, &tail, true, false, gm.row_tiles, qkv);
 }
 int plan_splits(double rate_256, double partial_bw, int cfg, int m, int n, int k, int cus) {
   const int tiles = ((m + gemm_tile_m(cfg) - 1) / gemm_tile_m(cfg)) * (n / gemm_tile_n(cfg));
@@ -581,6 +581,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   meta_take(ph, &h_merges, &d_merges, n_merges);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
   meta_take(ph, &ph.h_pos, &ph.d_pos, lb == 0 ? rows : 0);
+  meta_take(ph, &ph.h_place, &ph.d_place, rows);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
@@ -593,6 +594,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     bt_off += (int)s.pages.size();
     ph.h_rows[i] = r0 + lens[i] - 1;
     for (int j = 0; lb == 0 && j < lens[i]; j++) ph.h_pos[r0 + j] = s.len + j;
+    for (int j = 0; j < lens[i]; j++) ph.h_place[r0 + j] = s.pages[(s.len + j) / c->geo.page_tokens] * c->geo.page_tokens + (s.len + j) % c->geo.page_tokens;
     r0 += lens[i];
   }
   std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
@@ -620,8 +622,13 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     const LayerW& w = c->layers[l];
     ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
     if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
-    KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
-    KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
+    if (g_qkv.cfg == GEMM_256x256) {
+      const QkvOut out{ph.rot, ph.d_place, layer_pool(c, l), c->geo, d.n_q_heads};
+      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_QKV, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h, nullptr, &out));
+    } else {
+      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
+      KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
+    }
     KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
     KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
     if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
@@ -861,7 +868,7 @@ int alloc_phase(sts_ctx* c, int side) {
     // decode attention items: a context has at most 128 chunks, and fewer than one per 4 pages (chunks hold >= 8)
     const size_t dec_items = side == 1 ? nseq * (size_t)decode_max_chunks((int)mp) : 0;
     ph.meta_bytes = nseq * (sizeof(PrefillSeq) + sizeof(DecodeSeq) + sizeof(DecodeMerge) + sizeof(int)) + items * (sizeof(AttnItem) + sizeof(AttnMerge)) + dec_items * sizeof(DecodeItem) +
-                    2 * rows * sizeof(int) + nseq * mp * sizeof(int) + 8 * 256;
+                    3 * rows * sizeof(int) + nseq * mp * sizeof(int) + 9 * 256;
     STSCK(dev_alloc(c, &ph.d_meta, ph.meta_bytes + 16));      // copied in 16-byte pieces
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));
   }

@@ -58,6 +58,7 @@ struct GemmArgs {
   float* tail_ws;
   int row_blocks;             // gemm_rows_kernel: 32-row blocks of M, dealt evenly to tiles_m row tiles, or (tile_blocks > 0)
   int tile_blocks;            // tile_blocks to each and the rest to the last
+  QkvOut qkv;                 // EPI_QKV
 };
 
 // tile index -> tile coordinates: tiles are walked in groups of group_m tile rows so that
@@ -675,6 +676,79 @@ struct RowsPlan {
 
 typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
 __device__ __forceinline__ bf16x8 lds_read16(lds_cptr p) { return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(p); }
+// Output of one tile of the QKV projection, from its bf16 image [rows][256 + padding]: what rope_kv_prefill_kernel does, without the
+// pass over memory (8192 rows of 32 + 8 + 8 heads 59 us, 2048 on 224 CUs 17, 301 5.8). A tile is 256 / d whole heads of any kind.
+// Q and K: 16 threads a row, eight rotation pairs each. V: a thread per column; eight rows that fill half a page row leave as 16 bytes.
+template <int RS>
+__device__ __forceinline__ void store_qkv_image(const GemmArgs& g, const bf16* img, int m0, int n0, int rows) {
+  constexpr int BATCH = 4;                                   // rows of a thread under way
+  const QkvOut& o = g.qkv;
+  const int tid = threadIdx.x, lane = tid & 63, d = o.geo.d, half = d >> 1, head0 = n0 / d;
+  {
+    const int per_head = d >> 4, hd = head0 + (tid & 15) / per_head, i0 = (tid & 15) % per_head * 8, c0 = (hd - head0) * d + i0;
+    if (hd < o.n_q + o.geo.n_kv) {
+      const bool is_k = hd >= o.n_q;
+      for (int r0 = tid >> 4; r0 < rows; r0 += 16 * BATCH) {
+        f32x4 cs[BATCH][2], sn[BATCH][2];
+        int place[BATCH];
+#pragma unroll
+        for (int p = 0; p < BATCH; p++) {                    // rows past the tile's repeat its last one
+          const int row = min(r0 + 16 * p, rows - 1);
+          const float* t = o.rot + (size_t)(m0 + row) * d + i0;
+#pragma unroll
+          for (int q = 0; q < 2; q++) {
+            cs[p][q] = *reinterpret_cast<const f32x4*>(t + 4 * q);
+            sn[p][q] = *reinterpret_cast<const f32x4*>(t + half + 4 * q);
+          }
+          place[p] = is_k ? o.place[m0 + row] : 0;
+        }
+#pragma unroll
+        for (int p = 0; p < BATCH; p++) {
+          const int row = r0 + 16 * p;
+          const bf16* im = img + (size_t)min(row, rows - 1) * RS + c0;
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(im), b = *reinterpret_cast<const bf16x8*>(im + half);
+          bf16x8 ya, yb;
+#pragma unroll
+          for (int e = 0; e < 8; e++) {
+            float ra, rb;
+            rotate_pair(bf2f(a[e]), bf2f(b[e]), cs[p][e >> 2][e & 3], sn[p][e >> 2][e & 3], &ra, &rb);
+            ya[e] = f2bf(ra);
+            yb[e] = f2bf(rb);
+          }
+          bf16* dst = is_k ? o.pool + ((size_t)(place[p] >> 4) * o.geo.n_kv + (hd - o.n_q)) * o.geo.head_elems() + (size_t)(place[p] & 15) * d + i0
+                           : reinterpret_cast<bf16*>(g.C) + (size_t)(m0 + row) * g.ldc + n0 + c0;
+          if (row < rows) {
+            *reinterpret_cast<bf16x8*>(dst) = ya;
+            *reinterpret_cast<bf16x8*>(dst + half) = yb;
+          }
+        }
+      }
+    }
+  }
+  const int hv = head0 + tid / d - o.n_q - o.geo.n_kv;       // this column's V head
+  if (__any(hv >= 0)) {
+    bf16* vt = o.pool + (size_t)max(hv, 0) * o.geo.head_elems() + (size_t)16 * d + (size_t)(tid % d) * 16;
+    const bf16* col = img + tid;
+    for (int r0 = 0; r0 < rows; r0 += 64) {
+      const int cnt = min(64, rows - r0), mine = o.place[m0 + r0 + min(lane, cnt - 1)];   // a row's place per lane
+      for (int r = 0; r < cnt;) {
+        const int place = __builtin_amdgcn_readlane(mine, r);
+        bf16* dst = vt + (size_t)(place >> 4) * o.geo.page_elems() + (place & 15);
+        if ((place & 7) == 0 && r + 8 <= cnt && __builtin_amdgcn_readlane(mine, min(r + 7, 63)) == place + 7) {   // places of a sequence follow each other
+          bf16x8 v;
+#pragma unroll
+          for (int e = 0; e < 8; e++) v[e] = col[(size_t)(r0 + r + e) * RS];
+          if (hv >= 0) *reinterpret_cast<bf16x8*>(dst) = v;
+          r += 8;
+        } else {
+          if (hv >= 0) *dst = col[(size_t)(r0 + r) * RS];
+          r++;
+        }
+      }
+    }
+  }
+}
+
 template <int EPI, int TM>
 __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char* arena, int m0, int n0, int kbeg, int kend, int piece) {
   using P = RowsPlan<TM>;
@@ -921,6 +995,10 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
       }
     });
     __syncthreads();
+    if constexpr (EPI == EPI_QKV) {
+      store_qkv_image<RS>(g, img, m0, n0, min(BM, g.M - m0));
+      return;
+    }
     constexpr int CPRW = OC / 8;
 #pragma unroll
     for (int c = 0; c < BM * CPRW / NT; c++) {
@@ -1060,6 +1138,40 @@ __global__ void __launch_bounds__(WGM * 256, 2) gemm_rowmajor256_kernel(GemmArgs
   }
 }
 
+// store_fixed_up of the QKV projection: a thread whose columns are of a head's first half takes their rotation partners too.
+__device__ __forceinline__ void store_fixed_up_qkv(const GemmArgs& g, const float* p, int stride, int row, int col) {
+  const QkvOut& o = g.qkv;
+  const int d = o.geo.d, half = d >> 1, hd = col / d, i0 = col % d;
+  const bool rotated = hd < o.n_q + o.geo.n_kv;
+  if (rotated && i0 >= half) return;
+  f32x4 a = *reinterpret_cast<const f32x4*>(p), b = {0.f, 0.f, 0.f, 0.f};
+  if (rotated) b = *reinterpret_cast<const f32x4*>(p + half);
+  for (int z = 1; z < g.tail_f; z++) {
+    a += *reinterpret_cast<const f32x4*>(p + (size_t)z * stride);
+    if (rotated) b += *reinterpret_cast<const f32x4*>(p + (size_t)z * stride + half);
+  }
+  const int place = hd >= o.n_q ? o.place[row] : 0;
+  if (!rotated) {
+    bf16* v = o.pool + (size_t)(place >> 4) * o.geo.page_elems() + (size_t)(hd - o.n_q - o.geo.n_kv) * o.geo.head_elems() + (size_t)16 * d + (place & 15);
+#pragma unroll
+    for (int e = 0; e < 4; e++) v[(size_t)(i0 + e) * 16] = f2bf(a[e]);
+    return;
+  }
+  const f32x4 cs = *reinterpret_cast<const f32x4*>(o.rot + (size_t)row * d + i0), sn = *reinterpret_cast<const f32x4*>(o.rot + (size_t)row * d + half + i0);
+  bf16x4 ya, yb;
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    float ra, rb;
+    rotate_pair(bf2f(f2bf(a[e])), bf2f(f2bf(b[e])), cs[e], sn[e], &ra, &rb);   // the projection's result is rounded to bf16 first
+    ya[e] = f2bf(ra);
+    yb[e] = f2bf(rb);
+  }
+  bf16* dst = hd < o.n_q ? reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + col
+                         : o.pool + ((size_t)(place >> 4) * o.geo.n_kv + (hd - o.n_q)) * o.geo.head_elems() + (size_t)(place & 15) * d + i0;
+  *reinterpret_cast<bf16x4*>(dst) = ya;
+  *reinterpret_cast<bf16x4*>(dst + half) = yb;
+}
+
 // Adds the tail pieces of each split tile of gemm_rows_kernel in piece order and applies the epilogue. One thread per four
 // consecutive columns; blocks past the tile's height leave.
 template <int EPI>
@@ -1075,7 +1187,8 @@ __global__ void __launch_bounds__(256) gemm_rows_fixup(GemmArgs g) {
   if (r >= blocks * 32 || row >= g.M) return;
   if (EPI == EPI_SWIGLU_BF16 && ((c >> 5) & 1)) return;      // "up" columns are consumed by their gate thread
   const float* p = g.tail_ws + (size_t)t * g.tail_f * g.piece_stride + (size_t)r * BN + c;
-  store_fixed_up<EPI>(g, p, g.piece_stride, row, tn * BN, c);
+  if constexpr (EPI == EPI_QKV) store_fixed_up_qkv(g, p, g.piece_stride, row, tn * BN + c);
+  else store_fixed_up<EPI>(g, p, g.piece_stride, row, tn * BN, c);
 }
 
 // gemm_rows_fixup of a residual GEMM and the RMSNorm of the rows it finishes, in one pass: a workgroup takes a row, adds the
@@ -1326,22 +1439,26 @@ int gemm_wgs_per_cu(int cfg) { return cfg == GEMM_256x256 || cfg == GEMM_64x256 
 // launch (0: as few as 256 rows allow).
 hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, const bf16* W, int ldw,
                      void* C, int ldc, int M, int N, int K, int splits, long long split_stride, const GemmTail* tail, bool w_packed, bool stream_nt,
-                     int row_tiles) {
+                     int row_tiles, const QkvOut* qkv) {
   if (M < 1 || K % 64 != 0 || N % gemm_tile_n(cfg) != 0 || lda % 8 != 0 || ldw % 8 != 0) return hipErrorInvalidValue;
   if (w_packed && ldw != K) return hipErrorInvalidValue;          // packed blocks are addressed by K alone
   if (splits < 1 || (splits > 1 && epi != EPI_F32)) return hipErrorInvalidValue;
   // 16-byte output stores
-  if (w_packed && (cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 ? 8 : 4) != 0) return hipErrorInvalidValue;
+  if (w_packed && (cfg == GEMM_256x256 || cfg == GEMM_128x256) && ldc % (epi == EPI_BF16 || epi == EPI_SWIGLU_BF16 || epi == EPI_QKV ? 8 : 4) != 0) return hipErrorInvalidValue;
+  if (epi == EPI_QKV && (!qkv || cfg != GEMM_256x256 || !w_packed || (qkv->geo.d != 64 && qkv->geo.d != 128) || qkv->geo.page_tokens != 16 ||
+                         N != (qkv->n_q + 2 * qkv->geo.n_kv) * qkv->geo.d)) return hipErrorInvalidValue;
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_64x256) return hipErrorInvalidValue;   // its wave tile is one 32-column block, not a gate/up pair
   if (epi == EPI_SWIGLU_BF16 && cfg == GEMM_128x256) return hipErrorInvalidValue;  // not offered (the engine itself never takes this shape: its row tiles have any height)
   GemmArgs g{};
   g.A = A; g.W = W; g.C = C; g.lda = lda; g.ldw = ldw; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
+  if (qkv) g.qkv = *qkv;
   g.split_stride = split_stride; g.w_packed = w_packed ? 1 : 0; g.stream_nt = stream_nt ? 1 : 0;
   switch (epi) {
     case EPI_BF16: return launch_epi<EPI_BF16>(s, cfg, g, splits, tail, row_tiles);
     case EPI_F32: return launch_epi<EPI_F32>(s, cfg, g, splits, tail, row_tiles);
     case EPI_RESID_F32: return launch_epi<EPI_RESID_F32>(s, cfg, g, splits, tail, row_tiles);
     case EPI_SWIGLU_BF16: return launch_epi<EPI_SWIGLU_BF16>(s, cfg, g, 1, tail, row_tiles);
+    case EPI_QKV: return launch_rows<EPI_QKV>(s, g, 1, tail, row_tiles, 8);
     default: return hipErrorInvalidValue;
   }
 }

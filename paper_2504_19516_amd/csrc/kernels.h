@@ -7,7 +7,7 @@
 namespace sts {
 
 // ---- GEMM -------------------------------------------------------------------------------
-enum GemmEpilogue { EPI_BF16 = 0, EPI_F32 = 1, EPI_RESID_F32 = 2, EPI_SWIGLU_BF16 = 3 };
+enum GemmEpilogue { EPI_BF16 = 0, EPI_F32 = 1, EPI_RESID_F32 = 2, EPI_SWIGLU_BF16 = 3, EPI_QKV = 4 };
 // the same numbering as STS_GEMM_* in sts.h
 enum GemmConfig { GEMM_128x128 = 0, GEMM_64x256 = 1, GEMM_64x128 = 2, GEMM_256x256 = 3, GEMM_128x256 = 4, GEMM_64x256S = 5, GEMM_64x320S = 6, GEMM_64x384S = 7,
                   GEMM_64x448S = 8, GEMM_64x512S = 9, GEMM_NCFG = 10 };
@@ -17,13 +17,17 @@ int gemm_wgs_per_cu(int cfg);                       // resident workgroups per C
 // Tail splitting: `slots` = workgroups the stream's CU partition holds at once, `ws` = fp32 scratch.
 // norm: RMSNorm wanted of the finished rows of C (out: [M, N] bf16); `done` is set if the launch's last kernel writes it.
 struct ResidNorm { bf16* out; const float* gain; float eps; bool done; };
+// EPI_QKV (256x256, packed W): columns are n_q query heads, then n_kv K and n_kv V heads of geo.d. Q is rotated into C, K rotated and V
+// transposed into the rows' places in the KV pool; C's K and V columns are not written. rot: each row's angles; place: page *
+// page_tokens + slot of each row.
+struct QkvOut;
 struct GemmTail { int slots; float* ws; size_t ws_bytes; ResidNorm* norm = nullptr; };
 void gemm_tail_plan(int tiles, int ksteps, int slots, long long max_pieces, int* n_full, int* f);
 // W is either row-major [N, ldw] or (w_packed, the engine's weights; needs ldw == K) in
 // the packed layout below. The row-major form exists for the fp32-store epilogue only.
 hipError_t gemm_bf16(hipStream_t s, int cfg, int epi, const bf16* A, int lda, const bf16* W, int ldw,
                      void* C, int ldc, int M, int N, int K, int splits, long long split_stride,
-                     const GemmTail* tail = nullptr, bool w_packed = true, bool stream_nt = false, int row_tiles = 0);
+                     const GemmTail* tail = nullptr, bool w_packed = true, bool stream_nt = false, int row_tiles = 0, const QkvOut* qkv = nullptr);
 
 // Packed GEMM weights: blocks of 32 rows x 64 columns (4 KiB), stored one after the other along K, then
 // along N. A block is laid out the way the matrix cores take a W operand: four pieces of 1 KiB, one per
@@ -48,6 +52,8 @@ struct KvGeom {
   __host__ __device__ size_t head_elems() const { return (size_t)2 * page_tokens * d; }
   __host__ __device__ size_t page_elems() const { return head_elems() * n_kv; }
 };
+
+struct QkvOut { const float* rot; const int* place; bf16* pool; KvGeom geo; int n_q; };
 
 // Per-sequence metadata of one prefill launch (device array, one entry per sequence).
 struct PrefillSeq {

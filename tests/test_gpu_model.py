@@ -731,6 +731,37 @@ def test_prefill_rows_finished_and_normalised_in_one_kernel(wide_rows, cus, rows
     free_all(eng, [s])
 
 
+@pytest.mark.parametrize("cus", [256, 8])
+@pytest.mark.parametrize("nq,nkv,d", [(8, 2, 128), (8, 1, 128), (4, 4, 64), (8, 2, 64)])
+def test_qkv_tiles_rotate_and_append_as_the_separate_kernel(sts, nq, nkv, d, cus):
+    """256-column tiles of the QKV projection rotate Q and K and write K and V to the pages themselves: tiles of Q, K or V heads and of
+    several kinds, whole (8 CUs) and cut along K (256), chunks that start and end inside a page and inside a half of it, a row tile over
+    several sequences. Against the same tokens in steps of up to 64 rows, which take other tiles and a kernel of their own."""
+    desc = synth.ModelDesc(1, 512, nq, nkv, d, 512, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=79)
+    eng.set_partition(cus, 256)
+    lens, priors = [37, 130, 9, 200, 1], [5, 0, 16, 27, 1]
+    seqs = [eng.seq_create() for _ in lens]
+    again = [eng.seq_create() for _ in lens]
+    tok = [synth.tokens(820 + i, n + p, desc.vocab) for i, (n, p) in enumerate(zip(lens, priors))]
+    for s in (seqs, again):
+        for i, p in enumerate(priors):
+            if p:
+                eng.prefill_append(s[i], tok[i][:p], want_logits=False)
+    eng.kernel_timing(True)
+    eng.kernel_times(0, reset=True)
+    got = eng.prefill_batch(seqs, [t[p:] for t, p in zip(tok, priors)])
+    assert "rope" not in eng.kernel_times(0, reset=True)
+    eng.kernel_timing(False)
+    for i, (n, p) in enumerate(zip(lens, priors)):
+        for a in range(p, n + p, 64):
+            ref = eng.prefill_append(again[i], tok[i][a:min(a + 64, n + p)])
+        assert rel(got[i], np.asarray(ref).reshape(-1)) <= TOL
+        for x, y in zip(eng.kv_read(0, seqs[i], 0, n + p), eng.kv_read(0, again[i], 0, n + p)):
+            assert rel(x, y) <= 2.0 ** -7, i
+    eng.close()
+
+
 def test_rotated_keys_are_rounded_alike_by_every_kernel(sts):
     """Cached K of prefill (8192 tokens) and of decode steps (16 steps of 224 requests, and of 8: the split and the finishing
     GEMM form) against the documented rounding, bit by bit: bf16(fma(a, c, -(b s))) and bf16(fma(b, c, a s)) of the bf16
