@@ -532,8 +532,9 @@ int prefill_validate(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t*
 
 // Queues a validated slice whose pages are reserved. A failure in here (a HIP error) leaves the
 // batch description as it was before the call.
+struct DecodeRun;
 int prefill_launch_checked(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
-                           int lb, int le, bool want_logits);
+                           int lb, int le, bool want_logits, DecodeRun* beside = nullptr);
 
 int prefill_enqueue(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
                     int lb, int le, bool want_logits) {
@@ -544,107 +545,22 @@ int prefill_enqueue(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* 
 }
 
 int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
-                        int lb, int le, bool want_logits);
+                        int lb, int le, bool want_logits, DecodeRun* beside);
 
+// beside: a decode step that is queued in turns with this slice, a layer each, on its own stream; the caller queues what is left of it.
 int prefill_launch_checked(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
-                           int lb, int le, bool want_logits) {
+                           int lb, int le, bool want_logits, DecodeRun* beside) {
   if (lb == 0) {
     std::lock_guard<std::mutex> g(c->state_mu);
     c->pf_active = true; c->pf_next_layer = 0;
     c->pf_seqs.assign(seqs, seqs + n_seqs); c->pf_lens.assign(lens, lens + n_seqs);
   }
-  const int rc = prefill_launch_body(c, n_seqs, seqs, lens, tokens, lb, le, want_logits);
+  const int rc = prefill_launch_body(c, n_seqs, seqs, lens, tokens, lb, le, want_logits, beside);
   if (rc != STS_OK && lb == 0) {                             // the batch never started: later prefills are not blocked
     std::lock_guard<std::mutex> g(c->state_mu);
     c->pf_active = false; c->pf_seqs.clear(); c->pf_lens.clear();
   }
   return rc;
-}
-
-int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
-                        int lb, int le, bool want_logits) {
-  Phase& ph = c->ph[0];
-  const sts_model_desc& d = c->d;
-  int rows = 0;
-  for (int i = 0; i < n_seqs; i++) rows += lens[i];
-  std::vector<int> priors(n_seqs);
-  for (int i = 0; i < n_seqs; i++) priors[i] = c->seqs[seqs[i]].len;
-  const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
-                                          (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
-  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size();
-  // ---- stage metadata
-  ph.meta_used = 0;
-  meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
-  meta_take(ph, &ph.h_rows, &ph.d_rows, n_seqs);
-  meta_take(ph, &ph.h_items, &ph.d_items, n_items);
-  AttnMerge *h_merges = nullptr, *d_merges = nullptr;
-  meta_take(ph, &h_merges, &d_merges, n_merges);
-  meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
-  meta_take(ph, &ph.h_pos, &ph.d_pos, lb == 0 ? rows : 0);
-  meta_take(ph, &ph.h_place, &ph.d_place, rows);
-  size_t bt_entries = 0;                                     // block tables are packed back to back
-  for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
-  meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
-  if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
-  int r0 = 0, bt_off = 0;
-  for (int i = 0; i < n_seqs; i++) {
-    const Seq& s = c->seqs[seqs[i]];
-    ph.h_pseq[i] = PrefillSeq{r0, lens[i], s.len, bt_off, (int)s.pages.size()};
-    std::memcpy(ph.h_bt + bt_off, s.pages.data(), s.pages.size() * sizeof(int));
-    bt_off += (int)s.pages.size();
-    ph.h_rows[i] = r0 + lens[i] - 1;
-    for (int j = 0; lb == 0 && j < lens[i]; j++) ph.h_pos[r0 + j] = s.len + j;
-    for (int j = 0; j < lens[i]; j++) ph.h_place[r0 + j] = s.pages[(s.len + j) / c->geo.page_tokens] * c->geo.page_tokens + (s.len + j) % c->geo.page_tokens;
-    r0 += lens[i];
-  }
-  std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
-  if (n_merges > 0) std::memcpy(h_merges, attn.merges.data(), n_merges * sizeof(AttnMerge));
-  hipStream_t st = ph.stream;
-  HIPCK(hipEventRecord(ph.ev0, st));
-  if (lb == 0) std::memcpy(ph.h_tokens, tokens, rows * sizeof(int));
-  const int h = d.hidden;
-  const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
-  const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
-  // few rows: the embedding kernel reads tokens and positions from host memory itself and copies the metadata on the side
-  const bool fused_meta = fused_embed && rows <= META_FUSED_ROWS;
-  RowRotation rot{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
-  if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
-  if (fused_embed) {
-    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
-  } else if (lb == 0) {
-    KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, rows, h));
-    KL(ph, STS_K_ROPE, row_rotation(st, rot, rows));
-  }
-  auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
-  const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
-  bool normed = fused_embed;                                 // Xn holds this layer's input already
-  for (int l = lb; l < le; l++) {
-    const LayerW& w = c->layers[l];
-    ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
-    if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
-    if (g_qkv.cfg == GEMM_256x256) {
-      const QkvOut out{ph.rot, ph.d_place, layer_pool(c, l), c->geo, d.n_q_heads};
-      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_QKV, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h, nullptr, &out));
-    } else {
-      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
-      KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
-    }
-    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
-    KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
-    if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
-    KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
-    KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp, l + 1 < le ? &next : nullptr));
-    normed = next.done;
-  }
-  if (le == d.n_layers && want_logits) {
-    const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);
-    const bool direct = bytes <= DIRECT_LOGITS_BYTES;        // the head's last kernel stores to host memory
-    STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false, direct ? ph.h_logits : ph.logits));
-    if (!direct) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
-  }
-  HIPCK(hipEventRecord(ph.ev1, st));
-  ph.ran = true; ph.rows = rows;
-  return STS_OK;
 }
 
 int prefill_finish(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, int le, float* logits) {
@@ -711,7 +627,37 @@ int decode_enqueue(sts_ctx* c, const int32_t* seqs, const int32_t* in_tokens, in
   return decode_launch_checked(c, seqs, in_tokens, n, want_logits, want_next);
 }
 
+// A validated decode step whose pages are reserved, queued in pieces: its metadata and embedding, the layers one by one, the head.
+struct DecodeRun {
+  sts_ctx* c; const int32_t* seqs; const int32_t* in_tokens; int n; bool want_logits, want_next;
+  int rc = STS_OK, layer = -1;                               // first failure; next piece (-1: not begun)
+  int n_items = 0, n_multi = 0, chunk_pages = 0, max_chunks = 0;
+  DecodeMerge* d_multi = nullptr;
+  RowRotation rot{};
+  DecodePlan plan;
+  bool nt = false;
+  RowScale by_rms{}, xn_scale{nullptr, 0, 0.f};
+
+  int begin();
+  int one_layer(int l);
+  int end();
+  void turn() {                                              // the next piece; none once all layers are queued
+    if (rc != STS_OK || layer >= c->d.n_layers) return;
+    rc = layer < 0 ? begin() : one_layer(layer);
+    layer++;
+  }
+  int finish_queue() {                                       // what is left
+    while (rc == STS_OK && layer < c->d.n_layers) turn();
+    if (rc == STS_OK) rc = end();
+    return rc;
+  }
+};
+
 int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tokens, int n, bool want_logits, bool want_next) {
+  return DecodeRun{c, seqs, in_tokens, n, want_logits, want_next}.finish_queue();
+}
+
+int DecodeRun::begin() {
   Phase& ph = c->ph[1];
   const sts_model_desc& d = c->d;
   const int mp = c->p.max_pages_per_seq, pt = c->geo.page_tokens;
@@ -736,11 +682,9 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   }
   std::vector<int> np_list(n);
   for (int i = 0; i < n; i++) np_list[i] = ph.h_dseq[i].n_pages;
-  int chunk_pages, max_chunks;
   decode_chunk_plan(np_list.data(), n, d.n_kv_heads, ph.cus, pt, &chunk_pages, &max_chunks);
   if (max_chunks > decode_max_chunks(mp)) return STS_EINVAL;   // cannot happen within sts_init's bound on max_pages_per_seq
   // one attention workgroup row per context chunk that exists
-  int n_items = 0;
   for (int i = 0; i < n; i++) n_items += (ph.h_dseq[i].n_pages + chunk_pages - 1) / chunk_pages;
   meta_take(ph, &ph.h_ditems, &ph.d_ditems, n_items);
   if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
@@ -757,8 +701,7 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
     std::stable_sort(ph.h_ditems, ph.h_ditems + n_items, [&](const DecodeItem& a, const DecodeItem& b) { return chunk_len(a) > chunk_len(b); });
   }
   // requests whose context has more than one chunk: only they need the merge kernel
-  DecodeMerge *h_multi = nullptr, *d_multi = nullptr;
-  int n_multi = 0;
+  DecodeMerge* h_multi = nullptr;
   meta_take(ph, &h_multi, &d_multi, (size_t)n);
   if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
   for (int i = 0; i < n; i++)
@@ -768,7 +711,7 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   const int h = d.hidden;
   const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
   const bool fused_meta = h <= 8192 && n <= META_FUSED_ROWS;
-  RowRotation rot{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
+  rot = RowRotation{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
   if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
   if (h <= 8192) {
     KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, n, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
@@ -780,54 +723,154 @@ int decode_launch_checked(sts_ctx* c, const int32_t* seqs, const int32_t* in_tok
   // On a large partition the decode streams (K and V, the weights of the skinny tiles) are fetched with the non-temporal
   // hint: measured on a 6-layer model, the layer-step is 6 % shorter on 256 CUs (attention 72 -> 63 us), 3 % on 128,
   // and no different on 32, where the same hint cost a prefill slice running beside it 0.5 %.
-  const bool nt_attn = ph.cus >= 128, nt_w = nt_attn;
-  const DecodePlan plan = decode_layer_plan(c, n, ph.cus);
+  nt = ph.cus >= 128;
+  plan = decode_layer_plan(c, n, ph.cus);
+  // kslice layers: the residual GEMMs leave Xn scaled by the next gains and the rows' sums of squares in ssq
+  by_rms = RowScale{ph.ssq, h / kslice_cols(KS_RESID, h, ph.cus), d.rms_eps};
+  return STS_OK;
+}
+
+int DecodeRun::one_layer(int l) {
+  Phase& ph = c->ph[1];
+  const sts_model_desc& d = c->d;
+  const int h = d.hidden;
+  hipStream_t st = ph.stream;
   auto partials = [&](int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) -> int {
-    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt_w));
+    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt));
     return STS_OK;
   };
-  // kslice layers: the residual GEMMs leave Xn scaled by the next gains and the rows' sums of squares in ssq
-  const RowScale by_rms{ph.ssq, h / kslice_cols(KS_RESID, h, ph.cus), d.rms_eps};
-  RowScale xn_scale{nullptr, 0, 0.f};
-  for (int l = 0; l < d.n_layers; l++) {
-    const LayerW& w = c->layers[l];
-    const float* next_gain = (l + 1 < d.n_layers) ? c->layers[l + 1].g1 : c->gf;
-    if (plan.kslice) {
-      KL(ph, STS_K_QKV, kslice_qkv(st, KsliceIn{ph.Xn, h, xn_scale, w.wqkv, n, c->qkvn, h}, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, d.n_q_heads));
-    } else {
-      STSCK(partials(STS_K_QKV, plan.qkv, ph.Xn, w.wqkv, c->qkvn, h));
-      KL(ph, STS_K_ROPE, decode_qkv_finish(st, ph.part, plan.qkv.splits, (long long)n * c->qkvn, c->qkvn, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, n, d.n_q_heads));
-    }
-    KL(ph, STS_K_ATTN, attn_decode(st, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, nt_attn));
-    if (plan.kslice) {
-      KL(ph, STS_K_O, kslice_resid(st, KsliceIn{ph.A, c->qd, RowScale{nullptr, 0, 0.f}, w.wo, n, h, c->qd}, ph.cus, ph.X, w.g2, ph.Xn, ph.ssq));
-      KL(ph, STS_K_GATEUP, kslice_swiglu(st, KsliceIn{ph.Xn, h, by_rms, w.wgu, n, 2 * d.mlp, h}, ph.H));
-      KL(ph, STS_K_DOWN, kslice_resid(st, KsliceIn{ph.H, d.mlp, RowScale{nullptr, 0, 0.f}, w.wd, n, h, d.mlp}, ph.cus, ph.X, next_gain, ph.Xn, ph.ssq));
-      xn_scale = by_rms;
-      continue;
-    }
-    STSCK(partials(STS_K_O, plan.o, ph.A, w.wo, h, c->qd));
-    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.o.splits, (long long)n * h, ph.Xn, w.g2, d.rms_eps, n, h));
-    if (plan.gu_fused) {
-      KL(ph, STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt_w));
-    } else {
-      STSCK(partials(STS_K_GATEUP, plan.gu, ph.Xn, w.wgu, 2 * d.mlp, h));
-      KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));
-    }
-    STSCK(partials(STS_K_DOWN, plan.down, ph.H, w.wd, h, d.mlp));
-    KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.down.splits, (long long)n * h, ph.Xn, next_gain, d.rms_eps, n, h));
+  const LayerW& w = c->layers[l];
+  const float* next_gain = (l + 1 < d.n_layers) ? c->layers[l + 1].g1 : c->gf;
+  if (plan.kslice) {
+    KL(ph, STS_K_QKV, kslice_qkv(st, KsliceIn{ph.Xn, h, xn_scale, w.wqkv, n, c->qkvn, h}, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, d.n_q_heads));
+  } else {
+    STSCK(partials(STS_K_QKV, plan.qkv, ph.Xn, w.wqkv, c->qkvn, h));
+    KL(ph, STS_K_ROPE, decode_qkv_finish(st, ph.part, plan.qkv.splits, (long long)n * c->qkvn, c->qkvn, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, n, d.n_q_heads));
   }
+  KL(ph, STS_K_ATTN, attn_decode(st, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, nt));
+  if (plan.kslice) {
+    KL(ph, STS_K_O, kslice_resid(st, KsliceIn{ph.A, c->qd, RowScale{nullptr, 0, 0.f}, w.wo, n, h, c->qd}, ph.cus, ph.X, w.g2, ph.Xn, ph.ssq));
+    KL(ph, STS_K_GATEUP, kslice_swiglu(st, KsliceIn{ph.Xn, h, by_rms, w.wgu, n, 2 * d.mlp, h}, ph.H));
+    KL(ph, STS_K_DOWN, kslice_resid(st, KsliceIn{ph.H, d.mlp, RowScale{nullptr, 0, 0.f}, w.wd, n, h, d.mlp}, ph.cus, ph.X, next_gain, ph.Xn, ph.ssq));
+    xn_scale = by_rms;
+    return STS_OK;
+  }
+  STSCK(partials(STS_K_O, plan.o, ph.A, w.wo, h, c->qd));
+  KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.o.splits, (long long)n * h, ph.Xn, w.g2, d.rms_eps, n, h));
+  if (plan.gu_fused) {
+    KL(ph, STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt));
+  } else {
+    STSCK(partials(STS_K_GATEUP, plan.gu, ph.Xn, w.wgu, 2 * d.mlp, h));
+    KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));
+  }
+  STSCK(partials(STS_K_DOWN, plan.down, ph.H, w.wd, h, d.mlp));
+  KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.down.splits, (long long)n * h, ph.Xn, next_gain, d.rms_eps, n, h));
+  return STS_OK;
+}
+
+int DecodeRun::end() {
+  Phase& ph = c->ph[1];
+  const sts_model_desc& d = c->d;
+  hipStream_t st = ph.stream;
   if (want_logits || want_next) {
     // (the last reduce kernel of the split form has written Xn normalised)
     const size_t bytes = (size_t)n * d.vocab * sizeof(float);
     // small logits reach host memory from the kernel that reads them last, large ones by a copy
     const bool direct = want_logits && !want_next && bytes <= DIRECT_LOGITS_BYTES, beside = want_logits && want_next && bytes <= BESIDE_LOGITS_BYTES;
-    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt_w, direct ? ph.h_logits : ph.logits));
+    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt, direct ? ph.h_logits : ph.logits));
     if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_next, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
     if (want_logits && !direct && !beside) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
   ph.ran = true; ph.rows = n;
+  return STS_OK;
+}
+
+int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
+                        int lb, int le, bool want_logits, DecodeRun* beside) {
+  Phase& ph = c->ph[0];
+  const sts_model_desc& d = c->d;
+  int rows = 0;
+  for (int i = 0; i < n_seqs; i++) rows += lens[i];
+  std::vector<int> priors(n_seqs);
+  for (int i = 0; i < n_seqs; i++) priors[i] = c->seqs[seqs[i]].len;
+  const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
+                                          (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
+  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size();
+  // ---- stage metadata
+  ph.meta_used = 0;
+  meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
+  meta_take(ph, &ph.h_rows, &ph.d_rows, n_seqs);
+  meta_take(ph, &ph.h_items, &ph.d_items, n_items);
+  AttnMerge *h_merges = nullptr, *d_merges = nullptr;
+  meta_take(ph, &h_merges, &d_merges, n_merges);
+  meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
+  meta_take(ph, &ph.h_pos, &ph.d_pos, lb == 0 ? rows : 0);
+  meta_take(ph, &ph.h_place, &ph.d_place, rows);
+  size_t bt_entries = 0;                                     // block tables are packed back to back
+  for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
+  meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
+  if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
+  int r0 = 0, bt_off = 0;
+  for (int i = 0; i < n_seqs; i++) {
+    const Seq& s = c->seqs[seqs[i]];
+    ph.h_pseq[i] = PrefillSeq{r0, lens[i], s.len, bt_off, (int)s.pages.size()};
+    std::memcpy(ph.h_bt + bt_off, s.pages.data(), s.pages.size() * sizeof(int));
+    bt_off += (int)s.pages.size();
+    ph.h_rows[i] = r0 + lens[i] - 1;
+    for (int j = 0; lb == 0 && j < lens[i]; j++) ph.h_pos[r0 + j] = s.len + j;
+    for (int j = 0; j < lens[i]; j++) ph.h_place[r0 + j] = s.pages[(s.len + j) / c->geo.page_tokens] * c->geo.page_tokens + (s.len + j) % c->geo.page_tokens;
+    r0 += lens[i];
+  }
+  std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
+  if (n_merges > 0) std::memcpy(h_merges, attn.merges.data(), n_merges * sizeof(AttnMerge));
+  hipStream_t st = ph.stream;
+  HIPCK(hipEventRecord(ph.ev0, st));
+  if (lb == 0) std::memcpy(ph.h_tokens, tokens, rows * sizeof(int));
+  const int h = d.hidden;
+  const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
+  const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
+  // few rows: the embedding kernel reads tokens and positions from host memory itself and copies the metadata on the side
+  const bool fused_meta = fused_embed && rows <= META_FUSED_ROWS;
+  RowRotation rot{ph.rot, fused_meta ? ph.h_pos : ph.d_pos, c->inv_freq, d.head_dim};
+  if (!fused_meta) KL(ph, STS_K_EMBED, copy_in(st, meta));
+  if (fused_embed) {
+    KL(ph, STS_K_EMBED, embed_norm_rows(st, ph.X, ph.Xn, c->emb, fused_meta ? ph.h_tokens : ph.d_tokens, c->layers[0].g1, d.rms_eps, rows, h, rot, fused_meta ? meta : MetaCopy{nullptr, nullptr, 0}));
+  } else if (lb == 0) {
+    KL(ph, STS_K_EMBED, embed_rows(st, ph.X, c->emb, ph.d_tokens, rows, h));
+    KL(ph, STS_K_ROPE, row_rotation(st, rot, rows));
+  }
+  if (beside) beside->turn();
+  auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
+  const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
+  bool normed = fused_embed;                                 // Xn holds this layer's input already
+  for (int l = lb; l < le; l++) {
+    const LayerW& w = c->layers[l];
+    ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
+    if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
+    if (g_qkv.cfg == GEMM_256x256) {
+      const QkvOut out{ph.rot, ph.d_place, layer_pool(c, l), c->geo, d.n_q_heads};
+      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_QKV, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h, nullptr, &out));
+    } else {
+      KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
+      KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
+    }
+    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
+    KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
+    if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
+    KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
+    KL(ph, STS_K_DOWN, prefill_gemm(ph, g_down, EPI_RESID_F32, ph.H, d.mlp, w.wd, d.mlp, ph.X, h, rows, h, d.mlp, l + 1 < le ? &next : nullptr));
+    normed = next.done;
+    if (beside) beside->turn();
+  }
+  if (le == d.n_layers && want_logits) {
+    const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);
+    const bool direct = bytes <= DIRECT_LOGITS_BYTES;        // the head's last kernel stores to host memory
+    STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false, direct ? ph.h_logits : ph.logits));
+    if (!direct) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
+  }
+  HIPCK(hipEventRecord(ph.ev1, st));
+  ph.ran = true; ph.rows = rows;
   return STS_OK;
 }
 
@@ -1310,14 +1353,19 @@ extern "C" int sts_step_concurrent(sts_ctx* c, int32_t n_pseqs, const int32_t* p
   if (n_pseqs > 0) STSCK(prefill_validate(c, n_pseqs, pseqs, plens, ptokens, lb, le, &wants));
   if (n_decode > 0) STSCK(decode_validate(c, dseqs, dtokens, n_decode, &wants));
   STSCK(reserve_pages(c, wants));
-  if (n_pseqs > 0) STSCK(prefill_launch_checked(c, n_pseqs, pseqs, plens, ptokens, lb, le, plogits != nullptr));
-  const int64_t t1 = now_ns();
+  // Both phases are queued in turns, a layer each: queued one after the other, the second's stream stays idle for as long as the
+  // first's launches take.
+  DecodeRun run{c, dseqs, dtokens, n_decode, dlogits != nullptr, dnext != nullptr};
   int rc = STS_OK;
-  if (n_decode > 0) rc = decode_launch_checked(c, dseqs, dtokens, n_decode, dlogits != nullptr, dnext != nullptr);
+  if (n_pseqs > 0) rc = prefill_launch_checked(c, n_pseqs, pseqs, plens, ptokens, lb, le, plogits != nullptr, n_decode > 0 ? &run : nullptr);
+  const bool prefill_queued = n_pseqs > 0 && rc == STS_OK;
+  const int64_t t1 = now_ns();
+  if (rc == STS_OK && n_decode > 0) rc = run.finish_queue();
   const int64_t t2 = now_ns();
   if (rc != STS_OK) {
-    // only a HIP failure can get here; the prefill slice already queued is waited for and dropped
-    if (n_pseqs > 0) { (void)wait_stream(c->ph[0].stream); (void)k_collect(c, c->ph[0]); (void)sts_prefill_abort(c); }
+    // only a HIP failure can get here; what is queued already is waited for and dropped
+    if (n_decode > 0 && run.layer >= 0) { (void)wait_stream(c->ph[1].stream); (void)k_collect(c, c->ph[1]); }
+    if (prefill_queued) { (void)wait_stream(c->ph[0].stream); (void)k_collect(c, c->ph[0]); (void)sts_prefill_abort(c); }
     return rc;
   }
   if (n_pseqs > 0) STSCK(prefill_finish(c, n_pseqs, pseqs, plens, le, plogits));
