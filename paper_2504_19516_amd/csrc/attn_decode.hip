@@ -67,8 +67,11 @@ __global__ void __launch_bounds__(256, 2) attn_decode_mfma_kernel(const bf16* __
   constexpr int LOADS = 2 * IPP + 2 * DB;            // vector-memory loads a wave issues per block (K to LDS + V^T to registers)
   extern __shared__ __align__(16) unsigned char smem[];
 
-  const DecodeItem item = items[blockIdx.x];
-  const int chunk = item.chunk, kvh = blockIdx.y, req = item.seq;
+  // The heads of a chunk are neighbours in the launch: the workgroups running together then read whole pages, 8 KiB of each head in a
+  // row. With the heads as the slow index all of them read the same 8 KiB of every 64: 64 requests, 8 layers 1468 -> 1458 us a step,
+  // 223 requests, 4 layers 1492 -> 1458.
+  const DecodeItem item = items[blockIdx.x / geo.n_kv];
+  const int chunk = item.chunk, kvh = blockIdx.x % geo.n_kv, req = item.seq;
   const int len = item.cl + 1;
   const int n_pages = (len + 15) >> 4;
   const int cp = balanced_chunk_pages(n_pages, chunk_pages);
@@ -357,7 +360,7 @@ static void launch_decode_kernel(hipStream_t s, const bf16* q, bf16* out, const 
   constexpr int lds = attn_decode_mfma_lds<D>();
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_decode_mfma_kernel<D, G, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   (void)attr;
-  hipLaunchKernelGGL((attn_decode_mfma_kernel<D, G, NT>), dim3(n_items, geo.n_kv), dim3(256), lds, s, q, out, seqs, items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
+  hipLaunchKernelGGL((attn_decode_mfma_kernel<D, G, NT>), dim3((unsigned)n_items * geo.n_kv), dim3(256), lds, s, q, out, seqs, items, bt, pool, geo, n_q, chunk_pages, max_chunks, ws, sc);
 }
 
 template <int D, int G>
