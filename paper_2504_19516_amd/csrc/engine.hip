@@ -394,8 +394,28 @@ constexpr double SMALL_KERNEL_S = 4.5e-6;     // one of the kernels that add up 
 // estimates, with the reduce kernels of the split form, is the smaller one. Otherwise tile and split of each, with SwiGLU in the
 // gate/up GEMM unless cutting K is estimated faster. Both measured on 256 CUs, 8B shape: 1 row 73 us of GEMMs against 82 + 20 of
 // reduce kernels; at 32 rows 112 us against 86 + 20, so the form ends at 16 rows (one row block of the matrix cores).
-struct DecodeGemm { int cfg = 0, splits = 1; };
+struct DecodeGemm { int cfg = 0, splits = 1, row_tiles = 0; };
 struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu, down; };
+// More than 64 rows: the tiles for the slices that pick_decode_gemm decided on -- 128x128, or 256 columns with the rows in any number of
+// row tiles, whichever takes the least estimated time. The slices stay, and with them the order of the sums: every shape gives the same
+// bits. Estimate: rounds of workgroups at the tile's rate, and 8 us for the first loads and the partial sums of a launch. Measured / estimated
+// at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
+// slices 21 / 20 in one, 16 / 16 in two; 4096 x 14336 48 / 51 and 39 / 36; 28672 x 4096 in 2 slices 58 / 57 in one row tile.
+void pick_tall_tiles(const sts_ctx* ctx, int m, int n, int k, int cus, DecodeGemm* g) {
+  if (m <= 64 || n % 256 != 0) return;
+  const int c = std::max(cus, 8), ksteps = k / 64, len = (ksteps + g->splits - 1) / g->splits * 64, blocks = (m + 31) / 32;
+  double best = 1e300;
+  auto consider = [&](int cfg, int row_tiles, long long wgs, int slots, double tile_s) {
+    const double t = (double)((wgs + slots - 1) / slots) * tile_s;
+    if (t < best) { best = t; g->cfg = cfg; g->row_tiles = row_tiles; }
+  };
+  consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (ctx->rate_128 * 1e12 / 2));
+  const double tall_s = 2.0 * 256 * 256 * len / (ctx->rate_256 * 1e12);
+  const int least = (blocks + 7) / 8;
+  for (int t = least; t <= std::min(blocks, 2 * least + 2); t++)
+    consider(GEMM_256x256, t, (long long)t * (n / 256) * g->splits, c, TILE_HEIGHT_COST[(blocks + t - 1) / t - 1] * tall_s);
+}
+
 DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
   const sts_model_desc& d = ctx->d;
   DecodePlan p;
@@ -408,6 +428,10 @@ DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
   const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
   if (can_fuse && (t_fused <= t_split || p.gu.splits == 1)) { p.gu_fused = true; p.gu = fused; }
   t += (p.gu_fused ? t_fused : t_split) + 3 * SMALL_KERNEL_S;
+  pick_tall_tiles(ctx, n, ctx->qkvn, d.hidden, cus, &p.qkv);
+  pick_tall_tiles(ctx, n, d.hidden, ctx->qd, cus, &p.o);
+  pick_tall_tiles(ctx, n, d.hidden, d.mlp, cus, &p.down);
+  if (!p.gu_fused) pick_tall_tiles(ctx, n, 2 * d.mlp, d.hidden, cus, &p.gu);
   if (n <= KSLICE_MAX_ROWS)
     p.kslice = kslice_time(ctx, KS_QKV, n, ctx->qkvn, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, ctx->qd, cus) +
                kslice_time(ctx, KS_SWIGLU, n, 2 * d.mlp, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, d.mlp, cus) < t;
@@ -736,7 +760,7 @@ int DecodeRun::one_layer(int l) {
   const int h = d.hidden;
   hipStream_t st = ph.stream;
   auto partials = [&](int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) -> int {
-    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt));
+    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt, gm.row_tiles));
     return STS_OK;
   };
   const LayerW& w = c->layers[l];

@@ -701,6 +701,39 @@ def test_decode_gemms_that_finish_their_output(ragged_case, n, cus):
 
 
 @pytest.fixture(scope="module")
+def many_requests(sts):
+    """256 requests of 1 to 40 cached tokens; hidden 512, MLP 1280, groups of four query heads."""
+    desc = synth.ModelDesc(2, 512, 8, 2, 128, 1280, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=80, max_decode_batch=256, max_seqs=260, kv_pool_pages=1100, max_pages_per_seq=8)
+    eng.set_partition(256, 256)
+    seqs, ctx = [eng.seq_create() for _ in range(256)], [1 + 7 * i % 40 for i in range(256)]
+    for i, (s, n) in enumerate(zip(seqs, ctx)):
+        eng.kv_fill_random(s, n, 900 + i)
+    yield eng, seqs, ctx, synth.tokens(81, 256, desc.vocab)
+    eng.close()
+
+
+@pytest.mark.parametrize("cus", [256, 32])
+@pytest.mark.parametrize("n", [65, 96, 97, 128, 129, 224, 225, 256])
+def test_decode_gemm_tiles_above_64_rows(many_requests, n, cus):
+    """The GEMMs of large decode batches take 128x128 tiles or 256-column row tiles of any height for the same slices along K. The logits
+    against those of the same requests in batches of 64, which take other tiles."""
+    eng, seqs, ctx, tok = many_requests
+    eng.set_partition(256, cus)
+    got, nxt = eng.decode_step(seqs[:n], tok[:n])
+    for s, c in zip(seqs[:n], ctx):
+        eng.seq_truncate(s, c)
+    for a in range(0, n, 64):
+        b = min(a + 64, n)
+        ref, _ = eng.decode_step(seqs[a:b], tok[a:b])
+        for s, c in zip(seqs[a:b], ctx[a:b]):
+            eng.seq_truncate(s, c)
+        assert rel(got[a:b], ref) <= TOL
+    assert all(nxt[i] == int(np.argmax(got[i])) for i in range(n))
+    eng.set_partition(256, 256)
+
+
+@pytest.fixture(scope="module")
 def wide_rows(sts):
     """Three layers of hidden 1280 (five 256-column tiles; the norm's last 256 elements of its second 1024 are past the row)."""
     desc = synth.ModelDesc(3, 1280, 8, 2, 128, 2048, 640, 16, 1.0e4, 1.0e-5, "bf16")
