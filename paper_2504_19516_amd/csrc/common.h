@@ -64,6 +64,24 @@ __device__ __forceinline__ void lds_dma16(const void* base, unsigned lane_off, v
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "s"(m) : "memory");
 #endif
 }
+// lds_dma16 in two parts, so that a matrix instruction can stand in the wait state between them (dma_m0_idle where none does).
+template <int OFF>
+__device__ __forceinline__ void dma_m0(unsigned lds_base) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "scc", "memory");
+#endif
+}
+__device__ __forceinline__ void dma_m0_idle() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_nop 0");
+#endif
+}
+__device__ __forceinline__ void dma_load(const unsigned char* base, unsigned lane_off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
+#endif
+}
+
 // Wait until at most N of this wave's vector-memory loads are outstanding (they complete in
 // order); the other counters are left alone.
 template <int N>

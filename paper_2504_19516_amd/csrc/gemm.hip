@@ -630,24 +630,6 @@ __device__ __forceinline__ void load_w_off(bf16x8& dst, const unsigned char* bas
   asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(dst) : "v"(lane_off), "s"(base), "n"(OFF) : "memory");
 #endif
 }
-// lds_dma16 in two parts, so that a matrix instruction can stand in the wait state between them (dma_m0_idle where none does).
-template <int OFF>
-__device__ __forceinline__ void dma_m0(unsigned lds_base) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_add_u32 m0, %0, %1" ::"s"(lds_base), "n"(OFF) : "scc", "memory");
-#endif
-}
-__device__ __forceinline__ void dma_m0_idle() {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_nop 0");
-#endif
-}
-__device__ __forceinline__ void dma_load(const unsigned char* base, unsigned lane_off) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base) : "memory");
-#endif
-}
-
 // A K tile of one wave: U units of one 16-row block each. A half of the units is one 32-wide step; its vector-memory operations -- four W
 // loads and its share of the A pieces, alternating -- are dealt over its units.
 template <int TM>

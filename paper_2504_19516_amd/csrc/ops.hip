@@ -149,7 +149,7 @@ extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* 
       hipMemcpy(d_items, plan.items.data(), n_items * sizeof(AttnItem), hipMemcpyHostToDevice) != hipSuccess ||
       (n_merges > 0 && hipMemcpy(d_merges, plan.merges.data(), n_merges * sizeof(AttnMerge), hipMemcpyHostToDevice) != hipSuccess)) return STS_EHIP;
   if (kv_write_tokens(nullptr, pool, geo, d_bt, 0, total, dk, dv) != hipSuccess) return STS_EHIP;
-  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
+  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, plan.even, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
   if (e != hipSuccess) return e == hipErrorInvalidValue ? STS_EINVAL : STS_EHIP;
   int rc = download_bf16(b, out, dout, (size_t)t * n_q * d);
   if (hipDeviceSynchronize() != hipSuccess) return STS_EHIP;
