@@ -37,6 +37,10 @@ __device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, 
   *yb = fmaf(b, c, a * s);
 }
 
+// SwiGLU of one gate and up value: silu(gate) * up, in fp32, with the correctly rounded division. One function for every kernel that
+// finishes a gate/up GEMM, so that a row's bits do not depend on the tile that it fell into.
+__device__ __forceinline__ float swiglu(float gate, float up) { return gate / (1.f + __expf(-gate)) * up; }
+
 // 16 bytes per lane from global memory straight into LDS: lane l of the wave writes at
 // lds_dst + 16 * l (lds_dst must be wave-uniform); completion is counted by vmcnt. Buffers filled
 // this way are kept 1 KB above LDS address 0.

@@ -487,7 +487,7 @@ __global__ void __launch_bounds__(256) reduce_swiglu_kernel(bf16* H, const float
   const f32x4 g = add_partials<S>(zero, p, split_stride), u = add_partials<S>(zero, p + 32, split_stride);
   bf16x4 o;
 #pragma unroll
-  for (int e = 0; e < 4; e++) o[e] = f2bf(g[e] / (1.f + __expf(-g[e])) * u[e]);
+  for (int e = 0; e < 4; e++) o[e] = f2bf(swiglu(g[e], u[e]));
   *reinterpret_cast<bf16x4*>(H + (size_t)row * mlp + j) = o;
 }
 hipError_t reduce_swiglu(hipStream_t s, bf16* H, const float* partials, int splits, long long split_stride, int n, int mlp) {

@@ -125,7 +125,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, f32x16 (&acc)[BM /
 #pragma unroll
         for (int j = 0; j < TN; j += 2) {
           const float gate = acc[i][j][r], up = acc[i][j + 1][r];
-          out[(j >> 1) * 32] = f2bf(gate / (1.f + __expf(-gate)) * up);
+          out[(j >> 1) * 32] = f2bf(swiglu(gate, up));
         }
       } else {
 #pragma unroll
@@ -516,7 +516,7 @@ __device__ __forceinline__ void store_fixed_up(const GemmArgs& g, const float* p
   if constexpr (EPI == EPI_SWIGLU_BF16) {
     bf16x4 o;
 #pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = f2bf(sum[i] / (1.f + __expf(-sum[i])) * up[i]);
+    for (int i = 0; i < 4; i++) o[i] = f2bf(swiglu(sum[i], up[i]));
     const int ocol = ((n0 + (c & ~63)) >> 1) + (c & 31);
     *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + ocol) = o;
   } else if constexpr (EPI == EPI_BF16) {
@@ -579,15 +579,6 @@ __device__ __forceinline__ void row_range(const GemmArgs& g, int tm, int* row0, 
   const int b0 = g.tile_blocks ? tm * g.tile_blocks : (int)((long long)tm * g.row_blocks / g.tiles_m);
   const int b1 = g.tile_blocks ? min(b0 + g.tile_blocks, g.row_blocks) : (int)((long long)(tm + 1) * g.row_blocks / g.tiles_m);
   *row0 = b0 * 32; *blocks = b1 - b0;
-}
-
-// gate / (1 + exp(-gate)) * up. The quotient by a reciprocal and a correction step: as near as the division (which takes ten
-// instructions) but for the rounding of the product. The bound keeps the correction finite where exp overflows: the reciprocal is 0 there.
-__device__ __forceinline__ float silu_mul(float gate, float up) {
-  const float d = 1.f + fminf(__expf(-gate), 1e38f);
-  float r = __builtin_amdgcn_rcpf(d);
-  r = fmaf(fmaf(-d, r, 1.f), r, r);
-  return gate * r * up;
 }
 
 template <typename F, int... P>
@@ -968,7 +959,7 @@ __device__ __forceinline__ void gemm_rows_body(const GemmArgs& g, unsigned char*
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           if constexpr (SW) {
-            o[e] = f2bf(silu_mul(acc[i][j][e], acc[i][j + 2][e]));
+            o[e] = f2bf(swiglu(acc[i][j][e], acc[i][j + 2][e]));
           } else {
             o[e] = f2bf(acc[i][j][e]);
           }

@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(NW * 64, 4) gemm_kslice_kernel(KsArgs g) {
       const f32x4 gate = sum4(row, col), up = sum4(row, COLS - 16 + col);
       bf16x4 o;
 #pragma unroll
-      for (int e = 0; e < 4; e++) o[e] = f2bf(gate[e] / (1.f + __expf(-gate[e])) * up[e]);
+      for (int e = 0; e < 4; e++) o[e] = f2bf(swiglu(gate[e], up[e]));
       *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(g.C) + (size_t)row * g.ldc + blk * 16 + col) = o;
     }
   } else {

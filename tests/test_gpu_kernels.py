@@ -144,6 +144,26 @@ def test_gemm_row_tile_heights(sts, m, k, slots):
         assert rel(sts.op_gemm(a, w, "256x256", epilogue=1, split_k=2), ref) <= 1e-5
 
 
+def test_gemm_swiglu_is_the_same_in_every_tile(sts):
+    """Gates of -100 to 100, each the product of two bf16 numbers (exact in fp32), so that every tile finishes the same sums: whole
+    tiles of all shapes and the kernel that adds up the pieces of a cut tile give the same bits, also where exp(-gate) nears the end of fp32
+    and the result is as small as 1e-36."""
+    m, n, k = 64, 1280, 1088
+    gate = np.concatenate([np.linspace(-100, 100, n - 40), np.linspace(-89, -86.5, 40)])
+    a, w = np.zeros((m, k), np.float32), np.zeros((2 * n, k), np.float32)
+    a[:, 0], a[:, 700] = np.linspace(1.0, 0.985, m), np.linspace(0.5, 2.0, m)
+    w[:n, 0], w[n:, 700] = gate, np.linspace(3.0, 4.0, n)
+    a, w = synth.to_bf16(a), synth.to_bf16(w)
+    want = sts.op_gemm(a, w, "128x128", epilogue=3)
+    g64 = a[:, :1].astype(np.float64) * w[:n, 0]
+    ref = g64 / (1 + np.exp(-g64)) * (a[:, 700:701].astype(np.float64) * w[n:, 700])
+    near = (g64 > -88.6) & (g64 < -87.4)
+    assert near.sum() > 100 and (np.abs(want - ref)[near] <= 2.0 ** -8 * np.abs(ref)[near]).all()
+    assert rel(want, ref) <= BF16_TOL
+    for cfg, slots in [("64x128", 0), ("256x256", 0), ("256x256", 3), ("256x256", 64), ("128x128", 64), ("64x256s", 0), ("64x320s", 0), ("64x512s", 0)]:
+        assert np.array_equal(sts.op_gemm(a, w, cfg, epilogue=3, tail_slots=slots), want), (cfg, slots)
+
+
 @pytest.mark.parametrize("m,k", [(40, 64), (161, 192), (256, 320), (256, 256)])
 def test_gemm_row_tiles_keep_infinities_to_their_row(sts, m, k):
     """An odd number of K tiles starts with a null tile of zero operands: it must not meet the activations, an infinity of which
