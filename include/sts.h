@@ -85,6 +85,12 @@ int sts_max_pages_per_seq_limit(int32_t page_tokens);
 int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t cus, int32_t page_tokens,
                           int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks);
 
+/* Host only, no GPU state: how the attention of a prefill batch (lens[i] new tokens over priors[i] cached ones) is laid out on a
+ * partition of `cus` CUs: work items (query tiles of 128 rows, or parts of their key range), how many of them are parts of a cut
+ * range, and query heads of a KV group per workgroup (1 or 2). The engine cuts fewer ranges where its scratch is short. */
+int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* priors, int32_t n_q, int32_t n_kv, int32_t d, int32_t cus,
+                          int32_t* items, int32_t* parts, int32_t* heads);
+
 /* Host only, no GPU state: tile configuration (STS_GEMM_*) and split along K the engine gives a decode-side GEMM of m rows
  * (one token per request), n weight rows and k columns on a partition of `cus` CUs. Up to 64 rows the GEMM streams its
  * weights once and is planned by an estimate of rounds of workgroups and bytes per CU over the 64x128 tile and the skinny tiles
@@ -273,6 +279,14 @@ int sts_op_gemm_noalloc(const void* a_dev, const void* w_dev, float* c_dev, int3
  * ceil((prior+t)/16) distinct ids < n_pool_pages). out [t, n_q, d]. */
 int sts_op_attn_prefill(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
                         int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages);
+/* The same with the form of the kernel chosen by the caller: `heads` query heads of a KV group per workgroup, 1 or 2 (2 needs d = 128
+ * and an even number of heads a group, else STS_EINVAL), 0 = as the engine would. `stale`: k and v go on for that many tokens behind the
+ * context, to the end of its last page at most -- what a freed sequence left there; the output does not depend on them.
+ * heads_taken (may be NULL): the form that ran. Both forms give the same bits unless a later score outgrows the maximum
+ * of its row's first 64 keys by more than a factor of 2^8. */
+int sts_op_attn_prefill_form(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
+                             int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages, int32_t stale,
+                             int32_t heads, int32_t* heads_taken);
 /* Decode attention: q [n, n_q, d]; request r has ctx[r] cached tokens given in k,v (concatenated
  * over requests, [sum ctx, n_kv, d]) and attends to all of them. A context is cut into
  * ceil(pages / chunk_pages) equal chunks (chunk_pages 1..64) whose partial results are merged; a

@@ -101,7 +101,6 @@ __device__ __forceinline__ void attn_prefill_head(unsigned char* smem, const bf1
   const int* bt = block_tables + sq.bt_off;
 
   const int qloc = it.q0 + wave * 32 + l32;              // row inside the chunk
-  const bool q_valid = qloc < sq.sl;
   const int qpos = sq.p + qloc;                          // absolute position (causal limit)
   const int wave_min_qpos = sq.p + it.q0 + wave * 32;
   const int wave_max_qpos = wave_min_qpos + 31;
@@ -301,6 +300,8 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_kernel(const bf16* __rest
 // product against 34). The running maximum of a row, a chain from a tile's scores to its probabilities, is replaced by a fixed reference,
 // the maximum of the row's first tile: nothing waits, and nothing is rescaled. Probabilities are then above one where later scores are
 // higher; bf16 and fp32 hold them as well as those below one, up to a reach that the end of the kernel checks.
+// Products and sums run in the order of the kernel above, and so does its reference maximum until a score outgrows it by 2^RESCALE_LOG2:
+// up to there both give the same bits.
 // 2760 cycles a tile of two heads (64 products of 32); 8192 rows of 32 heads 505 -> 450 us (1.22 PFLOP/s), 1024 over 15 000 cached ones 246 ->
 // 212, 256 over 15 000 75 -> 63, 4096 over 8000 607 -> 520. What is left beside the loop, about 11 us a workgroup, is its start (the
 // first tiles' way from memory, their scores) and its output, which no second workgroup on the CU hides.
@@ -381,7 +382,6 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   const int* bt = block_tables + sq.bt_off;
 
   const int qloc = it.q0 + wave * 32 + l32;              // row inside the chunk
-  const bool q_valid = qloc < sq.sl;
   const int qpos = sq.p + qloc;                          // absolute position (causal limit)
   const int wave_min_qpos = sq.p + it.q0 + wave * 32;
   const int wave_max_qpos = wave_min_qpos + 31;
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     for (int b = 0; b < DB; b++)
 #pragma unroll
       for (int r = 0; r < 16; r++) o[x][b][r] = 0.f;
-  float nm[2] = {0.f, 0.f}, m_ref[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+  float nm[2] = {0.f, 0.f}, m_ref[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f}, l_tile[2] = {0.f, 0.f};
   f32x16 s[2][2];                                        // scores of a tile: [head][32-key block]
   u32x4 pb[2][4];                                        // probabilities: [head][page], bf16 pairs
 #pragma unroll
@@ -467,8 +467,9 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   float y_next = 0.f, p_last = 0.f, p_even = 0.f;
   auto finish = [&](auto q_c) {
     constexpr int q = decltype(q_c)::value, kb = q / 32 ^ 1, g = q / 16 % 2, x = q / 8 % 2, e = q % 8;
-    l_run[x] += p_last;                                  // this half's keys; halves are added at the end
-    pin_f32(l_run[x]);
+    // this half's keys, tile by tile as the kernel above adds them; halves are added at the end
+    if constexpr (kb == 0 && g == 0 && e == 0) l_tile[x] = p_last; else l_tile[x] += p_last;
+    if constexpr (kb == 1 && g == 1 && e == 7) { l_run[x] += l_tile[x]; pin_f32(l_run[x]); } else pin_f32(l_tile[x]);
     if constexpr (e & 1) pb[x][2 * kb + g][e / 2] = pin_pair(p_even, p_last);
     else p_even = p_last;
   };
@@ -742,30 +743,35 @@ AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n
   return plan;
 }
 
+// Heads per workgroup of a launch whose plan is `even` or not: two need d = 128 and an even group.
+int attn_prefill_heads(bool even, int n_q, int n_kv, int d) { return even && d == 128 && (n_q / n_kv) % 2 == 0 ? 2 : 1; }
+
 // qkv: packed [rows, ld] with Q of head h at columns [h*d, (h+1)*d), already rotated.
 // out: [rows, ldo], head h at the same columns. items: query tiles (sequence, first row, key tiles, part or -1);
-// one workgroup per (item, head), or per (item, two heads of a KV group) where `even` (of the plan), d and the group allow it. merges: the query tiles whose key range was cut. part_ws: attn_prefill_part_floats(n_q, d) per part.
+// one workgroup per (item, `heads` heads of a KV group, 1 or 2: attn_prefill_heads). merges: the query tiles whose key range was cut. part_ws:
+// attn_prefill_part_floats(n_q, d) per part.
 // Requires page_tokens == 16 and d in {64, 128}.
 hipError_t attn_prefill(hipStream_t s, const bf16* qkv, int ld, bf16* out, int ldo, const PrefillSeq* seqs,
-                        const AttnItem* items, int n_items, bool even, const AttnMerge* merges, int n_merges, const int* block_tables, const bf16* pool,
+                        const AttnItem* items, int n_items, int heads, const AttnMerge* merges, int n_merges, const int* block_tables, const bf16* pool,
                         KvGeom geo, int n_q, float* part_ws) {
   if (n_items == 0) return hipSuccess;
+  if (heads < 1 || heads > attn_prefill_heads(true, n_q, geo.n_kv, geo.d)) return hipErrorInvalidValue;
   if (geo.page_tokens != 16 || n_q % geo.n_kv != 0 || (n_merges > 0 && (!merges || !part_ws))) return hipErrorInvalidValue;
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)geo.d);
   auto launch = [&](auto d_c) {
     constexpr int D = decltype(d_c)::value;
-    auto run = [&](auto* kernel, hipError_t attr, int lds, int heads) {
+    auto run = [&](auto* kernel, hipError_t attr, int lds) {
       if (attr == hipSuccess)
         hipLaunchKernelGGL(kernel, dim3((unsigned)n_items * (n_q / heads)), dim3(256), lds, s, qkv, ld, out, ldo, seqs, items, block_tables, pool, geo, n_q, scale_log2e, part_ws);
       return attr;
     };
     hipError_t e;
-    if (D == 128 && even && (n_q / geo.n_kv) % 2 == 0) {
+    if (D == 128 && heads == 2) {
       static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_pair_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, attn_pair_lds());
-      e = run(&attn_prefill_pair_kernel, attr, attn_pair_lds(), 2);
+      e = run(&attn_prefill_pair_kernel, attr, attn_pair_lds());
     } else {
       static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_prefill_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize, attn_prefill_lds<D>());
-      e = run(&attn_prefill_kernel<D>, attr, attn_prefill_lds<D>(), 1);
+      e = run(&attn_prefill_kernel<D>, attr, attn_prefill_lds<D>());
     }
     if (e != hipSuccess) return e;
     if (n_merges > 0)

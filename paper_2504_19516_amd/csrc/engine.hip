@@ -820,7 +820,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   for (int i = 0; i < n_seqs; i++) priors[i] = c->seqs[seqs[i]].len;
   const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
                                           (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
-  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size();
+  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size(), attn_heads = attn_prefill_heads(attn.even, d.n_q_heads, d.n_kv_heads, d.head_dim);
   // ---- stage metadata
   ph.meta_used = 0;
   meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
@@ -879,7 +879,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
       KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
       KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
     }
-    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, attn.even, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
+    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, attn_heads, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
     KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
     if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
     KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
@@ -1073,6 +1073,14 @@ extern "C" int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus
   const double t = plan_decode_gemm(r, m, n, k, cus, may_split != 0, partials != 0, &cfg, &splits);
   *tile_cfg = cfg; *split_k = splits;
   if (est_ns) *est_ns = (int64_t)(t * 1e9);
+  return STS_OK;
+}
+extern "C" int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* priors, int32_t n_q, int32_t n_kv, int32_t d, int32_t cus,
+                                     int32_t* items, int32_t* parts, int32_t* heads) {
+  if (n_seqs < 1 || !lens || !priors || n_q < 1 || n_kv < 1 || n_q % n_kv != 0 || (d != 64 && d != 128) || cus < 1 || !items || !parts || !heads) return STS_EINVAL;
+  for (int i = 0; i < n_seqs; i++) if (lens[i] < 1 || priors[i] < 0 || lens[i] > (1 << 24) || priors[i] > (1 << 24)) return STS_EINVAL;
+  const AttnPlan plan = attn_prefill_plan(n_seqs, lens, priors, n_q, 2 * cus, 1 << 20, 1 << 20);
+  *items = (int)plan.items.size(); *parts = plan.parts; *heads = attn_prefill_heads(plan.even, n_q, n_kv, d);
   return STS_OK;
 }
 extern "C" int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t cus, int32_t page_tokens,

@@ -118,8 +118,15 @@ extern "C" int sts_op_gemm(const float* a, const float* w, float* c_inout, int32
 
 extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
                                    int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages) {
+  return sts_op_attn_prefill_form(q, k, v, out, t, prior, n_q, n_kv, d, pages, n_pool_pages, 0, 0, nullptr);
+}
+
+extern "C" int sts_op_attn_prefill_form(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
+                                        int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages, int32_t stale,
+                                        int32_t heads, int32_t* heads_taken) {
   if (!q || !k || !v || !out || !pages || t < 1 || prior < 0 || n_q < 1 || n_kv < 1 || n_q % n_kv || (d != 64 && d != 128)) return STS_EINVAL;
   const int total = prior + t, np = (total + 15) / 16;
+  if (stale < 0 || total + stale > np * 16 || heads < 0 || heads > attn_prefill_heads(true, n_q, n_kv, d)) return STS_EINVAL;
   for (int i = 0; i < np; i++) {
     if (pages[i] < 0 || pages[i] >= n_pool_pages) return STS_EINVAL;
     for (int j = 0; j < i; j++) if (pages[j] == pages[i]) return STS_EINVAL;
@@ -128,8 +135,9 @@ extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* 
   KvGeom geo{n_kv, d, 16};
   bf16* pool = b.get<bf16>((size_t)n_pool_pages * geo.page_elems());
   int* d_bt = b.get<int>(np);
-  float* dk = b.get<float>((size_t)total * n_kv * d);
-  float* dv = b.get<float>((size_t)total * n_kv * d);
+  const size_t written = (size_t)(total + stale) * n_kv * d;
+  float* dk = b.get<float>(written);
+  float* dv = b.get<float>(written);
   bf16* dq = upload_bf16(b, q, (size_t)t * n_q * d);
   bf16* dout = b.get<bf16>((size_t)t * n_q * d);
   PrefillSeq* d_seq = b.get<PrefillSeq>(1);
@@ -143,13 +151,15 @@ extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* 
   PrefillSeq sq{0, t, prior, 0, np};
   if (hipMemset(pool, 0, (size_t)n_pool_pages * geo.page_elems() * sizeof(bf16)) != hipSuccess ||
       hipMemcpy(d_bt, pages, np * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(dk, k, (size_t)total * n_kv * d * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(dv, v, (size_t)total * n_kv * d * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(dk, k, written * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(dv, v, written * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(d_seq, &sq, sizeof(sq), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(d_items, plan.items.data(), n_items * sizeof(AttnItem), hipMemcpyHostToDevice) != hipSuccess ||
       (n_merges > 0 && hipMemcpy(d_merges, plan.merges.data(), n_merges * sizeof(AttnMerge), hipMemcpyHostToDevice) != hipSuccess)) return STS_EHIP;
-  if (kv_write_tokens(nullptr, pool, geo, d_bt, 0, total, dk, dv) != hipSuccess) return STS_EHIP;
-  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, plan.even, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
+  if (kv_write_tokens(nullptr, pool, geo, d_bt, 0, total + stale, dk, dv) != hipSuccess) return STS_EHIP;
+  if (heads == 0) heads = attn_prefill_heads(plan.even, n_q, n_kv, d);
+  if (heads_taken) *heads_taken = heads;
+  hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, heads, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
   if (e != hipSuccess) return e == hipErrorInvalidValue ? STS_EINVAL : STS_EHIP;
   int rc = download_bf16(b, out, dout, (size_t)t * n_q * d);
   if (hipDeviceSynchronize() != hipSuccess) return STS_EHIP;

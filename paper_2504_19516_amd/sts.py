@@ -91,7 +91,7 @@ EXPORTS = [
     "sts_prefill_append", "sts_prefill_launch", "sts_decode_launch", "sts_phase_done", "sts_prefill_finish",
     "sts_decode_finish", "sts_prefill_abort", "sts_decode_step", "sts_step_concurrent", "sts_last_timing", "sts_read_hidden",
     "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_kernel_name",
-    "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_decode", "sts_wave_quant",
+    "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
     "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
     "sts_profile_tile_model",
@@ -368,6 +368,19 @@ def op_attn_prefill(q, k, v, prior, pages, n_pool_pages):
     return out
 
 
+def op_attn_prefill_form(q, k, v, prior, pages, n_pool_pages, heads=0, stale=0):
+    """op_attn_prefill with `heads` query heads per workgroup (1, 2, 0 = as the engine would); k and v go on for `stale` tokens
+    behind the context. Returns (out, heads taken)."""
+    q, k, v, pages = _f32(q), _f32(k), _f32(v), _i32(pages)
+    t, n_q, d = q.shape
+    if k.shape[0] != prior + t + stale or k.shape != v.shape:
+        raise ValueError("k and v must hold prior + t + stale tokens")
+    out, taken = np.empty_like(q), C.c_int32()
+    _ck(lib().sts_op_attn_prefill_form(_p(q, C.c_float), _p(k, C.c_float), _p(v, C.c_float), _p(out, C.c_float), t, prior,
+                                       n_q, k.shape[1], d, _p(pages), n_pool_pages, stale, heads, C.byref(taken)), "sts_op_attn_prefill_form")
+    return out, taken.value
+
+
 def op_attn_decode(q, k, v, ctx, chunk_pages):
     q, k, v, ctx = _f32(q), _f32(k), _f32(v), _i32(ctx)
     n, n_q, d = q.shape
@@ -394,6 +407,14 @@ def decode_chunk_plan(n_pages, n_kv_heads, cus, page_tokens, max_pages_per_seq):
     _ck(lib().sts_decode_chunk_plan(_p(a), a.size, n_kv_heads, cus, page_tokens, max_pages_per_seq, C.byref(cp), C.byref(mc), C.byref(ac)),
         "sts_decode_chunk_plan")
     return cp.value, mc.value, ac.value
+
+
+def attn_prefill_plan(lens, priors, n_q, n_kv, d, cus):
+    """(work items, parts among them, query heads per workgroup) of a prefill batch's attention; host only."""
+    lens, priors = _i32(lens), _i32(priors)
+    it, pa, hd = C.c_int32(), C.c_int32(), C.c_int32()
+    _ck(lib().sts_attn_prefill_plan(len(lens), _p(lens), _p(priors), n_q, n_kv, d, cus, C.byref(it), C.byref(pa), C.byref(hd)), "sts_attn_prefill_plan")
+    return it.value, pa.value, hd.value
 
 
 def decode_gemm_plan(m, n, k, cus, may_split=True, partials=True, gemm_rate_256=4967, partial_bw_cu=22504, stream_bw_cu=59000,

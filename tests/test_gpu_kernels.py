@@ -277,6 +277,21 @@ def test_prefill_attention_head_pairs(sts, nq, nkv, t, prior, grow):
         assert rel(got[:, h:h + 1], ref) <= BF16_TOL, h
 
 
+@pytest.mark.parametrize("nq,nkv,t,prior", [(512, 4, 1, 767), (512, 256, 31, 738), (256, 1, 200, 650), (4, 2, 65, 1000), (2, 1, 1500, 0), (8, 2, 250, 4099), (2, 1, 1, 0),
+                                            (4, 1, 130, 63), (2, 1, 33, 95)])
+def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t, prior):
+    """Both forms of the kernel multiply and add in the same order, so a layer's output does not depend on which of them a launch takes."""
+    q = synth.normal_bf16(107, (t, nq, 128))
+    k, v = synth.normal_bf16(108, (prior + t, nkv, 128)), synth.normal_bf16(109, (prior + t, nkv, 128))
+    n_pages = (prior + t + 15) // 16
+    pages = synth.page_permutation(110, n_pages + 2)[:n_pages]
+    (one, h1), (two, h2) = (sts.op_attn_prefill_form(q, k, v, prior, pages, n_pages + 2, heads=h) for h in (1, 2))
+    assert (h1, h2) == (1, 2)
+    assert np.array_equal(one, two)
+    taken = sts.op_attn_prefill_form(q, k, v, prior, pages, n_pages + 2)
+    assert taken[1] == sts.attn_prefill_plan([t], [prior], nq, nkv, 128, 256)[2] and np.array_equal(taken[0], one)
+
+
 def test_prefill_attention_head_pairs_near_the_end_of_fp32(sts):
     """Probabilities of up to 2^40 times values of 2^100: past fp32's range with the first tile's maximum as the reference, inside it with
     one that moves."""

@@ -252,6 +252,25 @@ def test_decode_chunk_sizing_stays_within_what_the_engine_allocates(sts):
         sts.decode_chunk_plan([limit + 1], 8, 32, 16, limit)       # a context longer than the block table
 
 
+def test_attn_prefill_plan_pairs_heads_where_the_launch_is_long_and_even():
+    """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only
+    where the query tiles have 12 key tiles of 64 on average and none outlasts 5/4 of an even deal over the CUs; key ranges are cut only
+    where a few long ones leave workgroup slots empty."""
+    from paper_2504_19516_amd import sts
+    assert sts.attn_prefill_plan([8192], [0], 32, 8, 128, 256) == (64, 0, 2)
+    assert sts.attn_prefill_plan([2048], [0], 32, 8, 128, 224)[2] == 1               # the longest tile outlasts the deal
+    assert sts.attn_prefill_plan([301], [0], 32, 8, 128, 256) == (3, 0, 1)
+    assert sts.attn_prefill_plan([1024], [15000], 32, 8, 128, 256) == (16, 16, 2)    # eight ranges in two parts each
+    assert sts.attn_prefill_plan([150, 37, 260], [800, 1003, 770], 8, 2, 128, 8) == (6, 0, 2)
+    for n_q, n_kv, d in ((32, 32, 128), (24, 8, 128), (32, 8, 64)):
+        assert sts.attn_prefill_plan([8192], [0], n_q, n_kv, d, 256)[2] == 1
+    assert sts.attn_prefill_plan([750], [0], 512, 4, 128, 256)[2] == 1               # mean of 12 tiles not reached
+    for bad in (([], [], 8, 2, 128, 8), ([0], [0], 8, 2, 128, 8), ([1], [-1], 8, 2, 128, 8), ([1], [0], 8, 3, 128, 8), ([1], [0], 8, 2, 96, 8), ([1], [0], 8, 2, 128, 0)):
+        with pytest.raises(sts.StsError) as e:
+            sts.attn_prefill_plan(*bad)
+        assert e.value.code == sts.EINVAL
+
+
 def test_decode_gemm_plan_fits_tiles_to_the_partition():
     """Host logic of the decode GEMM planner (no GPU): the tile width divides N, the split stays within what the K extent
     feeds and the library accepts (at most 8 slices of at least 512 columns); a GEMM that has to finish its own output is
