@@ -381,20 +381,23 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int* bt = block_tables + sq.bt_off;
 
-  const int qloc = it.q0 + wave * 32 + l32;              // row inside the chunk
+  // Rows past the chunk are its last row once more, with that row's keys: what a page holds behind the context, left by another
+  // sequence, must not decide whether the rows are taken again (below).
+  const int row_first = it.q0 + wave * 32, row_last = sq.sl - 1;
+  const int qloc = min(row_first + l32, row_last);       // row inside the chunk
   const int qpos = sq.p + qloc;                          // absolute position (causal limit)
-  const int wave_min_qpos = sq.p + it.q0 + wave * 32;
-  const int wave_max_qpos = wave_min_qpos + 31;
+  const int wave_min_qpos = sq.p + min(row_first, row_last);
+  const int wave_max_qpos = sq.p + min(row_first + 31, row_last);
   const int k_end = sq.p + min(it.q0 + BQ, sq.sl);       // keys [0, k_end) are needed by these query rows
   const int kt_end = min(it.kt1, (k_end + BKV - 1) / BKV);
   const int wave_end = min(kt_end, wave_max_qpos / BKV + 1);                   // tiles past it are masked for all of this wave's rows
   const int last_page = min(sq.n_pages, (k_end + 15) / 16) - 1;
 
-  // Q operands of both heads (rows past the chunk repeat its last row), in accumulation registers
+  // Q operands of both heads, in accumulation registers
   bf16x8 qf[2][KSTEPS];
 #pragma unroll
   for (int x = 0; x < 2; x++) {
-    const bf16* q = qkv + (size_t)(sq.row0 + min(qloc, sq.sl - 1)) * ld + (head0 + x) * D + 8 * lh;
+    const bf16* q = qkv + (size_t)(sq.row0 + qloc) * ld + (head0 + x) * D + 8 * lh;
 #pragma unroll
     for (int j = 0; j < KSTEPS; j++) qf[x][j] = *reinterpret_cast<const bf16x8*>(q + 16 * j);
   }

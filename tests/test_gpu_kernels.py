@@ -292,6 +292,26 @@ def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t,
     assert taken[1] == sts.attn_prefill_plan([t], [prior], nq, nkv, 128, 256)[2] and np.array_equal(taken[0], one)
 
 
+@pytest.mark.parametrize("t,prior", [(1, 768), (31, 738), (200, 653), (65, 1001)])
+def test_prefill_attention_head_pairs_ignore_what_lies_behind_the_context(sts, t, prior):
+    """Scores that outgrow the first 64 keys' maximum by more than 2^8 and less than 2^60: the two forms' roundings differ, which tells
+    them apart. Keys and values that another sequence left behind the context, in the last page's free slots, must not make the paired
+    form take its rows again the other way."""
+    nq, nkv, total = 4, 2, prior + t
+    free = -total % 16
+    assert free
+    q = synth.normal_bf16(111, (t, nq, 128), 2.0)
+    k, v = synth.normal_bf16(112, (total, nkv, 128), 2.0), synth.normal_bf16(113, (total, nkv, 128))
+    k[:64] *= 2.0 ** -6
+    left_k = np.broadcast_to(np.float32(64.0) * np.sign(q[-1, ::nq // nkv]), (free, nkv, 128))
+    pages = synth.page_permutation(114, (total + 15) // 16)
+    run = lambda heads, stale, kk, vv: sts.op_attn_prefill_form(q, kk, vv, prior, pages, len(pages), heads=heads, stale=stale)[0]
+    two = run(2, 0, k, v)
+    assert not np.array_equal(two, run(1, 0, k, v))
+    ks, vs = np.concatenate([k, left_k]), np.concatenate([v, np.full((free, nkv, 128), 2.0 ** 100, np.float32)])
+    assert np.array_equal(run(2, free, ks, vs), two)
+
+
 def test_prefill_attention_head_pairs_near_the_end_of_fp32(sts):
     """Probabilities of up to 2^40 times values of 2^100: past fp32's range with the first tile's maximum as the reference, inside it with
     one that moves."""
