@@ -282,8 +282,7 @@ int sts_op_attn_prefill(const float* q, const float* k, const float* v, float* o
 /* The same with the form of the kernel chosen by the caller: `heads` query heads of a KV group per workgroup, 1 or 2 (2 needs d = 128
  * and an even number of heads a group, else STS_EINVAL), 0 = as the engine would. `stale`: k and v go on for that many tokens behind the
  * context, to the end of its last page at most -- what a freed sequence left there; the output does not depend on them.
- * heads_taken (may be NULL): the form that ran. Both forms give the same bits unless a later score outgrows the maximum
- * of its row's first 64 keys by more than a factor of 2^8. */
+ * heads_taken (may be NULL): the form that ran. Both forms give the same bits. */
 int sts_op_attn_prefill_form(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
                              int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages, int32_t stale,
                              int32_t heads, int32_t* heads_taken);

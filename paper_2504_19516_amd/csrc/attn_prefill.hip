@@ -297,13 +297,12 @@ __global__ void __launch_bounds__(256, 2) attn_prefill_kernel(const bf16* __rest
 // instruction has a fixed piece of the rest placed behind it: one probability (exponential, fused multiply-add, sum, half a conversion),
 // an LDS read, a piece of the copy of the tile after the next. A K or V^T operand read from LDS feeds two products instead of one. An LDS
 // read stands right behind a product: ahead of it, it holds up the wave's vector instructions and with them the next product (44 cycles a
-// product against 34). The running maximum of a row, a chain from a tile's scores to its probabilities, is replaced by a fixed reference,
-// the maximum of the row's first tile: nothing waits, and nothing is rescaled. Probabilities are then above one where later scores are
-// higher; bf16 and fp32 hold them as well as those below one, up to a reach that the end of the kernel checks.
-// Products and sums run in the order of the kernel above, and so does its reference maximum until a score outgrows it by 2^RESCALE_LOG2:
-// up to there both give the same bits.
-// 2760 cycles a tile of two heads (64 products of 32); 8192 rows of 32 heads 505 -> 450 us (1.22 PFLOP/s), 1024 over 15 000 cached ones 246 ->
-// 212, 256 over 15 000 75 -> 63, 4096 over 8000 607 -> 520. What is left beside the loop, about 11 us a workgroup, is its start (the
+// product against 34). The reference maximum of a row, a chain from a tile's scores to its probabilities, moves by the rule of the kernel
+// above, but the first half of a tile's probabilities is made before all of its scores are known: where a score outgrows the reference,
+// which is rare, that half is made again. Products and sums run in the order of the kernel above, so both give the same bits.
+// 8192 rows of 32 heads 521 us with one head per workgroup, 486 with two; 1024 over 15 000 cached ones 260 / 234, 256 over 15 000 84 / 76, 4096 over
+// 8000 616 / 550. A reference that never moves saved the maxima (468, 230, 75, 535) but cost precision in rows that a late key dominates:
+// there the moved one makes that key's probability exactly 1. What is left beside the loop, 5 to 6 us a workgroup, is its start (the
 // first tiles' way from memory, their scores) and its output, which no second workgroup on the CU hides.
 // o += a * b with o in accumulation registers; s = a * b + (FIRST ? 0 : s) with b in accumulation registers. In assembly so that the
 // 128 accumulators stay in place and the scores come out in the registers the vector ALUs can read.
@@ -329,6 +328,13 @@ __device__ __forceinline__ void mma32_operand_idle() {   // between a vector-ALU
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_nop 1");
 #endif
+}
+// In assembly: the compiler would first quiet the operands, which it does not know.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("v_max3_f32 %0, %0, %1, %2" : "+v"(a) : "v"(b), "v"(c));
+#endif
+  return a;
 }
 __device__ __forceinline__ void pin_f32(float& x) {      // the sum is made here, not where the compiler would sink it to
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -359,7 +365,6 @@ template <int N, typename F>
 __device__ __forceinline__ void pair_for(F&& f) { pair_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
 constexpr int PAIR_STAGES = 4;
-constexpr float PAIR_REACH = 1.15292150e18f;      // 2^60: the largest sum of a row that is taken
 constexpr int attn_pair_lds() { return AP_LDS_BASE + PAIR_STAGES * 2 * BKV * 128 * 2; }
 
 __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* __restrict__ qkv, int ld, bf16* __restrict__ out, int ldo,
@@ -488,7 +493,26 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     finish(std::integral_constant<int, (q + 63) % 64>{});
     p_last = p;
   };
+  auto first_block = [&]() {                             // the first block's probabilities but the last five
+    exponent(std::integral_constant<int, 32>{});
+    pair_for<27>([&](auto q_c) {
+      constexpr int q = 32 + decltype(q_c)::value;
+      if constexpr (q == 32) {
+        const float y = y_next;
+        exponent(std::integral_constant<int, 33>{});
+        p_last = __builtin_amdgcn_exp2f(y);
+      } else score(std::integral_constant<int, q>{});
+    });
+  };
   bf16x8 kf[4], vf[2][DB];
+  // Largest score of the tile after the one in hand, of this lane half, before the causal mask: where it does not outgrow the reference, no
+  // masked one does.
+  float mx[2];
+  const float reach = RESCALE_LOG2 * 0.999f / scale_log2e;
+  auto max_of = [&](auto x_c, auto kb_c, auto r_c) {
+    constexpr int x = decltype(x_c)::value, kb = decltype(kb_c)::value, r = decltype(r_c)::value;
+    mx[x] = max3(mx[x], s[x][kb][r], s[x][kb][r + 1]);
+  };
 
   if (it.kt0 < kt_end) {
     fetch_ids(it.kt0);
@@ -529,15 +553,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       m_ref[x] = half_swap_max(m);
       nm[x] = -m_ref[x] * scale_log2e;
     }
-    exponent(std::integral_constant<int, 32>{});
-    pair_for<27>([&](auto q_c) {
-      constexpr int q = 32 + decltype(q_c)::value;
-      if constexpr (q == 32) {
-        const float y = y_next;
-        exponent(std::integral_constant<int, 33>{});
-        p_last = __builtin_amdgcn_exp2f(y);
-      } else score(std::integral_constant<int, q>{});
-    });
+    first_block();
     if (it.kt0 + 1 < wave_end) {                         // K operands of the next tile's first steps
 #pragma unroll
       for (int j = 0; j < 2; j++) kf[j] = lds16(lds0 + ((it.kt0 + 1) % NS) * STAGE + k_slot[j]);
@@ -554,6 +570,10 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   };
   // product i of 16 of a run of scores: head 0 two steps ahead of head 1
   static constexpr int SX[16] = {0, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 1}, SJ[16] = {0, 1, 0, 2, 1, 3, 2, 4, 3, 5, 4, 6, 5, 7, 6, 7};
+  // O and scores in turns; at the end the last four of the scores first, so that the tile's maxima are known when the iteration ends. (No
+  // product of O may come later than that: the probabilities of the next tile take the place of the ones it reads.)
+  static constexpr auto is_score = [](int u) { return u < 56 ? u % 2 == 1 : u < 60; };
+  static constexpr auto number = [](int u) { return u < 56 ? u % 32 / 2 : u < 60 ? u - 44 : u - 48; };
   int kt = it.kt0;
   const bf16* page = nullptr;
   for (; kt + 1 < wave_end; kt++) {
@@ -563,7 +583,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     if (kt + 2 - ids_kt >= 64) fetch_ids(kt + 2);
     page = page_base(kt + 2);
     pair_for<64>([&](auto u_c) {
-      constexpr int u = decltype(u_c)::value, half = u / 32, i = u % 32 / 2;
+      constexpr int u = decltype(u_c)::value, half = u / 32, i = number(u);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (u == 54) {
         wait_vmem<0>();                                  // tile kt + 2 has landed
@@ -573,7 +593,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       // this wave's page of tile kt + 2
       if constexpr (u < 16 && u % 2 == 1) dma_first(std::integral_constant<int, u / 2>{}, stage);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (u % 2 == 0) product_o(std::integral_constant<int, i>{}, std::integral_constant<int, half ? 0 : 2>{});
+      if constexpr (!is_score(u)) product_o(std::integral_constant<int, i>{}, std::integral_constant<int, half ? 0 : 2>{});
       else mma32_scores<(SJ[i] == 0)>(s[SX[i]][half], kf[SJ[i] % 4], qf[SX[i]][SJ[i]]);
       __builtin_amdgcn_sched_barrier(0);
       // LDS reads: V^T operands of a page once the page before is through, K operands of a step (head 0 takes it first) five to seven
@@ -582,17 +602,21 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       if constexpr (u >= 18 && u < 26 && u % 2 == 0) vf[0][u / 2 - 9] = lds16(vst + (u / 2 - 9) * 1024);
       if constexpr (u >= 34 && u < 42 && u % 2 == 0) vf[1][u / 2 - 17] = lds16(vst + PAGE + (u / 2 - 17) * 1024);
       if constexpr (u >= 48 && u < 56 && u % 2 == 0) vf[0][u / 2 - 24] = lds16(vst + 2 * PAGE + (u / 2 - 24) * 1024);
-      // step j of a run is read where the run stands at product KU[j]: steps 0 and 1 before it begins
-      constexpr int KU[8] = {-6, -4, 1, 5, 9, 13, 17, 21};
+      // step j of a run is read where the run stands at product KU[j] (KV[j] in the second half): steps 0 and 1 before it begins
+      constexpr int KU[8] = {-6, -4, 1, 5, 9, 13, 17, 21}, KV[8] = {-6, -4, 1, 5, 9, 13, 17, 19};
       pair_for<8>([&](auto j_c) {
         constexpr int j = decltype(j_c)::value;
-        if constexpr (KU[j] + 32 == u) kf[j % 4] = lds16(kst + k_slot[j] + 2 * PAGE);                       // second block
+        if constexpr (KV[j] + 32 == u) kf[j % 4] = lds16(kst + k_slot[j] + 2 * PAGE);                       // second block
         else if constexpr (KU[j] + 64 == u) kf[j % 4] = lds16(knext + k_slot[j]);                           // the tile after, first block
         else if constexpr (KU[j] == u) kf[j % 4] = lds16(kst + k_slot[j]);
       });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (u < 16 && u % 2 == 1) dma_second(std::integral_constant<int, u / 2>{}, page);
       score(std::integral_constant<int, (u + 59) % 64>{});
+      if constexpr (u == 36) mx[0] = mx[1] = -INFINITY;
+      if constexpr (u >= 37 && u < 53) max_of(std::integral_constant<int, (u - 37) / 8>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, (u - 37) % 8 * 2>{});
+      if constexpr (u >= 60)                               // head 0, then head 1: their scores are done with u = 57 and 59
+        pair_for<4>([&](auto r_c) { max_of(std::integral_constant<int, u / 62>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, u % 2 * 8 + decltype(r_c)::value * 2>{}); });
       if constexpr (u == 31 || u == 63) {
         __builtin_amdgcn_sched_barrier(0);
         if (kt + 1 >= unmasked) {
@@ -602,6 +626,48 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       }
     });
     __builtin_amdgcn_sched_barrier(0);
+    if (__any(mx[0] - m_ref[0] > reach || mx[1] - m_ref[1] > reach)) {
+      // A score of tile kt + 1 outgrows a reference: what is left of tile kt is added, then the references move, O and the sums are
+      // scaled, and the probabilities already made of tile kt + 1 are made again.
+      float corr[2];
+      bool moved = false;
+#pragma unroll
+      for (int x = 0; x < 2; x++) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int kb = 0; kb < 2; kb++)
+#pragma unroll
+          for (int r = 0; r < 16; r++) m = fmaxf(m, s[x][kb][r]);
+        m = half_swap_max(m);
+        const bool grow = (m - m_ref[x]) * scale_log2e > RESCALE_LOG2;
+        const float m_upd = grow ? m : m_ref[x];
+        corr[x] = grow ? __builtin_amdgcn_exp2f((m_ref[x] - m_upd) * scale_log2e) : 1.f;
+        m_ref[x] = m_upd;
+        moved |= grow;
+      }
+      if (__any(moved)) {
+#pragma unroll
+        for (int b = 0; b < DB; b++) vf[1][b] = lds16(vst + 3 * PAGE + b * 1024);
+        __builtin_amdgcn_sched_barrier(0);
+        pair_for<16>([&](auto i_c) { product_o(i_c, std::integral_constant<int, 2>{}); });
+        mma32_settle();
+        pair_for<2 * DB>([&](auto q) {
+          constexpr int x = decltype(q)::value / DB, b = decltype(q)::value % DB;
+          mma32_tie_acc(o[x][b]);
+#pragma unroll
+          for (int r = 0; r < 16; r++) o[x][b][r] *= corr[x];
+          mma32_tie_acc(o[x][b]);
+        });
+#pragma unroll
+        for (int x = 0; x < 2; x++) {
+          l_run[x] *= corr[x];
+          nm[x] = -m_ref[x] * scale_log2e;
+          pb[x][2] = pb[x][3] = u32x4{0u, 0u, 0u, 0u};
+        }
+        first_block();
+        mma32_settle();
+      }
+    }
   }
   if (it.kt0 < kt_end) {                                 // what is left of the wave's last tile
     const lds_cptr vprev = lds0 + ((kt > it.kt0 ? kt - 1 : kt) % NS) * STAGE + v_lane, vst = lds0 + (kt % NS) * STAGE + v_lane;
@@ -664,10 +730,10 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     for (int x = 0; x < 2; x++)
       over += store_rows<D, bf16>(buf, lane, o[x], 1.f / l_all[x], sq.sl - row0, out + (size_t)(sq.row0 + row0) * ldo + (head0 + x) * D, ldo);
   }
-  // Scores far above the first tile's maximum show in the sum, and so does anything not finite; V may take an output past fp32's range that
-  // is inside it with a higher reference. Then the workgroup takes its query tile again, head by head, with maxima that move, and a wave
-  // writes its rows once more. After the output, so that no accumulator has to live through it (in scratch: 10 us a workgroup).
-  if (__syncthreads_or(!(l_all[0] < PAIR_REACH) || !(l_all[1] < PAIR_REACH) || over != 0.f))
+  // An infinity or a NaN in Q, K or V, times a probability of zero here and left out there, may show in other rows than above. Then the
+  // workgroup takes its query tile again, head by head, and a wave writes its rows once more. After the output, so that no
+  // accumulator has to live through it (in scratch: 10 us a workgroup).
+  if (__syncthreads_or(!(l_all[0] < INFINITY) || !(l_all[1] < INFINITY) || over != 0.f))
     for (int x = 0; x < 2; x++) {
       __syncthreads();
       attn_prefill_head<D>(smem, qkv, ld, out, ldo, sq, it, head0 + x, block_tables, pool, geo, n_q, scale_log2e, part_ws);

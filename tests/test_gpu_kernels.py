@@ -279,10 +279,14 @@ def test_prefill_attention_head_pairs(sts, nq, nkv, t, prior, grow):
 
 @pytest.mark.parametrize("nq,nkv,t,prior", [(512, 4, 1, 767), (512, 256, 31, 738), (256, 1, 200, 650), (4, 2, 65, 1000), (2, 1, 1500, 0), (8, 2, 250, 4099), (2, 1, 1, 0),
                                             (4, 1, 130, 63), (2, 1, 33, 95)])
-def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t, prior):
-    """Both forms of the kernel multiply and add in the same order, so a layer's output does not depend on which of them a launch takes."""
-    q = synth.normal_bf16(107, (t, nq, 128))
-    k, v = synth.normal_bf16(108, (prior + t, nkv, 128)), synth.normal_bf16(109, (prior + t, nkv, 128))
+@pytest.mark.parametrize("grow", [1.0, 1.7, 3.0, 8.0])
+def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t, prior, grow):
+    """Both forms of the kernel multiply and add in the same order and move a row's reference maximum at the same scores (grow: never, in a few
+    rows, in many, in all and repeatedly), so a layer's output does not depend on which of them a launch takes."""
+    q = synth.normal_bf16(107, (t, nq, 128), grow)
+    k, v = synth.normal_bf16(108, (prior + t, nkv, 128), grow), synth.normal_bf16(109, (prior + t, nkv, 128))
+    if grow == 8.0:
+        k *= np.float32(2.0) ** -(6 - np.minimum(6, np.arange(prior + t) // 90))[:, None, None]
     n_pages = (prior + t + 15) // 16
     pages = synth.page_permutation(110, n_pages + 2)[:n_pages]
     (one, h1), (two, h2) = (sts.op_attn_prefill_form(q, k, v, prior, pages, n_pages + 2, heads=h) for h in (1, 2))
@@ -294,9 +298,8 @@ def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t,
 
 @pytest.mark.parametrize("t,prior", [(1, 768), (31, 738), (200, 653), (65, 1001)])
 def test_prefill_attention_head_pairs_ignore_what_lies_behind_the_context(sts, t, prior):
-    """Scores that outgrow the first 64 keys' maximum by more than 2^8 and less than 2^60: the two forms' roundings differ, which tells
-    them apart. Keys and values that another sequence left behind the context, in the last page's free slots, must not make the paired
-    form take its rows again the other way."""
+    """Keys and values that another sequence left behind the context, in the last page's free slots, with scores far above those of the
+    context: the rows past the chunk must not see them, and no form's output depends on them."""
     nq, nkv, total = 4, 2, prior + t
     free = -total % 16
     assert free
@@ -306,10 +309,9 @@ def test_prefill_attention_head_pairs_ignore_what_lies_behind_the_context(sts, t
     left_k = np.broadcast_to(np.float32(64.0) * np.sign(q[-1, ::nq // nkv]), (free, nkv, 128))
     pages = synth.page_permutation(114, (total + 15) // 16)
     run = lambda heads, stale, kk, vv: sts.op_attn_prefill_form(q, kk, vv, prior, pages, len(pages), heads=heads, stale=stale)[0]
-    two = run(2, 0, k, v)
-    assert not np.array_equal(two, run(1, 0, k, v))
+    want = run(1, 0, k, v)
     ks, vs = np.concatenate([k, left_k]), np.concatenate([v, np.full((free, nkv, 128), 2.0 ** 100, np.float32)])
-    assert np.array_equal(run(2, free, ks, vs), two)
+    assert all((run(heads, free, ks, vs) == want).all() for heads in (1, 2))
 
 
 def test_prefill_attention_head_pairs_near_the_end_of_fp32(sts):
