@@ -20,9 +20,12 @@
 // maxima and conversions, which only a second wave on the SIMD can overlap; LDS holds two workgroups per CU. Tiles staged through
 // registers, two barriers a tile and Q read from LDS took 658 us for 8192 rows of 32 heads (0.84 PFLOP/s), this form 505 (1.09); 2048
 // rows on 224 CUs 68 -> 54, 301 rows 14.2 -> 10.4. Where a launch has only one workgroup per CU (1024 new tokens over 15 000 cached
-// ones: 256) long key ranges are cut into parts (attn_prefill_plan), at the price of fp32 partial outputs. Launches of long and even key
+// ones: 256) long key ranges are cut into parts (attn_prefill_plan), at the price of fp32 partial outputs. Launches of many and long
 // ranges take two heads of a KV group in one workgroup (attn_prefill_pair_kernel).
 #include <algorithm>
+#include <functional>
+#include <numeric>
+#include <queue>
 #include <utility>
 
 #include "kernels.h"
@@ -781,11 +784,28 @@ size_t attn_prefill_part_floats(int n_q, int d) { return (size_t)n_q * BQ * (d +
 // are cut only where a few long ones leave slots empty: 1024 new tokens over 15 000 cached ones, 32 heads on 256 CUs, two parts
 // (406 -> 274 + 10 us a layer); a 2048-token prompt or 8192 rows on their own are not. At most `max_extra` items more than query tiles and
 // `max_parts` parts.
-// `even` says that two heads per workgroup, one workgroup per CU, is the faster form: the longest key range is at most 5/4 of an even deal
-// over the CUs (a pair takes twice a head's time, and a CU that has one has nothing else), and the mean is at least 12 tiles (what a
-// workgroup spends beside its tiles is hidden by nothing). One head / two heads per workgroup, 32 heads on 256 CUs, us:
-// longest / even deal 0.5 505 / 445, 0.97 142 / 121, 1.05 107 / 94, 1.18 80 / 79, 1.48 57 / 53, 1.52 62 / 65, 1.88 48 / 52, 2.3 62 / 67;
-// mean tiles 2 42 / 55, 3 51 / 61, 5 68 / 71, 9 between 50 / 49 and 104 / 96, 9.3 in ragged prompts level, 16 100 / 65, 17 79 / 71.
+// `pairs` says that two heads per workgroup is estimated the faster form. In units of a CU's time for 64 keys of two heads: pairs, one
+// workgroup per CU, take the busiest CU's tiles and 3 units beside them for each workgroup, which nothing hides; single heads,
+// two workgroups per CU, 1.12 times the mean of an even deal and the busiest slot's tiles (a workgroup that is alone on its CU runs faster),
+// and 3 units. Measured one / two heads per workgroup, us, 32 heads (estimated quotient of two and one in brackets):
+// 256 CUs: 8192 rows 521 / 486 (0.92), 4096 147 / 132 (0.93), 3000 86 / 85 (0.99), 2048 50 / 57 (1.14), 1024 over 15 000 cached 260 / 234 (0.91), over 4000
+// 92 / 89 (0.94), over 2000 66 / 76 (1.21), 8 x 512 over 700 86 / 81 (0.97), 4 x 2048 150 / 157 (1.01), 3 x 1500 73 / 81 (1.09), six ragged prompts 53 / 58
+// (1.09). 224 CUs: 8192 547 / 532 (0.94), 1024 over 15 000 334 / 356 (1.14: 256 workgroups), 8 x 512 over 700 92 / 97 (1.10). 64 CUs: 8192 1481 / 1434 (0.93), 2048
+// 114 / 125 (1.01), 1024 over 15 000 741 / 631 (0.90), 4 x 2048 454 / 469 (1.04). The faster form in all 34 launches measured.
+// Tiles of the busiest of `slots` slots where `n` workgroups of each item, of its tiles and `extra` units, go to the slot that is free first.
+static double busiest_slot(const std::vector<AttnItem>& items, int n, int slots, double extra) {
+  const int same = std::gcd(n, slots);               // so many slots and workgroups of an item at a time do alike
+  std::priority_queue<double, std::vector<double>, std::greater<double>> free_at(std::greater<double>(), std::vector<double>(slots / same, 0.0));
+  double end = 0.0;
+  for (const AttnItem& it : items)
+    for (int i = 0; i < n / same; i++) {
+      const double t = free_at.top() + (it.kt1 - it.kt0) + extra;
+      free_at.pop();
+      free_at.push(t);
+      end = std::max(end, t);
+    }
+  return end;
+}
 AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n_q, int slots, int max_extra, long long max_parts) {
   AttnPlan plan;
   struct Tile { int seq, q0, tiles; };
@@ -805,15 +825,15 @@ AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n
     if (parts > 1) { plan.merges.push_back(AttnMerge{t.seq, t.q0, plan.parts, parts}); plan.parts += parts; max_extra -= parts - 1; }
   }
   std::stable_sort(plan.items.begin(), plan.items.end(), [](const AttnItem& a, const AttnItem& b) { return a.kt1 - a.kt0 > b.kt1 - b.kt0; });
-  if (!plan.items.empty()) {
-    const int longest = plan.items[0].kt1 - plan.items[0].kt0;
-    plan.even = total >= 12 * (long long)plan.items.size() && longest <= 1.25 * ((double)total * n_q / std::max(1, slots));
+  if (n_q % 2 == 0 && slots >= 2) {
+    const double deal = (double)total * n_q / slots;
+    plan.pairs = busiest_slot(plan.items, n_q / 2, slots / 2, 3.0) < 1.12 * (0.5 * (deal + busiest_slot(plan.items, n_q, slots, 0.0)) + 3.0);
   }
   return plan;
 }
 
-// Heads per workgroup of a launch whose plan is `even` or not: two need d = 128 and an even group.
-int attn_prefill_heads(bool even, int n_q, int n_kv, int d) { return even && d == 128 && (n_q / n_kv) % 2 == 0 ? 2 : 1; }
+// Heads per workgroup of a launch whose plan wants `pairs` or not: two need d = 128 and an even group.
+int attn_prefill_heads(bool pairs, int n_q, int n_kv, int d) { return pairs && d == 128 && (n_q / n_kv) % 2 == 0 ? 2 : 1; }
 
 // qkv: packed [rows, ld] with Q of head h at columns [h*d, (h+1)*d), already rotated.
 // out: [rows, ldo], head h at the same columns. items: query tiles (sequence, first row, key tiles, part or -1);

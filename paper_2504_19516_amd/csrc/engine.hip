@@ -820,7 +820,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   for (int i = 0; i < n_seqs; i++) priors[i] = c->seqs[seqs[i]].len;
   const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
                                           (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
-  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size(), attn_heads = attn_prefill_heads(attn.even, d.n_q_heads, d.n_kv_heads, d.head_dim);
+  const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size(), attn_heads = attn_prefill_heads(attn.pairs, d.n_q_heads, d.n_kv_heads, d.head_dim);
   // ---- stage metadata
   ph.meta_used = 0;
   meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
@@ -1080,7 +1080,7 @@ extern "C" int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const 
   if (n_seqs < 1 || !lens || !priors || n_q < 1 || n_kv < 1 || n_q % n_kv != 0 || (d != 64 && d != 128) || cus < 1 || !items || !parts || !heads) return STS_EINVAL;
   for (int i = 0; i < n_seqs; i++) if (lens[i] < 1 || priors[i] < 0 || lens[i] > (1 << 24) || priors[i] > (1 << 24)) return STS_EINVAL;
   const AttnPlan plan = attn_prefill_plan(n_seqs, lens, priors, n_q, 2 * cus, 1 << 20, 1 << 20);
-  *items = (int)plan.items.size(); *parts = plan.parts; *heads = attn_prefill_heads(plan.even, n_q, n_kv, d);
+  *items = (int)plan.items.size(); *parts = plan.parts; *heads = attn_prefill_heads(plan.pairs, n_q, n_kv, d);
   return STS_OK;
 }
 extern "C" int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t cus, int32_t page_tokens,

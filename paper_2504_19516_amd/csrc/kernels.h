@@ -129,9 +129,9 @@ hipError_t attn_prefill(hipStream_t s, const bf16* qkv, int ld, bf16* out, int l
                         const AttnItem* items, int n_items, int heads, const AttnMerge* merges, int n_merges, const int* block_tables, const bf16* pool,
                         KvGeom geo, int n_q, float* part_ws);
 int attn_prefill_tile_q();
-struct AttnPlan { std::vector<AttnItem> items; std::vector<AttnMerge> merges; int parts = 0; bool even = false; };
+struct AttnPlan { std::vector<AttnItem> items; std::vector<AttnMerge> merges; int parts = 0; bool pairs = false; };
 AttnPlan attn_prefill_plan(int n_seqs, const int* lens, const int* priors, int n_q, int slots, int max_extra, long long max_parts);
-int attn_prefill_heads(bool even, int n_q, int n_kv, int d);
+int attn_prefill_heads(bool pairs, int n_q, int n_kv, int d);
 size_t attn_prefill_part_floats(int n_q, int d);   // of one part
 size_t attn_decode_ws_floats(int n, int n_q, int d, int max_chunks);
 hipError_t attn_decode(hipStream_t s, const bf16* q, bf16* out, const DecodeSeq* seqs, const DecodeItem* items, int n_items, const DecodeMerge* multi, int n_multi,

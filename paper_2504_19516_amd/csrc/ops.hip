@@ -157,7 +157,7 @@ extern "C" int sts_op_attn_prefill_form(const float* q, const float* k, const fl
       hipMemcpy(d_items, plan.items.data(), n_items * sizeof(AttnItem), hipMemcpyHostToDevice) != hipSuccess ||
       (n_merges > 0 && hipMemcpy(d_merges, plan.merges.data(), n_merges * sizeof(AttnMerge), hipMemcpyHostToDevice) != hipSuccess)) return STS_EHIP;
   if (kv_write_tokens(nullptr, pool, geo, d_bt, 0, total + stale, dk, dv) != hipSuccess) return STS_EHIP;
-  if (heads == 0) heads = attn_prefill_heads(plan.even, n_q, n_kv, d);
+  if (heads == 0) heads = attn_prefill_heads(plan.pairs, n_q, n_kv, d);
   if (heads_taken) *heads_taken = heads;
   hipError_t e = attn_prefill(nullptr, dq, n_q * d, dout, n_q * d, d_seq, d_items, n_items, heads, d_merges, n_merges, d_bt, pool, geo, n_q, part_ws);
   if (e != hipSuccess) return e == hipErrorInvalidValue ? STS_EINVAL : STS_EHIP;

@@ -252,19 +252,22 @@ def test_decode_chunk_sizing_stays_within_what_the_engine_allocates(sts):
         sts.decode_chunk_plan([limit + 1], 8, 32, 16, limit)       # a context longer than the block table
 
 
-def test_attn_prefill_plan_pairs_heads_where_the_launch_is_long_and_even():
-    """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only
-    where the query tiles have 12 key tiles of 64 on average and none outlasts 5/4 of an even deal over the CUs; key ranges are cut only
-    where a few long ones leave workgroup slots empty."""
+def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
+    """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only where
+    its whole workgroups on single CUs come out before the one-head form: the launches whose two forms were timed against each
+    other. Key ranges are cut only where a few long ones leave workgroup slots empty."""
     from paper_2504_19516_amd import sts
-    assert sts.attn_prefill_plan([8192], [0], 32, 8, 128, 256) == (64, 0, 2)
-    assert sts.attn_prefill_plan([2048], [0], 32, 8, 128, 224)[2] == 1               # the longest tile outlasts the deal
-    assert sts.attn_prefill_plan([301], [0], 32, 8, 128, 256) == (3, 0, 1)
-    assert sts.attn_prefill_plan([1024], [15000], 32, 8, 128, 256) == (16, 16, 2)    # eight ranges in two parts each
-    assert sts.attn_prefill_plan([150, 37, 260], [800, 1003, 770], 8, 2, 128, 8) == (6, 0, 2)
-    for n_q, n_kv, d in ((32, 32, 128), (24, 8, 128), (32, 8, 64)):
+    two = [([8192], [0], 256), ([4096], [0], 256), ([1024], [15000], 256), ([256], [15000], 256), ([4096], [8000], 256), ([1024], [4000], 256),
+           ([512] * 8, [700] * 8, 256), ([256] * 16, [1500] * 16, 256), ([8192], [0], 224), ([8192], [0], 64), ([1024], [15000], 64), ([1024], [2000], 64)]
+    one = [([2048], [0], 256), ([1024], [2000], 256), ([512], [3000], 256), ([2048], [1000], 256), ([613, 97, 1201, 35, 744, 1290], [0] * 6, 256), ([1024] * 6, [0] * 6, 256),
+           ([1500] * 3, [0] * 3, 256), ([2048], [0], 224), ([1024], [15000], 224), ([512] * 8, [700] * 8, 224), ([2048], [0], 64), ([2048] * 4, [0] * 4, 64), ([301], [0], 256)]
+    assert all(sts.attn_prefill_plan(n, p, 32, 8, 128, c)[2] == 2 for n, p, c in two)
+    assert all(sts.attn_prefill_plan(n, p, 32, 8, 128, c)[2] == 1 for n, p, c in one)
+    for n_q, n_kv, d in ((32, 32, 128), (24, 8, 128), (32, 8, 64), (3, 1, 128)):
         assert sts.attn_prefill_plan([8192], [0], n_q, n_kv, d, 256)[2] == 1
-    assert sts.attn_prefill_plan([750], [0], 512, 4, 128, 256)[2] == 1               # mean of 12 tiles not reached
+    assert sts.attn_prefill_plan([8192], [0], 32, 8, 128, 256)[:2] == (64, 0)
+    assert sts.attn_prefill_plan([1024], [15000], 32, 8, 128, 256)[:2] == (16, 16)   # eight ranges in two parts each
+    assert sts.attn_prefill_plan([1], [0], 1, 1, 128, 1) == (1, 0, 1)
     for bad in (([], [], 8, 2, 128, 8), ([0], [0], 8, 2, 128, 8), ([1], [-1], 8, 2, 128, 8), ([1], [0], 8, 3, 128, 8), ([1], [0], 8, 2, 96, 8), ([1], [0], 8, 2, 128, 0)):
         with pytest.raises(sts.StsError) as e:
             sts.attn_prefill_plan(*bad)
