@@ -624,6 +624,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
         __builtin_amdgcn_sched_barrier(0);
         if (kt + 1 >= unmasked) {
           mma32_settle();
+          pair_for<2>([&](auto x_c) { mma32_tie(s[decltype(x_c)::value][u / 32]); });
           mask(std::integral_constant<int, u / 32>{}, kt + 1);
         }
       }
