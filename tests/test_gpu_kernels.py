@@ -296,6 +296,24 @@ def test_prefill_attention_head_pairs_give_the_bits_of_one_head(sts, nq, nkv, t,
     assert taken[1] == sts.attn_prefill_plan([t], [prior], nq, nkv, 128, 256)[2] and np.array_equal(taken[0], one)
 
 
+@pytest.mark.parametrize("where", ["v_first", "v_late", "v_last", "k_first", "k_late", "k_minus", "q", "nan_v", "nan_k", "nan_q"])
+@pytest.mark.parametrize("t,prior", [(130, 700), (250, 4099)])
+def test_prefill_attention_head_pairs_with_infinities(sts, t, prior, where):
+    """An infinity or a NaN in Q, K or V: the paired form multiplies probabilities of zero with values that the one-head form leaves out, so
+    it hands such a workgroup to the one-head code. Same outputs as that, NaN for NaN; and rows that see none are finite."""
+    nq, nkv, total = 4, 2, prior + t
+    q = synth.normal_bf16(115, (t, nq, 128))
+    k, v = synth.normal_bf16(116, (total, nkv, 128)), synth.normal_bf16(117, (total, nkv, 128))
+    bad = np.nan if "nan" in where else -np.inf if where == "k_minus" else np.inf
+    row = {"v_first": 3, "v_late": 601, "v_last": total - 1, "k_first": 70, "k_late": 601, "k_minus": 5, "nan_v": 601, "nan_k": 601}.get(where)
+    x = {"v": v, "k": k, "q": q}[where.replace("nan_", "")[0]]
+    x[t - 7 if x is q else row, 0, 11] = bad
+    pages = synth.page_permutation(118, (total + 15) // 16)
+    one, two = (sts.op_attn_prefill_form(q, k, v, prior, pages, len(pages), heads=h)[0] for h in (1, 2))
+    assert np.array_equal(one, two, equal_nan=True)
+    assert np.isfinite(two[:, 2:]).all() and not np.isfinite(two).all()      # the other KV group
+
+
 @pytest.mark.parametrize("t,prior", [(1, 768), (31, 738), (200, 653), (65, 1001)])
 def test_prefill_attention_head_pairs_ignore_what_lies_behind_the_context(sts, t, prior):
     """Keys and values that another sequence left behind the context, in the last page's free slots, with scores far above those of the

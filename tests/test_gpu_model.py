@@ -795,6 +795,30 @@ def test_qkv_tiles_rotate_and_append_as_the_separate_kernel(sts, nq, nkv, d, cus
     eng.close()
 
 
+def test_ragged_prefill_batch_takes_paired_heads(sts):
+    """A batch of chunks over long contexts that ends inside pages and query tiles: on 8 CUs its attention takes two heads per workgroup,
+    on 256 CUs one. Same logits, same cached K and V of the layer behind it, and a decode step goes on from there."""
+    desc = synth.ModelDesc(2, 1024, 8, 2, 128, 512, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    lens, priors = [150, 37, 260], [1400, 1203, 1370]
+    assert [sts.attn_prefill_plan(lens, priors, 8, 2, 128, c)[1:] for c in (8, 256)] == [(0, 2), (0, 1)]
+    eng = new_engine(sts, desc, weight_seed=83, kv_pool_pages=512, max_prefill_tokens=1024, max_pages_per_seq=128)
+    tok, out = [synth.tokens(840 + i, n, desc.vocab) for i, n in enumerate(lens)], []
+    for cus in (8, 256):
+        eng.set_partition(cus, 256)
+        seqs = [eng.seq_create() for _ in lens]
+        for i, (s, p) in enumerate(zip(seqs, priors)):
+            eng.kv_fill_random(s, p, 850 + i)
+        logits = np.stack([np.asarray(x).reshape(-1) for x in eng.prefill_batch(seqs, tok)])
+        kv = [np.concatenate([np.ravel(x) for x in eng.kv_read(1, s, p, n)]) for s, p, n in zip(seqs, priors, lens)]
+        nxt, _ = eng.decode_step(seqs, [1, 2, 3])
+        out.append((logits, kv, np.asarray(nxt)))
+        free_all(eng, seqs)
+    (la, ka, da), (lb, kb, db) = out
+    assert rel(la, lb) <= TOL and rel(da, db) <= TOL
+    assert all(rel(x, y) <= TOL for x, y in zip(ka, kb))
+    eng.close()
+
+
 def test_rotated_keys_are_rounded_alike_by_every_kernel(sts):
     """Cached K of prefill (8192 tokens) and of decode steps (16 steps of 224 requests, and of 8: the split and the finishing
     GEMM form) against the documented rounding, bit by bit: bf16(fma(a, c, -(b s))) and bf16(fma(b, c, a s)) of the bf16
