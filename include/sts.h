@@ -205,6 +205,10 @@ enum { STS_K_EMBED = 0, STS_K_NORM, STS_K_QKV, STS_K_ROPE, STS_K_ATTN, STS_K_ATT
 int sts_kernel_timing(sts_ctx* ctx, int32_t on);
 int sts_kernel_times(sts_ctx* ctx, int32_t phase, int64_t* ns /*[STS_K_COUNT]*/, int64_t* launches /*[STS_K_COUNT]*/, int32_t reset);
 const char* sts_kernel_name(int32_t kind);
+/* For tests of failure handling: after `after` further kernel launches of a phase (0 = prefill, 1 = decode) one is not queued but
+ * reported as failed (STS_EHIP), once. -1: none. A step that fails so, or by a real HIP error, has nothing in flight when it returns, leaves
+ * every sequence's length as it was, and drops a layer-sliced prefill batch as sts_prefill_abort does. */
+int sts_fail_launch(sts_ctx* ctx, int32_t phase, int32_t after);
 /* Copy-kernel bandwidth on `cus` CUs of a phase's partition side (0 = prefill side, 1 = decode
  * side): the memory-copy probe of Section 3.2.2. Moves `bytes` (read + written = 2*bytes) per
  * iteration; returns device ns for `iters` iterations. */

@@ -80,6 +80,7 @@ struct Phase {
   // per-kernel timing
   std::vector<hipEvent_t> kev; std::vector<int> kkind; size_t kused = 0;
   int64_t kns[STS_K_COUNT] = {0}, kcnt[STS_K_COUNT] = {0};
+  int fail_after = -1;                        // sts_fail_launch: launches until one is reported as failed, -1: none
 };
 
 }  // namespace
@@ -199,6 +200,7 @@ int select_streams(sts_ctx* c) {
 
 // ---- per-kernel timing
 int k_begin(sts_ctx* c, Phase& ph, int kind) {
+  if (ph.fail_after >= 0 && ph.fail_after-- == 0) { g_hip_err = (int)hipErrorLaunchFailure; return STS_EHIP; }
   if (!c->ktiming) return STS_OK;
   if (ph.kused + 2 > ph.kev.size()) {
     for (int i = 0; i < 256; i++) { hipEvent_t e; HIPCK(hipEventCreate(&e)); ph.kev.push_back(e); }
@@ -457,6 +459,13 @@ hipError_t wait_stream(hipStream_t st) {
 bool valid_seq(sts_ctx* c, int s) { return s >= 0 && s < (int)c->seqs.size() && c->seqs[s].used; }
 
 // Make `seq` own enough pages for n_tokens; caller holds no lock.
+// After a failure between the launches of a step: waits for those already queued, whose metadata the next call rewrites, and
+// forgets their timing events.
+void drop_queued(Phase& ph) {
+  if (ph.stream) (void)wait_stream(ph.stream);
+  ph.kkind.clear(); ph.kused = 0;
+}
+
 int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {   // (seq, tokens)
   std::lock_guard<std::mutex> g(c->alloc_mu);
   size_t need = 0;
@@ -554,8 +563,8 @@ int prefill_validate(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t*
   return STS_OK;
 }
 
-// Queues a validated slice whose pages are reserved. A failure in here (a HIP error) leaves the
-// batch description as it was before the call.
+// Queues a validated slice whose pages are reserved. A failure in here (a HIP error) leaves nothing of it in flight and drops the
+// batch: the residual stream of its rows is neither that of this slice's beginning nor of its end.
 struct DecodeRun;
 int prefill_launch_checked(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
                            int lb, int le, bool want_logits, DecodeRun* beside = nullptr);
@@ -580,9 +589,9 @@ int prefill_launch_checked(sts_ctx* c, int n_seqs, const int32_t* seqs, const in
     c->pf_seqs.assign(seqs, seqs + n_seqs); c->pf_lens.assign(lens, lens + n_seqs);
   }
   const int rc = prefill_launch_body(c, n_seqs, seqs, lens, tokens, lb, le, want_logits, beside);
-  if (rc != STS_OK && lb == 0) {                             // the batch never started: later prefills are not blocked
-    std::lock_guard<std::mutex> g(c->state_mu);
-    c->pf_active = false; c->pf_seqs.clear(); c->pf_lens.clear();
+  if (rc != STS_OK) {
+    drop_queued(c->ph[0]);
+    (void)sts_prefill_abort(c);
   }
   return rc;
 }
@@ -673,6 +682,7 @@ struct DecodeRun {
   int finish_queue() {                                       // what is left
     while (rc == STS_OK && layer < c->d.n_layers) turn();
     if (rc == STS_OK) rc = end();
+    if (rc != STS_OK) drop_queued(c->ph[1]);
     return rc;
   }
 };
@@ -1390,22 +1400,21 @@ extern "C" int sts_step_concurrent(sts_ctx* c, int32_t n_pseqs, const int32_t* p
   DecodeRun run{c, dseqs, dtokens, n_decode, dlogits != nullptr, dnext != nullptr};
   int rc = STS_OK;
   if (n_pseqs > 0) rc = prefill_launch_checked(c, n_pseqs, pseqs, plens, ptokens, lb, le, plogits != nullptr, n_decode > 0 ? &run : nullptr);
-  const bool prefill_queued = n_pseqs > 0 && rc == STS_OK;
-  const int64_t t1 = now_ns();
+  const bool prefill_failed = rc != STS_OK;
   if (rc == STS_OK && n_decode > 0) rc = run.finish_queue();
-  const int64_t t2 = now_ns();
+  const int64_t t1 = now_ns();
   if (rc != STS_OK) {
-    // only a HIP failure can get here; what is queued already is waited for and dropped
-    if (n_decode > 0 && run.layer >= 0) { (void)wait_stream(c->ph[1].stream); (void)k_collect(c, c->ph[1]); }
-    if (prefill_queued) { (void)wait_stream(c->ph[0].stream); (void)k_collect(c, c->ph[0]); (void)sts_prefill_abort(c); }
+    // only a HIP failure can get here; the phase that failed has dropped its own part, what the other one has queued is dropped with it
+    if (prefill_failed) { if (n_decode > 0) drop_queued(c->ph[1]); }
+    else if (n_pseqs > 0) { drop_queued(c->ph[0]); (void)sts_prefill_abort(c); }
     return rc;
   }
   if (n_pseqs > 0) STSCK(prefill_finish(c, n_pseqs, pseqs, plens, le, plogits));
-  const int64_t t3 = now_ns();
+  const int64_t t2 = now_ns();
   if (n_decode > 0) STSCK(decode_finish(c, dseqs, n_decode, dlogits, dnext));
   c->last_wall_ns = now_ns() - t0;
-  if (getenv("STS_PROF")) fprintf(stderr, "[sts prof] prefill_enqueue %lld decode_enqueue %lld prefill_wait %lld decode_finish %lld us\n",
-                                  (long long)(t1 - t0) / 1000, (long long)(t2 - t1) / 1000, (long long)(t3 - t2) / 1000, (long long)(now_ns() - t3) / 1000);
+  if (getenv("STS_PROF")) fprintf(stderr, "[sts prof] enqueue %lld prefill_wait %lld decode_finish %lld us\n",
+                                  (long long)(t1 - t0) / 1000, (long long)(t2 - t1) / 1000, (long long)(now_ns() - t2) / 1000);
   return STS_OK;
 }
 extern "C" int sts_last_timing(sts_ctx* c, int64_t* prefill_ns, int64_t* decode_ns, int64_t* wall_ns) {
@@ -1468,6 +1477,11 @@ extern "C" int sts_get_partition(sts_ctx* c, int32_t* prefill_cus, int32_t* deco
 extern "C" int sts_kernel_timing(sts_ctx* c, int32_t on) {
   if (!c) return STS_EINVAL;
   c->ktiming = on != 0;
+  return STS_OK;
+}
+extern "C" int sts_fail_launch(sts_ctx* c, int32_t phase, int32_t after) {
+  if (!c || phase < 0 || phase > 1 || after < -1) return STS_EINVAL;
+  c->ph[phase].fail_after = after;
   return STS_OK;
 }
 extern "C" int sts_kernel_times(sts_ctx* c, int32_t phase, int64_t* ns, int64_t* launches, int32_t reset) {

@@ -90,7 +90,7 @@ EXPORTS = [
     "sts_seq_get_block_table", "sts_kv_write", "sts_kv_read", "sts_kv_fill_random", "sts_prefill_batch",
     "sts_prefill_append", "sts_prefill_launch", "sts_decode_launch", "sts_phase_done", "sts_prefill_finish",
     "sts_decode_finish", "sts_prefill_abort", "sts_decode_step", "sts_step_concurrent", "sts_last_timing", "sts_read_hidden",
-    "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_kernel_name",
+    "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_fail_launch", "sts_kernel_name",
     "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
     "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
@@ -267,6 +267,10 @@ class Engine:
 
     def prefill_abort(self):
         _ck(lib().sts_prefill_abort(self._ctx), "sts_prefill_abort")
+
+    def fail_launch(self, phase, after):
+        """For tests: the launch after `after` further ones of the phase is reported as failed and not queued."""
+        _ck(lib().sts_fail_launch(self._ctx, phase, after), "sts_fail_launch")
 
     def decode_step(self, seqs, in_tokens, want_logits=True, want_next=True):
         seqs, toks = _i32(seqs), _i32(in_tokens)

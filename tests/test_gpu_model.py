@@ -819,6 +819,50 @@ def test_ragged_prefill_batch_takes_paired_heads(sts):
     eng.close()
 
 
+@pytest.mark.parametrize("phase,after", [(0, 0), (0, 1), (0, 9), (0, 12), (1, 0), (1, 1), (1, 8), (1, 13)])
+def test_step_that_fails_between_its_launches(sts, phase, after):
+    """A launch of either phase fails while both are queued in turns: nothing is left in flight, no timing event is left over, lengths are as
+    before, a layer-sliced batch is dropped wherever it failed, and the next step gives what it would have given."""
+    desc = synth.ModelDesc(3, 512, 8, 2, 64, 512, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=84)
+    eng.set_partition(128, 128)
+    tok, dtok = synth.tokens(861, 150, desc.vocab), synth.tokens(862, 5, desc.vocab)
+    dseqs, ctx = [eng.seq_create() for _ in range(5)], [40, 17, 1, 64, 33]
+    for i, (s, n) in enumerate(zip(dseqs, ctx)):
+        eng.kv_fill_random(s, n, 863 + i)
+    pseq = eng.seq_create()
+    eng.kv_fill_random(pseq, 21, 870)
+
+    def step(lb, le):
+        out = eng.step_concurrent([pseq], [tok], lb, le, dseqs, dtok)
+        for s, n in zip(dseqs, ctx):
+            eng.seq_truncate(s, n)
+        return out
+    want = step(0, 3)
+    eng.seq_truncate(pseq, 21)
+    eng.kernel_timing(True)
+    eng.kernel_times(0, reset=True), eng.kernel_times(1, reset=True)
+    for lb, le in ((0, 3), (1, 3)):
+        if lb:
+            step(0, lb)
+            eng.kernel_times(0, reset=True), eng.kernel_times(1, reset=True)
+        eng.fail_launch(phase, after)
+        with pytest.raises(sts.StsError) as e:
+            eng.step_concurrent([pseq], [tok], lb, le, dseqs, dtok)
+        assert e.value.code == sts.EHIP
+        assert [eng.seq_length(s) for s in (pseq, *dseqs)] == [21, *ctx]
+        got = step(0, 3)                                       # STS_ESTATE if the batch were still there
+        assert all(np.array_equal(a, b) for a, b in zip(got, want))
+        assert all(eng.kernel_times(p, reset=True)["attn"][1] == 3 for p in (0, 1))
+        eng.seq_truncate(pseq, 21)
+    eng.fail_launch(phase, 2)
+    with pytest.raises(sts.StsError) as e:
+        eng.prefill_batch([pseq], [tok]) if phase == 0 else eng.decode_step(dseqs, dtok)
+    assert e.value.code == sts.EHIP and all(not eng.kernel_times(p, reset=True) for p in (0, 1))
+    assert np.array_equal(step(0, 3)[0], want[0])
+    eng.close()
+
+
 def test_rotated_keys_are_rounded_alike_by_every_kernel(sts):
     """Cached K of prefill (8192 tokens) and of decode steps (16 steps of 224 requests, and of 8: the split and the finishing
     GEMM form) against the documented rounding, bit by bit: bf16(fma(a, c, -(b s))) and bf16(fma(b, c, a s)) of the bf16
