@@ -144,6 +144,18 @@ def test_gemm_row_tile_heights(sts, m, k, slots):
         assert rel(sts.op_gemm(a, w, "256x256", epilogue=1, split_k=2), ref) <= 1e-5
 
 
+@pytest.mark.parametrize("m", [65, 96, 97, 129, 200, 225, 256, 300])
+@pytest.mark.parametrize("k,split", [(1088, 2), (1600, 3), (1024, 4), (4096, 6), (4096, 8), (640, 1)])
+def test_gemm_tiles_give_the_same_bits_for_the_same_slices(sts, m, k, split):
+    """Decode batches above 64 rows take 128x128 tiles or 256-column row tiles of any height for the slices the planner decided on: the matrix
+    instructions, the order along K and the null tile of an odd number of K tiles must not show in the sums."""
+    a, w = synth.normal_bf16(76, (m, k)), synth.normal_bf16(77, (512, k), 0.05)
+    want = sts.op_gemm(a, w, "128x128", epilogue=1, split_k=split)
+    for cfg in ("256x256", "128x256"):
+        assert (sts.op_gemm(a, w, cfg, epilogue=1, split_k=split) == want).all(), cfg
+    assert rel(want, T.op_linear(a.astype(np.float64), w.astype(np.float64))) <= 1e-5
+
+
 def test_gemm_swiglu_is_the_same_in_every_tile(sts):
     """Gates of -100 to 100, each the product of two bf16 numbers (exact in fp32), so that every tile finishes the same sums: whole
     tiles of all shapes and the kernel that adds up the pieces of a cut tile give the same bits, also where exp(-gate) nears the end of fp32
