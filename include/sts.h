@@ -95,7 +95,9 @@ int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* pr
  * (one token per request), n weight rows and k columns on a partition of `cus` CUs. Up to 64 rows the GEMM streams its
  * weights once and is planned by an estimate of rounds of workgroups and bytes per CU over the 64x128 tile and the skinny tiles
  * whose width divides n (Section 2.1: decode is bound by memory bandwidth; Section 3.2.1: what a partition can pull grows with
- * its CUs only up to a point); above that it takes a prefill tile shape. may_split: a split along K is allowed (its fp32 partial
+ * its CUs only up to a point); above that it takes a prefill tile shape: the split is planned for one, and a layer's GEMM that leaves
+ * partial sums then takes 128x128 or 256x256 tiles (these in row tiles of any height) for the same slices, whichever is estimated
+ * faster, here with 128x128 tiles at 0.757 of gemm_rate_256 (sts_decode_layer_plan: with both rates of a ctx's tile model). may_split: a split along K is allowed (its fp32 partial
  * sums are reduced by the caller's next kernel); partials: the output leaves as fp32 partial sums even when unsplit (0 = the
  * GEMM's own epilogue finishes it, as the fused SwiGLU of an unsplit gate/up GEMM does). gemm_rate_256 and partial_bw_cu: the
  * tile model's values (see sts_set_tile_model); stream_bw_cu and stream_bw_gpu: the stream model's (sts_set_stream_model).
@@ -103,6 +105,11 @@ int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* pr
 int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus, int32_t may_split, int32_t partials, int64_t gemm_rate_256,
                          int64_t partial_bw_cu, int64_t stream_bw_cu, int64_t stream_bw_gpu, int32_t* tile_cfg, int32_t* split_k,
                          int64_t* est_ns);
+
+/* The same of the four GEMMs of a layer -- QKV, O, gate/up, down -- as the engine will run a decode step of `batch` requests on `cus` CUs
+ * with the ctx's tile and stream models. tile_cfg -1: the form that cuts K inside the workgroups and finishes its own output (few
+ * rows). row_tiles: row tiles of a 256x256 launch, 0 = as few as 256 rows allow. Arrays of 4. */
+int sts_decode_layer_plan(sts_ctx* ctx, int32_t batch, int32_t cus, int32_t* tile_cfg, int32_t* split_k, int32_t* row_tiles);
 
 /* Weights. `name`: "emb", "lm" (layer ignored), "wq","wk","wv","wo","wg","wu","wd" (matrices,
  * row-major [out_features, in_features] fp32, rounded to bf16 on upload) or "g1","g2","gf"

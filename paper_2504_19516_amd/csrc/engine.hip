@@ -400,10 +400,10 @@ struct DecodeGemm { int cfg = 0, splits = 1, row_tiles = 0; };
 struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu, down; };
 // More than 64 rows: the tiles for the slices that pick_decode_gemm decided on -- 128x128, or 256 columns with the rows in any number of
 // row tiles, whichever takes the least estimated time. The slices stay, and with them the order of the sums: every shape gives the same
-// bits. Estimate: rounds of workgroups at the tile's rate, and 8 us for the first loads and the partial sums of a launch. Measured / estimated
-// at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
+// bits. Estimate: rounds of workgroups at the tile's rate; the first loads and the partial sums of a launch, 8 us, are much the same for all
+// shapes and left out. Measured / estimated (with the 8 us) at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
 // slices 21 / 20 in one, 16 / 16 in two; 4096 x 14336 48 / 51 and 39 / 36; 28672 x 4096 in 2 slices 58 / 57 in one row tile.
-void pick_tall_tiles(const sts_ctx* ctx, int m, int n, int k, int cus, DecodeGemm* g) {
+void pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, int cus, DecodeGemm* g) {
   if (m <= 64 || n % 256 != 0) return;
   const int c = std::max(cus, 8), ksteps = k / 64, len = (ksteps + g->splits - 1) / g->splits * 64, blocks = (m + 31) / 32;
   double best = 1e300;
@@ -411,8 +411,8 @@ void pick_tall_tiles(const sts_ctx* ctx, int m, int n, int k, int cus, DecodeGem
     const double t = (double)((wgs + slots - 1) / slots) * tile_s;
     if (t < best) { best = t; g->cfg = cfg; g->row_tiles = row_tiles; }
   };
-  consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (ctx->rate_128 * 1e12 / 2));
-  const double tall_s = 2.0 * 256 * 256 * len / (ctx->rate_256 * 1e12);
+  consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (rate_128 * 1e12 / 2));
+  const double tall_s = 2.0 * 256 * 256 * len / (rate_256 * 1e12);
   const int least = (blocks + 7) / 8;
   for (int t = least; t <= std::min(blocks, 2 * least + 2); t++)
     consider(GEMM_256x256, t, (long long)t * (n / 256) * g->splits, c, TILE_HEIGHT_COST[(blocks + t - 1) / t - 1] * tall_s);
@@ -430,10 +430,11 @@ DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
   const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
   if (can_fuse && (t_fused <= t_split || p.gu.splits == 1)) { p.gu_fused = true; p.gu = fused; }
   t += (p.gu_fused ? t_fused : t_split) + 3 * SMALL_KERNEL_S;
-  pick_tall_tiles(ctx, n, ctx->qkvn, d.hidden, cus, &p.qkv);
-  pick_tall_tiles(ctx, n, d.hidden, ctx->qd, cus, &p.o);
-  pick_tall_tiles(ctx, n, d.hidden, d.mlp, cus, &p.down);
-  if (!p.gu_fused) pick_tall_tiles(ctx, n, 2 * d.mlp, d.hidden, cus, &p.gu);
+  auto tall = [&](int gn, int gk, DecodeGemm* g) { pick_tall_tiles(ctx->rate_128, ctx->rate_256, n, gn, gk, cus, g); };
+  tall(ctx->qkvn, d.hidden, &p.qkv);
+  tall(d.hidden, ctx->qd, &p.o);
+  tall(d.hidden, d.mlp, &p.down);
+  if (!p.gu_fused) tall(2 * d.mlp, d.hidden, &p.gu);
   if (n <= KSLICE_MAX_ROWS)
     p.kslice = kslice_time(ctx, KS_QKV, n, ctx->qkvn, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, ctx->qd, cus) +
                kslice_time(ctx, KS_SWIGLU, n, 2 * d.mlp, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, d.mlp, cus) < t;
@@ -1081,8 +1082,17 @@ extern "C" int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus
   int cfg = 0, splits = 1;
   const StreamRates r{gemm_rate_256 * 1e-3, partial_bw_cu * 1e6, stream_bw_cu * 1e6, stream_bw_gpu * 1e6};
   const double t = plan_decode_gemm(r, m, n, k, cus, may_split != 0, partials != 0, &cfg, &splits);
-  *tile_cfg = cfg; *split_k = splits;
+  DecodeGemm g{cfg, splits, 0};
+  if (partials) pick_tall_tiles(0.757 * r.rate_256, r.rate_256, m, n, k, cus, &g);
+  *tile_cfg = g.cfg; *split_k = splits;
   if (est_ns) *est_ns = (int64_t)(t * 1e9);
+  return STS_OK;
+}
+extern "C" int sts_decode_layer_plan(sts_ctx* c, int32_t batch, int32_t cus, int32_t* tile_cfg, int32_t* split_k, int32_t* row_tiles) {
+  if (!c || batch < 1 || batch > c->p.max_decode_batch || cus < 8 || cus > c->n_cu || cus % 8 != 0 || !tile_cfg || !split_k || !row_tiles) return STS_EINVAL;
+  const DecodePlan p = decode_layer_plan(c, batch, cus);
+  const DecodeGemm g[4] = {p.qkv, p.o, p.gu, p.down};
+  for (int i = 0; i < 4; i++) { tile_cfg[i] = p.kslice ? -1 : g[i].cfg; split_k[i] = p.kslice ? 1 : g[i].splits; row_tiles[i] = p.kslice ? 0 : g[i].row_tiles; }
   return STS_OK;
 }
 extern "C" int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* priors, int32_t n_q, int32_t n_kv, int32_t d, int32_t cus,

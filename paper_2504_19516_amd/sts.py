@@ -93,7 +93,7 @@ EXPORTS = [
     "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_fail_launch", "sts_kernel_name",
     "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
-    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
+    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
     "sts_profile_tile_model",
 ]
 
@@ -267,6 +267,13 @@ class Engine:
 
     def prefill_abort(self):
         _ck(lib().sts_prefill_abort(self._ctx), "sts_prefill_abort")
+
+    def decode_layer_plan(self, batch, cus):
+        """(tile configuration name or "kslice", split along K, row tiles) of a layer's QKV, O, gate/up and down GEMM in a decode step."""
+        cfg, sp, rt = np.empty(4, np.int32), np.empty(4, np.int32), np.empty(4, np.int32)
+        _ck(lib().sts_decode_layer_plan(self._ctx, batch, cus, _p(cfg), _p(sp), _p(rt)), "sts_decode_layer_plan")
+        name = {v: k for k, v in GEMM_CFGS.items()}
+        return [(name.get(int(c), "kslice"), int(s), int(r)) for c, s, r in zip(cfg, sp, rt)]
 
     def fail_launch(self, phase, after):
         """For tests: the launch after `after` further ones of the phase is reported as failed and not queued."""

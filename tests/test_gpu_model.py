@@ -713,6 +713,34 @@ def many_requests(sts):
     eng.close()
 
 
+def test_decode_gemm_plan_is_what_the_engine_runs(sts):
+    """The host-only planner of one GEMM against the plan of a decode step's layer, with the rates of a profile: split, and tile shape below
+    and above 64 rows."""
+    p = sts.Profile(path=os.path.join(os.path.dirname(sts.__file__), "data", "mi355x_llama8b.profile"))
+    r128, r256, _, _, part = p.tile_model()
+    assert abs(r128 / r256 - 0.757) < 5e-4
+    cu, gpu = p.stream_model()
+    desc = synth.ModelDesc(1, 4096, 32, 8, 128, 14336, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=85, max_decode_batch=256, max_seqs=8)
+    eng.set_tile_model(*p.tile_model())
+    eng.set_stream_model(cu, gpu)
+    seen = set()
+    for cus in (8, 32, 64, 128, 256):
+        for n in (24, 64, 65, 96, 128, 129, 200, 223, 256):
+            plan = eng.decode_layer_plan(n, cus)
+            for (cfg, split, rows), (gn, gk) in zip(plan, ((6144, 4096), (4096, 4096), (28672, 4096), (4096, 14336))):
+                whole = gn == 28672 and split == 1 and n <= 64                   # gate/up that finishes its own output
+                want = sts.decode_gemm_plan(n, gn, gk, cus, not whole, not whole, r256, part, cu, gpu)
+                assert (cfg, split) == want[:2], (n, cus, gn, gk)
+                if n > 64:
+                    if cfg == "256x256":
+                        seen.add((n, cus))
+                    assert (rows > 0) == (cfg == "256x256") and rows * 256 >= (n if rows else 0)
+    assert len(seen) > 20
+    assert all(g == ("kslice", 1, 0) for g in eng.decode_layer_plan(1, 256))
+    eng.close()
+
+
 @pytest.mark.parametrize("cus", [256, 32])
 @pytest.mark.parametrize("n", [65, 96, 97, 128, 129, 224, 225, 256])
 def test_decode_gemm_tiles_above_64_rows(many_requests, n, cus):

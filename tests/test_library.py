@@ -305,6 +305,9 @@ def test_decode_gemm_plan_fits_tiles_to_the_partition():
     t32, t256 = sts.decode_gemm_plan(64, 28672, 4096, 32)[2], sts.decode_gemm_plan(64, 28672, 4096, 256)[2]
     assert t32 > 2.5 * t256 and t256 >= 2 * 28672 * 4096 / 5.5e12 * 1e9
     assert sts.decode_gemm_plan(200, 28672, 4096, 32)[0] in ("128x128", "256x256")
+    # what the engine takes there: measured at 223 rows on 256 CUs, one row tile of QKV and gate/up is faster than 128x128
+    assert [sts.decode_gemm_plan(223, n, k, 256)[:2] for n, k in ((6144, 4096), (28672, 4096), (4096, 14336))] == [("256x256", 6), ("256x256", 2), ("256x256", 8)]
+    assert sts.decode_gemm_plan(223, 1024 + 128, 4096, 256)[0] == "128x128"       # no whole 256-column tiles
     # the estimate follows the measured stream rates it is given: half the per-CU rate doubles a small partition's time,
     # and a whole GPU is held to the memory system's rate
     slow = sts.decode_gemm_plan(64, 28672, 4096, 32, stream_bw_cu=29500)[2]
