@@ -832,6 +832,10 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   const AttnPlan attn = attn_prefill_plan(n_seqs, lens, priors.data(), d.n_q_heads, 2 * ph.cus, ph.max_attn_extra,
                                           (long long)(ph.tail_ws_bytes / sizeof(float) / attn_prefill_part_floats(d.n_q_heads, d.head_dim)));
   const int n_items = (int)attn.items.size(), n_merges = (int)attn.merges.size(), attn_heads = attn_prefill_heads(attn.pairs, d.n_q_heads, d.n_kv_heads, d.head_dim);
+  auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
+  const int h = d.hidden;
+  const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
+  const bool qkv_places = g_qkv.cfg == GEMM_256x256;         // the QKV tiles write K and V to the rows' places themselves
   // ---- stage metadata
   ph.meta_used = 0;
   meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
@@ -841,7 +845,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   meta_take(ph, &h_merges, &d_merges, n_merges);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, lb == 0 ? rows : 0);
   meta_take(ph, &ph.h_pos, &ph.d_pos, lb == 0 ? rows : 0);
-  meta_take(ph, &ph.h_place, &ph.d_place, rows);
+  meta_take(ph, &ph.h_place, &ph.d_place, qkv_places ? rows : 0);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n_seqs; i++) bt_entries += c->seqs[seqs[i]].pages.size();
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
@@ -854,7 +858,10 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     bt_off += (int)s.pages.size();
     ph.h_rows[i] = r0 + lens[i] - 1;
     for (int j = 0; lb == 0 && j < lens[i]; j++) ph.h_pos[r0 + j] = s.len + j;
-    for (int j = 0; j < lens[i]; j++) ph.h_place[r0 + j] = s.pages[(s.len + j) / c->geo.page_tokens] * c->geo.page_tokens + (s.len + j) % c->geo.page_tokens;
+    for (int j = 0, pt = c->geo.page_tokens; qkv_places && j < lens[i];) {   // a page's slots follow each other
+      const int slot = (s.len + j) % pt, end = std::min(j + pt - slot, lens[i]);
+      for (int place = s.pages[(s.len + j) / pt] * pt + slot; j < end; j++) ph.h_place[r0 + j] = place++;
+    }
     r0 += lens[i];
   }
   std::memcpy(ph.h_items, attn.items.data(), n_items * sizeof(AttnItem));
@@ -862,7 +869,6 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   hipStream_t st = ph.stream;
   HIPCK(hipEventRecord(ph.ev0, st));
   if (lb == 0) std::memcpy(ph.h_tokens, tokens, rows * sizeof(int));
-  const int h = d.hidden;
   const bool fused_embed = lb == 0 && h <= 8192;             // the embedding kernel also writes layer 0's normalised rows
   const MetaCopy meta{ph.h_meta, ph.d_meta, (int)ph.meta_used};
   // few rows: the embedding kernel reads tokens and positions from host memory itself and copies the metadata on the side
@@ -876,14 +882,12 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     KL(ph, STS_K_ROPE, row_rotation(st, rot, rows));
   }
   if (beside) beside->turn();
-  auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
-  const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
   bool normed = fused_embed;                                 // Xn holds this layer's input already
   for (int l = lb; l < le; l++) {
     const LayerW& w = c->layers[l];
     ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
     if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
-    if (g_qkv.cfg == GEMM_256x256) {
+    if (qkv_places) {
       const QkvOut out{ph.rot, ph.d_place, layer_pool(c, l), c->geo, d.n_q_heads};
       KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_QKV, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h, nullptr, &out));
     } else {
