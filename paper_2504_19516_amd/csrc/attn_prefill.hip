@@ -26,7 +26,6 @@
 #include <functional>
 #include <numeric>
 #include <queue>
-#include <utility>
 
 #include "kernels.h"
 
@@ -362,11 +361,6 @@ __device__ __forceinline__ void mma32_tie_acc(f32x16& s) {
   asm volatile("" : "+a"(s));
 #endif
 }
-template <typename F, int... P>
-__device__ __forceinline__ void pair_for_impl(F&& f, std::integer_sequence<int, P...>) { (f(std::integral_constant<int, P>{}), ...); }
-template <int N, typename F>
-__device__ __forceinline__ void pair_for(F&& f) { pair_for_impl(f, std::make_integer_sequence<int, N>{}); }
-
 constexpr int PAIR_STAGES = 4;
 constexpr int attn_pair_lds() { return AP_LDS_BASE + PAIR_STAGES * 2 * BKV * 128 * 2; }
 
@@ -498,7 +492,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   };
   auto first_block = [&]() {                             // the first block's probabilities but the last five
     exponent(std::integral_constant<int, 32>{});
-    pair_for<27>([&](auto q_c) {
+    static_for<27>([&](auto q_c) {
       constexpr int q = 32 + decltype(q_c)::value;
       if constexpr (q == 32) {
         const float y = y_next;
@@ -521,7 +515,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     fetch_ids(it.kt0);
     for (int i = 0; i < 2; i++) {
       const bf16* page = page_base(it.kt0 + i);
-      pair_for<LOADS>([&](auto j_c) {
+      static_for<LOADS>([&](auto j_c) {
         dma_first(j_c, dma_base + ((it.kt0 + i) % NS) * STAGE);
         dma_m0_idle();
         dma_second(j_c, page);
@@ -532,7 +526,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     __builtin_amdgcn_sched_barrier(0);
     // the first one's scores, the reference maxima and the first block's probabilities but the last five
     const lds_cptr kst = lds0 + (it.kt0 % NS) * STAGE, vst = kst + v_lane;
-    pair_for<KSTEPS>([&](auto j_c) {
+    static_for<KSTEPS>([&](auto j_c) {
       constexpr int j = decltype(j_c)::value;
 #pragma unroll
       for (int kb = 0; kb < 2; kb++) kf[kb] = lds16(kst + k_slot[j] + kb * 2 * PAGE);
@@ -544,7 +538,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
 #pragma unroll
     for (int b = 0; b < DB; b++) vf[0][b] = lds16(vst + 2 * PAGE + b * 1024);
     mma32_settle();
-    pair_for<4>([&](auto q) { mma32_tie(s[decltype(q)::value / 2][decltype(q)::value % 2]); });
+    static_for<4>([&](auto q) { mma32_tie(s[decltype(q)::value / 2][decltype(q)::value % 2]); });
     if (it.kt0 >= unmasked) { mask(std::integral_constant<int, 0>{}, it.kt0); mask(std::integral_constant<int, 1>{}, it.kt0); }
 #pragma unroll
     for (int x = 0; x < 2; x++) {
@@ -585,7 +579,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     const unsigned stage = dma_base + ((kt + 2) % NS) * STAGE;
     if (kt + 2 - ids_kt >= 64) fetch_ids(kt + 2);
     page = page_base(kt + 2);
-    pair_for<64>([&](auto u_c) {
+    static_for<64>([&](auto u_c) {
       constexpr int u = decltype(u_c)::value, half = u / 32, i = number(u);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (u == 54) {
@@ -607,7 +601,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       if constexpr (u >= 48 && u < 56 && u % 2 == 0) vf[0][u / 2 - 24] = lds16(vst + 2 * PAGE + (u / 2 - 24) * 1024);
       // step j of a run is read where the run stands at product KU[j] (KV[j] in the second half): steps 0 and 1 before it begins
       constexpr int KU[8] = {-6, -4, 1, 5, 9, 13, 17, 21}, KV[8] = {-6, -4, 1, 5, 9, 13, 17, 19};
-      pair_for<8>([&](auto j_c) {
+      static_for<8>([&](auto j_c) {
         constexpr int j = decltype(j_c)::value;
         if constexpr (KV[j] + 32 == u) kf[j % 4] = lds16(kst + k_slot[j] + 2 * PAGE);                       // second block
         else if constexpr (KU[j] + 64 == u) kf[j % 4] = lds16(knext + k_slot[j]);                           // the tile after, first block
@@ -619,12 +613,12 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       if constexpr (u == 36) mx[0] = mx[1] = -INFINITY;
       if constexpr (u >= 37 && u < 53) max_of(std::integral_constant<int, (u - 37) / 8>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, (u - 37) % 8 * 2>{});
       if constexpr (u >= 60)                               // head 0, then head 1: their scores are done with u = 57 and 59
-        pair_for<4>([&](auto r_c) { max_of(std::integral_constant<int, u / 62>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, u % 2 * 8 + decltype(r_c)::value * 2>{}); });
+        static_for<4>([&](auto r_c) { max_of(std::integral_constant<int, u / 62>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, u % 2 * 8 + decltype(r_c)::value * 2>{}); });
       if constexpr (u == 31 || u == 63) {
         __builtin_amdgcn_sched_barrier(0);
         if (kt + 1 >= unmasked) {
           mma32_settle();
-          pair_for<2>([&](auto x_c) { mma32_tie(s[decltype(x_c)::value][u / 32]); });
+          static_for<2>([&](auto x_c) { mma32_tie(s[decltype(x_c)::value][u / 32]); });
           mask(std::integral_constant<int, u / 32>{}, kt + 1);
         }
       }
@@ -653,9 +647,9 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
 #pragma unroll
         for (int b = 0; b < DB; b++) vf[1][b] = lds16(vst + 3 * PAGE + b * 1024);
         __builtin_amdgcn_sched_barrier(0);
-        pair_for<16>([&](auto i_c) { product_o(i_c, std::integral_constant<int, 2>{}); });
+        static_for<16>([&](auto i_c) { product_o(i_c, std::integral_constant<int, 2>{}); });
         mma32_settle();
-        pair_for<2 * DB>([&](auto q) {
+        static_for<2 * DB>([&](auto q) {
           constexpr int x = decltype(q)::value / DB, b = decltype(q)::value % DB;
           mma32_tie_acc(o[x][b]);
 #pragma unroll
@@ -675,7 +669,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   }
   if (it.kt0 < kt_end) {                                 // what is left of the wave's last tile
     const lds_cptr vprev = lds0 + ((kt > it.kt0 ? kt - 1 : kt) % NS) * STAGE + v_lane, vst = lds0 + (kt % NS) * STAGE + v_lane;
-    pair_for<16>([&](auto u_c) {
+    static_for<16>([&](auto u_c) {
       constexpr int u = decltype(u_c)::value;
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (u < 4) vf[1][u] = lds16(vprev + 3 * PAGE + u * 1024);
@@ -684,7 +678,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       __builtin_amdgcn_sched_barrier(0);
       score(std::integral_constant<int, (u + 59) % 64>{});
     });
-    pair_for<21>([&](auto t_c) { score(std::integral_constant<int, 11 + decltype(t_c)::value>{}); });
+    static_for<21>([&](auto t_c) { score(std::integral_constant<int, 11 + decltype(t_c)::value>{}); });
     finish(std::integral_constant<int, 31>{});
 #pragma unroll
     for (int h = 0; h < 2; h++) {
@@ -694,7 +688,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
         for (int b = 0; b < DB; b++) vf[g][b] = lds16(vst + (2 * h + g) * PAGE + b * 1024);
       __builtin_amdgcn_sched_barrier(0);
       mma32_operand_idle();
-      pair_for<16>([&](auto i_c) { if (h == 0) product_o(i_c, std::integral_constant<int, 0>{}); else product_o(i_c, std::integral_constant<int, 2>{}); });
+      static_for<16>([&](auto i_c) { if (h == 0) product_o(i_c, std::integral_constant<int, 0>{}); else product_o(i_c, std::integral_constant<int, 2>{}); });
       __builtin_amdgcn_sched_barrier(0);
     }
     kt++;
@@ -702,7 +696,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   for (kt = kt - 1; kt + 1 < kt_end; kt++) {             // nothing left for this wave's rows: its pages for the others
     if (kt + 2 - ids_kt >= 64) fetch_ids(kt + 2);
     page = page_base(kt + 2);
-    pair_for<LOADS>([&](auto j_c) {
+    static_for<LOADS>([&](auto j_c) {
       dma_first(j_c, dma_base + ((kt + 2) % NS) * STAGE);
       dma_m0_idle();
       dma_second(j_c, page);
@@ -712,7 +706,7 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   }
   wait_vmem<0>();                                        // pieces on their way to LDS
   mma32_settle();
-  pair_for<2 * DB>([&](auto q) { mma32_tie_acc(o[decltype(q)::value / DB][decltype(q)::value % DB]); });
+  static_for<2 * DB>([&](auto q) { mma32_tie_acc(o[decltype(q)::value / DB][decltype(q)::value % DB]); });
 
   float l_all[2];
 #pragma unroll

@@ -581,11 +581,6 @@ __device__ __forceinline__ void row_range(const GemmArgs& g, int tm, int* row0, 
   *row0 = b0 * 32; *blocks = b1 - b0;
 }
 
-template <typename F, int... P>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, P...>) { (f(std::integral_constant<int, P>{}), ...); }
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
-
 // One product of the 256-column tiles. Written in assembly so that the sum stays where it is: left to itself the compiler gives
 // the result a register quad of its own and copies 256 accumulators per K tile. AG: the sum lives in an accumulation register.
 template <bool AG>
