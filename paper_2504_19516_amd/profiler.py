@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import os
 import threading
 import time
 
@@ -177,6 +178,15 @@ class Profiler:
         self.hw["stream_bw_cu"], self.hw["stream_bw_gpu"] = int(per_cu), int(max(whole, per_cu))
         log(f"read-only stream: {per_cu / 1e3:.1f} GB/s per CU on {small} CUs, {whole / 1e6:.2f} TB/s on {self.n_cu} CUs")
         self.eng.set_stream_model(self.hw["stream_bw_cu"], self.hw["stream_bw_gpu"])
+
+    def keep_rates(self, profile):
+        """Takes the tile and stream rates of an earlier profile in place of those just measured: GEMM plans follow them, and with the
+        plans the order of sums along K. A profile measured again on changed kernels keeps them unless plans are to change."""
+        tile = ("gemm_rate_128", "gemm_rate_256", "gemm_rate_128x256", "gemm_fixed_128x256", "partial_bw_cu")
+        self.hw.update(zip(tile, profile.tile_model()))
+        self.hw.update(zip(("stream_bw_cu", "stream_bw_gpu"), profile.stream_model()))
+        self.eng.set_tile_model(*profile.tile_model())
+        self.eng.set_stream_model(*profile.stream_model())
 
     def sweep_contention(self, dms=(32, 64, 128, 192), sls=(0, 2048, 8192), log=print):
         vals = [[int(self.corun_copy_bw(dm, sl)) for sl in sls] for dm in dms]
@@ -371,6 +381,7 @@ def main():
     ap.add_argument("--vocab", type=int, default=128256)
     ap.add_argument("--out", required=True)
     ap.add_argument("--report", default=None)
+    ap.add_argument("--keep-rates", default=None, metavar="PROFILE", help="keep this profile's tile and stream rates")
     args = ap.parse_args()
     desc = {"8b": synth.llama8b_model, "70b": synth.llama70b_model}.get(args.model, None)
     desc = desc(args.layers, args.vocab) if desc else synth.tiny_model()
@@ -382,6 +393,9 @@ def main():
 
     pr = Profiler(desc)
     pr.sweep_hardware(log)
+    if args.keep_rates:
+        pr.keep_rates(sts.Profile(path=args.keep_rates))
+        log(f"tile and stream rates kept from {os.path.basename(args.keep_rates)}")
     pr.sweep_contention(log=log)
     pr.sweep_prefill_corun(log=log)
     pr.calibrate_prefill(log=log)
