@@ -251,10 +251,12 @@ int pick_cfg(int m, int n, int k, int cus) {
 // per CU, the 256-column tiles one; rate_256 is that of the tallest. The latter come in heights of 32 to 256 rows: the rows
 // are dealt to any number of row tiles, so that they fill whole waves of workgroups.
 struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; };
-// Time of a 256-column tile of 32 (h + 1) rows against one of 256. Measured on 256 CUs at K = 4096 and 14336, weights from HBM and
-// from the memory-side cache; the mean (a short tile still streams its 256 columns of weights): 0.50 / 0.41 / 0.28 at 32 rows,
-// 0.68 / 0.56 / 0.53 at 128, 0.81 / 0.76 / 0.76 at 192. It serves smaller partitions too: on 32 to 256 CUs, 96 to 4096 rows, the choice made
-// with it is within 3 % of the fastest candidate in 259 of 288 launches.
+// Time of a 256-column tile of 32 (h + 1) rows against one of 256 (a short tile still streams its 256 columns of weights). Measured inside a
+// layer on 256 CUs at heights 32 / 64 / 96 / 128 / 160 / 192 / 224: 16 row tiles of 4096 x 4096 0.41 / 0.47 / 0.52 / 0.60 / 0.70 / 0.76 / 0.88, of 4096 x
+// 14336 0.42 / 0.48 / 0.52 / 0.59 / 0.67 / 0.77 / 0.88; two of 28672 x 4096, which wait for their weights, 0.54 / 0.66 / 0.72 / 0.77 / 0.83 / 0.88 / 0.93. It
+// serves smaller partitions too: on 32 to 256 CUs, 96 to 4096 rows, the choice made with it and with the profiles' rates is within
+// 3 % of the fastest candidate in 243 of 288 launches, within 8 % in 268; the worst, 14336-deep tiles of 256 rows on 32 CUs, takes 184 us for 142
+// because those rates are of slower tiles (4.97 TFLOP/s per CU for 5.52 now). They stay because they also decide where K is cut.
 constexpr double TILE_HEIGHT_COST[8] = {0.40, 0.43, 0.52, 0.59, 0.70, 0.78, 0.91, 1.0};
 PrefillGemm pick_prefill_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, size_t tail_ws_bytes) {
   PrefillGemm best;

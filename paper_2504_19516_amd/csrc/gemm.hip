@@ -563,8 +563,9 @@ __global__ void __launch_bounds__(256) gemm_tail_fixup(GemmArgs g) {
 // cycles; with the reads and loads of four row blocks in a run 2670, with eight waves of 32 columns, whose LDS reads are
 // twice as many, 68 % busy. The clock falls as the matrix cores get busier (1.7 GHz at 256 rows on a full GPU: power), so the rate gains
 // less than the cycles. Against eight waves, 256 CUs: 8192 x 28672 x 4096 1424 -> 1263 us (1.52 PFLOP/s), 8192 x 4096 x 14336 756 -> 657, 3980 x 28672 x
-// 4096 730 -> 638, 700 x 57344 x 8192 588 -> 513; two row tiles of 28672 x 4096 at heights 32 / 96 / 128 / 160 / 192 / 256: 36 / 48 / 59 / 74 / 84 / 109 us
-// before, 36 / 43 / 49 / 63 / 73 / 93 now. The W block is the first operand, so a lane holds four consecutive output columns: fp32
+// 4096 730 -> 638, 700 x 57344 x 8192 588 -> 513; two row tiles of 28672 x 4096 at heights 32 / 96 / 128 / 160 / 192 / 256, launched over and over with the
+// weights in the memory-side cache: 36 / 48 / 59 / 74 / 84 / 109 us before, 36 / 43 / 49 / 63 / 73 / 93 now. Inside a layer, weights from HBM, 51 / 69 / 73 / 79 /
+// 84 / 95: up to about 160 rows such a launch waits for its weights, and 301 rows gained 1 us of 79. The W block is the first operand, so a lane holds four consecutive output columns: fp32
 // results leave in 16-byte pieces. The 32 x 32 x 16 instruction gives the same bits but moves twice the accumulator registers per
 // product, which costs clock.
 //
