@@ -271,9 +271,9 @@ def test_prefill_attention_cuts_long_key_ranges(sts, nq, nkv, d, t, prior):
 @pytest.mark.parametrize("nq,nkv,t,prior", [(512, 4, 1, 767), (512, 256, 31, 738), (256, 1, 200, 650), (512, 4, 65, 1000), (128, 4, 1500, 0), (128, 2, 250, 4099)])
 @pytest.mark.parametrize("grow", [1.0, 8.0])
 def test_prefill_attention_head_pairs(sts, nq, nkv, t, prior, grow):
-    """Even launches of long key ranges take two heads of a group per workgroup. Key ranges that end at and around a tile's and a page's
-    end, waves with fewer tiles than others, rows past the chunk, one group per pair and many, a range in parts; and (grow 8) scores that
-    outgrow the first tile's maximum past the kernel's reach, which it then takes with maxima that move."""
+    """Two heads of a group per workgroup. Key ranges that end at and around a tile's and a page's end, waves with fewer tiles than others,
+    rows past the chunk, one group per pair and many, a range in parts; and (grow 8) scores that outgrow the first tile's maximum, with which
+    the reference moves."""
     q = synth.normal_bf16(101, (t, nq, 128), grow)
     k = synth.normal_bf16(102, (prior + t, nkv, 128), grow)
     v = synth.normal_bf16(103, (prior + t, nkv, 128))
@@ -281,8 +281,8 @@ def test_prefill_attention_head_pairs(sts, nq, nkv, t, prior, grow):
         k[:64] *= 2.0 ** -6
     n_pages = (prior + t + 15) // 16
     pages = synth.page_permutation(104, n_pages + 2)[:n_pages]
-    got = sts.op_attn_prefill(q, k, v, prior, pages, n_pages + 2)
-    assert np.isfinite(got).all()
+    got, heads = sts.op_attn_prefill_form(q, k, v, prior, pages, n_pages + 2, heads=2)
+    assert heads == 2 and np.isfinite(got).all()
     for h in (0, 1, nq // 2 - 1, nq - 2, nq - 1):
         g = h // (nq // nkv)
         ref = T.op_causal_attention(*(x.astype(np.float64) for x in (q[:, h:h + 1], k[:, g:g + 1], v[:, g:g + 1])), prior)
@@ -345,14 +345,14 @@ def test_prefill_attention_head_pairs_ignore_what_lies_behind_the_context(sts, t
 
 
 def test_prefill_attention_head_pairs_near_the_end_of_fp32(sts):
-    """Probabilities of up to 2^40 times values of 2^100: past fp32's range with the first tile's maximum as the reference, inside it with
-    one that moves."""
+    """Probabilities of up to 2^40 times values of 2^100: past fp32's range with the first tile's maximum as the reference, inside it where
+    the reference moves."""
     nq, t, prior = 512, 2, 766
     q = np.full((t, nq, 128), 1.25, np.float32)
     k = np.zeros((prior + t, 1, 128), np.float32)
     k[200] = 2.0                                           # 320 / sqrt(128) log2(e) = 40.8
     v = synth.normal_bf16(106, (prior + t, 1, 128)) * np.float32(2.0 ** 100)
-    got = sts.op_attn_prefill(q, k, v, prior, np.arange(48, dtype=np.int32), 48)
+    got = sts.op_attn_prefill_form(q, k, v, prior, np.arange(48, dtype=np.int32), 48, heads=2)[0]
     ref = T.op_causal_attention(q[:, :1].astype(np.float64), k.astype(np.float64), v.astype(np.float64), prior)
     assert np.isfinite(got).all() and rel(got, np.broadcast_to(ref, got.shape)) <= BF16_TOL
 

@@ -744,8 +744,8 @@ def test_decode_gemm_plan_is_what_the_engine_runs(sts):
 @pytest.mark.parametrize("cus", [256, 32])
 @pytest.mark.parametrize("n", [65, 96, 97, 128, 129, 224, 225, 256])
 def test_decode_gemm_tiles_above_64_rows(many_requests, n, cus):
-    """The GEMMs of large decode batches take 128x128 tiles or 256-column row tiles of any height for the same slices along K. The logits
-    against those of the same requests in batches of 64, which take other tiles."""
+    """The GEMMs of large decode batches take 128x128 tiles or 256-column row tiles of any height. The logits against those of the same
+    requests in batches of 64, which take other tiles and other slices along K."""
     eng, seqs, ctx, tok = many_requests
     eng.set_partition(256, cus)
     got, nxt = eng.decode_step(seqs[:n], tok[:n])
