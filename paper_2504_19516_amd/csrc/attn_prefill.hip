@@ -502,8 +502,8 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
     });
   };
   bf16x8 kf[4], vf[2][DB];
-  // Largest score of the tile after the one in hand, of this lane half, before the causal mask: where it does not outgrow the reference, no
-  // masked one does.
+  // Largest score of the tile after the one in hand, of this lane half, before the causal mask of its second block: where it does not
+  // outgrow the reference, no score does that counts.
   float mx[2];
   const float reach = RESCALE_LOG2 * 0.999f / scale_log2e;
   auto max_of = [&](auto x_c, auto kb_c, auto r_c) {
@@ -556,7 +556,8 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
       for (int j = 0; j < 2; j++) kf[j] = lds16(lds0 + ((it.kt0 + 1) % NS) * STAGE + k_slot[j]);
     }
   }
-  // One iteration, 64 products, turn by turn (a product depends on the fourth one before it at the nearest), a probability between any two:
+  // One iteration, 64 products, turn by turn (but for the last four of the scores a product depends on the fourth one before it at the
+  // nearest), a probability between any two:
   //   O += pages 2 and 3 of tile kt - 1, scores of the first 32 keys of kt + 1;   probabilities of the second 32 keys of tile kt
   //   O += pages 0 and 1 of tile kt, scores of the second 32 keys of kt + 1;      probabilities of the first 32 keys of tile kt + 1
   // The probabilities run five products behind: then a score is read well after its last product and before the next tile's first
@@ -567,8 +568,9 @@ __global__ void __launch_bounds__(256, 1) attn_prefill_pair_kernel(const bf16* _
   };
   // product i of 16 of a run of scores: head 0 two steps ahead of head 1
   static constexpr int SX[16] = {0, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 0, 1, 1}, SJ[16] = {0, 1, 0, 2, 1, 3, 2, 4, 3, 5, 4, 6, 5, 7, 6, 7};
-  // O and scores in turns; at the end the last four of the scores first, so that the tile's maxima are known when the iteration ends. (No
-  // product of O may come later than that: the probabilities of the next tile take the place of the ones it reads.)
+  // O and scores in turns; at the end the last four of the scores first, and the maxima of what they finish beside the last of O, so
+  // that the tile's maxima are known when the iteration ends. (No product of O may come later than that: the probabilities of the
+  // next tile take the place of the ones it reads.)
   static constexpr auto is_score = [](int u) { return u < 56 ? u % 2 == 1 : u < 60; };
   static constexpr auto number = [](int u) { return u < 56 ? u % 32 / 2 : u < 60 ? u - 44 : u - 48; };
   int kt = it.kt0;

@@ -463,10 +463,10 @@ bool valid_seq(sts_ctx* c, int s) { return s >= 0 && s < (int)c->seqs.size() && 
 
 // Make `seq` own enough pages for n_tokens; caller holds no lock.
 // After a failure between the launches of a step: waits for those already queued, whose metadata the next call rewrites, and
-// forgets their timing events.
+// forgets their timing events and those of the step (a beginning without an end).
 void drop_queued(Phase& ph) {
   if (ph.stream) (void)wait_stream(ph.stream);
-  ph.kkind.clear(); ph.kused = 0;
+  ph.kkind.clear(); ph.kused = 0; ph.ran = false;
 }
 
 int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {   // (seq, tokens)

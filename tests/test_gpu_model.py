@@ -886,7 +886,7 @@ def test_step_that_fails_between_its_launches(sts, phase, after):
     eng.fail_launch(phase, 2)
     with pytest.raises(sts.StsError) as e:
         eng.prefill_batch([pseq], [tok]) if phase == 0 else eng.decode_step(dseqs, dtok)
-    assert e.value.code == sts.EHIP and all(not eng.kernel_times(p, reset=True) for p in (0, 1))
+    assert e.value.code == sts.EHIP and all(not eng.kernel_times(p, reset=True) for p in (0, 1)) and eng.last_timing()[phase] == 0
     assert np.array_equal(step(0, 3)[0], want[0])
     eng.close()
 
