@@ -107,7 +107,8 @@ int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus, int32_t m
                          int64_t* est_ns);
 
 /* The same of the four GEMMs of a layer -- QKV, O, gate/up, down -- as the engine will run a decode step of `batch` requests on `cus` CUs
- * with the ctx's tile and stream models. tile_cfg -1: the form that cuts K inside the workgroups and finishes its own output (few
+ * with the ctx's tile and stream models; from 128 CUs a GEMM may run the same slices in the form of sts_op_gemm_cols, where that is estimated
+ * faster. tile_cfg -1: the form that cuts K inside the workgroups and finishes its own output (few
  * rows). row_tiles: row tiles of a 256x256 launch, 0 = as few as 256 rows allow. Arrays of 4. */
 int sts_decode_layer_plan(sts_ctx* ctx, int32_t batch, int32_t cus, int32_t* tile_cfg, int32_t* split_k, int32_t* row_tiles);
 
@@ -269,6 +270,9 @@ enum { STS_GEMM_128x128 = 0 /* 4 waves, two workgroups per CU */, STS_GEMM_64x25
        STS_GEMM_64x256S /* two workgroups per CU */, STS_GEMM_64x320S, STS_GEMM_64x384S, STS_GEMM_64x448S, STS_GEMM_64x512S };
 int sts_op_gemm(const float* a, const float* w, float* c_inout, int32_t m, int32_t n, int32_t k,
                 int32_t tile_cfg, int32_t epilogue, int32_t split_k, int32_t tail_slots);
+/* The decode GEMM that gives a workgroup all rows and 128 columns (m <= 256, the physical rows of w a multiple of 128): epilogue 1 (fp32, split_k slices
+ * along K) or 3 (SwiGLU of the slices' sums), arguments as in sts_op_gemm. The same slices give the same bits in both. */
+int sts_op_gemm_cols(const float* a, const float* w, float* c, int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t split_k);
 /* sts_op_gemm's fp32-store form (epilogue 1) for callers that cannot allocate -- code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc. a_dev [m, k] and w_dev [n, k]
  * are DEVICE pointers to bf16 (row-major, K contiguous), c_dev [m, n] a DEVICE pointer to fp32; all

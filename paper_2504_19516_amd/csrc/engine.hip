@@ -398,15 +398,15 @@ constexpr double SMALL_KERNEL_S = 4.5e-6;     // one of the kernels that add up 
 // estimates, with the reduce kernels of the split form, is the smaller one. Otherwise tile and split of each, with SwiGLU in the
 // gate/up GEMM unless cutting K is estimated faster. Both measured on 256 CUs, 8B shape: 1 row 73 us of GEMMs against 82 + 20 of
 // reduce kernels; at 32 rows 112 us against 86 + 20, so the form ends at 16 rows (one row block of the matrix cores).
-struct DecodeGemm { int cfg = 0, splits = 1, row_tiles = 0; };
+struct DecodeGemm { int cfg = 0, splits = 1, row_tiles = 0; bool cols = false; };
 struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu, down; };
 // More than 64 rows: the tiles for the slices that pick_decode_gemm decided on -- 128x128, or 256 columns with the rows in any number of
 // row tiles, whichever takes the least estimated time. The slices stay, and with them the order of the sums: every shape gives the same
 // bits. Estimate: rounds of workgroups at the tile's rate; the first loads and the partial sums of a launch, 8 us, are much the same for all
 // shapes and left out. Measured / estimated (with the 8 us) at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
 // slices 21 / 20 in one, 16 / 16 in two; 4096 x 14336 48 / 51 and 39 / 36; 28672 x 4096 in 2 slices 58 / 57 in one row tile.
-void pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, int cus, DecodeGemm* g) {
-  if (m <= 64 || n % 256 != 0) return;
+double pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, int cus, DecodeGemm* g) {
+  if (m <= 64 || n % 256 != 0) return HUGE_VAL;
   const int c = std::max(cus, 8), ksteps = k / 64, len = (ksteps + g->splits - 1) / g->splits * 64, blocks = (m + 31) / 32;
   double best = 1e300;
   auto consider = [&](int cfg, int row_tiles, long long wgs, int slots, double tile_s) {
@@ -418,6 +418,31 @@ void pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, int 
   const int least = (blocks + 7) / 8;
   for (int t = least; t <= std::min(blocks, 2 * least + 2); t++)
     consider(GEMM_256x256, t, (long long)t * (n / 256) * g->splits, c, TILE_HEIGHT_COST[(blocks + t - 1) / t - 1] * tall_s);
+  return best;
+}
+
+// gemm_cols in the place of tiles for the same slices (the same bits): it leaves partial sums as they do, or takes gate/up whole with
+// SwiGLU. Estimate of a launch: the lines its workgroups make a CU pull, or the weights at the whole GPU's rate, and 9 us of first loads,
+// output and launch. Measured / estimated on 256 CUs, 28672 x 4096 with SwiGLU: 64 rows 40 / 47 us, 128 rows 50 / 47, 192 rows 56 / 49, 256 rows
+// 67 / 63; 57344 x 8192: 96 rows 161 / 161, 192 rows 194 / 188, 256 rows 229 / 224 (tiles and their reduce kernel 214: they stay). Partitions below 128 CUs are not measured:
+// there the wide tiles of up to 64 rows read the activations less often.
+constexpr int COLS_MIN_CUS = 128;
+double cols_time(const sts_ctx* ctx, int m, int n, int k, int per_wg, int wgs, int cus) {
+  const int held = (wgs + cus - 1) / cus, rows = (m + 31) / 32 * 32;
+  return std::max(held * 2.0 * per_wg * (rows + 128) / ctx->stream_bw_cu, 2.0 * n * k / (0.95 * ctx->stream_bw_gpu)) + 9e-6;
+}
+// Where partial sums are left. A launch has to deal evenly: 288 workgroups on 256 CUs take as long as 512 (6144 x 4096 of 223 rows in 6 slices 28
+// us against 23). Slices under 16 K tiles gain nothing up to 160 rows, where either form is mostly its start and its output (4096 x 4096 in 8
+// slices: 64 rows 11.9 / 13.6 us, 96 rows 14.2 / 15.2, 160 rows 16.5 / 16.9, 223 rows 18.5 / 17.1). Up to 64 rows longer slices gain with one workgroup
+// a CU (4096 x 14336 23.9 / 21.7 us of 17 rows, 26.0 / 25.4 of 64; 8192 x 8192 26.5 / 24.5 of 24 rows) and with two up to 32 rows (128 CUs, 4096 x
+// 14336: 32 rows 31.3 / 29.5, 64 rows 36.1 / 36.8). Above, the tiles are taken at nine tenths of the estimate that chose their shape, which
+// rests on a slower tile's rate.
+bool cols_pays(const sts_ctx* ctx, int m, int n, int k, int splits, int cus, double t_tall) {
+  if (cus < COLS_MIN_CUS || m > COLS_MAX_ROWS || n % 128 != 0) return false;
+  const int wgs = n / 128 * splits, held = (wgs + cus - 1) / cus, len = (k / 64 + splits - 1) / splits;
+  if (held > gemm_cols_wgs_per_cu(m) || (held > 1 && 10 * wgs < 9 * held * cus)) return false;
+  if (m <= 64) return len >= 16 && (held == 1 || m <= 32);
+  return (len >= 16 || m > 160) && cols_time(ctx, m, n, k, len * 64, wgs, cus) < std::max(0.9 * t_tall, 2.0 * n * k / (0.85 * ctx->stream_bw_gpu)) + 9e-6;
 }
 
 DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
@@ -432,11 +457,16 @@ DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
   const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
   if (can_fuse && (t_fused <= t_split || p.gu.splits == 1)) { p.gu_fused = true; p.gu = fused; }
   t += (p.gu_fused ? t_fused : t_split) + 3 * SMALL_KERNEL_S;
-  auto tall = [&](int gn, int gk, DecodeGemm* g) { pick_tall_tiles(ctx->rate_128, ctx->rate_256, n, gn, gk, cus, g); };
-  tall(ctx->qkvn, d.hidden, &p.qkv);
-  tall(d.hidden, ctx->qd, &p.o);
-  tall(d.hidden, d.mlp, &p.down);
-  if (!p.gu_fused) tall(2 * d.mlp, d.hidden, &p.gu);
+  auto tall = [&](int gn, int gk, DecodeGemm* g) { return pick_tall_tiles(ctx->rate_128, ctx->rate_256, n, gn, gk, cus, g); };
+  auto partials = [&](int gn, int gk, DecodeGemm* g) { g->cols = cols_pays(ctx, n, gn, gk, g->splits, cus, tall(gn, gk, g)); };
+  partials(ctx->qkvn, d.hidden, &p.qkv);
+  partials(d.hidden, ctx->qd, &p.o);
+  partials(d.hidden, d.mlp, &p.down);
+  if (!p.gu_fused) {
+    const double t_tall = tall(2 * d.mlp, d.hidden, &p.gu), w_bytes = 4.0 * d.mlp * d.hidden, part_bytes = 8.0 * p.gu.splits * n * d.mlp;
+    const double t_two = n <= 64 ? t_split : std::max(0.9 * t_tall, w_bytes / (0.85 * ctx->stream_bw_gpu)) + 9e-6 + SMALL_KERNEL_S + part_bytes / (0.9 * ctx->stream_bw_gpu);
+    p.gu.cols = cus >= COLS_MIN_CUS && n <= COLS_MAX_ROWS && cols_time(ctx, n, 2 * d.mlp, d.hidden, d.hidden, d.mlp / 64, cus) < t_two;
+  }
   if (n <= KSLICE_MAX_ROWS)
     p.kslice = kslice_time(ctx, KS_QKV, n, ctx->qkvn, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, ctx->qd, cus) +
                kslice_time(ctx, KS_SWIGLU, n, 2 * d.mlp, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, d.mlp, cus) < t;
@@ -773,6 +803,10 @@ int DecodeRun::one_layer(int l) {
   const int h = d.hidden;
   hipStream_t st = ph.stream;
   auto partials = [&](int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) -> int {
+    if (gm.cols) {
+      KL(ph, kind, gemm_cols(st, EPI_F32, A, K, W, ph.part, N, n, N, K, gm.splits, (long long)n * N));
+      return STS_OK;
+    }
     KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt, gm.row_tiles));
     return STS_OK;
   };
@@ -796,6 +830,8 @@ int DecodeRun::one_layer(int l) {
   KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.o.splits, (long long)n * h, ph.Xn, w.g2, d.rms_eps, n, h));
   if (plan.gu_fused) {
     KL(ph, STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt));
+  } else if (plan.gu.cols) {
+    KL(ph, STS_K_GATEUP, gemm_cols(st, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, ph.H, d.mlp, n, 2 * d.mlp, h, plan.gu.splits, 0));
   } else {
     STSCK(partials(STS_K_GATEUP, plan.gu, ph.Xn, w.wgu, 2 * d.mlp, h));
     KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));

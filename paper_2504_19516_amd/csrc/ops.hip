@@ -116,6 +116,28 @@ extern "C" int sts_op_gemm(const float* a, const float* w, float* c_inout, int32
   return rc;
 }
 
+extern "C" int sts_op_gemm_cols(const float* a, const float* w, float* c, int32_t m, int32_t n, int32_t k, int32_t epilogue, int32_t split_k) {
+  if (!a || !w || !c || m < 1 || m > COLS_MAX_ROWS || n < 1 || k < 64 || k % 64 != 0 || split_k < 1 || split_k > 8) return STS_EINVAL;
+  if ((epilogue != EPI_F32 && epilogue != EPI_SWIGLU_BF16) || (epilogue == EPI_SWIGLU_BF16 ? 2 * n : n) % 128 != 0) return STS_EINVAL;
+  DevBufs b;
+  const bool sw = epilogue == EPI_SWIGLU_BF16;
+  const int wn = sw ? 2 * n : n, ksteps = k / 64, per = (ksteps + split_k - 1) / split_k, used = (ksteps + per - 1) / per;
+  bf16* dA = upload_bf16(b, a, (size_t)m * k);
+  bf16* dW = b.get<bf16>((size_t)wn * k);
+  float* tmp = b.get<float>((size_t)wn * k);
+  float* out = b.get<float>((size_t)used * m * n);                 // partial sums, or bf16 outputs
+  float* sum = b.get<float>((size_t)m * n);
+  if (!dA || !dW || !tmp || !out || !sum || hipMemcpy(tmp, w, (size_t)wn * k * sizeof(float), hipMemcpyHostToDevice) != hipSuccess) return STS_EHIP;
+  hipError_t e = convert_weight(nullptr, dW, k, tmp, n, k, 0, sw ? 32 : 0, 0, 1);
+  if (e == hipSuccess && sw) e = convert_weight(nullptr, dW, k, tmp + (size_t)n * k, n, k, 0, 32, 1, 1);
+  if (e != hipSuccess) return STS_EHIP;
+  e = gemm_cols(nullptr, epilogue, dA, k, dW, out, n, m, wn, k, split_k, (long long)m * n);
+  if (e != hipSuccess) return e == hipErrorInvalidValue ? STS_EINVAL : STS_EHIP;
+  if (sw) return download_bf16(b, c, reinterpret_cast<const bf16*>(out), (size_t)m * n);
+  if (reduce_f32(nullptr, sum, out, used, (long long)m * n, (size_t)m * n) != hipSuccess) return STS_EHIP;
+  return hipMemcpy(c, sum, (size_t)m * n * sizeof(float), hipMemcpyDeviceToHost) == hipSuccess ? STS_OK : STS_EHIP;
+}
+
 extern "C" int sts_op_attn_prefill(const float* q, const float* k, const float* v, float* out, int32_t t, int32_t prior,
                                    int32_t n_q, int32_t n_kv, int32_t d, const int32_t* pages, int32_t n_pool_pages) {
   return sts_op_attn_prefill_form(q, k, v, out, t, prior, n_q, n_kv, d, pages, n_pool_pages, 0, 0, nullptr);

@@ -93,7 +93,7 @@ EXPORTS = [
     "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_fail_launch", "sts_kernel_name",
     "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
-    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
+    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_op_gemm_cols", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
     "sts_profile_tile_model",
 ]
 
@@ -360,6 +360,15 @@ def op_gemm(a, w, tile_cfg="128x128", epilogue=1, split_k=1, c_in=None, tail_slo
     n = w.shape[0] // 2 if epilogue == 3 else w.shape[0]
     c = _f32(c_in).copy() if c_in is not None else np.zeros((m, n), np.float32)
     _ck(lib().sts_op_gemm(_p(a, C.c_float), _p(w, C.c_float), _p(c, C.c_float), m, n, k, GEMM_CFGS[tile_cfg], epilogue, split_k, tail_slots), "sts_op_gemm")
+    return c
+
+
+def op_gemm_cols(a, w, epilogue=1, split_k=1):
+    a, w = _f32(a), _f32(w)
+    m, k = a.shape
+    n = w.shape[0] // 2 if epilogue == 3 else w.shape[0]
+    c = np.zeros((m, n), np.float32)
+    _ck(lib().sts_op_gemm_cols(_p(a, C.c_float), _p(w, C.c_float), _p(c, C.c_float), m, n, k, epilogue, split_k), "sts_op_gemm_cols")
     return c
 
 

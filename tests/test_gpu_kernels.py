@@ -123,6 +123,34 @@ def test_gemm_skinny_tiles_epilogues(sts, cfg, width, m, k):
     assert rel(sts.op_gemm(a, w, cfg, epilogue=3), ref3) <= BF16_TOL
 
 
+@pytest.mark.parametrize("m", [1, 17, 32, 33, 64, 65, 96, 127, 160, 161, 192, 193, 224, 225, 256])
+@pytest.mark.parametrize("k,split", [(64, 1), (192, 2), (320, 1), (832, 3), (1088, 8), (2048, 2)])
+def test_gemm_all_rows_form_gives_the_bits_of_the_tiles(sts, m, k, split):
+    """Every height, rows that end inside a block, K ranges shorter than what is fetched ahead and not a multiple of it, unequal and fewer
+    slices, one and several column tiles. fp32: the bits of 128x128 tiles in the same slices. SwiGLU: their bits where one slice is the
+    whole K; else the slices' sums are those of the fp32 form and the result is one rounding of bf16 (2^-8 of the value) and the fp32 error of
+    the activation away from it in 64 bits."""
+    n = 384
+    a = synth.normal_bf16(171, (m, k))
+    w = synth.normal_bf16(172, (n, k), 0.05)
+    want = sts.op_gemm(a, w, "128x128", epilogue=1, split_k=split)
+    assert rel(want, T.op_linear(a.astype(np.float64), w.astype(np.float64))) <= 1e-5
+    assert np.array_equal(sts.op_gemm_cols(a, w, 1, split), want)
+    got = sts.op_gemm_cols(a, w, 3, split)
+    if split == 1:
+        assert np.array_equal(got, sts.op_gemm(a, w, "128x128", epilogue=3))
+    s64 = want.astype(np.float64)
+    ref = T.silu(s64[:, :192]) * s64[:, 192:]
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-6 * np.abs(s64[:, 192:]) + 1e-30)
+
+
+def test_gemm_all_rows_form_refuses(sts):
+    for m, rows, k, epilogue, split in ((257, 128, 64, 1, 1), (4, 192, 64, 1, 1), (4, 192, 64, 3, 1), (4, 128, 96, 1, 1), (4, 128, 64, 0, 1), (4, 128, 64, 1, 9), (4, 128, 64, 1, 0)):
+        with pytest.raises(sts.StsError) as e:
+            sts.op_gemm_cols(np.zeros((m, k), np.float32), np.zeros((rows, k), np.float32), epilogue, split)
+        assert e.value.code == sts.EINVAL
+
+
 @pytest.mark.parametrize("m", [1, 32, 33, 96, 97, 160, 192, 224, 225, 255, 257, 400])
 @pytest.mark.parametrize("k,slots", [(64, 0), (192, 0), (320, 0), (1088, 3)])
 def test_gemm_row_tile_heights(sts, m, k, slots):
