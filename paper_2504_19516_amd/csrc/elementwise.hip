@@ -386,16 +386,13 @@ hipError_t by_splits(int splits, F&& launch) {
 // Sums the split-K partials of the QKV projection, rotates q and k (rot: the step's angles), stores q
 // (bf16) for the attention kernel and appends k and v to the request's last page.
 template <int S>
-__global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* partials, long long split_stride, int ld,
-                                                                const DecodeSeq* seqs, const int* block_tables,
+__global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* partials, long long split_stride, int ld, const int* places,
                                                                 const float* rot, bf16* q_out, bf16* pool,
                                                                 KvGeom geo, int n_q) {
   // blockIdx.x = request, blockIdx.y = group of 8 head slots out of n_q (Q) + n_kv (K) + n_kv (V)
   const int row = blockIdx.x, d = geo.d, half = d >> 1;
   const int slot0 = blockIdx.y * 8, n_slots = n_q + 2 * geo.n_kv, slot1 = min(n_slots, slot0 + 8);
-  const DecodeSeq sq = seqs[row];
-  const int pos = sq.cl;
-  const int page = block_tables[sq.bt_off + pos / geo.page_tokens], slot = pos % geo.page_tokens;
+  const int place = places[row], page = place >> 4, slot = place & 15;
   const float* pr = partials + (size_t)row * ld;
   // a work item is four consecutive rotation pairs of a Q or K head, or four consecutive elements of a V head
   const int per_rot = half >> 2, per_v = d >> 2;
@@ -432,12 +429,12 @@ __global__ void __launch_bounds__(256) decode_qkv_finish_kernel(const float* par
   }
 }
 hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, long long split_stride, int ld,
-                             const DecodeSeq* seqs, const int* block_tables, const float* rot,
-                             bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q) {
+                             const int* place, const float* rot, bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q) {
   if (n == 0) return hipSuccess;
+  if (geo.page_tokens != 16) return hipErrorInvalidValue;
   return by_splits(splits, [&](auto S) {
-    hipLaunchKernelGGL((decode_qkv_finish_kernel<decltype(S)::value>), dim3(n, (n_q + 2 * geo.n_kv + 7) / 8), dim3(256), 0, s, partials, split_stride, ld, seqs,
-                       block_tables, rot, q_out, pool, geo, n_q);
+    hipLaunchKernelGGL((decode_qkv_finish_kernel<decltype(S)::value>), dim3(n, (n_q + 2 * geo.n_kv + 7) / 8), dim3(256), 0, s, partials, split_stride, ld, place, rot, q_out,
+                       pool, geo, n_q);
   });
 }
 

@@ -250,7 +250,7 @@ int pick_cfg(int m, int n, int k, int cus) {
 // Rates are measured busy-CU throughputs in TFLOP/s per CU: 128x128 tiles run two workgroups
 // per CU, the 256-column tiles one; rate_256 is that of the tallest. The latter come in heights of 32 to 256 rows: the rows
 // are dealt to any number of row tiles, so that they fill whole waves of workgroups.
-struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; };
+struct PrefillGemm { int cfg = GEMM_64x128, row_tiles = 0; double est_s = 0.0; };
 // Time of a 256-column tile of 32 (h + 1) rows against one of 256 (a short tile still streams its 256 columns of weights). Measured inside a
 // layer on 256 CUs at heights 32 / 64 / 96 / 128 / 160 / 192 / 224: 16 row tiles of 4096 x 4096 0.41 / 0.47 / 0.52 / 0.60 / 0.70 / 0.76 / 0.88, of 4096 x
 // 14336 0.42 / 0.48 / 0.52 / 0.59 / 0.67 / 0.77 / 0.88; two of 28672 x 4096, which wait for their weights, 0.54 / 0.66 / 0.72 / 0.77 / 0.83 / 0.88 / 0.93. It
@@ -276,7 +276,7 @@ PrefillGemm pick_prefill_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, 
     } else {
       t = (double)((tiles + slots - 1) / slots) * tile_s;
     }
-    if (t < best_cost) { best_cost = t; best = PrefillGemm{cfg, row_tiles}; }
+    if (t < best_cost) { best_cost = t; best = PrefillGemm{cfg, row_tiles, t}; }
   };
   consider(GEMM_128x128, 0, ((m + 127) / 128) * (n / 128), 2 * c, 128 * 128, 2.0 * 128 * 128 * k / (ctx->rate_128 * 1e12 / 2));
   if (n % 256 == 0) {
@@ -561,6 +561,72 @@ int run_head(sts_ctx* c, Phase& ph, const float* x, const int* idx, bf16* xn, Ro
   return STS_OK;
 }
 
+// The GEMMs of a layer's few rows and the kernels that finish them, around the attention: decode steps, and prefill batches of so few
+// rows that their GEMMs wait for weights.
+struct FewRows {
+  sts_ctx* c = nullptr; Phase* ph = nullptr; int n = 0;
+  DecodePlan plan;
+  bool nt = false;
+  RowScale by_rms{}, xn_scale{nullptr, 0, 0.f};
+
+  FewRows() = default;
+  FewRows(sts_ctx* c_, Phase& ph_, int n_, const DecodePlan& plan_) : c(c_), ph(&ph_), n(n_), plan(plan_) {
+    // On a large partition the decode streams (K and V, the weights of the skinny tiles) are fetched with the non-temporal
+    // hint: measured on a 6-layer model, the layer-step is 6 % shorter on 256 CUs (attention 72 -> 63 us), 3 % on 128,
+    // and no different on 32, where the same hint cost a prefill slice running beside it 0.5 %.
+    nt = ph->cus >= 128;
+    // kslice layers: the residual GEMMs leave Xn scaled by the next gains and the rows' sums of squares in ssq
+    by_rms = RowScale{ph->ssq, c->d.hidden / kslice_cols(KS_RESID, c->d.hidden, ph->cus), c->d.rms_eps};
+  }
+  int partials(int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) {
+    if (gm.cols) {
+      KL((*ph), kind, gemm_cols(ph->stream, EPI_F32, A, K, W, ph->part, N, n, N, K, gm.splits, (long long)n * N));
+    } else {
+      KL((*ph), kind, gemm_bf16(ph->stream, gm.cfg, EPI_F32, A, K, W, K, ph->part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt, gm.row_tiles));
+    }
+    return STS_OK;
+  }
+  // Xn (normalised, or as xn_scale says) through the QKV projection: rotated queries to q_out, K and V to the rows' places
+  int qkv(int l, bf16* q_out) {
+    const sts_model_desc& d = c->d;
+    const LayerW& w = c->layers[l];
+    if (plan.kslice) {
+      KL((*ph), STS_K_QKV, kslice_qkv(ph->stream, KsliceIn{ph->Xn, d.hidden, xn_scale, w.wqkv, n, c->qkvn, d.hidden}, ph->d_place, ph->rot, q_out, layer_pool(c, l), c->geo, d.n_q_heads));
+      return STS_OK;
+    }
+    STSCK(partials(STS_K_QKV, plan.qkv, ph->Xn, w.wqkv, c->qkvn, d.hidden));
+    KL((*ph), STS_K_ROPE, decode_qkv_finish(ph->stream, ph->part, plan.qkv.splits, (long long)n * c->qkvn, c->qkvn, ph->d_place, ph->rot, q_out, layer_pool(c, l), c->geo, n, d.n_q_heads));
+    return STS_OK;
+  }
+  // The attention's output through the rest of the layer. Leaves X, and Xn for the next layer, whose gains next_gain are.
+  int rest(int l, const float* next_gain) {
+    const sts_model_desc& d = c->d;
+    const LayerW& w = c->layers[l];
+    const int h = d.hidden, norm_kind = ph->side == 0 ? STS_K_NORM : STS_K_REDUCE;
+    hipStream_t st = ph->stream;
+    if (plan.kslice) {
+      KL((*ph), STS_K_O, kslice_resid(st, KsliceIn{ph->A, c->qd, RowScale{nullptr, 0, 0.f}, w.wo, n, h, c->qd}, ph->cus, ph->X, w.g2, ph->Xn, ph->ssq));
+      KL((*ph), STS_K_GATEUP, kslice_swiglu(st, KsliceIn{ph->Xn, h, by_rms, w.wgu, n, 2 * d.mlp, h}, ph->H));
+      KL((*ph), STS_K_DOWN, kslice_resid(st, KsliceIn{ph->H, d.mlp, RowScale{nullptr, 0, 0.f}, w.wd, n, h, d.mlp}, ph->cus, ph->X, next_gain, ph->Xn, ph->ssq));
+      xn_scale = by_rms;
+      return STS_OK;
+    }
+    STSCK(partials(STS_K_O, plan.o, ph->A, w.wo, h, c->qd));
+    KL((*ph), norm_kind, reduce_resid_norm(st, ph->X, ph->part, plan.o.splits, (long long)n * h, ph->Xn, w.g2, d.rms_eps, n, h));
+    if (plan.gu_fused) {
+      KL((*ph), STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph->Xn, h, w.wgu, h, ph->H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt));
+    } else if (plan.gu.cols) {
+      KL((*ph), STS_K_GATEUP, gemm_cols(st, EPI_SWIGLU_BF16, ph->Xn, h, w.wgu, ph->H, d.mlp, n, 2 * d.mlp, h, plan.gu.splits, 0));
+    } else {
+      STSCK(partials(STS_K_GATEUP, plan.gu, ph->Xn, w.wgu, 2 * d.mlp, h));
+      KL((*ph), STS_K_SWIGLU, reduce_swiglu(st, ph->H, ph->part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));
+    }
+    STSCK(partials(STS_K_DOWN, plan.down, ph->H, w.wd, h, d.mlp));
+    KL((*ph), norm_kind, reduce_resid_norm(st, ph->X, ph->part, plan.down.splits, (long long)n * h, ph->Xn, next_gain, d.rms_eps, n, h));
+    return STS_OK;
+  }
+};
+
 // ------------------------------------------------------------------------------------ prefill
 // Checks of a prefill slice that touch no state: arguments, the order of layer slices, and the
 // pages the batch will need (appended to `wants` for slice 0). Nothing is launched or reserved.
@@ -700,9 +766,7 @@ struct DecodeRun {
   int n_items = 0, n_multi = 0, chunk_pages = 0, max_chunks = 0;
   DecodeMerge* d_multi = nullptr;
   RowRotation rot{};
-  DecodePlan plan;
-  bool nt = false;
-  RowScale by_rms{}, xn_scale{nullptr, 0, 0.f};
+  FewRows few;
 
   int begin();
   int one_layer(int l);
@@ -732,6 +796,7 @@ int DecodeRun::begin() {
   meta_take(ph, &ph.h_dseq, &ph.d_dseq, n);
   meta_take(ph, &ph.h_tokens, &ph.d_tokens, n);
   meta_take(ph, &ph.h_pos, &ph.d_pos, n);
+  meta_take(ph, &ph.h_place, &ph.d_place, n);
   size_t bt_entries = 0;                                     // block tables are packed back to back
   for (int i = 0; i < n; i++) bt_entries += (c->seqs[seqs[i]].len + 1 + pt - 1) / pt;
   meta_take(ph, &ph.h_bt, &ph.d_bt, bt_entries);
@@ -746,6 +811,7 @@ int DecodeRun::begin() {
     max_pages = std::max(max_pages, np);
     ph.h_tokens[i] = in_tokens[i];
     ph.h_pos[i] = s.len;
+    ph.h_place[i] = s.pages[s.len / pt] * pt + s.len % pt;
   }
   std::vector<int> np_list(n);
   for (int i = 0; i < n; i++) np_list[i] = ph.h_dseq[i].n_pages;
@@ -787,58 +853,16 @@ int DecodeRun::begin() {
     KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, c->layers[0].g1, d.rms_eps, n, h));
     KL(ph, STS_K_ROPE, row_rotation(st, rot, n));
   }
-  // On a large partition the decode streams (K and V, the weights of the skinny tiles) are fetched with the non-temporal
-  // hint: measured on a 6-layer model, the layer-step is 6 % shorter on 256 CUs (attention 72 -> 63 us), 3 % on 128,
-  // and no different on 32, where the same hint cost a prefill slice running beside it 0.5 %.
-  nt = ph.cus >= 128;
-  plan = decode_layer_plan(c, n, ph.cus);
-  // kslice layers: the residual GEMMs leave Xn scaled by the next gains and the rows' sums of squares in ssq
-  by_rms = RowScale{ph.ssq, h / kslice_cols(KS_RESID, h, ph.cus), d.rms_eps};
+  few = FewRows(c, ph, n, decode_layer_plan(c, n, ph.cus));
   return STS_OK;
 }
 
 int DecodeRun::one_layer(int l) {
   Phase& ph = c->ph[1];
   const sts_model_desc& d = c->d;
-  const int h = d.hidden;
-  hipStream_t st = ph.stream;
-  auto partials = [&](int kind, const DecodeGemm& gm, const bf16* A, const bf16* W, int N, int K) -> int {
-    if (gm.cols) {
-      KL(ph, kind, gemm_cols(st, EPI_F32, A, K, W, ph.part, N, n, N, K, gm.splits, (long long)n * N));
-      return STS_OK;
-    }
-    KL(ph, kind, gemm_bf16(st, gm.cfg, EPI_F32, A, K, W, K, ph.part, N, n, N, K, gm.splits, (long long)n * N, nullptr, true, nt, gm.row_tiles));
-    return STS_OK;
-  };
-  const LayerW& w = c->layers[l];
-  const float* next_gain = (l + 1 < d.n_layers) ? c->layers[l + 1].g1 : c->gf;
-  if (plan.kslice) {
-    KL(ph, STS_K_QKV, kslice_qkv(st, KsliceIn{ph.Xn, h, xn_scale, w.wqkv, n, c->qkvn, h}, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, d.n_q_heads));
-  } else {
-    STSCK(partials(STS_K_QKV, plan.qkv, ph.Xn, w.wqkv, c->qkvn, h));
-    KL(ph, STS_K_ROPE, decode_qkv_finish(st, ph.part, plan.qkv.splits, (long long)n * c->qkvn, c->qkvn, ph.d_dseq, ph.d_bt, ph.rot, ph.Q, layer_pool(c, l), c->geo, n, d.n_q_heads));
-  }
-  KL(ph, STS_K_ATTN, attn_decode(st, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, nt));
-  if (plan.kslice) {
-    KL(ph, STS_K_O, kslice_resid(st, KsliceIn{ph.A, c->qd, RowScale{nullptr, 0, 0.f}, w.wo, n, h, c->qd}, ph.cus, ph.X, w.g2, ph.Xn, ph.ssq));
-    KL(ph, STS_K_GATEUP, kslice_swiglu(st, KsliceIn{ph.Xn, h, by_rms, w.wgu, n, 2 * d.mlp, h}, ph.H));
-    KL(ph, STS_K_DOWN, kslice_resid(st, KsliceIn{ph.H, d.mlp, RowScale{nullptr, 0, 0.f}, w.wd, n, h, d.mlp}, ph.cus, ph.X, next_gain, ph.Xn, ph.ssq));
-    xn_scale = by_rms;
-    return STS_OK;
-  }
-  STSCK(partials(STS_K_O, plan.o, ph.A, w.wo, h, c->qd));
-  KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.o.splits, (long long)n * h, ph.Xn, w.g2, d.rms_eps, n, h));
-  if (plan.gu_fused) {
-    KL(ph, STS_K_GATEUP, gemm_bf16(st, plan.gu.cfg, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, n, 2 * d.mlp, h, 1, 0, nullptr, true, nt));
-  } else if (plan.gu.cols) {
-    KL(ph, STS_K_GATEUP, gemm_cols(st, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, ph.H, d.mlp, n, 2 * d.mlp, h, plan.gu.splits, 0));
-  } else {
-    STSCK(partials(STS_K_GATEUP, plan.gu, ph.Xn, w.wgu, 2 * d.mlp, h));
-    KL(ph, STS_K_SWIGLU, reduce_swiglu(st, ph.H, ph.part, plan.gu.splits, (long long)n * 2 * d.mlp, n, d.mlp));
-  }
-  STSCK(partials(STS_K_DOWN, plan.down, ph.H, w.wd, h, d.mlp));
-  KL(ph, STS_K_REDUCE, reduce_resid_norm(st, ph.X, ph.part, plan.down.splits, (long long)n * h, ph.Xn, next_gain, d.rms_eps, n, h));
-  return STS_OK;
+  STSCK(few.qkv(l, ph.Q));
+  KL(ph, STS_K_ATTN, attn_decode(ph.stream, ph.Q, ph.A, ph.d_dseq, ph.d_ditems, n_items, d_multi, n_multi, ph.d_bt, layer_pool(c, l), c->geo, n, d.n_q_heads, chunk_pages, max_chunks, ph.attn_ws, few.nt));
+  return few.rest(l, (l + 1 < d.n_layers) ? c->layers[l + 1].g1 : c->gf);
 }
 
 int DecodeRun::end() {
@@ -850,13 +874,51 @@ int DecodeRun::end() {
     const size_t bytes = (size_t)n * d.vocab * sizeof(float);
     // small logits reach host memory from the kernel that reads them last, large ones by a copy
     const bool direct = want_logits && !want_next && bytes <= DIRECT_LOGITS_BYTES, beside = want_logits && want_next && bytes <= BESIDE_LOGITS_BYTES;
-    STSCK(run_head(c, ph, plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, xn_scale, n, ph.part, ph.part_floats, nt, direct ? ph.h_logits : ph.logits));
+    STSCK(run_head(c, ph, few.plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, few.xn_scale, n, ph.part, ph.part_floats, few.nt, direct ? ph.h_logits : ph.logits));
     if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_next, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
     if (want_logits && !direct && !beside) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
   ph.ran = true; ph.rows = n;
   return STS_OK;
+}
+
+// A prefill batch of few rows waits for its weights, as a decode step does, and takes the same GEMMs (but not the form that leaves rows
+// scaled: a row's norm is rounded as in a larger batch), where it has the whole GPU. Beside a decode step they are as fast, but take from
+// the decode step what they gain: 45 rows beside 71 requests on 128 / 128 CUs 418 -> 390 us for the slice, 499 -> 515 for the step; 100 rows beside 2 requests on 224 / 32
+// 370 -> 311 and 660 -> 702.
+// Up to 64 rows: its 64x128 tiles unsplit, with a cut last wave, pull less than split and skinny tiles. Device time of 2 layers, before / now: 1 row 264 / 187 us,
+// 16 rows 266 / 189, 64 rows 291 / 210; hidden 8192 8 rows 678 / 563, 64 rows 708 / 604. Not where the layer is launches (hidden 256: 8 rows 69 / 70).
+// Beyond, all four through gemm_cols in as many slices as give every CU a workgroup, where both sides' estimates say so: a tile launch and
+// its fix-up or norm at three quarters of the estimate that chose its shape (which rests on a slower tile's rate) plus 12 us. 65 rows 298 / 226 us, 96 rows 305 / 251,
+// 160 rows 358 / 294, 256 rows 389 / 360; hidden 8192 96 rows 740 / 657, 128 rows 776 / 711; 192 rows 888 for 820, which it leaves. Above 256 rows the tiles of
+// two row tiles are level.
+constexpr int FEW_ROWS_MAX = 256;
+bool prefill_few_rows(sts_ctx* c, Phase& ph, int rows, const PrefillGemm (&tiles)[4], FewRows* few) {
+  if (rows > FEW_ROWS_MAX || ph.cus < c->n_cu) return false;
+  const sts_model_desc& d = c->d;
+  const double w_s = 2.0 * ((double)c->qkvn * d.hidden + (double)d.hidden * c->qd + 3.0 * d.mlp * d.hidden) / c->stream_bw_gpu;   // a layer's weights
+  if ((rows <= 16 || rows > 64) && w_s < 20e-6) return false;
+  DecodePlan p = decode_layer_plan(c, rows, ph.cus);
+  p.kslice = false;
+  if (rows > 64) {
+    const int shape[4][2] = {{c->qkvn, d.hidden}, {d.hidden, c->qd}, {d.hidden, d.mlp}, {2 * d.mlp, d.hidden}};
+    DecodeGemm* gm[4] = {&p.qkv, &p.o, &p.down, &p.gu};
+    double t_tiles = 0.0, t_cols = 0.0;
+    for (int i = 0; i < 4; i++) {
+      const int n = shape[i][0], k = shape[i][1], cut = i == 3 ? 1 : std::max(1, std::min(std::min(8, k / 512), ph.cus / (n / 128)));
+      const int len = (k / 64 + cut - 1) / cut, used = (k / 64 + len - 1) / len;
+      *gm[i] = DecodeGemm{GEMM_128x128, used, 0, true};
+      t_tiles += std::max(0.75 * tiles[i].est_s, 2.0 * n * k / (0.85 * c->stream_bw_gpu)) + 12e-6;
+      t_cols += cols_time(c, rows, n, k, len * 64, n / 128 * used, ph.cus) + (i == 3 ? 0.0 : SMALL_KERNEL_S + 4.0 * used * rows * n / 4e12);
+    }
+    if (t_tiles <= 1.03 * t_cols) return false;
+    p.gu_fused = false;
+  }
+  auto fits = [&](const DecodeGemm& g, int n) { return (size_t)g.splits * rows * n <= ph.part_floats; };
+  if (!(fits(p.qkv, c->qkvn) && fits(p.o, d.hidden) && fits(p.down, d.hidden) && (p.gu_fused || p.gu.cols || fits(p.gu, 2 * d.mlp)))) return false;
+  *few = FewRows(c, ph, rows, p);
+  return true;
 }
 
 int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
@@ -873,7 +935,9 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   auto pick = [&](int n, int k) { return pick_prefill_gemm(c, rows, n, k, ph.cus, ph.tail_ws_bytes); };
   const int h = d.hidden;
   const PrefillGemm g_qkv = pick(c->qkvn, h), g_o = pick(h, c->qd), g_gu = pick(2 * d.mlp, h), g_down = pick(h, d.mlp);
-  const bool qkv_places = g_qkv.cfg == GEMM_256x256;         // the QKV tiles write K and V to the rows' places themselves
+  FewRows few;
+  const bool few_rows = prefill_few_rows(c, ph, rows, {g_qkv, g_o, g_down, g_gu}, &few);
+  const bool qkv_places = few_rows || g_qkv.cfg == GEMM_256x256;   // the QKV GEMM, or what finishes it, writes K and V to the rows' places
   // ---- stage metadata
   ph.meta_used = 0;
   meta_take(ph, &ph.h_pseq, &ph.d_pseq, n_seqs);
@@ -925,14 +989,22 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
     const LayerW& w = c->layers[l];
     ResidNorm post{ph.Xn, w.g2, d.rms_eps, false}, next{ph.Xn, l + 1 < le ? c->layers[l + 1].g1 : nullptr, d.rms_eps, false};
     if (!normed) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g1, d.rms_eps, rows, h));
-    if (qkv_places) {
+    if (few_rows) {
+      STSCK(few.qkv(l, ph.QKV));
+    } else if (qkv_places) {
       const QkvOut out{ph.rot, ph.d_place, layer_pool(c, l), c->geo, d.n_q_heads};
       KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_QKV, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h, nullptr, &out));
     } else {
       KL(ph, STS_K_QKV, prefill_gemm(ph, g_qkv, EPI_BF16, ph.Xn, h, w.wqkv, h, ph.QKV, c->qkvn, rows, c->qkvn, h));
       KL(ph, STS_K_ROPE, rope_kv_write_prefill(st, ph.QKV, c->qkvn, ph.d_pseq, n_seqs, ph.d_bt, ph.rot, layer_pool(c, l), c->geo, rows, d.n_q_heads));
     }
-    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, attn_heads, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
+    KL(ph, STS_K_ATTN, attn_prefill(st, ph.QKV, few_rows ? c->qd : c->qkvn, ph.A, c->qd, ph.d_pseq, ph.d_items, n_items, attn_heads, d_merges, n_merges, ph.d_bt, layer_pool(c, l), c->geo, d.n_q_heads, ph.tail_ws));
+    if (few_rows) {
+      STSCK(few.rest(l, l + 1 < d.n_layers ? c->layers[l + 1].g1 : c->gf));
+      normed = true;
+      if (beside) beside->turn();
+      continue;
+    }
     KL(ph, STS_K_O, prefill_gemm(ph, g_o, EPI_RESID_F32, ph.A, c->qd, w.wo, c->qd, ph.X, h, rows, h, c->qd, &post));
     if (!post.done) KL(ph, STS_K_NORM, rmsnorm_rows(st, ph.Xn, ph.X, w.g2, d.rms_eps, rows, h));
     KL(ph, STS_K_GATEUP, prefill_gemm(ph, g_gu, EPI_SWIGLU_BF16, ph.Xn, h, w.wgu, h, ph.H, d.mlp, rows, 2 * d.mlp, h));
@@ -980,6 +1052,7 @@ int alloc_phase(sts_ctx* c, int side) {
   STSCK(dev_alloc(c, &ph.Xlast_n, nseq * d.hidden));
   STSCK(dev_alloc(c, &ph.logits, nseq * d.vocab));
   STSCK(dev_alloc(c, &ph.rot, rows * d.head_dim));
+  STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
   {
     // prefill attention: a query tile per 128 rows, and as many again for the parts of cut key ranges
     const size_t q_tiles = side == 0 ? rows / attn_prefill_tile_q() + nseq + 1 : 0;
@@ -999,12 +1072,12 @@ int alloc_phase(sts_ctx* c, int side) {
     const size_t tail_floats = (size_t)c->n_cu * 256 * 256;   // one wave of partial tiles at the largest tile on every CU
     STSCK(dev_alloc(c, &ph.tail_ws, tail_floats));
     ph.tail_ws_bytes = tail_floats * sizeof(float);
+    ph.part = ph.tail_ws; ph.part_floats = tail_floats;       // partial sums of few rows
   } else {
     const size_t widest = std::max<size_t>(std::max(c->qkvn, 2 * d.mlp), d.hidden);
     const size_t max_chunks = decode_max_chunks((int)mp);
     ph.part_floats = 8 * rows * widest;
     STSCK(dev_alloc(c, &ph.part, ph.part_floats));
-    STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
     STSCK(dev_alloc(c, &ph.Q, rows * c->qd));
     STSCK(dev_alloc(c, &ph.attn_ws, attn_decode_ws_floats((int)rows, d.n_q_heads, d.head_dim, (int)max_chunks)));
   }

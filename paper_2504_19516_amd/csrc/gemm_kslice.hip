@@ -31,7 +31,7 @@ struct KsArgs {
   // outputs, by epilogue
   void* C; int ldc;                                  // logits (fp32) or MLP hidden (bf16)
   float* X; const float* gain; bf16* Xg; float* ssq_out;
-  const DecodeSeq* seqs; const int* block_tables; const float* rot; bf16* q_out; bf16* pool; KvGeom geo; int n_q;
+  const int* place; const float* rot; bf16* q_out; bf16* pool; KvGeom geo; int n_q;
 };
 
 // CB: 16-column blocks per workgroup; NW waves; PD K tiles in flight per wave.
@@ -215,8 +215,7 @@ __global__ void __launch_bounds__(NW * 64, 4) gemm_kslice_kernel(KsArgs g) {
       const int row = c >> 2, i0 = (c & 3) * 4, e0 = 16 * u + i0;
       if (row >= g.M) continue;
       const f32x4 a4 = sum4(row, i0), b4 = sum4(row, 16 + i0);
-      const DecodeSeq rq = g.seqs[row];
-      const int pos = rq.cl, page = g.block_tables[rq.bt_off + pos / g.geo.page_tokens], slot = pos % g.geo.page_tokens;
+      const int place = head < g.n_q ? 0 : g.place[row], page = place >> 4, slot = place & 15;
       if (head >= g.n_q + g.geo.n_kv) {
         bf16* v = g.pool + ((size_t)page * g.geo.n_kv + (head - g.n_q - g.geo.n_kv)) * g.geo.head_elems() + (size_t)g.geo.page_tokens * d;
 #pragma unroll
@@ -289,10 +288,10 @@ hipError_t kslice_swiglu(hipStream_t s, const KsliceIn& in, bf16* H) {
 }
 // The QKV projection of one new token per request, rotated (rot: [M][d / 2 cosines | d / 2 sines] of the requests' positions), q to
 // q_out, k and v appended to the requests' pages.
-hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const DecodeSeq* seqs, const int* block_tables, const float* rot, bf16* q_out, bf16* pool, KvGeom geo, int n_q) {
+hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const int* place, const float* rot, bf16* q_out, bf16* pool, KvGeom geo, int n_q) {
   KsArgs g;
   if (!fill(&g, in) || (geo.d != 64 && geo.d != 128) || in.N != (n_q + 2 * geo.n_kv) * geo.d || geo.page_tokens != 16) return hipErrorInvalidValue;
-  g.seqs = seqs; g.block_tables = block_tables; g.rot = rot; g.q_out = q_out; g.pool = pool; g.geo = geo; g.n_q = n_q;
+  g.place = place; g.rot = rot; g.q_out = q_out; g.pool = pool; g.geo = geo; g.n_q = n_q;
   return launch_ks<2, 16, 2, KS_QKV>(s, g, in.N / 32);
 }
 

@@ -105,9 +105,9 @@ hipError_t rmsnorm_rows(hipStream_t s, bf16* out, const float* X, const float* g
 hipError_t rope_kv_write_prefill(hipStream_t s, bf16* qkv, int ld, const PrefillSeq* seqs, int n_seqs,
                                  const int* block_tables, const float* rot, bf16* pool, KvGeom geo,
                                  int n_rows, int n_q);
+// place: page * page_tokens + slot of each row's K and V (also in kslice_qkv)
 hipError_t decode_qkv_finish(hipStream_t s, const float* partials, int splits, long long split_stride, int ld,
-                             const DecodeSeq* seqs, const int* block_tables, const float* rot,
-                             bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q);
+                             const int* place, const float* rot, bf16* q_out, bf16* pool, KvGeom geo, int n, int n_q);
 hipError_t reduce_resid_norm(hipStream_t s, float* X, const float* partials, int splits, long long split_stride,
                              bf16* out_norm, const float* gain, float eps, int n, int h);
 hipError_t reduce_swiglu(hipStream_t s, bf16* H, const float* partials, int splits, long long split_stride,
@@ -152,8 +152,7 @@ int kslice_cols(int epi, int n, int cus);
 hipError_t kslice_f32(hipStream_t s, const KsliceIn& in, int cus, float* C, int ldc);
 hipError_t kslice_resid(hipStream_t s, const KsliceIn& in, int cus, float* X, const float* gain, bf16* Xg, float* ssq_out);
 hipError_t kslice_swiglu(hipStream_t s, const KsliceIn& in, bf16* H);
-hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const DecodeSeq* seqs, const int* block_tables, const float* rot, bf16* q_out, bf16* pool,
-                      KvGeom geo, int n_q);
+hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const int* place, const float* rot, bf16* q_out, bf16* pool, KvGeom geo, int n_q);
 
 // ---- GEMMs of up to 256 rows that read their weights once (gemm_cols.hip) --------------------
 constexpr int COLS_MAX_ROWS = 256;

@@ -792,6 +792,54 @@ def test_prefill_rows_finished_and_normalised_in_one_kernel(wide_rows, cus, rows
     free_all(eng, [s])
 
 
+@pytest.fixture(scope="module")
+def wide_prefill(sts):
+    """Two layers of the 8B shape: enough weights a layer for the GEMMs of few rows."""
+    eng = sts.Engine(synth.llama8b_model(2, 1024), weight_seed=5, init_weights=True, kv_pool_pages=256, max_prefill_tokens=320, max_prefill_seqs=4,
+                     max_decode_batch=2, max_seqs=8, max_pages_per_seq=64)
+    yield eng
+    eng.close()
+
+
+@pytest.mark.parametrize("lens,priors", [((1,), (0,)), ((16,), (5,)), ((17,), (0,)), ((33, 31), (0, 40)), ((65,), (0,)), ((3, 90, 3), (16, 0, 31)), ((128,), (100,)), ((200, 56), (0, 7)),
+                                         ((257,), (0,))])
+def test_prefill_of_few_rows_equals_the_tiles(sts, wide_prefill, lens, priors):
+    """Up to 256 rows on the whole GPU take the decode step's GEMMs and a kernel that rotates and writes K and V (kind "rope"); on 224 CUs the same batch
+    takes the prefill tiles. Logits, and K and V of the new tokens in every layer, agree to the rounding of bf16 activations; ragged batches over
+    cached tokens, chunks that start inside a page; a slice a layer as well
+    as both layers at once."""
+    eng, desc = wide_prefill, wide_prefill.desc
+    rows = sum(lens)
+    toks = [synth.tokens(900 + rows + i, n, desc.vocab) for i, n in enumerate(lens)]
+    got = {}
+    for cus, sliced in ((256, False), (256, True), (224, False)):
+        eng.set_partition(cus, 256)
+        seqs = [eng.seq_create() for _ in lens]
+        for i, (s, p) in enumerate(zip(seqs, priors)):
+            if p:
+                eng.kv_fill_random(s, p, 40 + i)
+        eng.kernel_timing(True)
+        eng.kernel_times(0, reset=True)
+        if sliced:
+            eng.prefill_batch(seqs, toks, 0, 1, want_logits=False)
+            logits = eng.prefill_batch(seqs, toks, 1, 2)
+        else:
+            logits = eng.prefill_batch(seqs, toks)
+        kinds = eng.kernel_times(0, reset=True)
+        eng.kernel_timing(False)
+        if rows > 64:
+            assert ("rope" in kinds) == (cus == 256 and rows <= 256)
+        kv = [np.concatenate([np.stack(eng.kv_read(l, s, p, n)) for s, p, n in zip(seqs, priors, lens)], axis=1) for l in range(2)]
+        got[cus, sliced] = logits, kv
+        free_all(eng, seqs)
+    b, bkv = got.pop((224, False))
+    for a, akv in got.values():
+        assert rel(a, b) <= TOL
+        for x, y in zip(akv, bkv):                            # position by position: a token in the wrong slot cannot hide
+            assert np.all(np.abs(x - y).max(axis=(2, 3)) <= TOL * np.abs(y).max())
+    eng.set_partition(256, 256)
+
+
 @pytest.mark.parametrize("cus", [256, 8])
 @pytest.mark.parametrize("nq,nkv,d", [(8, 2, 128), (8, 1, 128), (4, 4, 64), (8, 2, 64)])
 def test_qkv_tiles_rotate_and_append_as_the_separate_kernel(sts, nq, nkv, d, cus):
