@@ -737,9 +737,10 @@ int decode_validate(sts_ctx* c, const int32_t* seqs, const int32_t* in_tokens, i
   const sts_model_desc& d = c->d;
   if (n < 1 || n > c->p.max_decode_batch || !seqs || !in_tokens) return STS_EINVAL;
   if (ph.stream == nullptr) return STS_ESTATE;               // decode suspended (0 CUs)
+  std::vector<char> seen(c->seqs.size());
   for (int i = 0; i < n; i++) {
     if (!valid_seq(c, seqs[i]) || in_tokens[i] < 0 || in_tokens[i] >= d.vocab) return STS_EINVAL;
-    for (int j = 0; j < i; j++) if (seqs[j] == seqs[i]) return STS_EINVAL;
+    if (seen[seqs[i]]++) return STS_EINVAL;
     if ((c->seqs[seqs[i]].len + 1 + c->geo.page_tokens - 1) / c->geo.page_tokens > c->p.max_pages_per_seq) return STS_EINVAL;
   }
   {
@@ -817,21 +818,23 @@ int DecodeRun::begin() {
   for (int i = 0; i < n; i++) np_list[i] = ph.h_dseq[i].n_pages;
   decode_chunk_plan(np_list.data(), n, d.n_kv_heads, ph.cus, pt, &chunk_pages, &max_chunks);
   if (max_chunks > decode_max_chunks(mp)) return STS_EINVAL;   // cannot happen within sts_init's bound on max_pages_per_seq
-  // one attention workgroup row per context chunk that exists
-  for (int i = 0; i < n; i++) n_items += (ph.h_dseq[i].n_pages + chunk_pages - 1) / chunk_pages;
+  // One attention workgroup row per context chunk that exists, longest chunks first: the workgroups that finish the launch are then the
+  // short ones. A context's chunks are equal (its pages / chunks), so a pass over the requests counts the items of each length and a second
+  // one places them, in the requests' order.
+  auto chunks_of = [&](int i) { return (np_list[i] + chunk_pages - 1) / chunk_pages; };
+  std::vector<int> place(chunk_pages + 2, 0);                // place[chunk_pages - length]: where the next item of that length goes
+  for (int i = 0; i < n; i++) {
+    const int chunks = chunks_of(i);
+    place[chunk_pages - (np_list[i] + chunks - 1) / chunks + 1] += chunks;
+    n_items += chunks;
+  }
+  for (int b = 1; b <= chunk_pages; b++) place[b] += place[b - 1];
   meta_take(ph, &ph.h_ditems, &ph.d_ditems, n_items);
   if (ph.meta_used > ph.meta_bytes) return STS_EINVAL;
-  n_items = 0;
-  for (int i = 0; i < n; i++)
-    for (int ch = 0; ch < (ph.h_dseq[i].n_pages + chunk_pages - 1) / chunk_pages; ch++) ph.h_ditems[n_items++] = DecodeItem{i, ch, ph.h_dseq[i].cl, ph.h_dseq[i].bt_off};
-  // longest chunks first (a context's chunks are equal, so its chunk length is pages / chunks): the workgroups
-  // that finish the launch are then the short ones
-  {
-    auto chunk_len = [&](const DecodeItem& it) {
-      const int np = ph.h_dseq[it.seq].n_pages, chunks = (np + chunk_pages - 1) / chunk_pages;
-      return (np + chunks - 1) / chunks;
-    };
-    std::stable_sort(ph.h_ditems, ph.h_ditems + n_items, [&](const DecodeItem& a, const DecodeItem& b) { return chunk_len(a) > chunk_len(b); });
+  for (int i = 0; i < n; i++) {
+    const int chunks = chunks_of(i);
+    int& at = place[chunk_pages - (np_list[i] + chunks - 1) / chunks];
+    for (int ch = 0; ch < chunks; ch++) ph.h_ditems[at++] = DecodeItem{i, ch, ph.h_dseq[i].cl, ph.h_dseq[i].bt_off};
   }
   // requests whose context has more than one chunk: only they need the merge kernel
   DecodeMerge* h_multi = nullptr;
