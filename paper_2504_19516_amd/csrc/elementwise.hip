@@ -509,51 +509,54 @@ hipError_t reduce_f32(hipStream_t s, float* out, const float* partials, int spli
 }
 
 // ------------------------------------------------------------------ greedy sampling
-// One workgroup of 1024 threads per row; 16-byte loads, four in flight per thread. The first
-// maximum wins: a thread scans its indices in ascending order and the tree keeps the lower index
-// on equal values. out is pinned host memory, and so is copy: where the caller wants small logits too, the pass that reads them
-// writes them there (a runtime copy leaves the stream idle for about 15 us).
-__global__ void __launch_bounds__(1024) argmax_kernel(int* out, const float* logits, int vocab, float* copy) {
-  __shared__ float bv[1024];
-  __shared__ int bi[1024];
-  const float* l = logits + (size_t)blockIdx.x * vocab;
+// A row is dealt to `parts` workgroups of 1024 threads (16-byte loads, four in flight per thread), and the host takes the best of their
+// maxima (in order, so that the first of equal values wins here as well): a thread scans its indices in ascending order and the lower index is kept
+// on equal values. Bound by what one workgroup loads and, with `copy` (pinned host memory, the logits again), by the bus: the pass that reads them stores
+// them there too (a runtime copy leaves the stream idle for about 15 us), and one workgroup a row asks for too little of either.
+// A step of one layer with tokens alone, 128256 columns, one workgroup a row / in parts: 1 row 266 / 260 us, 8 rows 275 / 269, 64 rows 349 / 335.
+__global__ void __launch_bounds__(1024) argmax_kernel(ArgBest* out, const float* logits, int vocab, int width, float* copy) {
+  __shared__ ArgBest wave_best[16];
+  const int tid = threadIdx.x, c0 = blockIdx.x * width, c1 = min(vocab, c0 + width);
+  const float* l = logits + (size_t)blockIdx.y * vocab;
   float best = -INFINITY; int idx = 0x7FFFFFFF;
   auto take = [&](float v, int c) { if (v > best) { best = v; idx = c; } };
   if ((vocab & 3) == 0) {
-    const float4* l4 = reinterpret_cast<const float4*>(l);
-    const int n4 = vocab >> 2;
-    int q = threadIdx.x;
+    const f32x4* l4 = reinterpret_cast<const f32x4*>(l);
+    f32x4* to = copy ? reinterpret_cast<f32x4*>(copy + (size_t)blockIdx.y * vocab) : nullptr;
+    const int n4 = c1 >> 2;
+    auto use = [&](const f32x4& v, int q) {
+#pragma unroll
+      for (int e = 0; e < 4; e++) take(v[e], 4 * q + e);
+      if (to) to[q] = v;
+    };
+    int q = (c0 >> 2) + tid;
     for (; q + 3 * 1024 < n4; q += 4 * 1024) {
-      const float4 a = l4[q], b = l4[q + 1024], c = l4[q + 2048], d = l4[q + 3072];
-      take(a.x, 4 * q); take(a.y, 4 * q + 1); take(a.z, 4 * q + 2); take(a.w, 4 * q + 3);
-      take(b.x, 4 * q + 4096); take(b.y, 4 * q + 4097); take(b.z, 4 * q + 4098); take(b.w, 4 * q + 4099);
-      take(c.x, 4 * q + 8192); take(c.y, 4 * q + 8193); take(c.z, 4 * q + 8194); take(c.w, 4 * q + 8195);
-      take(d.x, 4 * q + 12288); take(d.y, 4 * q + 12289); take(d.z, 4 * q + 12290); take(d.w, 4 * q + 12291);
+      const f32x4 a = l4[q], b = l4[q + 1024], c = l4[q + 2048], d = l4[q + 3072];
+      use(a, q); use(b, q + 1024); use(c, q + 2048); use(d, q + 3072);
     }
-    for (; q < n4; q += 1024) {
-      const float4 a = l4[q];
-      take(a.x, 4 * q); take(a.y, 4 * q + 1); take(a.z, 4 * q + 2); take(a.w, 4 * q + 3);
-    }
+    for (; q < n4; q += 1024) use(l4[q], q);
   } else {
-    for (int c = threadIdx.x; c < vocab; c += 1024) take(l[c], c);
+    for (int c = c0 + tid; c < c1; c += 1024) take(l[c], c);
   }
-  if (copy)
-    for (int c = threadIdx.x * 4; c < vocab; c += 4096) *reinterpret_cast<f32x4*>(copy + (size_t)blockIdx.x * vocab + c) = *reinterpret_cast<const f32x4*>(l + c);
-  bv[threadIdx.x] = best; bi[threadIdx.x] = idx;
+  auto join = [&](float v, int i) { if (v > best || (v == best && i < idx)) { best = v; idx = i; } };
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) join(__shfl_xor(best, o, 64), __shfl_xor(idx, o, 64));
+  if ((tid & 63) == 0) wave_best[tid >> 6] = ArgBest{best, idx};
   __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (threadIdx.x < o) {
-      const float v = bv[threadIdx.x + o]; const int i = bi[threadIdx.x + o];
-      if (v > bv[threadIdx.x] || (v == bv[threadIdx.x] && i < bi[threadIdx.x])) { bv[threadIdx.x] = v; bi[threadIdx.x] = i; }
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[blockIdx.x] = bi[0] == 0x7FFFFFFF ? 0 : bi[0];     // a row without any value above -inf
+  if (tid >= 64) return;
+  best = wave_best[tid & 15].value; idx = wave_best[tid & 15].index;
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) join(__shfl_xor(best, o, 64), __shfl_xor(idx, o, 64));
+  if (tid == 0) out[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = ArgBest{best, idx};
 }
-hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab, float* copy) {
+// Parts of a row: one load of every thread or more each, about two workgroups a CU in all.
+int argmax_parts(int n, int vocab) { return std::max(1, std::min({(vocab + 4095) / 4096, 512 / std::max(n, 1), ARGMAX_MAX_PARTS})); }
+// out: n x argmax_parts(n, vocab), pinned host memory
+hipError_t argmax_rows(hipStream_t s, ArgBest* out, const float* logits, int n, int vocab, float* copy) {
   if (n == 0) return hipSuccess;
   if (copy && vocab % 4 != 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(argmax_kernel, dim3(n), dim3(1024), 0, s, out, logits, vocab, copy);
+  const int parts = argmax_parts(n, vocab), width = ((vocab + parts - 1) / parts + 3) / 4 * 4;
+  hipLaunchKernelGGL(argmax_kernel, dim3(parts, n), dim3(1024), 0, s, out, logits, vocab, width, copy);
   return hipGetLastError();
 }
 

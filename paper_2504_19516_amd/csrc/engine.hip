@@ -75,7 +75,7 @@ struct Phase {
   // pinned staging
   int* h_tokens = nullptr; int* h_pos = nullptr; int* h_place = nullptr; int* h_bt = nullptr; int* h_rows = nullptr;
   PrefillSeq* h_pseq = nullptr; DecodeSeq* h_dseq = nullptr; AttnItem* h_items = nullptr; DecodeItem* h_ditems = nullptr;
-  float* h_logits = nullptr; int* h_next = nullptr;
+  float* h_logits = nullptr; ArgBest* h_best = nullptr;
   int rows = 0;                               // rows of the last call
   // per-kernel timing
   std::vector<hipEvent_t> kev; std::vector<int> kkind; size_t kused = 0;
@@ -524,12 +524,11 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
 // 21.3 / 19.3 on 64; at 1024 rows 19.6 / 15.1 on 256 CUs but 29.5 / 31.3 on 64, whose few workgroups wait for the bus in turn
 // (8192 rows: 50 / 56 and 114 / 188).
 constexpr int META_FUSED_ROWS = 512;
-// Logits a head's last kernel stores straight to host memory, and those that greedy sampling copies there on the side; larger ones
-// go by a runtime copy. A copy of more than 16 KiB leaves the stream idle for about 15 us (one layer, 16 rows of 1024: 124 us
-// against 109; with tokens, 256 rows 291 against 277). The lines lie where logits stop being small beside a step of real depth, not where
-// the copy becomes the faster way, which on an idle bus it does not: 4 MB (8 rows of 128256) 335 against 296 us stored by the
-// head, 342 against 335 by the sampling; 32 MB 892 against 810, and 903 against 904.
-constexpr size_t DIRECT_LOGITS_BYTES = 64 << 10, BESIDE_LOGITS_BYTES = 1 << 20;
+// Logits up to this size are stored to host memory by the kernel that reads or writes them last (the head, or greedy sampling on the side), larger ones
+// go by a runtime copy, which leaves the stream idle for about 15 us and for much longer between 2 and 8 MB. One layer of the 8B shape, vocabulary
+// 128256, us a step by copy / stored: with tokens 1 row 296 / 282, 4 rows 592 / 376, 8 rows 744 / 482, 16 rows 931 / 726, 64 rows (31 MiB)
+// 1989 / 2005; logits alone 293 / 270, 593 / 359, 744 / 453, 715 / 636, 1963 / 1880. More is not measured.
+constexpr size_t STORED_LOGITS_BYTES = 32 << 20;
 
 bf16* layer_pool(sts_ctx* c, int l) { return c->pool + (size_t)l * c->pool_layer_elems; }
 
@@ -875,10 +874,9 @@ int DecodeRun::end() {
   if (want_logits || want_next) {
     // (the last reduce kernel of the split form has written Xn normalised)
     const size_t bytes = (size_t)n * d.vocab * sizeof(float);
-    // small logits reach host memory from the kernel that reads them last, large ones by a copy
-    const bool direct = want_logits && !want_next && bytes <= DIRECT_LOGITS_BYTES, beside = want_logits && want_next && bytes <= BESIDE_LOGITS_BYTES;
+    const bool direct = want_logits && !want_next && bytes <= STORED_LOGITS_BYTES, beside = want_logits && want_next && bytes <= STORED_LOGITS_BYTES;
     STSCK(run_head(c, ph, few.plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, few.xn_scale, n, ph.part, ph.part_floats, few.nt, direct ? ph.h_logits : ph.logits));
-    if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_next, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
+    if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_best, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
     if (want_logits && !direct && !beside) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
@@ -1017,7 +1015,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   }
   if (le == d.n_layers && want_logits) {
     const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);
-    const bool direct = bytes <= DIRECT_LOGITS_BYTES;        // the head's last kernel stores to host memory
+    const bool direct = bytes <= STORED_LOGITS_BYTES;        // the head's last kernel stores to host memory
     STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false, direct ? ph.h_logits : ph.logits));
     if (!direct) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
@@ -1032,7 +1030,12 @@ int decode_finish(sts_ctx* c, const int32_t* seqs, int n, float* logits, int32_t
   STSCK(k_collect(c, ph));
   for (int i = 0; i < n; i++) c->seqs[seqs[i]].len += 1;
   if (logits) std::memcpy(logits, ph.h_logits, (size_t)n * c->d.vocab * sizeof(float));
-  if (next) std::memcpy(next, ph.h_next, n * sizeof(int));
+  for (int i = 0, parts = argmax_parts(n, c->d.vocab); next && i < n; i++) {
+    ArgBest best{-INFINITY, 0};                              // a row without any value above -inf: token 0
+    for (const ArgBest* p = ph.h_best + (size_t)i * parts; p < ph.h_best + (size_t)(i + 1) * parts; p++)
+      if (p->value > best.value) best = *p;
+    next[i] = best.index;
+  }
   return STS_OK;
 }
 
@@ -1069,7 +1072,7 @@ int alloc_phase(sts_ctx* c, int side) {
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));
   }
   STSCK(host_alloc(&ph.h_logits, nseq * d.vocab));
-  STSCK(host_alloc(&ph.h_next, nseq));
+  STSCK(host_alloc(&ph.h_best, nseq * ARGMAX_MAX_PARTS));
   if (side == 0) {
     STSCK(dev_alloc(c, &ph.QKV, rows * c->qkvn));
     const size_t tail_floats = (size_t)c->n_cu * 256 * 256;   // one wave of partial tiles at the largest tile on every CU
@@ -1244,7 +1247,7 @@ extern "C" int sts_destroy(sts_ctx* c) {
     if (ph.ev0) (void)hipEventDestroy(ph.ev0);
     if (ph.ev1) (void)hipEventDestroy(ph.ev1);
     for (hipEvent_t e : ph.kev) (void)hipEventDestroy(e);
-    void* hosts[] = {ph.h_meta, ph.h_logits, ph.h_next};
+    void* hosts[] = {ph.h_meta, ph.h_logits, ph.h_best};
     for (void* p : hosts) if (p) (void)hipHostFree(p);
   }
   trace("destroy: device memory");

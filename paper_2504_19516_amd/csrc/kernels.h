@@ -113,8 +113,12 @@ hipError_t reduce_resid_norm(hipStream_t s, float* X, const float* partials, int
 hipError_t reduce_swiglu(hipStream_t s, bf16* H, const float* partials, int splits, long long split_stride,
                          int n, int mlp);
 hipError_t reduce_f32(hipStream_t s, float* out, const float* partials, int splits, long long split_stride, size_t n);
+// Largest value of a part of a row and its first index; index 0x7FFFFFFF: no value above -inf.
+struct ArgBest { float value; int index; };
+constexpr int ARGMAX_MAX_PARTS = 32;
+int argmax_parts(int n, int vocab);
 // copy: the logits again (pinned host memory), or null
-hipError_t argmax_rows(hipStream_t s, int* out, const float* logits, int n, int vocab, float* copy = nullptr);
+hipError_t argmax_rows(hipStream_t s, ArgBest* out, const float* logits, int n, int vocab, float* copy = nullptr);
 hipError_t copy_probe(hipStream_t s, void* dst, const void* src, size_t bytes, int grid);
 hipError_t read_probe(hipStream_t s, const void* src, size_t bytes, unsigned* sink, int grid);    // the read half alone; sink: 4 bytes of device memory
 hipError_t kv_fill_random(hipStream_t s, bf16* pool, KvGeom geo, const int* block_table, int pos0, int n,

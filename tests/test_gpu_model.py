@@ -1042,8 +1042,33 @@ def test_prefill_attention_parts_limited_by_the_work_list(sts):
     assert rel(got[0], got[1]) <= TOL
 
 
+def test_greedy_tokens_of_rows_sampled_in_parts(sts):
+    """A vocabulary of 12416 takes four parts of a row, of 3104 columns each; one of 4224 two. LM rows that repeat with period 3000 make the largest
+    logit appear several times, in different parts and inside one: the first wins. Logits are the same with and without sampling."""
+    for vocab in (12416, 4224, 128):
+        desc = synth.ModelDesc(1, 256, 4, 4, 64, 512, vocab, 16, 1.0e4, 1.0e-5, "bf16")
+        eng = new_engine(sts, desc, max_decode_batch=130, max_seqs=130, kv_pool_pages=140)
+        lm = synth.normal_bf16(861, (min(vocab, 3000), 256), 0.05)
+        eng.load_weights(0, "lm", np.concatenate([lm] * 5)[:vocab])
+        seqs = [eng.seq_create() for _ in range(130)]
+        for i, s in enumerate(seqs):
+            eng.kv_fill_random(s, 5, 870 + i)
+        toks = synth.tokens(862, 130, vocab)
+        for n in (1, 3, 17, 130):
+            got = []
+            for logits, nxt in ((True, True), (False, True), (True, False)):
+                got.append(eng.decode_step(seqs[:n], toks[:n], want_logits=logits, want_next=nxt))
+                for s in seqs[:n]:
+                    eng.seq_truncate(s, 5)
+            assert np.array_equal(got[0][0], got[2][0])
+            assert np.array_equal(got[0][1], got[0][0].argmax(1)) and np.array_equal(got[1][1], got[0][1]), (vocab, n)
+            if vocab > 3000:
+                assert np.array_equal(got[0][0][:, :vocab - 3000], got[0][0][:, 3000:]) and got[0][1].max() < 3000
+        eng.close()
+
+
 def test_results_at_the_lines_between_stored_and_copied(sts, tiny):
-    """Logits of 64 KiB (16 rows of 1024) and a row more, of 1 MiB and a row more: stored by the head, by the sampling or copied, they
+    """Logits of 64 KiB (16 rows of 1024) and a row more, of 1 MiB and a row more: stored by the head or by the sampling, they
     are the same numbers. Prompts of 512 and 513 rows (tokens and positions read from host memory, or copied first) match the oracle."""
     desc, w = tiny
     eng = new_engine(sts, desc, max_prefill_tokens=513, max_prefill_seqs=17, max_decode_batch=257, max_seqs=280, kv_pool_pages=900)
