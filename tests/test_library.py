@@ -252,6 +252,16 @@ def test_decode_chunk_sizing_stays_within_what_the_engine_allocates(sts):
         sts.decode_chunk_plan([limit + 1], 8, 32, 16, limit)       # a context longer than the block table
 
 
+@pytest.mark.parametrize("pages,cus,whole", [([10], 256, True), ([40], 256, False), ([40], 64, False), ([8, 3], 256, True), ([26] * 62, 256, True), ([26] * 64, 256, True),
+                                             ([26] * 65, 256, False), ([64] * 16, 256, True), ([65] * 16, 256, False), ([60] + [2] * 15, 256, False), ([44] * 8, 64, True),
+                                             ([16] * 16, 64, True), ([16] * 17, 64, False), ([1] * 300, 256, True), ([64], 8, True)])
+def test_decode_chunk_plan_leaves_contexts_whole_where_a_merge_costs_more(sts, pages, cus, whole):
+    """A context of up to 64 pages is one chunk where its workgroups (eight KV heads each) are resident at once and the longest one ends before the
+    chunks and their merge would; one page or one request beyond, or one long context among short ones, and it is cut as before."""
+    cp, mc, _ = sts.decode_chunk_plan(pages, 8, cus, 16, 128)
+    assert (mc == 1) == whole and cp in (8, 16, 32, 64) and mc == -(-max(pages) // cp)
+
+
 def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
     """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only where
     its whole workgroups on single CUs come out before the one-head form: the launches whose two forms were timed against each
