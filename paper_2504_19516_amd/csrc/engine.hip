@@ -434,7 +434,9 @@ double cols_time(const sts_ctx* ctx, int m, int n, int k, int per_wg, int wgs, i
 // Where partial sums are left. Slices under 16 K tiles gain nothing up to 160 rows, where either form is mostly its start and its output (4096 x 4096 in 8
 // slices: 64 rows 11.9 / 13.6 us, 96 rows 14.2 / 15.2, 160 rows 16.5 / 16.9, 223 rows 18.5 / 17.1). Longer ones, tiles / this: up to 32 rows they gain
 // however the CUs are dealt (one workgroup a CU: 4096 x 14336 of 17 rows 23.9 / 21.7 us, 8192 x 8192 of 24 rows 26.5 / 24.5; two on all 128 CUs 4096 x 14336 of 32 rows 31.3 / 29.5;
-// two on some: 10240 x 8192 of 24 rows in 4 slices 39.0 / 36.5 on 256 CUs, 37.3 / 33.2 on 192, 8192 x 28672 in 5 slices 91.6 / 83.8 on 192, 4096 x 14336 30.2 / 29.6). Up to 64 rows
+// two on some: 10240 x 8192 of 24 rows in 4 slices 39.0 / 36.5 on 256 CUs, 37.3 / 33.2 on 192, 8192 x 28672 in 5 slices 91.6 / 83.8 on 192, 4096 x 14336 30.2 / 29.6;
+// and three or four a CU, two at a time, in slices of 16 to 31 K tiles, which are short for tiles of 512 columns: on 128 CUs 10240 x 8192 of 24 rows in 6 slices 67.7 / 42.7, 8192 x 8192
+// in 8 slices 36.8 / 33.5; longer slices lose: 10240 x 8192 of 32 rows in 4 39.9 / 45.0, 8192 x 28672 in 8 93.5 / 98.1). Up to 64 rows
 // they gain with one workgroup a CU (4096 x 14336 26.0 / 25.4 us of 64) and, from 32 K tiles, where some CUs hold one and some two (10240 x 8192 of
 // 64 rows 43.4 / 40.9, 8192 x 28672 on 192 CUs 104.8 / 100.5; 26 tiles: 8192 x 8192 34.6 / 35.2), not with two on all (128 CUs: 4096 x 14336 36.1 / 36.8, 8192 x 8192 in 4 slices 38.4 / 40.5). Above, a
 // launch has to deal evenly: 288 workgroups on 256 CUs take as long as 512 (6144 x 4096 of 223 rows in 6 slices 28 us against 23), and the tiles
@@ -442,6 +444,7 @@ double cols_time(const sts_ctx* ctx, int m, int n, int k, int per_wg, int wgs, i
 bool cols_pays(const sts_ctx* ctx, int m, int n, int k, int splits, int cus, double t_tall) {
   if (cus < COLS_MIN_CUS || m > COLS_MAX_ROWS || n % 128 != 0) return false;
   const int wgs = n / 128 * splits, held = (wgs + cus - 1) / cus, len = (k / 64 + splits - 1) / splits;
+  if (m <= 32 && (held == 3 || held == 4)) return len >= 16 && len < 32;
   if (held > gemm_cols_wgs_per_cu(m)) return false;
   const bool even = held == 1 || 10 * wgs >= 9 * held * cus;
   if (m <= 32) return len >= 16;
