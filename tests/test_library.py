@@ -262,6 +262,17 @@ def test_decode_chunk_plan_leaves_contexts_whole_where_a_merge_costs_more(sts, p
     assert (mc == 1) == whole and cp in (8, 16, 32, 64) and mc == -(-max(pages) // cp)
 
 
+@pytest.mark.parametrize("pages,kv,cus", [([10], 4, 256), ([15, 9, 4, 12, 7, 10, 14, 8], 4, 128), ([26] * 62, 8, 256), ([64] * 16, 8, 256), ([44] * 8, 8, 64)])
+def test_decode_chunk_plan_cuts_contexts_of_small_heads(sts, pages, kv, cus):
+    """The costs behind whole contexts are those of heads of 128 elements: with 64 a context is cut into the chunks that fill the partition."""
+    cp, mc, _ = sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=64)
+    assert cp < max(pages) and mc == -(-max(pages) // cp)
+    assert sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=128)[1] == 1
+    for bad in (0, 32, 256):
+        with pytest.raises(sts.StsError):
+            sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=bad)
+
+
 def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
     """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only where
     its whole workgroups on single CUs come out before the one-head form: the launches whose two forms were timed against each
