@@ -721,7 +721,8 @@ int prefill_finish(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* l
 void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cus, int page_tokens, int* chunk_pages_out, int* max_chunks_out) {
   int max_pages = 1;
   for (int i = 0; i < n; i++) max_pages = std::max(max_pages, n_pages[i]);
-  int chunk_pages = attn_decode_max_chunk_tokens() / page_tokens;
+  const int limit = attn_decode_max_chunk_tokens() / page_tokens;
+  int chunk_pages = limit;
   const int floor_pages = std::max(8, (max_pages + 127) / 128);
   while (chunk_pages / 2 >= floor_pages) {
     long long wgs = 0;
@@ -736,7 +737,7 @@ void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cu
   // 62 of 400 134.7 / 126.1, of 1000 152.2 / 152.8; on 64 CUs 8 of 700 195.9 / 186.6, 16 of 250 193.6 / 187.5; hidden 8192 on 128 CUs 16 of 700 408 / 398.
   // Distance of the logits from 64 bits, mean of 15 steps: 0.008617 / 0.008562. Heads of 64 elements stay cut: whole they were 2 us a layer faster (four KV heads,
   // 1 request of 150 tokens 26.0 / 24.3) but no nearer to 64 bits (0.004103 / 0.004107 over 36 steps), and their pages of 4 KB are not what the costs above are of.
-  if (head_dim == 128 && max_pages > chunk_pages && max_pages <= attn_decode_max_chunk_tokens() / page_tokens && (long long)n * n_kv <= 2LL * cus) {
+  if (head_dim == 128 && max_pages > chunk_pages && max_pages <= limit && (long long)n * n_kv <= 2LL * cus) {
     long long total = 0, merged = 0;
     int longest = 1;
     for (int i = 0; i < n; i++) {
@@ -745,7 +746,7 @@ void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cu
     }
     const long long all = total * n_kv / std::min(cus, 114);
     if (std::max<long long>(max_pages, all) <= std::max<long long>(longest, all) + 13 + merged / 8)
-      while (chunk_pages < max_pages) chunk_pages *= 2;
+      while (chunk_pages < max_pages) chunk_pages = std::min(2 * chunk_pages, limit);
   }
   *chunk_pages_out = chunk_pages;
   *max_chunks_out = (max_pages + chunk_pages - 1) / chunk_pages;

@@ -273,6 +273,14 @@ def test_decode_chunk_plan_cuts_contexts_of_small_heads(sts, pages, kv, cus):
             sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=bad)
 
 
+@pytest.mark.parametrize("page_tokens,pages", [(12, [81] * 16), (24, [42] * 16), (48, [21] * 16), (12, [85] * 16), (10, [100] * 16), (16, [64] * 16), (20, [51, 1])])
+def test_decode_chunks_hold_no_more_than_the_kernel_takes(sts, page_tokens, pages):
+    """Page sizes whose chunk limit is no power of two: halved and doubled again, a chunk stays within the 1024 tokens the kernel takes."""
+    for cus in (8, 64, 128, 256):
+        cp, mc, _ = sts.decode_chunk_plan(pages, 8, cus, page_tokens, 128)
+        assert cp * page_tokens <= 1024 and mc == -(-max(pages) // cp), cus
+
+
 def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
     """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only where
     its whole workgroups on single CUs come out before the one-head form: the launches whose two forms were timed against each
