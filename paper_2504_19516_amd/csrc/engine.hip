@@ -1256,7 +1256,7 @@ extern "C" int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t 
 }
 extern "C" int sts_decode_chunk_plan_dim(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t head_dim, int32_t cus, int32_t page_tokens,
                                          int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks) {
-  if (!n_pages || n < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || cus < 1 || page_tokens < 1 || !chunk_pages || !max_chunks || !allocated_chunks) return STS_EINVAL;
+  if (!n_pages || n < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || cus < 1 || page_tokens < 1 || page_tokens > attn_decode_max_chunk_tokens() || !chunk_pages || !max_chunks || !allocated_chunks) return STS_EINVAL;
   for (int i = 0; i < n; i++) if (n_pages[i] < 1 || n_pages[i] > max_pages_per_seq) return STS_EINVAL;
   decode_chunk_plan(n_pages, n, n_kv_heads, head_dim, cus, page_tokens, chunk_pages, max_chunks);
   *allocated_chunks = decode_max_chunks(max_pages_per_seq);

@@ -281,6 +281,13 @@ def test_decode_chunks_hold_no_more_than_the_kernel_takes(sts, page_tokens, page
         assert cp * page_tokens <= 1024 and mc == -(-max(pages) // cp), cus
 
 
+def test_decode_chunk_plan_refuses_pages_larger_than_a_chunk(sts):
+    assert sts.decode_chunk_plan([3], 8, 256, 1024, 128)[:2] == (1, 3)
+    with pytest.raises(sts.StsError) as e:
+        sts.decode_chunk_plan([3], 8, 256, 1025, 128)
+    assert e.value.code == sts.EINVAL
+
+
 def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
     """Host logic of the prefill attention's layout (no GPU): two heads per workgroup only for d = 128 and an even group, and only where
     its whole workgroups on single CUs come out before the one-head form: the launches whose two forms were timed against each
