@@ -730,11 +730,14 @@ void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cu
     if (wgs * n_kv >= 4LL * cus) break;
     chunk_pages /= 2;
   }
-  // Contexts that fit one chunk each need no merge, whose kernel takes 2 us and its partial outputs 0.02 us a chunk more. Against that stand
+  // Contexts that fit one chunk each need no merge, whose kernel takes 2 us and its partial outputs 0.02 us a chunk of eight KV heads
+  // more (of fewer heads as much less). Against that stand
   // the longest context in one workgroup, which reads a page of a KV head (8 KB) in 0.15 us, and all pages at what the CUs, or from 114 of them
   // on the memory, give; all in pages here. Only where every workgroup is resident at once. Cut / whole, us a layer: hidden 4096 on
   // 256 CUs 1 request of 150 tokens 88.0 / 86.4 (from 300 tokens on it stays cut: 88.7 / 89.8 at 450), 16 of 700 107.3 / 104.2, 32 of 700 122.1 / 115.1,
   // 62 of 400 134.7 / 126.1, of 1000 152.2 / 152.8; on 64 CUs 8 of 700 195.9 / 186.6, 16 of 250 193.6 / 187.5; hidden 8192 on 128 CUs 16 of 700 408 / 398.
+  // Fewer heads, hidden 2048: two 32 requests of 400 61.7 / 61.8 (of 700, 64.0 / 64.7, and of 1000, 65.3 / 67.6, they stay cut), four 32 of 700 67.9 / 64.9 (16 of 700, 51.9 / 52.7,
+  // and of 1000, 53.0 / 55.9, stay cut). More than eight are counted as eight: 32 heads 16 of 400 113.2 / 110.1.
   // Distance of the logits from 64 bits, mean of 15 steps: 0.008617 / 0.008562. Heads of 64 elements stay cut: whole they were 2 us a layer faster (four KV heads,
   // 1 request of 150 tokens 26.0 / 24.3) but no nearer to 64 bits (0.004103 / 0.004107 over 36 steps), and their pages of 4 KB are not what the costs above are of.
   if (head_dim == 128 && max_pages > chunk_pages && max_pages <= limit && (long long)n * n_kv <= 2LL * cus) {
@@ -745,7 +748,7 @@ void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cu
       total += n_pages[i]; merged += chunks > 1 ? chunks : 0; longest = std::max(longest, (n_pages[i] + chunks - 1) / chunks);
     }
     const long long all = total * n_kv / std::min(cus, 114);
-    if (std::max<long long>(max_pages, all) <= std::max<long long>(longest, all) + 13 + merged / 8)
+    if (std::max<long long>(max_pages, all) <= std::max<long long>(longest, all) + 13 + merged * std::min(n_kv, 8) / 64)
       while (chunk_pages < max_pages) chunk_pages = std::min(2 * chunk_pages, limit);
   }
   *chunk_pages_out = chunk_pages;

@@ -273,6 +273,14 @@ def test_decode_chunk_plan_cuts_contexts_of_small_heads(sts, pages, kv, cus):
             sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=bad)
 
 
+@pytest.mark.parametrize("pages,kv,cus,whole", [([63] * 16, 4, 256, False), ([44] * 16, 4, 256, False), ([44] * 32, 4, 256, True), ([63] * 64, 4, 256, True),
+                                                ([26] * 16, 2, 256, False), ([63] * 32, 2, 256, False), ([26] * 32, 2, 256, True), ([10] * 16, 2, 256, True), ([26] * 16, 32, 256, True)])
+def test_decode_chunk_plan_prices_a_merge_by_its_heads(sts, pages, kv, cus, whole):
+    """A chunk's partial outputs are those of the KV heads that a model has: with two or four of them a merge is cheaper, and contexts that eight heads
+    would leave whole stay cut."""
+    assert (sts.decode_chunk_plan(pages, kv, cus, 16, 128)[1] == 1) == whole
+
+
 @pytest.mark.parametrize("page_tokens,pages", [(12, [81] * 16), (24, [42] * 16), (48, [21] * 16), (12, [85] * 16), (10, [100] * 16), (16, [64] * 16), (20, [51, 1])])
 def test_decode_chunks_hold_no_more_than_the_kernel_takes(sts, page_tokens, pages):
     """Page sizes whose chunk limit is no power of two: halved and doubled again, a chunk stays within the 1024 tokens the kernel takes."""
