@@ -109,10 +109,16 @@ int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus, int32_t m
                          int64_t* est_ns);
 
 /* The same of the four GEMMs of a layer -- QKV, O, gate/up, down -- as the engine will run a decode step of `batch` requests on `cus` CUs
- * with the ctx's tile and stream models; from 128 CUs a GEMM may run the same slices in the form of sts_op_gemm_cols, where that is estimated
- * faster. tile_cfg -1: the form that cuts K inside the workgroups and finishes its own output (few
+ * with the ctx's tile and stream models; from 128 CUs a GEMM may run the same slices in the form of sts_op_gemm_cols instead of these tiles
+ * (sts_decode_layer_all_rows says which). tile_cfg -1: the form that cuts K inside the workgroups and finishes its own output (few
  * rows). row_tiles: row tiles of a 256x256 launch, 0 = as few as 256 rows allow. Arrays of 4. */
 int sts_decode_layer_plan(sts_ctx* ctx, int32_t batch, int32_t cus, int32_t* tile_cfg, int32_t* split_k, int32_t* row_tiles);
+/* Which of them run in the form of sts_op_gemm_cols, with all rows in a workgroup (1), and not in tiles (0). Array of 4. */
+int sts_decode_layer_all_rows(sts_ctx* ctx, int32_t batch, int32_t cus, int32_t* all_rows);
+/* Host only, no GPU state: the same of one GEMM that leaves partial sums, or (swiglu) of gate/up, whose n weight rows are gate and up. Rates as
+ * in sts_set_tile_model and sts_set_stream_model; not for layers of up to 16 rows that finish their own output. */
+int sts_decode_gemm_all_rows(int32_t m, int32_t n, int32_t k, int32_t cus, int32_t swiglu, int64_t gemm_rate_128, int64_t gemm_rate_256, int64_t partial_bw_cu,
+                             int64_t stream_bw_cu, int64_t stream_bw_gpu, int32_t* all_rows);
 
 /* Weights. `name`: "emb", "lm" (layer ignored), "wq","wk","wv","wo","wg","wu","wd" (matrices,
  * row-major [out_features, in_features] fp32, rounded to bf16 on upload) or "g1","g2","gf"

@@ -330,12 +330,13 @@ int plan_splits(double rate_256, double partial_bw, int cfg, int m, int n, int k
 // rounds.
 // `partials`: the output goes through fp32 partial sums (a split needs that; the caller's next kernel reads them).
 // Returns the estimated seconds.
-struct StreamRates { double rate_256, partial_bw, stream_bw_cu, stream_bw_gpu; };
+struct StreamRates { double rate_128, rate_256, partial_bw, stream_bw_cu, stream_bw_gpu; };
 double plan_decode_gemm(const StreamRates& r, int m, int n, int k, int cus, bool may_split, bool partials, int* cfg, int* splits);
+StreamRates rates_of(const sts_ctx* ctx) { return StreamRates{ctx->rate_128, ctx->rate_256, ctx->partial_bw, ctx->stream_bw_cu, ctx->stream_bw_gpu}; }
 double pick_decode_gemm(const sts_ctx* ctx, int m, int n, int k, int cus, bool may_split, bool partials, int* cfg, int* splits) {
-  return plan_decode_gemm(StreamRates{ctx->rate_256, ctx->partial_bw, ctx->stream_bw_cu, ctx->stream_bw_gpu}, m, n, k, cus, may_split, partials, cfg, splits);
+  return plan_decode_gemm(rates_of(ctx), m, n, k, cus, may_split, partials, cfg, splits);
 }
-// r: measured on the part by the offline profiler -- rate_256 (TFLOP/s per busy CU of the 256x256 tile) and partial_bw (bytes/s
+// r: measured on the part by the offline profiler -- rate_128 and rate_256 (TFLOP/s per busy CU of 128x128 and 256x256 tiles) and partial_bw (bytes/s
 // per CU for partial sums) of the tile model; stream_bw_cu and stream_bw_gpu, what a plain read-only stream reaches per CU of a
 // 32-CU partition and on the whole GPU. A GEMM's weight stream gets 0.93 and 0.85 of those (its loads share the CU with the
 // operand reads and the matrix cores; the best decode GEMMs measured 55 of 58-59 GB/s per CU and 5.1 of 6 TB/s).
@@ -405,7 +406,7 @@ struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu
 // bits. Estimate: rounds of workgroups at the tile's rate; the first loads and the partial sums of a launch, 8 us, are much the same for all
 // shapes and left out. Measured / estimated (with the 8 us) at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
 // slices 21 / 20 in one, 16 / 16 in two; 4096 x 14336 48 / 51 and 39 / 36; 28672 x 4096 in 2 slices 58 / 57 in one row tile.
-double pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, int cus, DecodeGemm* g) {
+double pick_tall_tiles(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g) {
   if (m <= 64 || n % 256 != 0) return HUGE_VAL;
   const int c = std::max(cus, 8), ksteps = k / 64, len = (ksteps + g->splits - 1) / g->splits * 64, blocks = (m + 31) / 32;
   double best = 1e300;
@@ -413,8 +414,8 @@ double pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, in
     const double t = (double)((wgs + slots - 1) / slots) * tile_s;
     if (t < best) { best = t; g->cfg = cfg; g->row_tiles = row_tiles; }
   };
-  consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (rate_128 * 1e12 / 2));
-  const double tall_s = 2.0 * 256 * 256 * len / (rate_256 * 1e12);
+  consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (r.rate_128 * 1e12 / 2));
+  const double tall_s = 2.0 * 256 * 256 * len / (r.rate_256 * 1e12);
   const int least = (blocks + 7) / 8;
   for (int t = least; t <= std::min(blocks, 2 * least + 2); t++)
     consider(GEMM_256x256, t, (long long)t * (n / 256) * g->splits, c, TILE_HEIGHT_COST[(blocks + t - 1) / t - 1] * tall_s);
@@ -427,9 +428,9 @@ double pick_tall_tiles(double rate_128, double rate_256, int m, int n, int k, in
 // 67 / 63; 57344 x 8192: 96 rows 161 / 161, 192 rows 194 / 188, 256 rows 229 / 224 (tiles and their reduce kernel 214: they stay). Partitions below 128 CUs are not measured:
 // there the wide tiles of up to 64 rows read the activations less often.
 constexpr int COLS_MIN_CUS = 128;
-double cols_time(const sts_ctx* ctx, int m, int n, int k, int per_wg, int wgs, int cus) {
+double cols_time(const StreamRates& r, int m, int n, int k, int per_wg, int wgs, int cus) {
   const int held = (wgs + cus - 1) / cus, rows = (m + 31) / 32 * 32;
-  return std::max(held * 2.0 * per_wg * (rows + 128) / ctx->stream_bw_cu, 2.0 * n * k / (0.95 * ctx->stream_bw_gpu)) + 9e-6;
+  return std::max(held * 2.0 * per_wg * (rows + 128) / r.stream_bw_cu, 2.0 * n * k / (0.95 * r.stream_bw_gpu)) + 9e-6;
 }
 // Where partial sums are left. Slices under 16 K tiles gain nothing up to 160 rows, where either form is mostly its start and its output (4096 x 4096 in 8
 // slices: 64 rows 11.9 / 13.6 us, 96 rows 14.2 / 15.2, 160 rows 16.5 / 16.9, 223 rows 18.5 / 17.1). Longer ones, tiles / this: up to 32 rows they gain
@@ -441,7 +442,7 @@ double cols_time(const sts_ctx* ctx, int m, int n, int k, int per_wg, int wgs, i
 // 64 rows 43.4 / 40.9, 8192 x 28672 on 192 CUs 104.8 / 100.5; 26 tiles: 8192 x 8192 34.6 / 35.2), not with two on all (128 CUs: 4096 x 14336 36.1 / 36.8, 8192 x 8192 in 4 slices 38.4 / 40.5). Above, a
 // launch has to deal evenly: 288 workgroups on 256 CUs take as long as 512 (6144 x 4096 of 223 rows in 6 slices 28 us against 23), and the tiles
 // are taken at nine tenths of the estimate that chose their shape, which rests on a slower tile's rate.
-bool cols_pays(const sts_ctx* ctx, int m, int n, int k, int splits, int cus, double t_tall) {
+bool cols_pays(const StreamRates& r, int m, int n, int k, int splits, int cus, double t_tall) {
   if (cus < COLS_MIN_CUS || m > COLS_MAX_ROWS || n % 128 != 0) return false;
   const int wgs = n / 128 * splits, held = (wgs + cus - 1) / cus, len = (k / 64 + splits - 1) / splits;
   if (m <= 32 && (held == 3 || held == 4)) return len >= 16 && len < 32;
@@ -449,31 +450,35 @@ bool cols_pays(const sts_ctx* ctx, int m, int n, int k, int splits, int cus, dou
   const bool even = held == 1 || 10 * wgs >= 9 * held * cus;
   if (m <= 32) return len >= 16;
   if (m <= 64) return held == 1 ? len >= 16 : !even && len >= 32;
-  return even && (len >= 16 || m > 160) && cols_time(ctx, m, n, k, len * 64, wgs, cus) < std::max(0.9 * t_tall, 2.0 * n * k / (0.85 * ctx->stream_bw_gpu)) + 9e-6;
+  return even && (len >= 16 || m > 160) && cols_time(r, m, n, k, len * 64, wgs, cus) < std::max(0.9 * t_tall, 2.0 * n * k / (0.85 * r.stream_bw_gpu)) + 9e-6;
+}
+
+// A GEMM whose partial sums the layer's next kernel adds up, and gate/up, whose SwiGLU is its epilogue or (not fused) that kernel's. Both return
+// the estimate that the choice between the layer's forms goes by, which is of the tiles.
+double plan_partials(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g) {
+  const double t = plan_decode_gemm(r, m, n, k, cus, true, true, &g->cfg, &g->splits);
+  g->cols = cols_pays(r, m, n, k, g->splits, cus, pick_tall_tiles(r, m, n, k, cus, g));
+  return t;
+}
+double plan_gateup(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g, bool* gu_fused) {
+  DecodeGemm fused;
+  const double t_split = plan_decode_gemm(r, m, n, k, cus, true, true, &g->cfg, &g->splits) + 4e-6;
+  const double t_fused = plan_decode_gemm(r, m, n, k, cus, false, false, &fused.cfg, &fused.splits);
+  const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
+  *gu_fused = can_fuse && (t_fused <= t_split || g->splits == 1);
+  if (*gu_fused) { *g = fused; return t_fused; }
+  const double t_tall = pick_tall_tiles(r, m, n, k, cus, g), w_bytes = 2.0 * n * k, part_bytes = 4.0 * g->splits * m * n;
+  const double t_two = m <= 64 ? t_split : std::max(0.9 * t_tall, w_bytes / (0.85 * r.stream_bw_gpu)) + 9e-6 + SMALL_KERNEL_S + part_bytes / (0.9 * r.stream_bw_gpu);
+  g->cols = cus >= COLS_MIN_CUS && m <= COLS_MAX_ROWS && cols_time(r, m, n, k, k, n / 128, cus) < t_two;
+  return t_split;
 }
 
 DecodePlan decode_layer_plan(const sts_ctx* ctx, int n, int cus) {
   const sts_model_desc& d = ctx->d;
+  const StreamRates r = rates_of(ctx);
   DecodePlan p;
-  DecodeGemm fused;
-  double t = pick_decode_gemm(ctx, n, ctx->qkvn, d.hidden, cus, true, true, &p.qkv.cfg, &p.qkv.splits);
-  t += pick_decode_gemm(ctx, n, d.hidden, ctx->qd, cus, true, true, &p.o.cfg, &p.o.splits);
-  t += pick_decode_gemm(ctx, n, d.hidden, d.mlp, cus, true, true, &p.down.cfg, &p.down.splits);
-  const double t_split = pick_decode_gemm(ctx, n, 2 * d.mlp, d.hidden, cus, true, true, &p.gu.cfg, &p.gu.splits) + 4e-6;
-  const double t_fused = pick_decode_gemm(ctx, n, 2 * d.mlp, d.hidden, cus, false, false, &fused.cfg, &fused.splits);
-  const bool can_fuse = fused.cfg == GEMM_64x128 || (fused.cfg >= GEMM_64x256S && fused.cfg <= GEMM_64x512S);
-  if (can_fuse && (t_fused <= t_split || p.gu.splits == 1)) { p.gu_fused = true; p.gu = fused; }
-  t += (p.gu_fused ? t_fused : t_split) + 3 * SMALL_KERNEL_S;
-  auto tall = [&](int gn, int gk, DecodeGemm* g) { return pick_tall_tiles(ctx->rate_128, ctx->rate_256, n, gn, gk, cus, g); };
-  auto partials = [&](int gn, int gk, DecodeGemm* g) { g->cols = cols_pays(ctx, n, gn, gk, g->splits, cus, tall(gn, gk, g)); };
-  partials(ctx->qkvn, d.hidden, &p.qkv);
-  partials(d.hidden, ctx->qd, &p.o);
-  partials(d.hidden, d.mlp, &p.down);
-  if (!p.gu_fused) {
-    const double t_tall = tall(2 * d.mlp, d.hidden, &p.gu), w_bytes = 4.0 * d.mlp * d.hidden, part_bytes = 8.0 * p.gu.splits * n * d.mlp;
-    const double t_two = n <= 64 ? t_split : std::max(0.9 * t_tall, w_bytes / (0.85 * ctx->stream_bw_gpu)) + 9e-6 + SMALL_KERNEL_S + part_bytes / (0.9 * ctx->stream_bw_gpu);
-    p.gu.cols = cus >= COLS_MIN_CUS && n <= COLS_MAX_ROWS && cols_time(ctx, n, 2 * d.mlp, d.hidden, d.hidden, d.mlp / 64, cus) < t_two;
-  }
+  double t = plan_partials(r, n, ctx->qkvn, d.hidden, cus, &p.qkv) + plan_partials(r, n, d.hidden, ctx->qd, cus, &p.o) + plan_partials(r, n, d.hidden, d.mlp, cus, &p.down);
+  t += plan_gateup(r, n, 2 * d.mlp, d.hidden, cus, &p.gu, &p.gu_fused) + 3 * SMALL_KERNEL_S;
   if (n <= KSLICE_MAX_ROWS)
     p.kslice = kslice_time(ctx, KS_QKV, n, ctx->qkvn, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, ctx->qd, cus) +
                kslice_time(ctx, KS_SWIGLU, n, 2 * d.mlp, d.hidden, cus) + kslice_time(ctx, KS_RESID, n, d.hidden, d.mlp, cus) < t;
@@ -940,7 +945,7 @@ bool prefill_few_rows(sts_ctx* c, Phase& ph, int rows, const PrefillGemm (&tiles
       const int len = (k / 64 + cut - 1) / cut, used = (k / 64 + len - 1) / len;
       *gm[i] = DecodeGemm{GEMM_128x128, used, 0, true};
       t_tiles += std::max(0.75 * tiles[i].est_s, 2.0 * n * k / (0.85 * c->stream_bw_gpu)) + 12e-6;
-      t_cols += cols_time(c, rows, n, k, len * 64, n / 128 * used, ph.cus) + (i == 3 ? 0.0 : SMALL_KERNEL_S + 4.0 * used * rows * n / 4e12);
+      t_cols += cols_time(rates_of(c), rows, n, k, len * 64, n / 128 * used, ph.cus) + (i == 3 ? 0.0 : SMALL_KERNEL_S + 4.0 * used * rows * n / 4e12);
     }
     if (t_tiles <= 1.03 * t_cols) return false;
     p.gu_fused = false;
@@ -1230,10 +1235,10 @@ extern "C" int sts_decode_gemm_plan(int32_t m, int32_t n, int32_t k, int32_t cus
   if (m < 1 || n < 128 || n % 128 != 0 || k < 64 || k % 64 != 0 || cus < 1 || gemm_rate_256 < 1 || partial_bw_cu < 1 || stream_bw_cu < 1 ||
       stream_bw_gpu < 1 || !tile_cfg || !split_k) return STS_EINVAL;
   int cfg = 0, splits = 1;
-  const StreamRates r{gemm_rate_256 * 1e-3, partial_bw_cu * 1e6, stream_bw_cu * 1e6, stream_bw_gpu * 1e6};
+  const StreamRates r{0.757 * gemm_rate_256 * 1e-3, gemm_rate_256 * 1e-3, partial_bw_cu * 1e6, stream_bw_cu * 1e6, stream_bw_gpu * 1e6};
   const double t = plan_decode_gemm(r, m, n, k, cus, may_split != 0, partials != 0, &cfg, &splits);
   DecodeGemm g{cfg, splits, 0};
-  if (partials) pick_tall_tiles(0.757 * r.rate_256, r.rate_256, m, n, k, cus, &g);
+  if (partials) pick_tall_tiles(r, m, n, k, cus, &g);
   *tile_cfg = g.cfg; *split_k = splits;
   if (est_ns) *est_ns = (int64_t)(t * 1e9);
   return STS_OK;
@@ -1243,6 +1248,25 @@ extern "C" int sts_decode_layer_plan(sts_ctx* c, int32_t batch, int32_t cus, int
   const DecodePlan p = decode_layer_plan(c, batch, cus);
   const DecodeGemm g[4] = {p.qkv, p.o, p.gu, p.down};
   for (int i = 0; i < 4; i++) { tile_cfg[i] = p.kslice ? -1 : g[i].cfg; split_k[i] = p.kslice ? 1 : g[i].splits; row_tiles[i] = p.kslice ? 0 : g[i].row_tiles; }
+  return STS_OK;
+}
+extern "C" int sts_decode_layer_all_rows(sts_ctx* c, int32_t batch, int32_t cus, int32_t* all_rows) {
+  if (!c || batch < 1 || batch > c->p.max_decode_batch || cus < 8 || cus > c->n_cu || cus % 8 != 0 || !all_rows) return STS_EINVAL;
+  const DecodePlan p = decode_layer_plan(c, batch, cus);
+  const DecodeGemm g[4] = {p.qkv, p.o, p.gu, p.down};
+  for (int i = 0; i < 4; i++) all_rows[i] = !p.kslice && g[i].cols;
+  return STS_OK;
+}
+extern "C" int sts_decode_gemm_all_rows(int32_t m, int32_t n, int32_t k, int32_t cus, int32_t swiglu, int64_t gemm_rate_128, int64_t gemm_rate_256, int64_t partial_bw_cu,
+                                        int64_t stream_bw_cu, int64_t stream_bw_gpu, int32_t* all_rows) {
+  if (m < 1 || n < 128 || n % 128 != 0 || k < 64 || k % 64 != 0 || cus < 1 || gemm_rate_128 < 1 || gemm_rate_256 < 1 || partial_bw_cu < 1 || stream_bw_cu < 1 ||
+      stream_bw_gpu < 1 || !all_rows) return STS_EINVAL;
+  const StreamRates r{gemm_rate_128 * 1e-3, gemm_rate_256 * 1e-3, partial_bw_cu * 1e6, stream_bw_cu * 1e6, stream_bw_gpu * 1e6};
+  DecodeGemm g;
+  bool fused;
+  if (swiglu) plan_gateup(r, m, n, k, cus, &g, &fused);
+  else plan_partials(r, m, n, k, cus, &g);
+  *all_rows = g.cols;
   return STS_OK;
 }
 extern "C" int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const int32_t* priors, int32_t n_q, int32_t n_kv, int32_t d, int32_t cus,

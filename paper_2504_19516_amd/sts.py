@@ -93,7 +93,7 @@ EXPORTS = [
     "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_fail_launch", "sts_kernel_name",
     "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
-    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_chunk_plan_dim", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_op_gemm_cols", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
+    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_chunk_plan_dim", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_decode_layer_all_rows", "sts_decode_gemm_all_rows", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_op_gemm_cols", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
     "sts_profile_tile_model",
 ]
 
@@ -286,6 +286,12 @@ class Engine:
         name = {v: k for k, v in GEMM_CFGS.items()}
         return [(name.get(int(c), "kslice"), int(s), int(r)) for c, s, r in zip(cfg, sp, rt)]
 
+    def decode_layer_all_rows(self, batch, cus):
+        """Which of these GEMMs run in the form of op_gemm_cols."""
+        r = np.empty(4, np.int32)
+        _ck(lib().sts_decode_layer_all_rows(self._ctx, batch, cus, _p(r)), "sts_decode_layer_all_rows")
+        return [bool(x) for x in r]
+
     def fail_launch(self, phase, after):
         """For tests: the launch after `after` further ones of the phase is reported as failed and not queued."""
         _ck(lib().sts_fail_launch(self._ctx, phase, after), "sts_fail_launch")
@@ -457,6 +463,14 @@ def decode_gemm_plan(m, n, k, cus, may_split=True, partials=True, gemm_rate_256=
         "sts_decode_gemm_plan")
     name = {v: k_ for k_, v in GEMM_CFGS.items()}[cfg.value]
     return name, sp.value, ns.value
+
+
+def decode_gemm_all_rows(m, n, k, cus, swiglu=False, gemm_rate_128=3766, gemm_rate_256=4974, partial_bw_cu=22595, stream_bw_cu=58464, stream_bw_gpu=6507368):
+    """Whether a decode step runs this GEMM (gate/up: swiglu) in the form of op_gemm_cols; host only."""
+    r = C.c_int32()
+    _ck(lib().sts_decode_gemm_all_rows(m, n, k, cus, int(swiglu), C.c_int64(int(gemm_rate_128)), C.c_int64(int(gemm_rate_256)), C.c_int64(int(partial_bw_cu)),
+                                       C.c_int64(int(stream_bw_cu)), C.c_int64(int(stream_bw_gpu)), C.byref(r)), "sts_decode_gemm_all_rows")
+    return bool(r.value)
 
 
 # ---- performance estimator and scheduler (host only)

@@ -741,6 +741,35 @@ def test_decode_gemm_plan_is_what_the_engine_runs(sts):
     eng.close()
 
 
+def test_decode_gemm_forms_are_what_the_engine_runs(sts):
+    """The host-only choice of each GEMM's form against that of a layer, and what a step launches: gate/up with all rows in a workgroup leaves no
+    partial sums, so no SwiGLU kernel follows it."""
+    p = sts.Profile(path=os.path.join(os.path.dirname(sts.__file__), "data", "mi355x_llama8b.profile"))
+    r128, r256, _, _, part = p.tile_model()
+    desc = synth.ModelDesc(1, 4096, 32, 8, 128, 14336, 512, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=85, max_decode_batch=256, max_seqs=256)
+    eng.set_tile_model(*p.tile_model())
+    eng.set_stream_model(*p.stream_model())
+    seqs, tok, seen = [eng.seq_create() for _ in range(256)], synth.tokens(86, 256, 512), set()
+    eng.kernel_timing(True)
+    for cus in (64, 128, 192, 256):
+        eng.set_partition(256, cus)
+        for n in (1, 16, 17, 24, 64, 65, 96, 160, 223, 256):
+            forms, plan = eng.decode_layer_all_rows(n, cus), eng.decode_layer_plan(n, cus)
+            kslice = plan[0][0] == "kslice"
+            for i, (gn, gk) in enumerate(((6144, 4096), (4096, 4096), (28672, 4096), (4096, 14336))):
+                assert forms[i] == (not kslice and sts.decode_gemm_all_rows(n, gn, gk, cus, i == 2, r128, r256, part, *p.stream_model())), (n, cus, i)
+            eng.kernel_times(1, reset=True)
+            eng.decode_step(seqs[:n], tok[:n])
+            for s in seqs[:n]:
+                eng.seq_truncate(s, 0)
+            fused = n <= 64 and plan[2][1] == 1
+            assert ("swiglu" in eng.kernel_times(1, reset=True)) == (not kslice and not forms[2] and not fused), (n, cus)
+            seen.add((forms[2], forms[3]))
+    assert len(seen) > 2
+    eng.close()
+
+
 @pytest.mark.parametrize("cus", [256, 32])
 @pytest.mark.parametrize("n", [65, 96, 97, 128, 129, 224, 225, 256])
 def test_decode_gemm_tiles_above_64_rows(many_requests, n, cus):

@@ -318,6 +318,21 @@ def test_attn_prefill_plan_pairs_heads_where_that_is_faster():
         assert e.value.code == sts.EINVAL
 
 
+@pytest.mark.parametrize("n,k,swiglu,cus,yes,no", [(4096, 14336, False, 256, (17, 32, 64, 65, 96, 128, 160, 192, 193, 223, 256), (257, 300)),
+                                                   (28672, 4096, True, 256, (17, 24, 64, 65, 96, 128, 223, 256), (257, 400)),
+                                                   (4096, 4096, False, 256, (), (17, 32, 33, 64, 65, 96, 128, 160)),
+                                                   (8192, 28672, False, 256, (17, 64, 65, 96, 160, 192), (193, 256, 257)),
+                                                   (4096, 14336, False, 96, (), (17, 64, 96, 223)), (28672, 4096, True, 96, (), (17, 64, 96, 223)),
+                                                   (4096, 14336, False, 120, (), (17, 64, 96, 223)), (28672, 4096, True, 120, (), (17, 64, 96, 223))])
+def test_decode_gemm_form_at_its_edges(sts, n, k, swiglu, cus, yes, no):
+    """Where a decode GEMM takes all its rows in one workgroup: from 128 CUs, 17 to 256 rows, slices long enough, launches that deal evenly."""
+    for m in yes + no:
+        assert sts.decode_gemm_all_rows(m, n, k, cus, swiglu) == (m in yes), m
+    for bad in ((0, n, k, cus), (17, 64, k, cus), (17, n + 64, k, cus), (17, n, 96, cus), (17, n, k, 0)):
+        with pytest.raises(sts.StsError):
+            sts.decode_gemm_all_rows(*bad)
+
+
 def test_decode_gemm_plan_fits_tiles_to_the_partition():
     """Host logic of the decode GEMM planner (no GPU): the tile width divides N, the split stays within what the K extent
     feeds and the library accepts (at most 8 slices of at least 512 columns); a GEMM that has to finish its own output is
