@@ -407,7 +407,7 @@ struct DecodePlan { bool kslice = false, gu_fused = false; DecodeGemm qkv, o, gu
 // shapes and left out. Measured / estimated (with the 8 us) at 223 rows on 256 CUs: 6144 x 4096 in 6 slices 31 / 32 us as 128x128, 26 / 25 in one row tile, 29 / 30 in two; 4096 x 4096 in 8
 // slices 21 / 20 in one, 16 / 16 in two; 4096 x 14336 48 / 51 and 39 / 36; 28672 x 4096 in 2 slices 58 / 57 in one row tile.
 double pick_tall_tiles(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g) {
-  if (m <= 64 || n % 256 != 0) return HUGE_VAL;
+  if (m <= 64) return HUGE_VAL;
   const int c = std::max(cus, 8), ksteps = k / 64, len = (ksteps + g->splits - 1) / g->splits * 64, blocks = (m + 31) / 32;
   double best = 1e300;
   auto consider = [&](int cfg, int row_tiles, long long wgs, int slots, double tile_s) {
@@ -417,7 +417,7 @@ double pick_tall_tiles(const StreamRates& r, int m, int n, int k, int cus, Decod
   consider(GEMM_128x128, 0, (long long)((m + 127) / 128) * (n / 128) * g->splits, 2 * c, 2.0 * 128 * 128 * len / (r.rate_128 * 1e12 / 2));
   const double tall_s = 2.0 * 256 * 256 * len / (r.rate_256 * 1e12);
   const int least = (blocks + 7) / 8;
-  for (int t = least; t <= std::min(blocks, 2 * least + 2); t++)
+  for (int t = least; n % 256 == 0 && t <= std::min(blocks, 2 * least + 2); t++)
     consider(GEMM_256x256, t, (long long)t * (n / 256) * g->splits, c, TILE_HEIGHT_COST[(blocks + t - 1) / t - 1] * tall_s);
   return best;
 }
@@ -469,7 +469,11 @@ double plan_gateup(const StreamRates& r, int m, int n, int k, int cus, DecodeGem
   if (*gu_fused) { *g = fused; return t_fused; }
   const double t_tall = pick_tall_tiles(r, m, n, k, cus, g), w_bytes = 2.0 * n * k, part_bytes = 4.0 * g->splits * m * n;
   const double t_two = m <= 64 ? t_split : std::max(0.9 * t_tall, w_bytes / (0.85 * r.stream_bw_gpu)) + 9e-6 + SMALL_KERNEL_S + part_bytes / (0.9 * r.stream_bw_gpu);
-  g->cols = cus >= COLS_MIN_CUS && m <= COLS_MAX_ROWS && cols_time(r, m, n, k, k, n / 128, cus) < t_two;
+  // Widths without 256-column tiles (odd multiples of 128) leave 128x128 tiles, which were slower than their estimate and than all rows in a workgroup in each
+  // of 105 launches on 128 to 256 CUs: 28800 x 4224 of 96 rows 76.7 / 49.9 us and of 256 rows 109.3 / 73.4 on 256 CUs, 57472 x 8192 of 128 rows on 128 CUs 317 / 303,
+  // 11392 x 2176 of 65 rows on 256 CUs 25.0 / 22.9.
+  const bool no_tall = m > 64 && n % 256 != 0;
+  g->cols = cus >= COLS_MIN_CUS && m <= COLS_MAX_ROWS && (no_tall || cols_time(r, m, n, k, k, n / 128, cus) < t_two);
   return t_split;
 }
 

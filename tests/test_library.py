@@ -333,6 +333,20 @@ def test_decode_gemm_form_at_its_edges(sts, n, k, swiglu, cus, yes, no):
             sts.decode_gemm_all_rows(*bad)
 
 
+def test_decode_gemm_form_of_widths_without_256_column_tiles(sts):
+    """An odd multiple of 128 columns has 128x128 tiles alone above 64 rows: gate/up takes all rows in a workgroup, partial sums weigh both estimates."""
+    for n, k in ((4224, 4096), (11392, 2176), (28800, 4224), (57472, 8192)):
+        for cus in (128, 192, 256):
+            for m in (65, 96, 160, 256):
+                assert sts.decode_gemm_all_rows(m, n, k, cus, True), (m, n, k, cus)
+                assert sts.decode_gemm_plan(m, n, k, cus)[0] == "128x128"
+            assert not sts.decode_gemm_all_rows(257, n, k, cus, True)
+    # partial sums: tiles that were fast enough would be taken, so their estimate is their own and not infinite
+    fast = dict(gemm_rate_128=10 ** 6, gemm_rate_256=10 ** 6, stream_bw_gpu=10 ** 9)
+    for m in (96, 160, 192, 256):
+        assert sts.decode_gemm_all_rows(m, 3968, 14336, 256) and not sts.decode_gemm_all_rows(m, 3968, 14336, 256, **fast), m
+
+
 def test_decode_gemm_plan_fits_tiles_to_the_partition():
     """Host logic of the decode GEMM planner (no GPU): the tile width divides N, the split stays within what the K extent
     feeds and the library accepts (at most 8 slices of at least 512 columns); a GEMM that has to finish its own output is
