@@ -425,39 +425,49 @@ double pick_tall_tiles(const StreamRates& r, int m, int n, int k, int cus, Decod
 // gemm_cols in the place of tiles for the same slices (the same bits): it leaves partial sums as they do, or takes gate/up whole with
 // SwiGLU. Estimate of a launch: the lines its workgroups make a CU pull, or the weights at the whole GPU's rate, and 9 us of first loads,
 // output and launch. Measured / estimated on 256 CUs, 28672 x 4096 with SwiGLU: 64 rows 40 / 47 us, 128 rows 50 / 47, 192 rows 56 / 49, 256 rows
-// 67 / 63; 57344 x 8192: 96 rows 161 / 161, 192 rows 194 / 188, 256 rows 229 / 224 (tiles and their reduce kernel 214: they stay). Partitions below 128 CUs are not measured:
-// there the wide tiles of up to 64 rows read the activations less often.
-constexpr int COLS_MIN_CUS = 128;
+// 67 / 63; 57344 x 8192: 96 rows 161 / 161, 192 rows 194 / 188, 256 rows 229 / 224 (tiles and their reduce kernel 214: they stay).
 double cols_time(const StreamRates& r, int m, int n, int k, int per_wg, int wgs, int cus) {
   const int held = (wgs + cus - 1) / cus, rows = (m + 31) / 32 * 32;
   return std::max(held * 2.0 * per_wg * (rows + 128) / r.stream_bw_cu, 2.0 * n * k / (0.95 * r.stream_bw_gpu)) + 9e-6;
 }
-// Where partial sums are left. Slices under 16 K tiles gain nothing up to 160 rows, where either form is mostly its start and its output (4096 x 4096 in 8
-// slices: 64 rows 11.9 / 13.6 us, 96 rows 14.2 / 15.2, 160 rows 16.5 / 16.9, 223 rows 18.5 / 17.1). Longer ones, tiles / this: up to 32 rows they gain
-// however the CUs are dealt (one workgroup a CU: 4096 x 14336 of 17 rows 23.9 / 21.7 us, 8192 x 8192 of 24 rows 26.5 / 24.5; two on all 128 CUs 4096 x 14336 of 32 rows 31.3 / 29.5;
-// two on some: 10240 x 8192 of 24 rows in 4 slices 39.0 / 36.5 on 256 CUs, 37.3 / 33.2 on 192, 8192 x 28672 in 5 slices 91.6 / 83.8 on 192, 4096 x 14336 30.2 / 29.6;
-// and three or four a CU, two at a time, in slices of 16 to 31 K tiles, which are short for tiles of 512 columns: on 128 CUs 10240 x 8192 of 24 rows in 6 slices 67.7 / 42.7, 8192 x 8192
-// in 8 slices 36.8 / 33.5; longer slices lose: 10240 x 8192 of 32 rows in 4 39.9 / 45.0, 8192 x 28672 in 8 93.5 / 98.1). Up to 64 rows
-// they gain with one workgroup a CU (4096 x 14336 26.0 / 25.4 us of 64) and, from 32 K tiles, where some CUs hold one and some two (10240 x 8192 of
-// 64 rows 43.4 / 40.9, 8192 x 28672 on 192 CUs 104.8 / 100.5; 26 tiles: 8192 x 8192 34.6 / 35.2), not with two on all (128 CUs: 4096 x 14336 36.1 / 36.8, 8192 x 8192 in 4 slices 38.4 / 40.5). Above, a
-// launch has to deal evenly: 288 workgroups on 256 CUs take as long as 512 (6144 x 4096 of 223 rows in 6 slices 28 us against 23), and the tiles
-// are taken at nine tenths of the estimate that chose their shape, which rests on a slower tile's rate.
-bool cols_pays(const StreamRates& r, int m, int n, int k, int splits, int cus, double t_tall) {
-  if (cus < COLS_MIN_CUS || m > COLS_MAX_ROWS || n % 128 != 0) return false;
+// Partitions that it was measured on, from 128 CUs by 32 (the scheduler's step). On others the shader engines have unequal CUs and two workgroups
+// meet on one: 16640 x 4096 with SwiGLU, 130 workgroups on 144 CUs, 96 rows in tiles 55.5 us, so 67.3 (on 160 CUs 55.7 / 43.5).
+// Fewer than 128: there the wide tiles of up to 64 rows read the activations less often.
+bool cols_covers(int m, int n, int cus) { return cus >= 128 && cus % 32 == 0 && m <= COLS_MAX_ROWS && n % 128 == 0; }
+// Where partial sums are left, by 2 500 launches of twelve models on 128 to 256 CUs in both forms (cfg: the tile that it would replace; us in tiles / so).
+// Up to 64 rows it replaces 64x128 tiles, which read the same operands, in slices that are long enough beside its start: with one workgroup a CU
+// from 16 K tiles up to 32 rows and 24 up to 64 (4096 x 14336 of 17 rows 23.9 / 21.7, of 64 26.2 / 26.0; 22 tiles: 5120 x 8192 of 64 21.1 / 22.2), with two from 20 up
+// to 32 rows (10240 x 8192 of 24 rows in 4 slices 39.0 / 36.5; 16 tiles: 6144 x 6144 of 32 on 160 CUs 16.8 / 20.7) and, up to 64, from 32 where some CUs hold one and
+// some two (43.4 / 40.9; on all: 8192 x 8192 in 4 slices on 128 CUs 38.4 / 40.5). Skinny tiles of 256 columns and more stay: they pull the rows less often (5120 x 13824 of 32 rows on 128 CUs 34.6 / 40.3,
+// 24576 x 16384 of 24 on 224 119 / 136), but for 512 columns in slices of 16 to 31 tiles up to 32 rows, which are short for them (10240 x 8192 of 24 rows in 6 slices on
+// 128 CUs 67.7 / 42.7; 56 tiles: 8192 x 28672 of 24 93.6 / 97.9).
+// Above 64 rows the launch has to deal evenly (288 workgroups on 256 CUs take as long as 512) and to be estimated faster than the tiles, these at nine tenths
+// of the estimate that chose their shape, which rests on a slower tile's rate. With one workgroup on at least three quarters of the CUs (64 workgroups on
+// 160, 2048 x 2048 of 256 rows: 13.9 / 17.1) from 16 K tiles (4096 x 14336 of 96 rows 32.9 / 29.0, of 256 43.9 / 41.1), or from 8 above 192 rows with one on every CU and 32 MB of weights (4096 x 4096
+// of 223 rows 20.0 / 18.3, but 4608 x 3072 of 224 18.4 / 20.2). With two a CU, up to 192 rows (a CU has LDS for one workgroup of more), from 224 CUs, where HBM and not
+// what a CU pulls decides: from 16 tiles up to 96 rows (8192 x 8192 of 80 on 256 32.3 / 30.4, on 192 32.5 / 35.1), from 48 above (8192 x 28672 of 160 112 / 98; 16384 x 8192 in 32 of 160 60.1 / 63.5).
+// Three a CU above 64 rows were 0.8 to 0.95 of the tiles' time and are not taken yet.
+bool cols_pays(const StreamRates& r, int m, int n, int k, int cfg, int splits, int cus, double t_tall) {
+  if (!cols_covers(m, n, cus)) return false;
   const int wgs = n / 128 * splits, held = (wgs + cus - 1) / cus, len = (k / 64 + splits - 1) / splits;
-  if (m <= 32 && (held == 3 || held == 4)) return len >= 16 && len < 32;
-  if (held > gemm_cols_wgs_per_cu(m)) return false;
   const bool even = held == 1 || 10 * wgs >= 9 * held * cus;
-  if (m <= 32) return len >= 16;
-  if (m <= 64) return held == 1 ? len >= 16 : !even && len >= 32;
-  return even && (len >= 16 || m > 160) && cols_time(r, m, n, k, len * 64, wgs, cus) < std::max(0.9 * t_tall, 2.0 * n * k / (0.85 * r.stream_bw_gpu)) + 9e-6;
+  if (m <= 64) {
+    if (cfg == GEMM_64x512S) return m <= 32 && (held == 3 || held == 4) && len >= 16 && len < 32;
+    if (cfg != GEMM_64x128 || held > 2) return false;
+    if (held == 1) return len >= (m <= 32 ? 16 : 24);
+    return m <= 32 ? len >= 20 : !even && len >= 32;
+  }
+  if (held == 1 ? 4 * wgs < 3 * cus || (len < 16 && (m <= 192 || wgs < cus || (long long)n * k < 1 << 24))
+                : held > 2 || m > 192 || !even || cus < 224 || len < (m <= 96 ? 16 : 48)) return false;
+  return cols_time(r, m, n, k, len * 64, wgs, cus) < std::max(0.9 * t_tall, 2.0 * n * k / (0.85 * r.stream_bw_gpu)) + 9e-6;
 }
 
 // A GEMM whose partial sums the layer's next kernel adds up, and gate/up, whose SwiGLU is its epilogue or (not fused) that kernel's. Both return
 // the estimate that the choice between the layer's forms goes by, which is of the tiles.
 double plan_partials(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g) {
   const double t = plan_decode_gemm(r, m, n, k, cus, true, true, &g->cfg, &g->splits);
-  g->cols = cols_pays(r, m, n, k, g->splits, cus, pick_tall_tiles(r, m, n, k, cus, g));
+  const double t_tall = pick_tall_tiles(r, m, n, k, cus, g);
+  g->cols = cols_pays(r, m, n, k, g->cfg, g->splits, cus, t_tall);
   return t;
 }
 double plan_gateup(const StreamRates& r, int m, int n, int k, int cus, DecodeGemm* g, bool* gu_fused) {
@@ -473,7 +483,7 @@ double plan_gateup(const StreamRates& r, int m, int n, int k, int cus, DecodeGem
   // of 105 launches on 128 to 256 CUs: 28800 x 4224 of 96 rows 76.7 / 49.9 us and of 256 rows 109.3 / 73.4 on 256 CUs, 57472 x 8192 of 128 rows on 128 CUs 317 / 303,
   // 11392 x 2176 of 65 rows on 256 CUs 25.0 / 22.9.
   const bool no_tall = m > 64 && n % 256 != 0;
-  g->cols = cus >= COLS_MIN_CUS && m <= COLS_MAX_ROWS && (no_tall || cols_time(r, m, n, k, k, n / 128, cus) < t_two);
+  g->cols = cols_covers(m, n, cus) && (no_tall || cols_time(r, m, n, k, k, n / 128, cus) < t_two);
   return t_split;
 }
 

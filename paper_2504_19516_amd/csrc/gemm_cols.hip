@@ -62,7 +62,8 @@ __device__ __forceinline__ void wait_for4(bf16x8& a, bf16x8& b, bf16x8& c, bf16x
 #endif
 }
 
-// K tiles ahead; the stages of two workgroups fit a CU up to 192 rows.
+// K tiles ahead. By LDS and registers (98 to 126 of them up to 96 rows) a CU holds four workgroups that leave partial sums up to 32 rows, three up to 96, two up to
+// 192 and one of more; which of that pays is the engine's to decide.
 constexpr int cols_pd(int tm) { return tm <= 2 ? 4 : tm <= 4 ? 3 : 2; }
 constexpr int COLS_BASE = 1024;                // buffers filled by direct-to-LDS loads stay clear of address 0
 constexpr int cols_lds(int tm) { return COLS_BASE + (cols_pd(tm) + 1) * tm * 4096; }
@@ -272,9 +273,6 @@ hipError_t launch_cols_rows(hipStream_t s, const ColsArgs& g, int grid) {
 }
 
 }  // namespace
-
-// Workgroups that leave partial sums a CU holds, by their LDS.
-int gemm_cols_wgs_per_cu(int rows) { return rows <= 192 ? 2 : 1; }
 
 // A [M, lda] row-major, W [N, K] packed. EPI_F32: C + z * split_stride = the partial sums of slice z, `splits` slices of K as
 // gemm_bf16 makes them (fewer where K has not as many tiles). EPI_SWIGLU_BF16: C[M, N / 2] = silu(gate) * up of the slices' sums.

@@ -160,7 +160,6 @@ hipError_t kslice_qkv(hipStream_t s, const KsliceIn& in, const int* place, const
 
 // ---- GEMMs of up to 256 rows that read their weights once (gemm_cols.hip) --------------------
 constexpr int COLS_MAX_ROWS = 256;
-int gemm_cols_wgs_per_cu(int rows);
 hipError_t gemm_cols(hipStream_t s, int epi, const bf16* A, int lda, const bf16* W, void* C, int ldc, int M, int N, int K, int splits, long long split_stride);
 
 }  // namespace sts

@@ -333,6 +333,39 @@ def test_decode_gemm_form_at_its_edges(sts, n, k, swiglu, cus, yes, no):
             sts.decode_gemm_all_rows(*bad)
 
 
+@pytest.mark.parametrize("n,k,cus,yes,no", [
+    (4096, 14336, 128, (17, 24, 32), (33, 64, 65, 96, 160, 256)),                 # two a CU
+    (4096, 14336, 224, (17, 32, 33, 64, 160, 192, 193, 256), (65, 96, 128)),      # tiles of 65 to 128 rows are as fast on 224
+    (5120, 13824, 128, (), (17, 24, 32, 33, 64, 96)),                             # skinny tiles of 320 columns: 33.2 us at 17 rows, 37.5 in this form
+    (24576, 16384, 224, (), (17, 24, 32, 33, 64, 96)),                            # of 256 columns: 118 and 135
+    (24576, 16384, 256, (), (17, 24, 32, 64)),
+    (8192, 28672, 128, (), (17, 24, 32, 64)),                                     # 512 columns, slices of 56 K tiles: 93.6 and 97.9 at 24 rows
+    (10240, 8192, 128, (17, 24), (32, 33, 64)),                                   # 512 columns, slices of 22: 67.7 and 42.7; 320 columns at 32 rows
+    (6144, 6144, 160, (), (32, 33, 48)),                                          # two a CU, slices of 16: 16.8 and 20.7 at 32 rows
+    (5120, 8192, 256, (32,), (33, 48, 64)),                                       # one a CU, slices of 22: 21.1 and 22.2 at 64 rows
+    (8192, 8192, 192, (), (65, 80, 96, 128, 160)),                                # two a CU above 64 rows: 32.5 and 35.1 at 80
+    (8192, 8192, 256, (65, 80, 96), (97, 128, 160, 192)),
+    (6144, 16384, 192, (), (65, 80, 96, 128)),                                    # 54.3 and 57.8 at 128
+    (8192, 28672, 256, (65, 96, 128, 192), (193, 256)),                           # slices of 56
+    (4608, 3072, 256, (), (161, 193, 224, 256)),                                  # short slices: 18.4 and 20.2 at 224
+    (3072, 2048, 128, (), (161, 192, 224, 256)),                                  # 96 workgroups on 128 CUs: 15.7 and 18.7 at 256
+    (4096, 4096, 256, (193, 223, 256), (160, 161, 192)),
+    (2048, 8192, 192, (), (96, 192, 224, 256)),                                   # 128 workgroups on 192 CUs: 21.4 and 22.2 at 224
+])
+def test_decode_gemm_form_of_partial_sums_where_it_was_measured(sts, n, k, cus, yes, no):
+    """Both sides of each line of the rule, us in tiles and so on the same partition."""
+    for m in yes + no:
+        assert sts.decode_gemm_all_rows(m, n, k, cus) == (m in yes), m
+
+
+@pytest.mark.parametrize("cus", [8, 96, 120, 127, 136, 144, 176, 208, 248, 255])
+def test_decode_gemm_form_on_partitions_that_deal_unevenly(sts, cus):
+    """Partitions below 128 CUs and those that are no multiple of 32 keep their tiles: with 130 workgroups on 144 CUs gate/up took 67.3 us for 55.5."""
+    for m in (17, 24, 64, 65, 96, 128, 192, 223, 256):
+        for n, k, swiglu in ((4096, 14336, False), (28672, 4096, True), (16640, 4096, True), (8192, 28672, False), (4096, 4096, False)):
+            assert not sts.decode_gemm_all_rows(m, n, k, cus, swiglu), (m, n, k)
+
+
 def test_decode_gemm_form_of_widths_without_256_column_tiles(sts):
     """An odd multiple of 128 columns has 128x128 tiles alone above 64 rows: gate/up takes all rows in a workgroup, partial sums weigh both estimates."""
     for n, k in ((4224, 4096), (11392, 2176), (28800, 4224), (57472, 8192)):
