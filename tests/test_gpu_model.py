@@ -770,6 +770,40 @@ def test_decode_gemm_forms_are_what_the_engine_runs(sts):
     eng.close()
 
 
+@pytest.mark.parametrize("model,batches", [("8b", ((24, 128, 136), (17, 192, 200), (32, 256, 248), (64, 256, 248), (65, 256, 248), (96, 256, 248), (160, 192, 200), (223, 256, 248), (256, 256, 248))),
+                                           ("70b", ((24, 128, 136), (24, 192, 184), (32, 256, 248), (64, 192, 200), (96, 256, 248), (160, 256, 248)))])
+def test_decode_with_all_rows_in_a_workgroup_equals_the_tiles(sts, model, batches):
+    """Decode steps at the widths of both models on partitions that take this form, and on ones eight CUs off, which do not: the residual stream behind the last
+    layer, K and V of the new tokens. Where both plan the same slices they are the same bits, gate/up through several slices included."""
+    prof = sts.Profile(path=os.path.join(os.path.dirname(sts.__file__), "data", f"mi355x_llama{model}.profile"))
+    desc = (synth.llama8b_model if model == "8b" else synth.llama70b_model)(2, 512)
+    eng = new_engine(sts, desc, weight_seed=88, max_decode_batch=256, max_seqs=256, kv_pool_pages=600, max_pages_per_seq=8)
+    eng.set_tile_model(*prof.tile_model())
+    eng.set_stream_model(*prof.stream_model())
+    seqs, ctx, tok = [eng.seq_create() for _ in range(256)], [1 + 5 * i % 30 for i in range(256)], synth.tokens(89, 256, 512)
+    for i, (s, n) in enumerate(zip(seqs, ctx)):
+        eng.kv_fill_random(s, n, 300 + i)
+    used, same = np.zeros(4, bool), 0
+    for n, cus, other in batches:
+        forms, plans = eng.decode_layer_all_rows(n, cus), [[g[1] for g in eng.decode_layer_plan(n, c)] for c in (cus, other)]
+        assert any(forms) and not any(eng.decode_layer_all_rows(n, other)), (n, cus)
+        used |= forms
+        got = []
+        for c in (cus, other):
+            eng.set_partition(256, c)
+            eng.decode_step(seqs[:n], tok[:n])
+            got.append((eng.read_hidden(1, n), np.stack([np.concatenate([np.stack(eng.kv_read(l, s, p, 1)) for s, p in zip(seqs[:n], ctx)]) for l in range(2)])))
+            for s, p in zip(seqs[:n], ctx):
+                eng.seq_truncate(s, p)
+        for a, b in zip(*got):
+            assert rel(a, b) <= TOL, (n, cus)
+            if plans[0] == plans[1]:
+                assert np.array_equal(a, b), (n, cus)
+        same += plans[0] == plans[1]
+    assert used.sum() >= 3 and same >= 4
+    eng.close()
+
+
 @pytest.mark.parametrize("cus", [256, 32])
 @pytest.mark.parametrize("n", [65, 96, 97, 128, 129, 224, 225, 256])
 def test_decode_gemm_tiles_above_64_rows(many_requests, n, cus):
