@@ -482,8 +482,9 @@ double plan_gateup(const StreamRates& r, int m, int n, int k, int cus, DecodeGem
   // Widths without 256-column tiles (odd multiples of 128) leave 128x128 tiles, which were slower than their estimate and than all rows in a workgroup in each
   // of 105 launches on 128 to 256 CUs: 28800 x 4224 of 96 rows 76.7 / 49.9 us and of 256 rows 109.3 / 73.4 on 256 CUs, 57472 x 8192 of 128 rows on 128 CUs 317 / 303,
   // 11392 x 2176 of 65 rows on 256 CUs 25.0 / 22.9.
+  // Above 192 rows a CU has LDS for one workgroup, and launches of more than one a CU lose: 51200 x 5120 of 256 rows on 256 CUs 155.5 / 169.1.
   const bool no_tall = m > 64 && n % 256 != 0;
-  g->cols = cols_covers(m, n, cus) && (no_tall || cols_time(r, m, n, k, k, n / 128, cus) < t_two);
+  g->cols = cols_covers(m, n, cus) && (m <= 192 || n / 128 <= cus || no_tall) && (no_tall || cols_time(r, m, n, k, k, n / 128, cus) < t_two);
   return t_split;
 }
 

@@ -358,6 +358,14 @@ def test_decode_gemm_form_of_partial_sums_where_it_was_measured(sts, n, k, cus, 
         assert sts.decode_gemm_all_rows(m, n, k, cus) == (m in yes), m
 
 
+def test_decode_gateup_form_of_more_workgroups_than_cus(sts):
+    """400 workgroups of gate/up: up to 192 rows two of them share a CU, above that they would take turns (256 rows: 155.5 us in tiles, 169.1 so)."""
+    for cus in (224, 256):
+        for m, yes in ((96, True), (160, True), (193, False), (224, False), (256, False)):
+            assert sts.decode_gemm_all_rows(m, 51200, 5120, cus, True) == yes, (m, cus)
+    assert sts.decode_gemm_all_rows(256, 28672, 4096, 224, True)                  # 224 of them on 224 CUs
+
+
 @pytest.mark.parametrize("cus", [8, 96, 120, 127, 136, 144, 176, 208, 248, 255])
 def test_decode_gemm_form_on_partitions_that_deal_unevenly(sts, cus):
     """Partitions below 128 CUs and those that are no multiple of 32 keep their tiles: with 130 workgroups on 144 CUs gate/up took 67.3 us for 55.5."""
