@@ -77,6 +77,7 @@ struct Phase {
   PrefillSeq* h_pseq = nullptr; DecodeSeq* h_dseq = nullptr; AttnItem* h_items = nullptr; DecodeItem* h_ditems = nullptr;
   float* h_logits = nullptr; ArgBest* h_best = nullptr;
   int rows = 0;                               // rows of the last call
+  bool alone = false;                         // no step of the other phase was in flight when this one was queued
   // per-kernel timing
   std::vector<hipEvent_t> kev; std::vector<int> kkind; size_t kused = 0;
   int64_t kns[STS_K_COUNT] = {0}, kcnt[STS_K_COUNT] = {0};
@@ -551,11 +552,14 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
 // 21.3 / 19.3 on 64; at 1024 rows 19.6 / 15.1 on 256 CUs but 29.5 / 31.3 on 64, whose few workgroups wait for the bus in turn
 // (8192 rows: 50 / 56 and 114 / 188).
 constexpr int META_FUSED_ROWS = 512;
-// Logits up to this size are stored to host memory by the kernel that reads or writes them last (the head, or greedy sampling on the side), larger ones
-// go by a runtime copy, which leaves the stream idle for about 15 us and for much longer between 2 and 8 MB. One layer of the 8B shape, vocabulary
-// 128256, us a step by copy / stored: with tokens 1 row 296 / 282, 4 rows 592 / 376, 8 rows 744 / 482, 16 rows 931 / 726, 64 rows (31 MiB)
-// 1989 / 2005; logits alone 293 / 270, 593 / 359, 744 / 453, 715 / 636, 1963 / 1880. More is not measured.
-constexpr size_t STORED_LOGITS_BYTES = 32 << 20;
+// Logits up to these sizes are stored to host memory by the kernel that reads or writes them last (the head, or greedy sampling on the side), larger ones
+// go by a runtime copy, which leaves the stream idle for about 15 us. One layer of the 8B shape, vocabulary 128256, us a step by copy / stored.
+// A phase alone, logits of a decode step on 256 CUs: 1 row 294 / 270, 16 rows 711 / 627, 64 rows (31 MiB) 1985 / 1896; of a prefill batch of 8 tokens each 311 / 285, 774 / 700,
+// 2179 / 2095, on 32 CUs 1085 / 1065 and (64 rows) 3653 / 3102. With tokens: 1 row 298 / 284, 16 rows 721 / 705, 40 rows 1361 / 1342, 48 rows (23.5 MiB) 1591 / 1583, 64 rows 1979 / 1987.
+// Both phases at once store at each other's expense on the bus (rows of each, with tokens): 256 / 256 CUs 8 rows 1301 / 907, 16 rows (7.8 MiB) 2457 / 2490, 24 rows 3147 / 3261, 64 rows 6452 / 6858;
+// 128 / 128 16 rows 1311 / 1305, 32 rows 2075 / 2173; 224 / 32 16 rows 1557 / 1526, 20 rows 1778 / 1848, 32 rows 2104 / 2294.
+constexpr size_t STORED_LOGITS_BYTES = 32 << 20, STORED_WITH_TOKENS_BYTES = 24 << 20, STORED_BESIDE_BYTES = 8 << 20;
+size_t stored_logits_bytes(const Phase& ph, bool with_tokens) { return !ph.alone ? STORED_BESIDE_BYTES : with_tokens ? STORED_WITH_TOKENS_BYTES : STORED_LOGITS_BYTES; }
 
 bf16* layer_pool(sts_ctx* c, int l) { return c->pool + (size_t)l * c->pool_layer_elems; }
 
@@ -923,10 +927,10 @@ int DecodeRun::end() {
   if (want_logits || want_next) {
     // (the last reduce kernel of the split form has written Xn normalised)
     const size_t bytes = (size_t)n * d.vocab * sizeof(float);
-    const bool direct = want_logits && !want_next && bytes <= STORED_LOGITS_BYTES, beside = want_logits && want_next && bytes <= STORED_LOGITS_BYTES;
+    const bool stored = want_logits && bytes <= stored_logits_bytes(ph, want_next), direct = stored && !want_next;
     STSCK(run_head(c, ph, few.plan.kslice ? ph.X : nullptr, nullptr, ph.Xn, few.xn_scale, n, ph.part, ph.part_floats, few.nt, direct ? ph.h_logits : ph.logits));
-    if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_best, ph.logits, n, d.vocab, beside ? ph.h_logits : nullptr));
-    if (want_logits && !direct && !beside) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
+    if (want_next) KL(ph, STS_K_SAMPLE, argmax_rows(st, ph.h_best, ph.logits, n, d.vocab, stored ? ph.h_logits : nullptr));
+    if (want_logits && !stored) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
   HIPCK(hipEventRecord(ph.ev1, st));
   ph.ran = true; ph.rows = n;
@@ -1064,7 +1068,7 @@ int prefill_launch_body(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32
   }
   if (le == d.n_layers && want_logits) {
     const size_t bytes = (size_t)n_seqs * d.vocab * sizeof(float);
-    const bool direct = bytes <= STORED_LOGITS_BYTES;        // the head's last kernel stores to host memory
+    const bool direct = bytes <= stored_logits_bytes(ph, false);   // the head's last kernel stores to host memory
     STSCK(run_head(c, ph, ph.X, ph.d_rows, ph.Xlast_n, RowScale{nullptr, 0, 0.f}, n_seqs, ph.tail_ws, ph.tail_ws_bytes / sizeof(float), false, direct ? ph.h_logits : ph.logits));
     if (!direct) HIPCK(hipMemcpyAsync(ph.h_logits, ph.logits, bytes, hipMemcpyDeviceToHost, st));
   }
@@ -1503,11 +1507,16 @@ extern "C" int sts_kv_fill_random(sts_ctx* c, int32_t seq, int32_t n, uint64_t s
 }
 
 // ---- the step
+static bool in_flight(sts_ctx* c, int side) {
+  std::lock_guard<std::mutex> g(c->state_mu);
+  return !(side == 0 ? c->pend_pseqs : c->pend_dseqs).empty();
+}
 extern "C" int sts_prefill_batch(sts_ctx* c, int32_t n_seqs, const int32_t* seqs, const int32_t* lens, const int32_t* tokens,
                                  int32_t lb, int32_t le, float* logits) {
   if (!c) return STS_EINVAL;
   if (c->pend_prefill) return STS_ESTATE;
   const int64_t t0 = now_ns();
+  c->ph[0].alone = !in_flight(c, 1);
   STSCK(prefill_enqueue(c, n_seqs, seqs, lens, tokens, lb, le, logits != nullptr));
   STSCK(prefill_finish(c, n_seqs, seqs, lens, le, logits));
   c->last_wall_ns = now_ns() - t0;
@@ -1522,6 +1531,7 @@ extern "C" int sts_prefill_launch(sts_ctx* c, int32_t n_seqs, const int32_t* seq
                                   int32_t lb, int32_t le, int32_t want_logits) {
   if (!c) return STS_EINVAL;
   if (c->pend_prefill) return STS_ESTATE;
+  c->ph[0].alone = false;                                    // a decode step may be launched beside it
   STSCK(prefill_enqueue(c, n_seqs, seqs, lens, tokens, lb, le, want_logits != 0));
   std::lock_guard<std::mutex> g(c->state_mu);
   c->pend_prefill = true; c->pend_le = le;
@@ -1537,6 +1547,7 @@ extern "C" int sts_decode_launch(sts_ctx* c, const int32_t* seqs, const int32_t*
     std::lock_guard<std::mutex> g(c->state_mu);
     c->pend_dseqs.assign(seqs, seqs + std::max(n, 0));
   }
+  c->ph[1].alone = false;                                    // a prefill may be launched beside it
   const int rc = decode_enqueue(c, seqs, in_tokens, n, want_logits != 0, want_next != 0);
   if (rc != STS_OK) { std::lock_guard<std::mutex> g(c->state_mu); c->pend_dseqs.clear(); return rc; }
   c->pend_decode = true;
@@ -1579,6 +1590,7 @@ extern "C" int sts_decode_step(sts_ctx* c, const int32_t* seqs, const int32_t* i
   if (!c) return STS_EINVAL;
   if (c->pend_decode) return STS_ESTATE;
   const int64_t t0 = now_ns();
+  c->ph[1].alone = !in_flight(c, 0);
   STSCK(decode_enqueue(c, seqs, in_tokens, n, logits != nullptr, next != nullptr));
   STSCK(decode_finish(c, seqs, n, logits, next));
   c->last_wall_ns = now_ns() - t0;
@@ -1592,6 +1604,7 @@ extern "C" int sts_step_concurrent(sts_ctx* c, int32_t n_pseqs, const int32_t* p
   for (int i = 0; i < n_pseqs; i++) for (int j = 0; j < n_decode; j++) if (pseqs && dseqs && pseqs[i] == dseqs[j]) return STS_EINVAL;
   const int64_t t0 = now_ns();
   c->ph[0].ran = c->ph[1].ran = false;
+  c->ph[0].alone = n_decode == 0; c->ph[1].alone = n_pseqs == 0;
   // Both sides are checked and the pages of both are reserved in one step before anything is
   // queued: an invalid argument or an exhausted pool on either side leaves every sequence as it was.
   std::vector<std::pair<int, int>> wants;

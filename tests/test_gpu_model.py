@@ -1130,8 +1130,61 @@ def test_greedy_tokens_of_rows_sampled_in_parts(sts):
         eng.close()
 
 
-def test_results_at_the_lines_between_stored_and_copied(sts, tiny):
-    """Logits of 64 KiB (16 rows of 1024) and a row more, of 1 MiB and a row more: stored by the head or by the sampling, they
+def test_logits_on_both_sides_of_the_lines_between_stored_and_copied(sts):
+    """Rows of 128256 logits up to 8 MiB (16 of them), 24 MiB (49) and 32 MiB (65), and one more each: stored by the head, stored by the sampling or copied, alone and with the
+    other phase beside it, they are those of batches of 11. Two sets of tokens in turn, so that logits left from the call before would show."""
+    desc = synth.ModelDesc(1, 256, 4, 4, 64, 512, 128256, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, max_prefill_tokens=140, max_prefill_seqs=66, max_decode_batch=66, max_seqs=132, kv_pool_pages=140, max_pages_per_seq=2)
+    ds, ps = [eng.seq_create() for _ in range(66)], [eng.seq_create() for _ in range(66)]
+    for i, s in enumerate(ds):
+        eng.kv_fill_random(s, 5, 880 + i)
+    dtok = [synth.tokens(881 + k, 66, desc.vocab) for k in range(2)]
+    ptok = [[synth.tokens(1000 + 100 * k + i, 2, desc.vocab) for i in range(66)] for k in range(2)]
+
+    def back(n):
+        for s in ds[:n]:
+            eng.seq_truncate(s, 5)
+        for s in ps[:n]:
+            eng.seq_truncate(s, 0)
+
+    dref, pref = [], []
+    for k in range(2):
+        d, p = [], []
+        for a in range(0, 66, 11):
+            d.append(eng.decode_step(ds[a:a + 11], dtok[k][a:a + 11], want_next=False)[0])
+            p.append(eng.prefill_batch(ps[a:a + 11], ptok[k][a:a + 11]))
+        back(66)
+        dref.append(np.concatenate(d)), pref.append(np.concatenate(p))
+    assert rel(dref[0], dref[1]) > 0.5 and rel(pref[0], pref[1]) > 0.5
+    for n in (16, 17, 49, 50, 65, 66):
+        for k in range(2):
+            a, _ = eng.decode_step(ds[:n], dtok[k][:n], want_next=False)
+            back(n)
+            b, g = eng.decode_step(ds[:n], dtok[k][:n])
+            back(n)
+            assert rel(a, dref[k][:n]) <= TOL and np.array_equal(a, b) and np.array_equal(g, b.argmax(1)), n
+            p = eng.prefill_batch(ps[:n], ptok[k][:n])
+            back(n)
+            assert rel(p, pref[k][:n]) <= TOL, n
+            for next_too in (False, True):
+                q, c, g = eng.step_concurrent(ps[:n], ptok[k][:n], 0, 1, ds[:n], dtok[k][:n], want_dnext=next_too)
+                back(n)
+                assert np.array_equal(q, p) and np.array_equal(c, a) and (not next_too or np.array_equal(g, a.argmax(1))), n
+            eng.decode_launch(ds[:n], dtok[k][:n], want_logits=True)
+            q = eng.prefill_batch(ps[:n], ptok[k][:n])
+            c, g = eng.decode_finish(n, want_logits=True)
+            back(n)
+            assert np.array_equal(q, p) and np.array_equal(c, a) and np.array_equal(g, a.argmax(1)), n
+            eng.prefill_launch(ps[:n], ptok[k][:n], 0, 1, want_logits=True)
+            c, _ = eng.decode_step(ds[:n], dtok[k][:n])
+            q = eng.prefill_finish(n, want_logits=True)
+            back(n)
+            assert np.array_equal(q, p) and np.array_equal(c, a), n
+    eng.close()
+
+
+def test_results_of_small_logits_and_of_prompts_at_the_metadata_line(sts, tiny):
+    """Logits of 64 KiB (16 rows of 1024) to 1 MiB and a row more: stored by the head or by the sampling, they
     are the same numbers. Prompts of 512 and 513 rows (tokens and positions read from host memory, or copied first) match the oracle."""
     desc, w = tiny
     eng = new_engine(sts, desc, max_prefill_tokens=513, max_prefill_seqs=17, max_decode_batch=257, max_seqs=280, kv_pool_pages=900)
