@@ -938,11 +938,16 @@ int DecodeRun::end() {
 }
 
 // A prefill batch of few rows waits for its weights, as a decode step does, and takes the same GEMMs (but not the form that leaves rows
-// scaled: a row's norm is rounded as in a larger batch), where it has the whole GPU. Beside a decode step they are as fast, but take from
-// the decode step what they gain: 45 rows beside 71 requests on 128 / 128 CUs 418 -> 390 us for the slice, 499 -> 515 for the step; 100 rows beside 2 requests on 224 / 32
-// 370 -> 311 and 660 -> 702.
+// scaled: a row's norm is rounded as in a larger batch), where its partition is the whole GPU. On a part of it they are as fast, but take from
+// the decode step beside them what they gain: 45 rows beside 71 requests on 128 / 128 CUs 418 -> 390 us for the slice, 499 -> 515 for the step; 100 rows beside 2 requests on 224 / 32
+// 370 -> 311 and 660 -> 702. Where both phases have the whole GPU and a decode step does run beside, the whole step is the shorter one (four layers, us: 45 rows beside 16 requests
+// 906 -> 734, 100 beside 71 1066 -> 983, 200 beside 2 999 -> 934; hidden 8192, two layers, 16 beside 16 1241 -> 1132, 100 beside 71 1468 -> 1422; 16 beside 71 934 -> 952 is the one of 24 that is
+// not), though one phase of it may take longer (hidden 8192, 45 beside 2: the slice 1207 -> 1163, the decode step 898 -> 1062). So the partition alone decides, and a
+// batch's numbers do not depend on what runs beside it.
+// Distance of the logits from 64 bits, tiles / so: 0.01154 / 0.01156 in the mean of 90 batches of 25 to 256 rows.
 // Up to 64 rows: its 64x128 tiles unsplit, with a cut last wave, pull less than split and skinny tiles. Device time of 2 layers, before / now: 1 row 264 / 187 us,
-// 16 rows 266 / 189, 64 rows 291 / 210; hidden 8192 8 rows 678 / 563, 64 rows 708 / 604. Not where the layer is launches (hidden 256: 8 rows 69 / 70).
+// 16 rows 266 / 189, 64 rows 291 / 210; hidden 8192 8 rows 678 / 563, 64 rows 708 / 604. Up to 16 rows not where the layer is launches (hidden 256: 8 rows 69 / 70). From 17 to 64 rows in a
+// layer of any size (four layers, 17 and 64 rows: hidden 256 144 / 139 and 169 / 146, 512 176 / 168 and 183 / 177, 1024 201 / 169 and 214 / 182, 2048 273 / 209 and 298 / 233, 3072 407 / 304 and 433 / 352).
 // Beyond, all four through gemm_cols in as many slices as give every CU a workgroup, where both sides' estimates say so: a tile launch and
 // its fix-up or norm at three quarters of the estimate that chose its shape (which rests on a slower tile's rate) plus 12 us. 65 rows 298 / 226 us, 96 rows 305 / 251,
 // 160 rows 358 / 294, 256 rows 389 / 360; hidden 8192 96 rows 740 / 657, 128 rows 776 / 711; 192 rows 888 for 820, which it leaves. Above 256 rows the tiles of

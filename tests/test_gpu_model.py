@@ -892,6 +892,7 @@ def test_prefill_of_few_rows_equals_the_tiles(sts, wide_prefill, lens, priors):
         eng.kernel_timing(False)
         if rows > 64:
             assert ("rope" in kinds) == (cus == 256 and rows <= 256)
+        assert (kinds["norm"][1] >= 5) == (cus == 256 and rows <= 256)        # behind O and down of every layer, at the head; tiles: at most 4
         kv = [np.concatenate([np.stack(eng.kv_read(l, s, p, n)) for s, p, n in zip(seqs, priors, lens)], axis=1) for l in range(2)]
         got[cus, sliced] = logits, kv
         free_all(eng, seqs)
@@ -901,6 +902,60 @@ def test_prefill_of_few_rows_equals_the_tiles(sts, wide_prefill, lens, priors):
         for x, y in zip(akv, bkv):                            # position by position: a token in the wrong slot cannot hide
             assert np.all(np.abs(x - y).max(axis=(2, 3)) <= TOL * np.abs(y).max())
     eng.set_partition(256, 256)
+
+
+@pytest.mark.parametrize("rows", [16, 45, 100, 256])
+def test_prefill_of_few_rows_beside_a_decode_step_on_the_whole_gpu(sts, wide_prefill, rows):
+    """Both phases on 256 CUs: a batch takes the same GEMMs whether a decode step runs beside it or not, in one call or launched, so it has the same bits; so has the decode step."""
+    eng, desc = wide_prefill, wide_prefill.desc
+    eng.set_partition(256, 256)
+    tok, dtok, ds, p = synth.tokens(960 + rows, rows, desc.vocab), synth.tokens(961, 2, desc.vocab), [eng.seq_create() for _ in range(2)], eng.seq_create()
+    for i, s in enumerate(ds):
+        eng.kv_fill_random(s, 50 + 20 * i, 60 + i)
+
+    def back():
+        eng.seq_truncate(p, 0)
+        for i, s in enumerate(ds):
+            eng.seq_truncate(s, 50 + 20 * i)
+
+    pre, dec = eng.prefill_batch([p], [tok]), eng.decode_step(ds, dtok)[0]
+    back()
+    for _ in range(3):
+        eng.kernel_timing(True)
+        eng.kernel_times(0, reset=True)
+        a, b, _ = eng.step_concurrent([p], [tok], 0, 2, ds, dtok)
+        assert eng.kernel_times(0, reset=True)["norm"][1] >= 5
+        eng.kernel_timing(False)
+        back()
+        assert np.array_equal(a, pre) and np.array_equal(b, dec)
+    eng.decode_launch(ds, dtok, want_logits=True)
+    assert np.array_equal(eng.prefill_batch([p], [tok]), pre)
+    assert np.array_equal(eng.decode_finish(2, want_logits=True)[0], dec)
+    free_all(eng, ds + [p])
+
+
+@pytest.mark.parametrize("lens", [(30,), (64,), (9, 20, 5), (160,), (100, 31), (256,)])
+def test_prefill_of_few_rows_against_the_oracle(sts, lens):
+    """The same GEMMs against 64 bits, one layer of hidden 2048 with weights enough for the route, over 7 tokens cached by a batch of their own."""
+    desc = synth.ModelDesc(1, 2048, 16, 4, 128, 12288, 256, 16, 1.0e4, 1.0e-5, "bf16")
+    eng = new_engine(sts, desc, weight_seed=87, max_prefill_tokens=256)
+    w = {n: eng.read_weights(0, n, desc.shape(n)) for n in ("emb", "lm")}
+    w["gf"] = np.ones(2048, np.float32)
+    w["layers"] = [dict({n: eng.read_weights(0, n, desc.shape(n)) for n in synth.SLOT}, g1=np.ones(2048, np.float32), g2=np.ones(2048, np.float32))]
+    orc = T.Oracle(desc, w, 40)
+    eng.set_partition(256, 256)
+    seqs, toks = [eng.seq_create() for _ in lens], [synth.tokens(970 + i, 7 + n, desc.vocab) for i, n in enumerate(lens)]
+    for s, t in zip(seqs, toks):
+        eng.prefill_append(s, t[:7], want_logits=False)
+    eng.kernel_timing(True)
+    eng.kernel_times(0, reset=True)
+    got = eng.prefill_batch(seqs, [t[7:] for t in toks])
+    assert eng.kernel_times(0, reset=True)["norm"][1] == 3
+    for i, t in enumerate(toks):
+        orc.kv.add_sequence(i, list(range(20 * i, 20 * i + 20)) if len(lens) < 3 else list(range(4 * i, 4 * i + 4)))
+        orc.prefill_append(i, t[:7])
+        assert rel(got[i], orc.prefill_append(i, t[7:])) <= TOL
+    eng.close()
 
 
 @pytest.mark.parametrize("cus", [256, 8])
