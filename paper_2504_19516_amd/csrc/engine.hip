@@ -1116,7 +1116,6 @@ int alloc_phase(sts_ctx* c, int side) {
   STSCK(dev_alloc(c, &ph.Xlast_n, nseq * d.hidden));
   STSCK(dev_alloc(c, &ph.logits, nseq * d.vocab));
   STSCK(dev_alloc(c, &ph.rot, rows * d.head_dim));
-  STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
   {
     // prefill attention: a query tile per 128 rows, and as many again for the parts of cut key ranges
     const size_t q_tiles = side == 0 ? rows / attn_prefill_tile_q() + nseq + 1 : 0;
@@ -1130,7 +1129,6 @@ int alloc_phase(sts_ctx* c, int side) {
     STSCK(host_alloc(&ph.h_meta, ph.meta_bytes + 16));
   }
   STSCK(host_alloc(&ph.h_logits, nseq * d.vocab));
-  STSCK(host_alloc(&ph.h_best, nseq * ARGMAX_MAX_PARTS));
   if (side == 0) {
     STSCK(dev_alloc(c, &ph.QKV, rows * c->qkvn));
     const size_t tail_floats = (size_t)c->n_cu * 256 * 256;   // one wave of partial tiles at the largest tile on every CU
@@ -1142,6 +1140,8 @@ int alloc_phase(sts_ctx* c, int side) {
     const size_t max_chunks = decode_max_chunks((int)mp);
     ph.part_floats = 8 * rows * widest;
     STSCK(dev_alloc(c, &ph.part, ph.part_floats));
+    STSCK(dev_alloc(c, &ph.ssq, (size_t)KSLICE_MAX_ROWS * (d.hidden / 16)));
+    STSCK(host_alloc(&ph.h_best, nseq * ARGMAX_MAX_PARTS));
     STSCK(dev_alloc(c, &ph.Q, rows * c->qd));
     STSCK(dev_alloc(c, &ph.attn_ws, attn_decode_ws_floats((int)rows, d.n_q_heads, d.head_dim, (int)max_chunks)));
   }
