@@ -266,8 +266,9 @@ class Profiler:
             log(f"alpha_prefill pm={pm}: {[round(v / PPM, 3) for v in row]}")
         self.grids["alpha_prefill"] = ([list(pms), list(tokens)], vals)
 
-    def calibrate_decode(self, dms=(32, 64, 128, 256), batches=(8, 16, 17, 64, 224), mean_ctx=(256, 2048), log=print):
-        """16 and 17 requests: a sample on either side of the line where the decode GEMMs change their form."""
+    def calibrate_decode(self, dms=(32, 64, 128, 192, 224, 256), batches=(8, 16, 17, 64, 224), mean_ctx=(256, 2048), log=print):
+        """16 and 17 requests: a sample on either side of the line where the decode GEMMs change their form. 192 and 224 CUs: between 128 and 256 a step does not
+        grow evenly shorter (hidden 8192, 48 requests on 224 CUs: 6.45 ms, 5.79 interpolated)."""
         vals = np.zeros((len(dms), len(batches), len(mean_ctx)), dtype=np.int64)
         ctx_axis = None
         for bi, b in enumerate(batches):
