@@ -553,7 +553,7 @@ int reserve_pages(sts_ctx* c, const std::vector<std::pair<int, int>>& wants) {  
 // (8192 rows: 50 / 56 and 114 / 188).
 constexpr int META_FUSED_ROWS = 512;
 // Logits up to these sizes are stored to host memory by the kernel that reads or writes them last (the head, or greedy sampling on the side), larger ones
-// go by a runtime copy, which leaves the stream idle for about 15 us. One layer of the 8B shape, vocabulary 128256, us a step by copy / stored.
+// go by a runtime copy, which leaves the stream idle for about 15 us (a program that copied 2 to 4 MB on every step lost 200: 4 rows 590, stored 369). One layer of the 8B shape, vocabulary 128256, us a step by copy / stored.
 // A phase alone, logits of a decode step on 256 CUs: 1 row 294 / 270, 16 rows 711 / 627, 64 rows (31 MiB) 1985 / 1896; of a prefill batch of 8 tokens each 311 / 285, 774 / 700,
 // 2179 / 2095, on 32 CUs 1085 / 1065 and (64 rows) 3653 / 3102. With tokens: 1 row 298 / 284, 16 rows 721 / 705, 40 rows 1361 / 1342, 48 rows (23.5 MiB) 1591 / 1583, 64 rows 1979 / 1987.
 // Both phases at once store at each other's expense on the bus (rows of each, with tokens): 256 / 256 CUs 8 rows 1301 / 907, 16 rows (7.8 MiB) 2457 / 2490, 24 rows 3147 / 3261, 64 rows 6452 / 6858;

@@ -1,5 +1,5 @@
-// Decode GEMMs of 17 to 256 rows on large partitions, gfx950: a workgroup takes all the rows and 128 columns, so that every weight
-// byte is asked for once.
+// GEMMs of 1 to 256 rows, gfx950: a workgroup takes all the rows and 128 columns, so that every weight byte is asked for once. For decode steps of 17
+// rows and more on large partitions (fewer take gemm_kslice.hip) and prefill batches on the whole GPU.
 //
 // What bounds them is what a CU pulls: about 256 lines of 128 bytes are under way at a time, whatever instruction asks for them, which
 // is 57 GB/s of lines that come from HBM (63 with the non-temporal hint), 103 from the memory-side cache and 140 from L2, and lines
