@@ -81,11 +81,9 @@ int sts_max_pages_per_seq_limit(int32_t page_tokens);
 /* Host only, no GPU state: how a decode step over contexts of n_pages[i] pages is cut into chunks on
  * a partition of `cus` CUs (pages per chunk, chunks of the longest context), next to the chunk count
  * the engine allocates its merge workspace and work list for when max_pages_per_seq is the bound.
- * max_chunks <= allocated_chunks holds for every input sts_init accepts. For heads of 128 elements; the _dim form takes 64 as well. */
+ * max_chunks <= allocated_chunks holds for every input sts_init accepts. */
 int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t cus, int32_t page_tokens,
                           int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks);
-int sts_decode_chunk_plan_dim(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t head_dim, int32_t cus, int32_t page_tokens,
-                              int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks);
 
 /* Host only, no GPU state: how the attention of a prefill batch (lens[i] new tokens over priors[i] cached ones) is laid out on a
  * partition of `cus` CUs: work items (query tiles of 128 rows, or parts of their key range), how many of them are parts of a cut

@@ -741,39 +741,20 @@ int prefill_finish(sts_ctx* c, int n_seqs, const int32_t* seqs, const int32_t* l
 // ------------------------------------------------------------------------------------ decode
 // Context chunks of at most chunk_pages pages: the largest of 64/32/16/8 that still yields about
 // four workgroups per CU of the partition (8 pages keep the four waves of a workgroup busy with
-// one two-page block each), never more than 128 chunks for the longest context.
-void decode_chunk_plan(const int* n_pages, int n, int n_kv, int head_dim, int cus, int page_tokens, int* chunk_pages_out, int* max_chunks_out) {
+// one two-page block each), never more than 128 chunks for the longest context. Also where every context would fit one chunk and need no merge: left whole, 1
+// request of 150 tokens took 86.4 us a layer for 88.0, 32 of 700 115.1 for 122.1 (256 CUs, hidden 4096), but the logits were further from 64 bits, 0.008363 ->
+// 0.008398 in the mean of 230 steps (paired difference 3.5e-5 +- 0.5e-5, with other weights 3.2e-5): the largest probability of a wave's part of a chunk is
+// 1, which bf16 holds exactly, and fewer chunks have fewer of them.
+void decode_chunk_plan(const int* n_pages, int n, int n_kv, int cus, int page_tokens, int* chunk_pages_out, int* max_chunks_out) {
   int max_pages = 1;
   for (int i = 0; i < n; i++) max_pages = std::max(max_pages, n_pages[i]);
-  const int limit = attn_decode_max_chunk_tokens() / page_tokens;
-  int chunk_pages = limit;
+  int chunk_pages = attn_decode_max_chunk_tokens() / page_tokens;
   const int floor_pages = std::max(8, (max_pages + 127) / 128);
   while (chunk_pages / 2 >= floor_pages) {
     long long wgs = 0;
     for (int i = 0; i < n; i++) wgs += (n_pages[i] + chunk_pages - 1) / chunk_pages;
     if (wgs * n_kv >= 4LL * cus) break;
     chunk_pages /= 2;
-  }
-  // Contexts that fit one chunk each need no merge, whose kernel takes 2 us and its partial outputs 0.02 us a chunk of eight KV heads
-  // more (of fewer heads as much less). Against that stand
-  // the longest context in one workgroup, which reads a page of a KV head (8 KB) in 0.15 us, and all pages at what the CUs, or from 114 of them
-  // on the memory, give; all in pages here. Only where every workgroup is resident at once. Cut / whole, us a layer: hidden 4096 on
-  // 256 CUs 1 request of 150 tokens 88.0 / 86.4 (from 300 tokens on it stays cut: 88.7 / 89.8 at 450), 16 of 700 107.3 / 104.2, 32 of 700 122.1 / 115.1,
-  // 62 of 400 134.7 / 126.1, of 1000 152.2 / 152.8; on 64 CUs 8 of 700 195.9 / 186.6, 16 of 250 193.6 / 187.5; hidden 8192 on 128 CUs 16 of 700 408 / 398.
-  // Fewer heads, hidden 2048: two 32 requests of 400 61.7 / 61.8 (of 700, 64.0 / 64.7, and of 1000, 65.3 / 67.6, they stay cut), four 32 of 700 67.9 / 64.9 (16 of 700, 51.9 / 52.7,
-  // and of 1000, 53.0 / 55.9, stay cut). More than eight are counted as eight: 32 heads 16 of 400 113.2 / 110.1.
-  // Distance of the logits from 64 bits, mean of 15 steps: 0.008617 / 0.008562. Heads of 64 elements stay cut: whole they were 2 us a layer faster (four KV heads,
-  // 1 request of 150 tokens 26.0 / 24.3) but no nearer to 64 bits (0.004103 / 0.004107 over 36 steps), and their pages of 4 KB are not what the costs above are of.
-  if (head_dim == 128 && max_pages > chunk_pages && max_pages <= limit && (long long)n * n_kv <= 2LL * cus) {
-    long long total = 0, merged = 0;
-    int longest = 1;
-    for (int i = 0; i < n; i++) {
-      const int chunks = (n_pages[i] + chunk_pages - 1) / chunk_pages;
-      total += n_pages[i]; merged += chunks > 1 ? chunks : 0; longest = std::max(longest, (n_pages[i] + chunks - 1) / chunks);
-    }
-    const long long all = total * n_kv / std::min(cus, 114);
-    if (std::max<long long>(max_pages, all) <= std::max<long long>(longest, all) + 13 + merged * std::min(n_kv, 8) / 64)
-      while (chunk_pages < max_pages) chunk_pages = std::min(2 * chunk_pages, limit);
   }
   *chunk_pages_out = chunk_pages;
   *max_chunks_out = (max_pages + chunk_pages - 1) / chunk_pages;
@@ -868,7 +849,7 @@ int DecodeRun::begin() {
   }
   std::vector<int> np_list(n);
   for (int i = 0; i < n; i++) np_list[i] = ph.h_dseq[i].n_pages;
-  decode_chunk_plan(np_list.data(), n, d.n_kv_heads, d.head_dim, ph.cus, pt, &chunk_pages, &max_chunks);
+  decode_chunk_plan(np_list.data(), n, d.n_kv_heads, ph.cus, pt, &chunk_pages, &max_chunks);
   if (max_chunks > decode_max_chunks(mp)) return STS_EINVAL;   // cannot happen within sts_init's bound on max_pages_per_seq
   // One attention workgroup row per context chunk that exists, longest chunks first: the workgroups that finish the launch are then the
   // short ones. A context's chunks are equal (its pages / chunks), so a pass over the requests counts the items of each length and a second
@@ -1304,13 +1285,9 @@ extern "C" int sts_attn_prefill_plan(int32_t n_seqs, const int32_t* lens, const 
 }
 extern "C" int sts_decode_chunk_plan(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t cus, int32_t page_tokens,
                                      int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks) {
-  return sts_decode_chunk_plan_dim(n_pages, n, n_kv_heads, 128, cus, page_tokens, max_pages_per_seq, chunk_pages, max_chunks, allocated_chunks);
-}
-extern "C" int sts_decode_chunk_plan_dim(const int32_t* n_pages, int32_t n, int32_t n_kv_heads, int32_t head_dim, int32_t cus, int32_t page_tokens,
-                                         int32_t max_pages_per_seq, int32_t* chunk_pages, int32_t* max_chunks, int32_t* allocated_chunks) {
-  if (!n_pages || n < 1 || n_kv_heads < 1 || (head_dim != 64 && head_dim != 128) || cus < 1 || page_tokens < 1 || page_tokens > attn_decode_max_chunk_tokens() || !chunk_pages || !max_chunks || !allocated_chunks) return STS_EINVAL;
+  if (!n_pages || n < 1 || n_kv_heads < 1 || cus < 1 || page_tokens < 1 || page_tokens > attn_decode_max_chunk_tokens() || !chunk_pages || !max_chunks || !allocated_chunks) return STS_EINVAL;
   for (int i = 0; i < n; i++) if (n_pages[i] < 1 || n_pages[i] > max_pages_per_seq) return STS_EINVAL;
-  decode_chunk_plan(n_pages, n, n_kv_heads, head_dim, cus, page_tokens, chunk_pages, max_chunks);
+  decode_chunk_plan(n_pages, n, n_kv_heads, cus, page_tokens, chunk_pages, max_chunks);
   *allocated_chunks = decode_max_chunks(max_pages_per_seq);
   return STS_OK;
 }

@@ -93,7 +93,7 @@ EXPORTS = [
     "sts_set_partition", "sts_get_partition", "sts_kernel_timing", "sts_kernel_times", "sts_fail_launch", "sts_kernel_name",
     "sts_probe_copy", "sts_profile_observe", "sts_op_gemm", "sts_op_attn_prefill", "sts_op_attn_prefill_form", "sts_attn_prefill_plan", "sts_op_attn_decode", "sts_wave_quant",
     "sts_profile_parse", "sts_profile_load", "sts_profile_dump", "sts_profile_free", "sts_latency_query",
-    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_chunk_plan_dim", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_decode_layer_all_rows", "sts_decode_gemm_all_rows", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_op_gemm_cols", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
+    "sts_latency_roofline", "sts_sched_decide", "sts_sched_replay", "sts_max_pages_per_seq_limit", "sts_decode_chunk_plan", "sts_decode_gemm_plan", "sts_decode_layer_plan", "sts_decode_layer_all_rows", "sts_decode_gemm_all_rows", "sts_probe_read", "sts_set_stream_model", "sts_profile_stream_model", "sts_op_gemm_noalloc", "sts_op_gemm_cols", "sts_weight_packed_index", "sts_probe_gemm", "sts_set_tile_model",
     "sts_profile_tile_model",
 ]
 
@@ -437,12 +437,12 @@ def max_pages_per_seq_limit(page_tokens=16):
     return lib().sts_max_pages_per_seq_limit(page_tokens)
 
 
-def decode_chunk_plan(n_pages, n_kv_heads, cus, page_tokens, max_pages_per_seq, head_dim=128):
+def decode_chunk_plan(n_pages, n_kv_heads, cus, page_tokens, max_pages_per_seq):
     """(pages per chunk, chunks of the longest context, chunks per context the engine allocates for)."""
     a = _i32(n_pages)
     cp, mc, ac = C.c_int32(), C.c_int32(), C.c_int32()
-    _ck(lib().sts_decode_chunk_plan_dim(_p(a), a.size, n_kv_heads, head_dim, cus, page_tokens, max_pages_per_seq, C.byref(cp), C.byref(mc), C.byref(ac)),
-        "sts_decode_chunk_plan_dim")
+    _ck(lib().sts_decode_chunk_plan(_p(a), a.size, n_kv_heads, cus, page_tokens, max_pages_per_seq, C.byref(cp), C.byref(mc), C.byref(ac)),
+        "sts_decode_chunk_plan")
     return cp.value, mc.value, ac.value
 
 

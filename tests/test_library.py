@@ -252,38 +252,18 @@ def test_decode_chunk_sizing_stays_within_what_the_engine_allocates(sts):
         sts.decode_chunk_plan([limit + 1], 8, 32, 16, limit)       # a context longer than the block table
 
 
-@pytest.mark.parametrize("pages,cus,whole", [([10], 256, True), ([40], 256, False), ([40], 64, False), ([8, 3], 256, True), ([26] * 62, 256, True), ([26] * 64, 256, True),
-                                             ([26] * 65, 256, False), ([64] * 16, 256, True), ([65] * 16, 256, False), ([60] + [2] * 15, 256, False), ([44] * 8, 64, True),
-                                             ([16] * 16, 64, True), ([16] * 17, 64, False), ([1] * 300, 256, True), ([64], 8, True)])
-def test_decode_chunk_plan_leaves_contexts_whole_where_a_merge_costs_more(sts, pages, cus, whole):
-    """A context of up to 64 pages is one chunk where its workgroups (eight KV heads each) are resident at once and the longest one ends before the
-    chunks and their merge would; one page or one request beyond, or one long context among short ones, and it is cut as before."""
-    cp, mc, _ = sts.decode_chunk_plan(pages, 8, cus, 16, 128)
-    assert (mc == 1) == whole and cp in (8, 16, 32, 64) and mc == -(-max(pages) // cp)
-
-
-@pytest.mark.parametrize("pages,kv,cus", [([10], 4, 256), ([15, 9, 4, 12, 7, 10, 14, 8], 4, 128), ([26] * 62, 8, 256), ([64] * 16, 8, 256), ([44] * 8, 8, 64)])
-def test_decode_chunk_plan_cuts_contexts_of_small_heads(sts, pages, kv, cus):
-    """The costs behind whole contexts are those of heads of 128 elements: with 64 a context is cut into the chunks that fill the partition."""
-    cp, mc, _ = sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=64)
-    assert cp < max(pages) and mc == -(-max(pages) // cp)
-    assert sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=128)[1] == 1
-    for bad in (0, 32, 256):
-        with pytest.raises(sts.StsError):
-            sts.decode_chunk_plan(pages, kv, cus, 16, 128, head_dim=bad)
-
-
-@pytest.mark.parametrize("pages,kv,cus,whole", [([63] * 16, 4, 256, False), ([44] * 16, 4, 256, False), ([44] * 32, 4, 256, True), ([63] * 64, 4, 256, True),
-                                                ([26] * 16, 2, 256, False), ([63] * 32, 2, 256, False), ([26] * 32, 2, 256, True), ([10] * 16, 2, 256, True), ([26] * 16, 32, 256, True)])
-def test_decode_chunk_plan_prices_a_merge_by_its_heads(sts, pages, kv, cus, whole):
-    """A chunk's partial outputs are those of the KV heads that a model has: with two or four of them a merge is cheaper, and contexts that eight heads
-    would leave whole stay cut."""
-    assert (sts.decode_chunk_plan(pages, kv, cus, 16, 128)[1] == 1) == whole
+@pytest.mark.parametrize("pages,kv,cus,chunk", [([10], 8, 256, 8), ([40], 8, 64, 8), ([8, 3], 8, 256, 8), ([26] * 62, 8, 256, 8), ([26] * 65, 8, 256, 16), ([64] * 16, 8, 256, 8), ([44] * 8, 8, 64, 8),
+                                                ([44] * 8, 8, 32, 32), ([16] * 17, 8, 64, 8), ([1] * 300, 8, 256, 64), ([64], 8, 8, 16), ([64] * 128, 8, 256, 64), ([44] * 32, 4, 256, 8),
+                                                ([15, 9, 4, 12, 7, 10, 14, 8], 4, 128, 8), ([64] * 16, 32, 256, 32)])
+def test_decode_chunk_plan_fills_the_partition(sts, pages, kv, cus, chunk):
+    """Chunks are the largest of 64, 32, 16 and 8 pages that give the partition four workgroups a CU, also where every context would fit one chunk: fewer chunks
+    leave the logits further from 64 bits."""
+    assert sts.decode_chunk_plan(pages, kv, cus, 16, 128)[:2] == (chunk, -(-max(pages) // chunk))
 
 
 @pytest.mark.parametrize("page_tokens,pages", [(12, [81] * 16), (24, [42] * 16), (48, [21] * 16), (12, [85] * 16), (10, [100] * 16), (16, [64] * 16), (20, [51, 1])])
 def test_decode_chunks_hold_no_more_than_the_kernel_takes(sts, page_tokens, pages):
-    """Page sizes whose chunk limit is no power of two: halved and doubled again, a chunk stays within the 1024 tokens the kernel takes."""
+    """Page sizes whose chunk limit is no power of two: a chunk stays within the 1024 tokens the kernel takes."""
     for cus in (8, 64, 128, 256):
         cp, mc, _ = sts.decode_chunk_plan(pages, 8, cus, page_tokens, 128)
         assert cp * page_tokens <= 1024 and mc == -(-max(pages) // cp), cus
