@@ -77,7 +77,7 @@ struct Phase {
   PrefillSeq* h_pseq = nullptr; DecodeSeq* h_dseq = nullptr; AttnItem* h_items = nullptr; DecodeItem* h_ditems = nullptr;
   float* h_logits = nullptr; ArgBest* h_best = nullptr;
   int rows = 0;                               // rows of the last call
-  bool alone = false;                         // no step of the other phase was in flight when this one was queued
+  bool alone = false;                         // neither queued together with the other phase nor while a launched step of it was in flight (blocking calls of two threads do not see each other)
   // per-kernel timing
   std::vector<hipEvent_t> kev; std::vector<int> kkind; size_t kused = 0;
   int64_t kns[STS_K_COUNT] = {0}, kcnt[STS_K_COUNT] = {0};
